@@ -115,7 +115,7 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
     A(&c.lm_val, (size_t)(m->vocab / 16) * T * 4);
     A(&c.lm_idx, (size_t)(m->vocab / 16) * T * 4);
   }
-  A(&c.samp_stats, T * 2 * 4);
+  A(&c.samp_stats, T * EVICT_SAMP_STATS * 4);
   A(&c.stack_buf[0], T * d * eb);
   A(&c.stack_buf[1], T * d * eb);
   if (!rc) {

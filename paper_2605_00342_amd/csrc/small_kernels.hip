@@ -373,34 +373,78 @@ __global__ __launch_bounds__(64) void accept_path_kernel(
 // ------------------------------------------------------------------------------------
 constexpr int kSampThreads = 1024;
 constexpr int kSampWaves = kSampThreads / 64;
+// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials.
+constexpr int kSampStats = EVICT_SAMP_STATS;
+static_assert(kSampStats == 2 * kSampWaves, "one partial maximum and one partial sum per column group");
 
-// Per node: maximum of the logits and the sum of exp((logit - max) / temperature) over the
-// vocabulary -- the two numbers that turn any logit of the row into a probability.
-__global__ __launch_bounds__(kSampThreads) void softmax_stats_kernel(const float* __restrict__ logits, int V, float inv_temp,
-                                                                     float* __restrict__ stats, const int* __restrict__ t_dev) {
-  __shared__ float s_red[kSampWaves];
-  if ((int)blockIdx.x >= dyn_tokens(t_dev, (int)gridDim.x)) return;  // (rows past the call's actual token count)
-  const float* row = logits + (size_t)blockIdx.x * V;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// Per node, the two numbers that turn any logit of the row into a probability -- the maximum and the sum of
+// exp((logit - max) / temperature) over the vocabulary -- as kSampWaves partial results each, one wavefront per
+// (row, part), so that a few rows still fill the chip: a row is 0.6 MB at a vocabulary of 151936, and one workgroup
+// walking it alone is bound by the latency of its loads (89 us for 128 rows; this way the two launches take 12 and 13 us,
+// 78 MB read by each, 6 TB/s).
+// The maxima come first, in a launch of their own: each sum needs the whole row's. Parts of the maximum are contiguous
+// ranges. Part w of the sum is what wavefront w of a 1024-thread workgroup striding over the row would add up: lane l
+// takes elements 64w + l + 1024j in ascending j, and the row's sum is the parts' in ascending w. The order of every
+// addition is fixed by the vocabulary size alone.
+constexpr int kStatsThreads = 256;
+constexpr int kStatsWgs = kSampThreads / kStatsThreads;  // workgroups per row
+constexpr int kStatsBatch = 32;                          // loads in flight per lane
+
+__global__ __launch_bounds__(kStatsThreads) void row_max_kernel(const float* __restrict__ logits, int V, float* __restrict__ stats,
+                                                                int T, const int* __restrict__ t_dev) {
+  const int r = (int)blockIdx.x / kStatsWgs;
+  if (r >= dyn_tokens(t_dev, T)) return;  // (rows past the call's actual token count)
+  const int lane = threadIdx.x & 63;
+  const int part = ((int)blockIdx.x % kStatsWgs) * (kStatsThreads / 64) + (threadIdx.x >> 6);
+  const float* row = logits + (size_t)r * V;
+  const int seg = (V + kSampWaves - 1) / kSampWaves;
+  const int lo = part * seg, hi = lo + seg < V ? lo + seg : V;
   float m = -INFINITY;
-  for (int i = tid; i < V; i += kSampThreads) m = fmaxf(m, row[i]);
-  m = wave_max(m);
-  if (lane == 0) s_red[w] = m;
-  __syncthreads();
-  m = s_red[0];
-  for (int i = 1; i < kSampWaves; ++i) m = fmaxf(m, s_red[i]);
-  __syncthreads();
-  float z = 0.0f;
-  for (int i = tid; i < V; i += kSampThreads) z += __expf((row[i] - m) * inv_temp);
-  z = wave_sum(z);
-  if (lane == 0) s_red[w] = z;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.0f;
-    for (int i = 0; i < kSampWaves; ++i) t += s_red[i];
-    stats[2 * blockIdx.x] = m;
-    stats[2 * blockIdx.x + 1] = t;
+  for (int i0 = lo; i0 < hi; i0 += 64 * kStatsBatch) {
+    float v[kStatsBatch];
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      v[u] = i < hi ? row[i] : -INFINITY;
+    }
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) m = fmaxf(m, v[u]);
   }
+  m = wave_max(m);
+  if (lane == 0) stats[(size_t)r * kSampStats + part] = m;
+}
+
+// maximum of a row from its partial maxima
+__device__ __forceinline__ float stats_max(const float* __restrict__ st) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kSampWaves; ++i) m = fmaxf(m, st[i]);
+  return m;
+}
+
+__global__ __launch_bounds__(kStatsThreads) void row_expsum_kernel(const float* __restrict__ logits, int V, float inv_temp,
+                                                                   float* __restrict__ stats, int T, const int* __restrict__ t_dev) {
+  const int r = (int)blockIdx.x / kStatsWgs;
+  if (r >= dyn_tokens(t_dev, T)) return;
+  const int lane = threadIdx.x & 63;
+  const int part = ((int)blockIdx.x % kStatsWgs) * (kStatsThreads / 64) + (threadIdx.x >> 6);
+  const float* row = logits + (size_t)r * V;
+  float* st = stats + (size_t)r * kSampStats;
+  const float m = stats_max(st);
+  float z = 0.0f;
+  for (int i0 = part * 64; i0 < V; i0 += kSampThreads * kStatsBatch) {
+    float v[kStatsBatch];
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) {
+      const int i = i0 + u * kSampThreads + lane;
+      v[u] = i < V ? row[i] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u)
+      if (i0 + u * kSampThreads + lane < V) z += __expf((v[u] - m) * inv_temp);
+  }
+  z = wave_sum(z);
+  if (lane == 0) st[kSampWaves + part] = z;
 }
 
 __device__ __forceinline__ float wave_incl_scan_f32(float v, int lane) {
@@ -413,13 +457,17 @@ __device__ __forceinline__ float wave_incl_scan_f32(float v, int lane) {
 }
 
 // One workgroup per tree. Step 1, all threads: the target probability of every node's token
-// under its parent's distribution. Step 2, one thread: the walk of Eq. 3 on values in LDS --
+// under its parent's distribution. Step 2, one wavefront: the walk of Eq. 3 on values in LDS --
 // child c of the surviving node is accepted when u_node[c] < p(c) / (1 - mass rejected so
 // far at this node), which is what the repeated renormalisation amounts to; a token already
-// rejected at this node has no mass left. Step 3, all threads: the final draw from the
+// rejected at this node has no mass left. The children of a node are found 64 nodes at a time by a
+// ballot. Step 3, all threads: the final draw from the
 // distribution at the last node with the rejected tokens removed, by inverting the cumulative
 // sum at u_bonus: 16 contiguous vocabulary segments are summed (one per wavefront), the
 // segment holding the target mass is cut into 64 contiguous pieces, the piece is walked.
+// What bounds step 3 is the latency of one workgroup's loads, so kStatsBatch of them are in flight per lane, and the
+// pieces, which a lane adds up element by element, come through LDS in chunks of 64 elements that all wavefronts fetch
+// coalesced (168 -> 31 us for four trees at a vocabulary of 151936; the additions and their order are unchanged).
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
@@ -430,10 +478,12 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   __shared__ float s_p[kMaxSel];
   __shared__ float s_u[kMaxSel];
   __shared__ int s_rej[kMaxSel];
-  __shared__ int s_cur, s_nrej, s_seg, s_found;
+  __shared__ float s_piece[64][65];  // chunk of 64 elements of each of the 64 pieces (rows one bank apart)
+  __shared__ int s_cur, s_nrej, s_seg;
   __shared__ float s_segsum[kSampWaves];
   __shared__ float s_rem;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = tree_off[b];
   int n = tree_off[b + 1] - lo;
   n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
@@ -447,7 +497,12 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
       if (tk < 0 || tk >= V) { bad = true; tk = -1; }  // an invalid token id is never accepted and removes no mass
       else {
         const size_t prow = (size_t)(lo + pa);
-        pr = __expf((logits[prow * V + tk] - stats[2 * prow]) * inv_temp) / stats[2 * prow + 1];
+        const float* st = stats + prow * kSampStats;
+        const float logit = logits[prow * V + tk];
+        float z = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kSampWaves; ++q) z += st[kSampWaves + q];
+        pr = __expf((logit - stats_max(st)) * inv_temp) / z;
       }
     }
     s_par[i] = i == 0 ? -1 : pa;
@@ -459,38 +514,45 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   int32_t* my = path + (size_t)b * path_stride;
   for (int i = tid; i < path_stride; i += kSampThreads) my[i] = i == 0 ? 0 : -1;
   __syncthreads();
-  if (tid == 0) {
+  if (w == 0) {
     int cur = 0, len = 1, nrej = 0;
     while (true) {
       float removed = 0.0f;
       nrej = 0;
       int nxt = -1;
-      for (int c = cur + 1; c < n; ++c) {
-        if (s_par[c] != cur) continue;
-        const int tk = s_tok[c];
-        float pc = s_p[c];
-        for (int r = 0; r < nrej; ++r)
-          if (s_rej[r] == tk) pc = 0.0f;
-        if (s_u[c] < pc / (1.0f - removed)) { nxt = c; break; }
-        removed += pc;
-        s_rej[nrej++] = tk;
+      for (int base = cur + 1; base < n && nxt < 0; base += 64) {
+        const int c0 = base + lane;
+        unsigned long long kids = __ballot(c0 < n && s_par[c0] == cur);
+        while (kids) {  // children in ascending order
+          const int c = base + __ffsll((long long)kids) - 1;
+          kids &= kids - 1;
+          const int tk = s_tok[c];
+          float pc = s_p[c];
+          for (int r = 0; r < nrej; ++r)
+            if (s_rej[r] == tk) pc = 0.0f;
+          if (s_u[c] < pc / (1.0f - removed)) { nxt = c; break; }
+          removed += pc;
+          if (lane == 0) s_rej[nrej] = tk;  // (LDS operations of one wavefront complete in order)
+          ++nrej;
+        }
       }
       if (nxt < 0) break;
       cur = nxt;  // strictly increasing: the walk ends
-      if (len < path_stride) my[len] = cur;
+      if (lane == 0 && len < path_stride) my[len] = cur;
       ++len;
     }
-    path_len[b] = len;
-    s_cur = cur;
-    s_nrej = nrej;
-    s_found = -1;
+    if (lane == 0) {
+      path_len[b] = len;
+      s_cur = cur;
+      s_nrej = nrej;
+    }
   }
   __syncthreads();
-  const int cur = s_cur, nrej = s_nrej;
+  const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const float* row = logits + (size_t)(lo + cur) * V;
-  const float m = stats[2 * (size_t)(lo + cur)];
-  auto mass = [&](int i) {
-    float e = __expf((row[i] - m) * inv_temp);
+  const float m = stats_max(stats + (size_t)(lo + cur) * kSampStats);
+  auto mass = [&](float v, int i) {
+    float e = __expf((v - m) * inv_temp);
     for (int r = 0; r < nrej; ++r)
       if (s_rej[r] == i) e = 0.0f;
     return e;
@@ -500,7 +562,29 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   const int sb = w * seg;
   const int se = sb + seg < V ? sb + seg : V;
   float acc = 0.0f;
-  for (int i = sb + lane; i < se; i += 64) acc += mass(i);
+  for (int i0 = sb; i0 < se; i0 += 64 * kStatsBatch) {
+    float e[kStatsBatch];
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      e[u] = i < se ? row[i] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) {
+      const int i = i0 + u * 64 + lane;
+      e[u] = i < se ? __expf((e[u] - m) * inv_temp) : 0.0f;
+    }
+    for (int r = 0; r < nrej; ++r) {  // (the same for the whole wavefront, and rarely inside this batch)
+      const int at = __builtin_amdgcn_readfirstlane(s_rej[r]) - i0;
+      if (at >= 0 && at < 64 * kStatsBatch) {
+#pragma unroll
+        for (int u = 0; u < kStatsBatch; ++u)
+          if (u * 64 + lane == at) e[u] = 0.0f;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) acc += e[u];  // (adding a zero leaves a sum of non-negative terms as it is)
+  }
   acc = wave_sum(acc);
   if (lane == 0) s_segsum[w] = acc;
   __syncthreads();
@@ -524,13 +608,23 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     s_rem = target - before;
   }
   __syncthreads();
+  const int cl = seg >> 6;  // contiguous piece per lane of the first wavefront
+  const int base = __builtin_amdgcn_readfirstlane(s_seg) * seg;
+  float psum = 0.0f;
+  for (int c0 = 0; c0 < cl; c0 += 64) {
+    const int cn = cl - c0 < 64 ? cl - c0 : 64;
+#pragma unroll
+    for (int q = 0; q < 64 / kSampWaves; ++q) {
+      const int piece = w * (64 / kSampWaves) + q;
+      const int i = base + piece * cl + c0 + lane;
+      if (lane < cn) s_piece[piece][lane] = i < V ? mass(row[i], i) : 0.0f;
+    }
+    __syncthreads();
+    if (w == 0)
+      for (int j = 0; j < cn; ++j) psum += s_piece[lane][j];
+    __syncthreads();
+  }
   if (w == 0) {
-    const int cl = seg >> 6;  // contiguous piece per lane
-    const int pb = s_seg * seg + lane * cl;
-    int pe = pb + cl;
-    pe = pe < V ? pe : V;
-    float psum = 0.0f;
-    for (int i = pb; i < pe; ++i) psum += mass(i);
     const float incl = wave_incl_scan_f32(psum, lane);
     const float rem = s_rem;
     const unsigned long long hit = __ballot(psum > 0.0f && rem < incl);
@@ -538,23 +632,41 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     int owner = -1;
     if (hit) owner = __ffsll((long long)hit) - 1;
     else if (any) owner = 63 - __clzll((long long)any);  // rounding: the last piece with mass takes it
-    if (lane == owner) {
-      const float r2 = rem - (incl - psum);
+    int pick = -1;
+    if (owner >= 0) {
+      // the owner's piece, element by element, 64 of them fetched at a time
+      const float r2 = __shfl(rem - (incl - psum), owner);
+      const int pb = base + owner * cl;
       float run = 0.0f;
-      int pick = -1;
-      for (int i = pb; i < pe; ++i) {
-        const float e = mass(i);
-        if (e > 0.0f) {
-          pick = i;
-          run += e;
-          if (r2 < run) break;
+      bool inside = false;
+      for (int c0 = 0; c0 < cl && !inside; c0 += 64) {
+        const int i = pb + c0 + lane;
+        const int ebits = __float_as_int((c0 + lane < cl && i < V) ? mass(row[i], i) : 0.0f);
+        for (int j = 0; j < 64 && !inside; ++j) {
+          const float e = __int_as_float(__builtin_amdgcn_readlane(ebits, j));
+          if (e > 0.0f) {
+            pick = pb + c0 + j;
+            run += e;
+            inside = r2 < run;
+          }
         }
       }
-      s_found = pick;
     }
+    if (lane == 0) bonus[b] = pick < 0 ? 0 : pick;
   }
-  __syncthreads();
-  if (tid == 0) bonus[b] = s_found < 0 ? 0 : s_found;
+}
+
+// the launches of acceptance under sampling on `stats`, [T][kSampStats] floats of scratch
+int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const int32_t* tok, const float* logits, int V,
+                          float inv_temp, float* stats, const float* u_node, const float* u_bonus, int B, int T, int32_t* path,
+                          int path_stride, int32_t* path_len, int32_t* bonus, int32_t* status, const int32_t* t_dev, hipStream_t s) {
+  hipLaunchKernelGGL(row_max_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, stats, T, t_dev);
+  hipLaunchKernelGGL(row_expsum_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, inv_temp, stats, T, t_dev);
+  int rc = launch_status("softmax statistics kernels");
+  if (rc) return rc;
+  hipLaunchKernelGGL(accept_sampled_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                     u_node, u_bonus, path, path_stride, path_len, bonus, status);
+  return launch_status("accept_sampled_kernel");
 }
 
 constexpr int kUnionThreads = 1024;  // >= the largest supported E: one expert per thread in the scan
@@ -705,10 +817,10 @@ int union_mask_plan(int T, int k, int E, size_t* lds_bytes) {
 using namespace evict;
 
 // ---- scratch of the allocation-free entry point (evict_accept_path_sampled_noalloc) ----
-// Per-node softmax statistics [EVICT_NOALLOC_MAX_NODES][2] floats. Every GPU the library runs on holds its
+// Per-node softmax statistics [EVICT_NOALLOC_MAX_NODES][EVICT_SAMP_STATS] floats. Every GPU the library runs on holds its
 // own copy of this array until the process ends. In host code the array's name is only a stand-in: the
 // device address is looked up once per device and kept; kernels and copies use that pointer.
-static __device__ __align__(256) float scratch[EVICT_NOALLOC_MAX_NODES * 2];
+static __device__ __align__(256) float scratch[EVICT_NOALLOC_MAX_NODES * EVICT_SAMP_STATS];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -871,12 +983,8 @@ int evict_accept_path_sampled(evict_ctx* ctx, const int32_t* tree_off, const int
   EVICT_REQUIRE(path_stride >= 1, EVICT_E_INVALID, "evict_accept_path_sampled: path_stride must be >= 1");
   const float inv_temp = 1.0f / temperature;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(softmax_stats_kernel, dim3(T), dim3(kSampThreads), 0, s, logits, vocab, inv_temp, ctx->samp_stats, ctx->t_dev);
-  int rc = launch_status("softmax_stats_kernel");
-  if (rc) return rc;
-  hipLaunchKernelGGL(accept_sampled_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, draft_tok, logits, vocab,
-                     inv_temp, ctx->samp_stats, u_node, u_bonus, path, path_stride, path_len, bonus_tok, ctx->status);
-  return launch_status("accept_sampled_kernel");
+  return launch_accept_sampled(tree_off, parent, draft_tok, logits, vocab, inv_temp, ctx->samp_stats, u_node, u_bonus, B, T, path,
+                               path_stride, path_len, bonus_tok, ctx->status, ctx->t_dev, s);
 }
 
 int evict_accept_path_sampled_noalloc(evict_ctx* ctx, const int32_t* tree_off, const int32_t* parent, const int32_t* draft_tok,
@@ -900,12 +1008,8 @@ int evict_accept_path_sampled_noalloc(evict_ctx* ctx, const int32_t* tree_off, c
   const float inv_temp = 1.0f / temperature;
   hipStream_t s = (hipStream_t)stream;
   // (rows [0, T) of the statistics are written in full before they are read: nothing has to start at zero)
-  hipLaunchKernelGGL(softmax_stats_kernel, dim3(T), dim3(kSampThreads), 0, s, logits, vocab, inv_temp, stats, ctx ? ctx->t_dev : nullptr);
-  rc = launch_status("softmax_stats_kernel");
-  if (rc) return rc;
-  hipLaunchKernelGGL(accept_sampled_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, draft_tok, logits, vocab,
-                     inv_temp, stats, u_node, u_bonus, path, path_stride, path_len, bonus_tok, ctx ? ctx->status : nullptr);
-  return launch_status("accept_sampled_kernel");
+  return launch_accept_sampled(tree_off, parent, draft_tok, logits, vocab, inv_temp, stats, u_node, u_bonus, B, T, path, path_stride,
+                               path_len, bonus_tok, ctx ? ctx->status : nullptr, ctx ? ctx->t_dev : nullptr, s);
 }
 
 static int kv_commit_impl(const char* who, evict_ctx* ctx, int dtype, int Hkv, int D, const void* const* k_new,

@@ -183,3 +183,17 @@ def test_lm_head_logits_then_sampling():
         assert check_against_oracle([par], tree_off, got, tok, u_node, u_bonus, 1.0, path, plen, bonus) == 0
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("V", [1, 63, 64, 65, 1023, 1025, 16384 + 1, 32768, 65536 + 17, 200003])
+def test_vocabulary_edges(ctx_small, V):
+    """Row lengths around the batches, segments and pieces the kernels cut a score row into; some pieces and whole
+    segments are empty, tokens near the ends are drawn."""
+    kids = min(V, 8)
+    sizes = [1, kids, 2 * kids]
+    parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(100 + V % 97, sizes, V)
+    for u in (0.0, 0.5, 1.0 - 2.0 ** -24):
+        u_bonus[:] = u
+        path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, u_bonus, max(sizes))
+        assert np.all((bonus >= 0) & (bonus < V))
+        check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus)
