@@ -57,6 +57,88 @@ __device__ void compact_tree(int n, int kstar, const int* s_par, const int* s_ra
   }
 }
 
+// One tree of at most 64 nodes in one wavefront, node i in lane i, everything in registers and
+// cross-lane operations: the same arithmetic in the same order as the workgroup path of select_prefix_kernel (one
+// rounded multiply per node top-down, ranking by (score descending, index ascending), sequential
+// fp32 running sum, IEEE division, first maximum), without LDS round trips and barriers.
+// Arrays start at the tree's first node. Every lane returns its rank, its (checked) parent, k* and S_{k*}.
+struct WaveSelection { int rank, parent, kstar; float est; };
+__device__ __forceinline__ WaveSelection select_wave(
+    const int32_t* __restrict__ parent, const float* __restrict__ prob, const float* __restrict__ cost, int kmax, int n,
+    float rho, int32_t* __restrict__ order_out, float* __restrict__ psum_out, int32_t* __restrict__ status) {
+  const int lane = lane_id();
+  const bool live = lane < n;
+  int p = -1;
+  float q = 0.0f, c = 1.0f;
+  if (live) {
+    int bad_in = 0;
+    p = parent[lane];
+    q = prob[lane];
+    if (cost && lane < kmax) c = cost[lane + 1];  // C(lane + 1)
+    if (lane == 0) p = -1;
+    else if (p < 0 || p >= lane) { p = 0; bad_in |= ST_BAD_PARENT; }  // invalid ids are clamped and flagged
+    // a probability outside [0, 1] (or NaN) could rank a child above its parent and break the ancestor-closure
+    // of the prefixes (Sec. 3.2.1): clamped and flagged; an unusable cost entry is never selected
+    if (lane > 0 && !(q >= 0.0f && q <= 1.0f)) { q = q > 1.0f ? 1.0f : 0.0f; bad_in |= ST_BAD_PROB; }
+    if (!(c > 0.0f)) { c = 0.0f; bad_in |= ST_BAD_COST; }
+    if (bad_in && status) atomicOr(status, bad_in);
+  }
+  // depth by walking up in lock step
+  int dep = 0, a = p;
+  while (__ballot(a >= 0)) {
+    const int up = __shfl(p, a < 0 ? 0 : a);
+    if (a >= 0) { ++dep; a = up; }
+  }
+  int maxdep = dep;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const int other = __shfl_xor(maxdep, o);
+    maxdep = other > maxdep ? other : maxdep;
+  }
+  // Score(v) = Score(parent(v)) * q(v), level by level (Eq. 7); the root counts as probability 1
+  float sc = lane == 0 ? 1.0f : 0.0f;
+  for (int lvl = 1; lvl <= maxdep; ++lvl) {
+    const float sp = __shfl(sc, p < 0 ? 0 : p);
+    if (live && dep == lvl) sc = __fmul_rn(sp, q);
+  }
+  // rank by (score descending, index ascending); lanes past the tree keep their own position
+  int r = lane;
+  if (live) r = 0;
+  const int sbits = __float_as_int(sc);
+  for (int j = 0; j < n; ++j) {
+    const float sj = __int_as_float(__builtin_amdgcn_readlane(sbits, j));
+    if (live) r += (sj > sc || (sj == sc && j < lane)) ? 1 : 0;
+  }
+  if (live && order_out) order_out[r] = lane;
+  // scores in rank order: lane i sends its score to lane r
+  const int sorted_bits = __builtin_amdgcn_ds_permute(r << 2, live ? sbits : 0);
+  // S_k: sequential fp32 running sum over the ranking
+  float acc = 0.0f, S = 0.0f;
+  for (int j = 0; j < n; ++j) {
+    acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(sorted_bits, j)));
+    if (lane == j) S = acc;
+  }
+  if (live && psum_out) psum_out[lane] = S;
+  const int kk = n < kmax ? n : kmax;
+  const float total = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(S), n - 1));
+  float bv = -1.0f;
+  int bi = 0x7fffffff;
+  if (lane < kk) {
+    bv = rho >= 0.0f ? (__fdiv_rn(S, total) >= rho ? 1.0f : 0.0f) : (c > 0.0f ? __fdiv_rn(S, c) : -1.0f);
+    bi = lane;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float ov = __shfl_xor(bv, o);
+    const int oi = __shfl_xor(bi, o);
+    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+  }
+  if (rho >= 0.0f && bv == 0.0f) bi = kk - 1;  // coverage not reached within kmax: the whole budget
+  const int kstar = bi + 1;
+  const float est = __shfl(S, bi);
+  return WaveSelection{r, p, kstar, est};
+}
+
 // One workgroup per tree. Writes k*, S_{k*}, the ranking and the running sums; when
 // `single` it also writes the compacted tree (B == 1), otherwise ranks go to rank_ws for
 // the second kernel.
@@ -83,6 +165,18 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
   const int lo = n_single > 0 ? 0 : tree_off[b];
   int n = n_single > 0 ? n_single : tree_off[b + 1] - lo;
   n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
+  if (!single && n <= 64) {
+    // a small tree of a batch fits one wavefront's registers: 12 -> 6 us for trees of 64 nodes
+    if (w > 0) return;  // (whole wavefronts, before any barrier)
+    const WaveSelection sel = select_wave(parent + lo, prob + lo, cost, kmax, n, rho, order_out ? order_out + lo : nullptr,
+                                          psum_out ? psum_out + lo : nullptr, status);
+    if (lane < n) rank_ws[lo + lane] = sel.rank;
+    if (lane == 0) {
+      k_star[b] = sel.kstar;
+      est_len[b] = sel.est;
+    }
+    return;
+  }
 
   if (tid == 0) s_maxdep = 0;
   int bad_in = 0;
@@ -203,10 +297,7 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
   }
 }
 
-// One tree of at most 64 nodes in one wavefront, node i in lane i, everything in registers and
-// cross-lane operations: the same arithmetic in the same order as select_prefix_kernel (one
-// rounded multiply per node top-down, ranking by (score descending, index ascending), sequential
-// fp32 running sum, IEEE division, first maximum), without LDS round trips and barriers.
+// a single tree of at most 64 nodes: selection and compaction in one wavefront
 __global__ __launch_bounds__(64) void select_prefix_wave_kernel(
     const int32_t* __restrict__ parent, const float* __restrict__ prob, const float* __restrict__ cost, int kmax, int n,
     float rho, int32_t* __restrict__ k_star, float* __restrict__ est_len, int32_t* __restrict__ order_out,
@@ -214,74 +305,8 @@ __global__ __launch_bounds__(64) void select_prefix_wave_kernel(
     int32_t* __restrict__ new_tree_off, int32_t* __restrict__ status) {
   const int lane = threadIdx.x;
   const bool live = lane < n;
-  int p = -1;
-  float q = 0.0f, c = 1.0f;
-  if (live) {
-    int bad_in = 0;
-    p = parent[lane];
-    q = prob[lane];
-    if (cost && lane < kmax) c = cost[lane + 1];  // C(lane + 1)
-    if (lane == 0) p = -1;
-    else if (p < 0 || p >= lane) { p = 0; bad_in |= ST_BAD_PARENT; }  // invalid ids are clamped and flagged
-    // a probability outside [0, 1] (or NaN) could rank a child above its parent and break the ancestor-closure
-    // of the prefixes (Sec. 3.2.1): clamped and flagged; an unusable cost entry is never selected
-    if (lane > 0 && !(q >= 0.0f && q <= 1.0f)) { q = q > 1.0f ? 1.0f : 0.0f; bad_in |= ST_BAD_PROB; }
-    if (!(c > 0.0f)) { c = 0.0f; bad_in |= ST_BAD_COST; }
-    if (bad_in && status) atomicOr(status, bad_in);
-  }
-  // depth by walking up in lock step
-  int dep = 0, a = p;
-  while (__ballot(a >= 0)) {
-    const int up = __shfl(p, a < 0 ? 0 : a);
-    if (a >= 0) { ++dep; a = up; }
-  }
-  int maxdep = dep;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const int other = __shfl_xor(maxdep, o);
-    maxdep = other > maxdep ? other : maxdep;
-  }
-  // Score(v) = Score(parent(v)) * q(v), level by level (Eq. 7); the root counts as probability 1
-  float sc = lane == 0 ? 1.0f : 0.0f;
-  for (int lvl = 1; lvl <= maxdep; ++lvl) {
-    const float sp = __shfl(sc, p < 0 ? 0 : p);
-    if (live && dep == lvl) sc = __fmul_rn(sp, q);
-  }
-  // rank by (score descending, index ascending); lanes past the tree keep their own position
-  int r = lane;
-  if (live) r = 0;
-  const int sbits = __float_as_int(sc);
-  for (int j = 0; j < n; ++j) {
-    const float sj = __int_as_float(__builtin_amdgcn_readlane(sbits, j));
-    if (live) r += (sj > sc || (sj == sc && j < lane)) ? 1 : 0;
-  }
-  if (live && order_out) order_out[r] = lane;
-  // scores in rank order: lane i sends its score to lane r
-  const int sorted_bits = __builtin_amdgcn_ds_permute(r << 2, live ? sbits : 0);
-  // S_k: sequential fp32 running sum over the ranking
-  float acc = 0.0f, S = 0.0f;
-  for (int j = 0; j < n; ++j) {
-    acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(sorted_bits, j)));
-    if (lane == j) S = acc;
-  }
-  if (live && psum_out) psum_out[lane] = S;
-  const int kk = n < kmax ? n : kmax;
-  const float total = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(S), n - 1));
-  float bv = -1.0f;
-  int bi = 0x7fffffff;
-  if (lane < kk) {
-    bv = rho >= 0.0f ? (__fdiv_rn(S, total) >= rho ? 1.0f : 0.0f) : (c > 0.0f ? __fdiv_rn(S, c) : -1.0f);
-    bi = lane;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const float ov = __shfl_xor(bv, o);
-    const int oi = __shfl_xor(bi, o);
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-  }
-  if (rho >= 0.0f && bv == 0.0f) bi = kk - 1;  // coverage not reached within kmax: the whole budget
-  const int kstar = bi + 1;
-  const float est = __shfl(S, bi);
+  const WaveSelection sel = select_wave(parent, prob, cost, kmax, n, rho, order_out, psum_out, status);
+  const int r = sel.rank, p = sel.parent, kstar = sel.kstar;
   // kept nodes ascending, parents re-indexed by counting kept nodes below
   const unsigned long long kept = __ballot(live && r < kstar);
   if (live && r < kstar) {
@@ -291,41 +316,82 @@ __global__ __launch_bounds__(64) void select_prefix_wave_kernel(
   }
   if (lane == 0) {
     k_star[0] = kstar;
-    est_len[0] = est;
+    est_len[0] = sel.est;
     new_tree_off[0] = 0;
     new_tree_off[1] = kstar;
   }
 }
 
-// Second step for batches: one workgroup walks the trees in order, so that tree b's
-// compacted output (which starts at or before tree b's own input offset) never overwrites
-// ranks of a tree not yet read. rank_ws aliases new_parent.
-__global__ __launch_bounds__(kSelThreads) void compact_batch_kernel(
+// Second step for batches: one workgroup compacts all trees, one wavefront per tree. Tree b's compacted output starts at
+// or before tree b's own input offset and so lands on the ranks of earlier trees (rank_ws aliases new_parent): the ranks
+// of a group of trees are taken into LDS, with the parents, before any of its output is written, and a group is as many
+// trees as fit there (kCompactNodes nodes, one tree per thread in the scans). 16 trees of 64 nodes: 20 us with the trees
+// walked one after the other by the whole workgroup, 6 us this way.
+constexpr int kCompactThreads = 1024;
+constexpr int kCompactNodes = 10 * 1024;
+static_assert(kCompactNodes >= kMaxSel && kMaxSel <= 0xFFFF, "a tree fits a group; ranks and ids fit 16 bits");
+__global__ __launch_bounds__(kCompactThreads) void compact_batch_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ k_star,
     int B, int32_t* rank_ws, int32_t* keep, int32_t* new_parent, int32_t* __restrict__ new_tree_off) {
-  __shared__ int s_par[kMaxSel];
-  __shared__ int s_rank[kMaxSel];
-  __shared__ int s_new[kMaxSel];
+  __shared__ uint32_t s_node[kCompactNodes];  // parent << 16 (0xFFFF: root) | rank, later the new id
+  __shared__ int s_lo[kCompactThreads], s_n[kCompactThreads], s_ks[kCompactThreads], s_at[kCompactThreads], s_out[kCompactThreads];
   __shared__ int s_wave[16];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int out = 0;
-  for (int b = 0; b < B; ++b) {
-    const int lo = tree_off[b];
-    int n = tree_off[b + 1] - lo;
-    n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
-    const int ks = k_star[b];
-    __syncthreads();
-    for (int i = tid; i < n; i += kSelThreads) {
-      int p = parent[lo + i];
-      if (i == 0) p = -1;
-      else if (p < 0 || p >= i) p = 0;
-      s_par[i] = p;
-      s_rank[i] = rank_ws[lo + i];
+  for (int b0 = 0; b0 < B;) {
+    // this thread's tree, where its nodes sit in LDS and its output, and how many trees the group holds
+    const int b = b0 + tid;
+    int lo = 0, n = 0, ks = 0;
+    if (b < B) {
+      lo = tree_off[b];
+      n = tree_off[b + 1] - lo;
+      n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
+      ks = k_star[b];
+    }
+    int total;
+    const int at = block_excl_scan(n, s_wave, &total);
+    const bool in = b < B && at + n <= kCompactNodes;
+    const int ntrees = __syncthreads_count(in);
+    const int before = block_excl_scan(in ? ks : 0, s_wave, &total);
+    if (in) {
+      s_lo[tid] = lo; s_n[tid] = n; s_ks[tid] = ks; s_at[tid] = at;
+      s_out[tid] = out + before;
+      new_tree_off[b] = out + before;
     }
     __syncthreads();
-    if (tid == 0) new_tree_off[b] = out;
-    compact_tree(n, ks, s_par, s_rank, s_new, s_wave, keep + out, new_parent + out);
-    out += ks;
+    for (int t = w; t < ntrees; t += kCompactThreads / 64) {
+      const int tlo = s_lo[t], tn = s_n[t], tat = s_at[t];
+      for (int i = lane; i < tn; i += 64) {
+        int p = parent[tlo + i];
+        if (i == 0) p = 0xFFFF;
+        else if (p < 0 || p >= i) p = 0;
+        s_node[tat + i] = ((uint32_t)p << 16) | (uint32_t)rank_ws[tlo + i];
+      }
+    }
+    __syncthreads();  // every rank of the group is in LDS before its first output is written
+    for (int t = w; t < ntrees; t += kCompactThreads / 64) {
+      const int tn = s_n[t], tks = s_ks[t], tout = s_out[t];
+      uint32_t* node = s_node + s_at[t];
+      int kept = 0;
+      for (int c0 = 0; c0 < tn; c0 += 64) {  // nodes in ascending order: a parent has its new id before its children ask
+        const int i = c0 + lane;
+        const uint32_t v = i < tn ? node[i] : 0xFFFFu;
+        const bool keeps = i < tn && (int)(v & 0xFFFFu) < tks;
+        const unsigned long long m = __ballot(keeps);
+        const int ni = kept + __popcll(m & ((1ull << lane) - 1ull));
+        if (keeps) node[i] = (v & 0xFFFF0000u) | (uint32_t)ni;  // (LDS operations of one wavefront complete in order)
+        if (keeps) {
+          const uint32_t p = v >> 16;
+          keep[tout + ni] = i;
+          new_parent[tout + ni] = p == 0xFFFFu ? -1 : (int)(node[p] & 0xFFFFu);
+        }
+        kept += __popcll(m);
+      }
+    }
+    out += total;
+    b0 += ntrees;
+    __syncthreads();
   }
   if (tid == 0) new_tree_off[B] = out;
 }
@@ -722,15 +788,24 @@ __global__ __launch_bounds__(256) void probe_copy_kernel(const probe_u32x4* __re
   }
 }
 
-__global__ void gather_rows_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int row_words,
+// One workgroup per destination row. The row's tree is found by counting, a wavefront at a time, the trees that end at or
+// before it; rows that are whole 16-byte pieces on both sides move as such (W = uint4), the rest as 4-byte words.
+template <typename W>
+__global__ __launch_bounds__(128) void gather_rows_kernel(const W* __restrict__ src, W* __restrict__ dst, int row_words,
                                    const int32_t* __restrict__ tree_off, const int32_t* __restrict__ new_tree_off,
                                    const int32_t* __restrict__ keep, int B) {
   const int r = blockIdx.x;  // destination row
   if (r >= new_tree_off[B]) return;
+  const int node = keep[r];
   int b = 0;
-  while (b + 1 < B && new_tree_off[b + 1] <= r) ++b;
-  const int s = tree_off[b] + keep[r];
-  for (int i = threadIdx.x; i < row_words; i += blockDim.x) dst[(size_t)r * row_words + i] = src[(size_t)s * row_words + i];
+  for (int b0 = 0; b0 + 1 < B; b0 += 64) {
+    const int t = b0 + lane_id();
+    const unsigned long long m = __ballot(t + 1 < B && new_tree_off[t + 1] <= r);
+    b += __popcll(m);
+    if (m != ~0ull) break;  // the offsets ascend
+  }
+  const int s = tree_off[b] + node;
+  for (int i = threadIdx.x; i < row_words; i += 128) dst[(size_t)r * row_words + i] = src[(size_t)s * row_words + i];
 }
 
 // Commit of the accepted path to the KV cache: the j-th accepted node of sequence b (depth j, so
@@ -891,7 +966,7 @@ static int select_prefix_impl(const char* who, evict_ctx* ctx, const int32_t* tr
   int rc = launch_status("select_prefix_kernel");
   if (rc) return rc;
   if (!single) {
-    hipLaunchKernelGGL(compact_batch_kernel, dim3(1), dim3(kSelThreads), 0, s, tree_off, parent, k_star, B,
+    hipLaunchKernelGGL(compact_batch_kernel, dim3(1), dim3(kCompactThreads), 0, s, tree_off, parent, k_star, B,
                        new_parent, keep, new_parent, new_tree_off);
     rc = launch_status("compact_batch_kernel");
   }
@@ -964,8 +1039,12 @@ int evict_gather_rows(const void* src, void* dst, int row_bytes, const int32_t* 
   EVICT_REQUIRE(row_bytes > 0 && row_bytes % 4 == 0, EVICT_E_INVALID, "evict_gather_rows: row_bytes must be a positive multiple of 4");
   EVICT_REQUIRE(B >= 1 && T >= 1, EVICT_E_INVALID, "evict_gather_rows: B, T must be >= 1");
   EVICT_REQUIRE(src != dst, EVICT_E_INVALID, "evict_gather_rows: in-place gather is not supported");
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(T), dim3(128), 0, (hipStream_t)stream, (const uint32_t*)src,
-                     (uint32_t*)dst, row_bytes / 4, tree_off, new_tree_off, keep, B);
+  if (row_bytes % 16 == 0 && aligned16(src) && aligned16(dst))
+    hipLaunchKernelGGL(gather_rows_kernel<uint4>, dim3(T), dim3(128), 0, (hipStream_t)stream, (const uint4*)src, (uint4*)dst,
+                       row_bytes / 16, tree_off, new_tree_off, keep, B);
+  else
+    hipLaunchKernelGGL(gather_rows_kernel<uint32_t>, dim3(T), dim3(128), 0, (hipStream_t)stream, (const uint32_t*)src,
+                       (uint32_t*)dst, row_bytes / 4, tree_off, new_tree_off, keep, B);
   return launch_status("gather_rows_kernel");
 }
 

@@ -293,3 +293,29 @@ def test_host_twins_equal_the_device_entry_points(sizes, kind, seed):
     assert hu["status"] == ev.EVICT_ST_BAD_EXPERT
     for n_ in d:
         assert np.array_equal(d[n_].cpu().numpy(), hu[n_]), n_
+
+
+@pytest.mark.parametrize("sizes,seed", [
+    ([63, 64, 65, 1, 2], 40),                     # one-wavefront trees next to workgroup ones
+    ([1024] * 11 + [3, 64, 65], 41),              # more nodes than one compaction group holds
+    ([1 + b % 3 for b in range(1100)], 42),       # more trees than one group holds
+])
+def test_select_prefix_batch_groups_bit_exact(sizes, seed):
+    test_select_prefix_bit_exact(sizes, "random", seed)
+
+
+@pytest.mark.parametrize("row_bytes,B", [(16, 3), (20, 65), (4096, 130), (2064, 64)])
+def test_gather_rows_widths_and_batches(row_bytes, B):
+    """Rows moved as 16-byte pieces and as words; more trees than one wavefront counts at a time."""
+    sizes = [1 + (b * 7) % 9 for b in range(B)]
+    off, par, pars, q, qs = _trees(sizes, 43, "random")
+    got = _select_gpu(off, par, q, synth.cost_linear_in_union(9, 128, 8), 9)
+    T, w = int(off[-1]), row_bytes // 4
+    src = torch.arange(T * w, dtype=torch.int32, device=DEV).reshape(T, w)
+    dst = torch.full((T, w), -1, dtype=torch.int32, device=DEV)
+    ev.evict_gather_rows(src, dst, row_bytes, _i32(off), _i32(got["new_off"]), _i32(got["keep"]), B, T)
+    torch.cuda.synchronize()
+    n_new = int(got["new_off"][B])
+    rows = np.concatenate([off[b] + got["keep"][got["new_off"][b]:got["new_off"][b + 1]] for b in range(B)])
+    assert np.array_equal(dst[:n_new].cpu().numpy(), src.cpu().numpy()[rows])
+    assert bool((dst[n_new:] == -1).all())
