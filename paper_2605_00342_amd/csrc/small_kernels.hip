@@ -22,7 +22,8 @@ void set_error(const char* fmt, ...) {
 
 namespace {
 
-constexpr int kSelThreads = 256;
+constexpr int kSelThreads = 1024;       // one tree of more than 64 nodes
+constexpr int kSelThreadsSmall = 256;   // batches of trees of at most 64 nodes on average: mostly one wavefront's work
 constexpr int kMaxSel = EVICT_MAX_SELECT_NODES;
 
 // Kept-set compaction of one tree: nodes with rank < kstar, ascending node id; parents
@@ -102,21 +103,27 @@ __device__ __forceinline__ WaveSelection select_wave(
     if (live && dep == lvl) sc = __fmul_rn(sp, q);
   }
   // rank by (score descending, index ascending); lanes past the tree keep their own position
-  int r = lane;
-  if (live) r = 0;
+  int r = 0;
   const int sbits = __float_as_int(sc);
-  for (int j = 0; j < n; ++j) {
-    const float sj = __int_as_float(__builtin_amdgcn_readlane(sbits, j));
-    if (live) r += (sj > sc || (sj == sc && j < lane)) ? 1 : 0;
+  for (int j0 = 0; j0 < n; j0 += 8) {  // (lanes past the tree hold zeros and come after every node: never counted)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float sj = __int_as_float(__builtin_amdgcn_readlane(sbits, j0 + j));
+      r += (sj > sc || (sj == sc && j0 + j < lane)) ? 1 : 0;
+    }
   }
+  r = live ? r : lane;
   if (live && order_out) order_out[r] = lane;
   // scores in rank order: lane i sends its score to lane r
   const int sorted_bits = __builtin_amdgcn_ds_permute(r << 2, live ? sbits : 0);
   // S_k: sequential fp32 running sum over the ranking
   float acc = 0.0f, S = 0.0f;
-  for (int j = 0; j < n; ++j) {
-    acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(sorted_bits, j)));
-    if (lane == j) S = acc;
+  for (int j0 = 0; j0 < n; j0 += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(sorted_bits, j0 + j)));
+      if (lane == j0 + j) S = acc;
+    }
   }
   if (live && psum_out) psum_out[lane] = S;
   const int kk = n < kmax ? n : kmax;
@@ -139,6 +146,15 @@ __device__ __forceinline__ WaveSelection select_wave(
   return WaveSelection{r, p, kstar, est};
 }
 
+// how many of the four scores s4 of nodes j .. j + 3 rank before node i of score si (LDS broadcast reads, four at a time)
+__device__ __forceinline__ int rank_among4(const float4 s4, int j, float si, int i) {
+  int r = (s4.x > si || (s4.x == si && j < i)) ? 1 : 0;
+  r += (s4.y > si || (s4.y == si && j + 1 < i)) ? 1 : 0;
+  r += (s4.z > si || (s4.z == si && j + 2 < i)) ? 1 : 0;
+  r += (s4.w > si || (s4.w == si && j + 3 < i)) ? 1 : 0;
+  return r;
+}
+
 // One workgroup per tree. Writes k*, S_{k*}, the ranking and the running sums; when
 // `single` it also writes the compacted tree (B == 1), otherwise ranks go to rank_ws for
 // the second kernel.
@@ -155,18 +171,18 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
   __shared__ int s_rank[kMaxSel];
   __shared__ int s_aux[kMaxSel];  // depth, later new index
   __shared__ int s_wave[16];
-  __shared__ float s_bestv[4];
-  __shared__ int s_besti[4];
+  __shared__ float s_bestv[16];
+  __shared__ int s_besti[16];
   __shared__ int s_maxdep;
 
   const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-  const int nthreads = blockDim.x, nwaves = nthreads >> 6;  // 64 threads for small trees: barriers cost nothing
+  const int nthreads = blockDim.x, nwaves = nthreads >> 6;
   // a single tree spans [0, T): its offsets need not be fetched
   const int lo = n_single > 0 ? 0 : tree_off[b];
   int n = n_single > 0 ? n_single : tree_off[b + 1] - lo;
   n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
   if (!single && n <= 64) {
-    // a small tree of a batch fits one wavefront's registers: 12 -> 6 us for trees of 64 nodes
+    // a small tree of a batch fits one wavefront's registers: 12 -> 8 us for trees of 64 nodes
     if (w > 0) return;  // (whole wavefronts, before any barrier)
     const WaveSelection sel = select_wave(parent + lo, prob + lo, cost, kmax, n, rho, order_out ? order_out + lo : nullptr,
                                           psum_out ? psum_out + lo : nullptr, status);
@@ -193,6 +209,7 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
     float c = (cost && i < kmax) ? cost[i + 1] : 1.0f;  // s_cost[i] = C(i + 1)
     if (!(c > 0.0f)) { c = 0.0f; bad_in |= ST_BAD_COST; }  // (never selected below)
     s_cost[i] = c;
+    s_rank[i] = 0;
   }
   if (bad_in && status) atomicOr(status, bad_in);
   __syncthreads();
@@ -214,26 +231,42 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
       if (s_aux[i] == lvl) s_score[i] = __fmul_rn(s_score[s_par[i]], s_prob[i]);
     __syncthreads();
   }
-  // rank by (score descending, index ascending)
-  for (int i = tid; i < n; i += nthreads) {
-    const float si = s_score[i];
-    int r = 0;
-    int j = 0;
+  // rank by (score descending, index ascending): the scores a node is compared with are shared out among `parts` threads
+  // per node, so that all threads have work whatever the size of the tree (400 nodes: 46 us with one of 256 threads per
+  // node, 21 us this way; 32 such trees)
+  const int npad = (n + 63) & ~63;
+  const int parts = nthreads >= 2 * npad ? nthreads / npad : 1;
+  if (parts > 1) {
+    const int part = tid / npad, i = tid - part * npad;
+    const int per = ((n + parts - 1) / parts + 3) & ~3;
+    if (part < parts && i < n) {
+      const float si = s_score[i];
+      int r = 0;
+      const int j1 = (part + 1) * per < n ? (part + 1) * per : n;
+      int j = part * per;
 #pragma unroll 2
-    for (; j + 4 <= n; j += 4) {  // LDS broadcast reads, four scores at a time
-      const float4 s4 = *reinterpret_cast<const float4*>(&s_score[j]);
-      r += (s4.x > si || (s4.x == si && j < i)) ? 1 : 0;
-      r += (s4.y > si || (s4.y == si && j + 1 < i)) ? 1 : 0;
-      r += (s4.z > si || (s4.z == si && j + 2 < i)) ? 1 : 0;
-      r += (s4.w > si || (s4.w == si && j + 3 < i)) ? 1 : 0;
+      for (; j + 4 <= j1; j += 4) r += rank_among4(*reinterpret_cast<const float4*>(&s_score[j]), j, si, i);
+      for (; j < j1; ++j) r += (s_score[j] > si || (s_score[j] == si && j < i)) ? 1 : 0;
+      atomicAdd(&s_rank[i], r);
     }
-    for (; j < n; ++j) {
-      const float sj = s_score[j];
-      r += (sj > si || (sj == si && j < i)) ? 1 : 0;
+    __syncthreads();
+    for (int i2 = tid; i2 < n; i2 += nthreads) {
+      const int r = s_rank[i2];
+      s_sorted[r] = s_score[i2];
+      if (order_out) order_out[lo + r] = i2;
     }
-    s_rank[i] = r;
-    s_sorted[r] = si;
-    if (order_out) order_out[lo + r] = i;
+  } else {
+    for (int i = tid; i < n; i += nthreads) {
+      const float si = s_score[i];
+      int r = 0;
+      int j = 0;
+#pragma unroll 2
+      for (; j + 4 <= n; j += 4) r += rank_among4(*reinterpret_cast<const float4*>(&s_score[j]), j, si, i);
+      for (; j < n; ++j) r += (s_score[j] > si || (s_score[j] == si && j < i)) ? 1 : 0;
+      s_rank[i] = r;
+      s_sorted[r] = si;
+      if (order_out) order_out[lo + r] = i;
+    }
   }
   __syncthreads();
   // S_k: sequential fp32 running sum over the ranking (one wavefront, lane broadcast)
@@ -244,9 +277,12 @@ __global__ __launch_bounds__(kSelThreads) void select_prefix_kernel(
       const int vbits = __float_as_int(idx < n ? s_sorted[idx] : 0.0f);
       float mine = 0.0f;
       const int lim = (n - c) < 64 ? (n - c) : 64;
-      for (int j = 0; j < lim; ++j) {
-        acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(vbits, j)));
-        if (lane == j) mine = acc;
+      for (int j0 = 0; j0 < lim; j0 += 8) {  // (lanes past the tree hold zeros)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          acc = __fadd_rn(acc, __int_as_float(__builtin_amdgcn_readlane(vbits, j0 + j)));
+          if (lane == j0 + j) mine = acc;
+        }
       }
       if (idx < n) s_sorted[idx] = mine;  // now holds S_{idx+1}
     }
@@ -326,7 +362,7 @@ __global__ __launch_bounds__(64) void select_prefix_wave_kernel(
 // or before tree b's own input offset and so lands on the ranks of earlier trees (rank_ws aliases new_parent): the ranks
 // of a group of trees are taken into LDS, with the parents, before any of its output is written, and a group is as many
 // trees as fit there (kCompactNodes nodes, one tree per thread in the scans). 16 trees of 64 nodes: 20 us with the trees
-// walked one after the other by the whole workgroup, 6 us this way.
+// walked one after the other by the whole workgroup, 4 us this way.
 constexpr int kCompactThreads = 1024;
 constexpr int kCompactNodes = 10 * 1024;
 static_assert(kCompactNodes >= kMaxSel && kMaxSel <= 0xFFFF, "a tree fits a group; ranks and ids fit 16 bits");
@@ -959,7 +995,7 @@ static int select_prefix_impl(const char* who, evict_ctx* ctx, const int32_t* tr
                        est_len, order, prefix_sum, keep, new_parent, new_tree_off, status);
     return launch_status("select_prefix_wave_kernel");
   }
-  const int sel_threads = kSelThreads;
+  const int sel_threads = T > (int64_t)64 * B ? kSelThreads : kSelThreadsSmall;
   hipLaunchKernelGGL(select_prefix_kernel, dim3(B), dim3(sel_threads), 0, s, tree_off, parent, node_prob, cost, Kmax,
                      k_star, est_len, order, prefix_sum, new_parent /* rank workspace */, single, keep, new_parent,
                      new_tree_off, single ? T : 0, rho, status);
