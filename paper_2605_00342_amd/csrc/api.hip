@@ -384,13 +384,27 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   rc = launch_router(ctx, w->g_moe, w->wg_packed, T, aux, s);
   if (rc) return rc;
   EVICT_MARK(5);
-  // token tiles per work-list slot of the grouped GEMMs: 2 once experts mostly have more than 16 tokens
+  // token tiles of 16 per work-list slot of the grouped GEMMs
   const int nt_exp = ctx->moe_nt ? ctx->moe_nt : 1;
+  GemmArgs gu = {}, dn = {};
+  gu.n_strips = 2 * m.F / 16;
+  gu.nkb = m.d * eb / 64;
+  dn.n_strips = m.d / 16;
+  dn.nkb = m.F * eb / 64;
+  // The tiled kernels take up to 96 tokens of an expert through one weight stream where the kernels below take 16 (or 32)
+  // at a time, but their workgroups run longer: they pay once experts mostly have several token tiles. Measured on whole
+  // layers (us, before -> tiled): 128 experts 96 nodes 143 -> 131, 175 -> 173, 217 -> 211 (child noise 0.2, 0.5, 1.0) but
+  // 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; 64 experts of width 1408 64 nodes 186 -> 163; 8 ranks' share of 128 experts
+  // 96 nodes 162 -> 163, 128 nodes 175 -> 166. So the line is an average of 6 tokens per expert.
+  const bool moe_auto = ctx->moe_nt == 0 && ctx->moe_gateup_kernel == 2 && ctx->moe_down_kernel == 1 && ctx->moe_pair_down == 2 &&
+                        ctx->moe_down_ws == 0;
+  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= 6 * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
+                     tile_grouped_applies(dn, EPI_F32);
   // expert weights fetched with non-temporal loads: they are read once per call (up to the further token tiles
   // of an expert, which run next to the first on the same XCD), and kept out of the caches they leave the
   // activations and projection weights of the next kernels there
   const int moe_nt = ctx->moe_nt_loads == 2 ? 1 : ctx->moe_nt_loads;
-  rc = launch_topk_union(ctx, T, aux, 16 * nt_exp, s);
+  rc = launch_topk_union(ctx, T, aux, tiled ? kTileSlotTokens : 16 * nt_exp, s);
   if (rc) return rc;
   if (aux) {
     if (aux->union_ids) EVICT_HIP_CHECK(hipMemcpyAsync(aux->union_ids, ctx->union_ids, (size_t)m.E * 4, hipMemcpyDeviceToDevice, s));
@@ -399,12 +413,10 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   }
   EVICT_MARK(6);
   {  // gate/up projections of the union experts + SiLU gating
-    GemmArgs a = {};
+    GemmArgs a = gu;
     a.W = (const u32x4*)w->w_gateup_packed;
     a.W_shared = (const u32x4*)w->ws_gateup_packed;
     a.n_routed = m.E;
-    a.n_strips = 2 * m.F / 16;
-    a.nkb = m.d * eb / 64;
     a.group_stride = (long long)a.n_strips * a.nkb * 64;
     a.X = ctx->h_norm;
     a.ldx_bytes = (long long)m.d * eb;
@@ -420,17 +432,15 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     // where its chunks line up with the XCDs, see gateup_waves, else from 128)
     a.wave_strip = ctx->moe_gateup_kernel == 2 ? (T >= (gateup_waves(a) != 4 ? 64 : 128) ? 1 : 0) : ctx->moe_gateup_kernel;
     a.chunk_units = ctx->moe_chunk_gateup;
-    rc = launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
+    rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }
   EVICT_MARK(7);
   {  // down projections
-    GemmArgs a = {};
+    GemmArgs a = dn;
     a.W = (const u32x4*)w->w_down_packed;
     a.W_shared = (const u32x4*)w->ws_down_packed;
     a.n_routed = m.E;
-    a.n_strips = m.d / 16;
-    a.nkb = m.F * eb / 64;
     a.group_stride = (long long)a.n_strips * a.nkb * 64;
     a.X = ctx->act;
     a.ldx_bytes = (long long)m.F * eb;
@@ -453,7 +463,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     const bool can_pair = nt_exp == 1 && a.wave_strip && a.n_strips % 8 == 0 && (a.nkb * 2 <= 64 || wide16);
     const bool pair = can_pair && (ctx->moe_pair_down == 2 ? T >= 128 : ctx->moe_pair_down == 1);
     a.pair_tiles = pair ? 1 : 0;
-    rc = launch_gemm(m.dtype, EPI_F32, a, pair ? 2 : nt_exp, ctx->moe_grid, s);
+    rc = tiled ? launch_gemm_tile_grouped(EPI_F32, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_F32, a, pair ? 2 : nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }
   EVICT_MARK(8);

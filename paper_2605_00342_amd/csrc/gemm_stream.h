@@ -771,4 +771,210 @@ __global__ __launch_bounds__(WS * 64) void gemm_dense_strip_kernel(const GemmArg
   }
 }
 
+// ------------------------------------------------------------------------------------
+// Tiled GEMM for many tokens per weight matrix: WS wavefronts take WS * NS consecutive strips (NS per wavefront, NS = 2
+// for a gate / up pair) and up to 16 * NT tokens at once. The weight blocks of a strip go from global memory straight
+// into the registers of the one wavefront that owns the strip (packed layout: a block is one coalesced load and one
+// MFMA operand), a rolling window of WIN blocks per strip; the token operand, which all wavefronts share, goes through
+// LDS in stages of WS contraction blocks, two buffers, each wavefront fetching one block of every token tile D stages
+// ahead (loads return in order: an operand stage is behind the weights requested before it, so with short stages one
+// stage ahead exposes the latency of memory in each). So LDS holds 2 * NT * WS KiB whatever the contraction length, an
+// expert's weights are fetched once for all of its (up to 16 * NT) tokens, and every LDS fragment feeds NS MFMAs, every
+// weight register one per token tile.
+// Sums run over the contraction in ascending order in one accumulator, as in the strip kernels above: same results bit
+// for bit. All loops are unrolled over the compile-time block count NKB so that every wait is by queue position.
+// Bound by memory up to a few tokens tiles per expert, by the L2 -> CU path beyond. Gate / up of 128 experts 2048 x 768,
+// 912 tokens (57 per expert): one 16-token tile at a time re-reads every expert four times, 312 us; this kernel 154 us
+// (5.2 TB/s of weights read once); 226 tokens over 111 experts 125 -> 109 us (6.4 TB/s). Down: 145 -> 91, 68 -> 61.5 us.
+// ------------------------------------------------------------------------------------
+template <int EPI, int NT, int NS, int WS, int WIN, int D, int NKB, bool GROUPED, bool NTL>
+__global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_tile_kernel(const GemmArgs a) {
+  static_assert(EPI != EPI_SWIGLU || NS == 2, "a gate / up pair per wavefront");
+  constexpr int KC = WS;                        // contraction blocks per stage
+  constexpr int NST = (NKB + KC - 1) / KC;      // stages
+  static_assert(WIN <= NKB, "the window holds blocks of one strip");
+  extern __shared__ __attribute__((aligned(16))) u32x4 s_x[];  // [2][NT][KC][64]
+  const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nsg = (a.n_strips + WS * NS - 1) / (WS * NS);  // strip groups
+  bool first = true;
+
+  // NTL_: live token tiles of this piece of work
+  auto run = [&](auto ntl_tag, const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
+    constexpr int NTT = decltype(ntl_tag)::value;
+    const int strip_raw = (sg * WS + w) * NS;
+    const bool active = strip_raw < a.n_strips;  // the last group may be short: its idle wavefronts still stage and wait
+    const int strip = active ? strip_raw : a.n_strips - NS;
+    const char* xrow[NTT];
+    bool valid[NTT];
+#pragma unroll
+    for (int t = 0; t < NTT; ++t) {
+      int col = tok0 + t * 16 + lc;
+      valid[t] = active && col < ntok;
+      col = col < ntok ? col : ntok - 1;  // padded columns repeat the last token; never stored
+      const long long xr = GROUPED ? (a.x_by_token ? a.tok_of_pos[p0 + col] : p0 + col) : col;
+      xrow[t] = (const char*)a.X + xr * a.ldx_bytes + (lane >> 4) * 16;
+    }
+    const u32x4* wp = wbase + (long long)strip * NKB * 64 + lane;
+    auto load_w = [&](int i, int j) __attribute__((always_inline)) {
+      const u32x4* p = wp + ((long long)i * NKB + j) * 64;
+      return NTL ? __builtin_nontemporal_load(p) : *p;
+    };
+    u32x4 st[D][NTT], A[NS][WIN];
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+      if (s * KC + KC <= NKB || s * KC + w < NKB) {
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>(xrow[t] + (s * KC + w) * 64);
+      }
+    };
+    auto put = [&](int s) __attribute__((always_inline)) {
+      if (s * KC + KC <= NKB || s * KC + w < NKB) {
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) s_x[(((s & 1) * NT + t) * KC + w) * 64 + lane] = st[s % D][t];
+      }
+    };
+    // token operand first, weights behind it: the in-order load counter lets the operand be consumed while the weights fly
+    fetch(0);
+#pragma unroll
+    for (int j = 0; j < WIN; ++j)
+#pragma unroll
+      for (int i = 0; i < NS; ++i) A[i][j] = load_w(i, j);
+#pragma unroll
+    for (int s = 1; s < D; ++s)
+      if (s < NST) fetch(s);
+    if (!first) lds_barrier();  // every wavefront is done with the previous piece's operand
+    first = false;
+    put(0);
+    lds_barrier();
+    f32x4 acc[NS][NTT];
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int t = 0; t < NTT; ++t) acc[i][t] = f32x4{0, 0, 0, 0};
+    const int m0 = (lane >> 4) * 4;  // first of this lane's 4 rows in a strip
+    uint2 res[NS][NTT];              // residual values of this lane's elements, requested ahead of the stream
+    if (EPI == EPI_RESID) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) {
+          const int col = tok0 + t * 16 + lc;
+          res[i][t] = *reinterpret_cast<const uint2*>((const uint16_t*)a.resid + (long long)(col < ntok ? col : ntok - 1) * a.ldo + (strip + i) * 16 + m0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+      const int kn = s * KC + KC <= NKB ? KC : NKB - s * KC;
+      if (s + D < NST) fetch(s + D);
+      const u32x4* sx = s_x + (s & 1) * NT * KC * 64 + lane;
+      u32x4 b[2][NTT];
+#pragma unroll
+      for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64];
+#pragma unroll
+      for (int jj = 0; jj < kn; ++jj) {
+        const int j = s * KC + jj;
+        if (jj + 1 < kn) {
+#pragma unroll
+          for (int t = 0; t < NTT; ++t) b[(jj + 1) & 1][t] = sx[(t * KC + jj + 1) * 64];
+        }
+#pragma unroll
+        for (int t = 0; t < NTT; ++t)
+#pragma unroll
+          for (int i = 0; i < NS; ++i) acc[i][t] = mfma_block<BF16>(A[i][j % WIN], b[jj & 1][t], acc[i][t]);
+        if (j + WIN < NKB) {
+#pragma unroll
+          for (int i = 0; i < NS; ++i) A[i][j % WIN] = load_w(i, j + WIN);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the refills stay right behind their MFMAs: the window stays full
+      }
+      if (s + 1 < NST) {
+        put(s + 1);  // (that buffer's last readers passed the barrier before this stage)
+        lds_barrier();
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < NTT; ++t) {
+      const int col = tok0 + t * 16 + lc;
+      if (EPI == EPI_SWIGLU) {
+        if (valid[t]) {
+          f32x4 r4;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) r4[q] = (acc[0][t][q] / (1.0f + __expf(-acc[0][t][q]))) * acc[NS - 1][t][q];
+          store4<BF16>(a.out0, (long long)(p0 + col) * a.ldo + (strip >> 1) * 16 + m0, r4);
+        }
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const f32x4 sum = acc[i][t];
+        const bool ok = valid[t] && strip + i < a.n_strips;
+        if (EPI == EPI_F32) {
+          if (ok) *reinterpret_cast<f32x4*>((float*)a.out0 + (long long)(p0 + col) * a.ldo + (strip + i) * 16 + m0) = sum;
+        } else if (EPI == EPI_RESID) {
+          if (ok) {
+            const long long o = (long long)col * a.ldo + (strip + i) * 16 + m0;
+            const f32x4 r = {__uint_as_float(res[i][t].x << 16), __uint_as_float(res[i][t].x & 0xFFFF0000u),
+                             __uint_as_float(res[i][t].y << 16), __uint_as_float(res[i][t].y & 0xFFFF0000u)};
+            store4<BF16>(a.out0, o, r + sum);
+          }
+        } else if (EPI == EPI_QKV) {  // rotate pairs (i, i + D/2), which sit 32 lanes apart
+          const int spd = a.D >> 4;  // strips per head
+          const int head = (strip + i) / spd, js = strip + i - head * spd;
+          const int half = a.D >> 1;
+          const int g4 = lane >> 4;
+          const int idx = js * 8 + (g4 & 1) * 4;  // index inside the half
+          const bool rot = head < a.Hq + a.Hkv;
+          const float* cs = a.rope_cs + (long long)(col < ntok ? col : 0) * a.D + idx;
+          const f32x4 cv = *reinterpret_cast<const f32x4*>(cs), sv = *reinterpret_cast<const f32x4*>(cs + half);
+          f32x4 other, r4;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) other[q] = __shfl_xor(sum[q], 32);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float c1 = rot ? cv[q] : 1.0f, s1 = rot ? sv[q] : 0.0f;
+            r4[q] = (g4 < 2) ? (sum[q] * c1 - other[q] * s1) : (sum[q] * c1 + other[q] * s1);
+          }
+          if (ok) {
+            const int hrow = (g4 < 2 ? 0 : half) + idx;
+            if (head < a.Hq) store4<BF16>(a.out0, ((long long)col * a.Hq + head) * a.D + hrow, r4);
+            else if (head < a.Hq + a.Hkv) store4<BF16>(a.out1, ((long long)col * a.Hkv + (head - a.Hq)) * a.D + hrow, r4);
+            else store4<BF16>(a.out2, ((long long)col * a.Hkv + (head - a.Hq - a.Hkv)) * a.D + hrow, r4);
+          }
+        }
+      }
+    }
+  };
+  // the number of live token tiles is known per piece of work: one compiled body for each (for a token group of a dense
+  // projection, where all but the last are full: one for a single tile, one for more)
+  auto dispatch = [&](const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
+    const int live = (ntok - tok0 + 15) >> 4;
+    if (live <= 1) run(std::integral_constant<int, 1>{}, wbase, sg, p0, ntok, tok0);
+    else if (GROUPED && NT >= 3 && live == 2) run(std::integral_constant<int, (GROUPED && NT >= 3 ? 2 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else if (GROUPED && NT >= 4 && live == 3) run(std::integral_constant<int, (GROUPED && NT >= 4 ? 3 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else if (GROUPED && NT >= 5 && live == 4) run(std::integral_constant<int, (GROUPED && NT >= 5 ? 4 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else run(std::integral_constant<int, NT>{}, wbase, sg, p0, ntok, tok0);
+  };
+
+  if (GROUPED) {
+    const int total = *a.union_count * nsg;
+    for (int chunk = blockIdx.x; chunk < total; chunk += gridDim.x) {
+      const int slot = chunk / nsg;
+      const WorkRec* rec = a.work + slot;
+      const int ex = rec->expert;
+      const u32x4* wbase = ex < a.n_routed ? a.W + (long long)ex * a.group_stride
+                                           : a.W_shared + (long long)(ex - a.n_routed) * a.group_stride;
+      dispatch(wbase, chunk - slot * nsg, rec->p0, rec->ntok, 0);
+    }
+  } else {
+    // workgroup ids go round-robin over the 8 XCDs: the token groups of a strip group are 8 apart and share an L2
+    const int T = dyn_tokens(a.T_dev, a.T);
+    const unsigned ntg = (unsigned)a.dense_tiles;
+    const unsigned xcd = blockIdx.x & 7u, q = blockIdx.x >> 3;
+    const unsigned tg = q % ntg, sg = (q / ntg) * 8u + xcd;
+    if (sg >= (unsigned)nsg || (int)tg * NT * 16 >= T) return;  // (whole workgroup, before any barrier)
+    const int tok0 = (int)tg * NT * 16;
+    dispatch(a.W, (int)sg, 0, T < tok0 + NT * 16 ? T : tok0 + NT * 16, tok0);
+  }
+}
+
 }  // namespace evict

@@ -1393,6 +1393,24 @@ int launch_gemm_st(const GemmArgs& a, int nt, int grid, hipStream_t s) {
   EVICT_DENSE_STRIP_SHAPES(X, F32, EPI_QKV, 0) EVICT_DENSE_STRIP_SHAPES(X, F32, EPI_RESID, 0)
 constexpr size_t kDenseStripLdsMax = 128 * 1024;
 
+// tiled GEMM (see gemm_tile_kernel). Every instantiation, once, for the launchers and for the LDS attribute:
+// X(epilogue, token tiles, strips per wavefront, wavefronts, weight window, operand stages ahead, contraction blocks, grouped).
+// Grouped: slots of kTileSlotTokens tokens. Six wavefronts make 8 chunks of the 48 strip pairs of expert width 768, so the
+// same strips of an expert's consecutive slots share an XCD; fewer token tiles re-read the weights of busy experts (912
+// tokens, 128 experts: 172 us with four tiles, 153 with six), more spill.
+#define EVICT_TILE_GROUPED(X) \
+  X(EPI_SWIGLU, 6, 2, 6, 8, 1, 64, true) X(EPI_SWIGLU, 6, 2, 6, 8, 1, 128, true) \
+  X(EPI_F32, 6, 2, 4, 8, 1, 24, true) X(EPI_F32, 6, 2, 4, 8, 1, 44, true) X(EPI_F32, 6, 2, 4, 6, 1, 6, true) X(EPI_F32, 6, 2, 4, 8, 1, 8, true)
+// Dense: from the smallest tile of strips x tokens to the largest.
+#define EVICT_TILE_DENSE_NKB(X, EPI_, NKB_) \
+  X(EPI_, 2, 1, 4, 16, 4, NKB_, false) X(EPI_, 3, 1, 4, 8, 2, NKB_, false) X(EPI_, 2, 2, 4, 8, 2, NKB_, false) \
+  X(EPI_, 3, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 4, 8, 2, NKB_, false)
+#define EVICT_TILE_DENSE(X) \
+  EVICT_TILE_DENSE_NKB(X, EPI_QKV, 64) X(EPI_QKV, 6, 2, 4, 8, 2, 64, false) X(EPI_QKV, 6, 2, 8, 8, 2, 64, false) \
+  EVICT_TILE_DENSE_NKB(X, EPI_QKV, 128) X(EPI_QKV, 6, 2, 4, 8, 2, 128, false) X(EPI_QKV, 6, 2, 8, 8, 2, 128, false) \
+  EVICT_TILE_DENSE_NKB(X, EPI_RESID, 32) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 64) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 128)
+constexpr size_t tile_lds_bytes(int nt, int ws) { return (size_t)2 * nt * ws * 1024; }
+
 }  // namespace
 
 // Strip pairs (wavefronts) per workgroup: 6 when that makes the chunks per slot a multiple of 8. Chunk ids go
@@ -1433,6 +1451,72 @@ int launch_gemm_dense_strip(int dtype, int epi, GemmArgs a, int ntw, hipStream_t
     return EVICT_E_INVALID;
   }
   return launch_status("gemm_dense_strip_kernel");
+}
+
+bool tile_grouped_applies(const GemmArgs& a, int epi) {
+#define EVICT_TILE_HAS(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_) \
+  if (epi == EPI_ && a.nkb == NKB_) return a.n_strips % NS_ == 0;
+  EVICT_TILE_GROUPED(EVICT_TILE_HAS)
+#undef EVICT_TILE_HAS
+  return false;
+}
+
+// bf16; the caller has checked tile_grouped_applies and built the work list with slots of kTileSlotTokens tokens
+int launch_gemm_tile_grouped(int epi, const GemmArgs& a, int grid, hipStream_t s) {
+#define EVICT_TILE_LAUNCH(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                     \
+  static_assert(NT_ * 16 == kTileSlotTokens, "one slot is one workgroup's tokens");                                          \
+  if (epi == EPI_ && a.nkb == NKB_) {                                                                                        \
+    hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>), dim3(grid), dim3(WS_ * 64),  \
+                       tile_lds_bytes(NT_, WS_), s, a);                                                                      \
+    return launch_status("gemm_tile_kernel");                                                                                \
+  }
+  EVICT_TILE_GROUPED(EVICT_TILE_LAUNCH)
+#undef EVICT_TILE_LAUNCH
+  set_error("gemm_tile_kernel: no grouped variant for epilogue %d, %d contraction blocks", epi, a.nkb);
+  return EVICT_E_INVALID;
+}
+
+// The dense tile for this many strips and tokens: the smallest whose workgroups all run at once (one round of the 256
+// CUs), since a tile twice as large re-reads half as much but a workgroup's walk over the contraction costs the same
+// 10-20 us however few there are; the largest when none does. Measured (us): 320 strips x 64 blocks at 80 / 128 / 160 /
+// 226 / 400 / 912 tokens 10.5 / 12.1 / 15.7 / 17.6 / 25.6 / 38.9 by this rule; the next smaller or larger tile 0.5-5 more.
+constexpr int kTileRound = 256;
+bool tile_dense_applies(const GemmArgs& a, int epi) {
+#define EVICT_TILE_HAS(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_) \
+  if (epi == EPI_ && a.nkb == NKB_) return a.n_strips % 2 == 0;
+  EVICT_TILE_DENSE(EVICT_TILE_HAS)
+#undef EVICT_TILE_HAS
+  return false;
+}
+
+int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
+  // two passes over the tiles, smallest first: the first that fits one round, else the last there is
+  int fit = -1, i = 0, last = -1;
+#define EVICT_TILE_FIT(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                        \
+  if (epi == EPI_ && a.nkb == NKB_) {                                                                                        \
+    const int wgs = ((a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_)) * ((a.T + 16 * NT_ - 1) / (16 * NT_));                      \
+    if (fit < 0 && wgs <= kTileRound) fit = i;                                                                               \
+    last = i;                                                                                                                \
+  }                                                                                                                          \
+  ++i;
+  EVICT_TILE_DENSE(EVICT_TILE_FIT)
+#undef EVICT_TILE_FIT
+  if (fit < 0) fit = last;
+  i = 0;
+#define EVICT_TILE_LAUNCH(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                     \
+  if (i++ == fit) {                                                                                                          \
+    a.dense_tiles = (a.T + 16 * NT_ - 1) / (16 * NT_);                                                                       \
+    const int nsg = (a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_);                                                              \
+    hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, false>),                             \
+                       dim3(((nsg + 7) / 8) * 8 * a.dense_tiles), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);           \
+  }
+  EVICT_TILE_DENSE(EVICT_TILE_LAUNCH)
+#undef EVICT_TILE_LAUNCH
+  if (fit < 0) {
+    set_error("gemm_tile_kernel: no dense variant for epilogue %d, %d contraction blocks", epi, a.nkb);
+    return EVICT_E_INVALID;
+  }
+  return launch_status("gemm_tile_kernel");
 }
 
 int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStream_t s) {
@@ -1504,6 +1588,13 @@ int kernels_setup(const evict_model_desc& m) {
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDenseStripLdsMax));
   EVICT_DENSE_STRIP_ALL(EVICT_DS_ATTR)
 #undef EVICT_DS_ATTR
+#define EVICT_TILE_ATTR(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                       \
+  if (tile_lds_bytes(NT_, WS_) > 64 * 1024)                                                                                  \
+    EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, GROUPED_>, \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(NT_, WS_)));
+  EVICT_TILE_GROUPED(EVICT_TILE_ATTR)
+  EVICT_TILE_DENSE(EVICT_TILE_ATTR)
+#undef EVICT_TILE_ATTR
   EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_wave_gateup_kernel<BF16, 16, 16, 6, 64, 2>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
   EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)attn_partial_kernel<BF16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_partial_lds_bytes(128)));

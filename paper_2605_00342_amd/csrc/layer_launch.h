@@ -11,6 +11,11 @@ int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStre
 bool dense_strip_applies(const GemmArgs& a, int ntw);
 int gateup_waves(const GemmArgs& a);
 int launch_gemm_dense_strip(int dtype, int epi, GemmArgs a, int ntw, hipStream_t s);
+constexpr int kTileSlotTokens = 96;  // tokens per work-list slot of the grouped tiled GEMM
+bool tile_grouped_applies(const GemmArgs& a, int epi);
+int launch_gemm_tile_grouped(int epi, const GemmArgs& a, int grid, hipStream_t s);
+bool tile_dense_applies(const GemmArgs& a, int epi);
+int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s);
 int launch_pack(const void* src, long long src_group_bytes, int rows, int cols, int dtype, void* dst, int dst_strip0,
                 int dst_strip_step, long long dst_group_strips, int groups, int head_dim, hipStream_t s);
 int launch_prep(const evict_ctx* c, const int32_t* tree_off, const int32_t* parent, int B, int T, const int32_t* ctx_len,
