@@ -309,12 +309,16 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // QKV takes two token tiles per workgroup already from 17 tokens on: as fast as two workgroups per strip when
   // both tiles are full (9.6 vs 9.8 us at 32 tokens), and when the count in device memory turns out to fill one
   // tile only, there is no second grid half whose workgroups leave at once (7.3 vs 9.4 us at 7 of 32 tokens)
-  const int nt_qkv = ctx->dense_nt ? ctx->dense_nt : (T > 16 ? 2 : 1);
+  // (fewer strips than CUs, as in one rank's share of a layer: one strip per workgroup, and one token tile while that is
+  // one round of workgroups. 80 strips of 128 blocks, 32 tokens: 22 us with four strips each, 9 this way)
+  const int qkv_strips = (m.Hq + 2 * m.Hkv) * m.D / 16;
+  const bool few_strips = qkv_strips < 256;
+  const int nt_qkv = ctx->dense_nt ? ctx->dense_nt : ((few_strips ? qkv_strips * ((T + 15) / 16) > 256 : T > 16) ? 2 : 1);
   const int qkv_tiles = (T + 16 * nt_qkv - 1) / (16 * nt_qkv);
   // QKV: a workgroup takes several consecutive strips, so its token operand is fetched once and its weight loads
   // run ahead across the strips (measured: 2 strips with one token tile, 4 with more; the output projection, with a
   // third of the strips and twice the contraction length, is better left at one)
-  const int qkv_units = ctx->dense_units ? ctx->dense_units : (qkv_tiles >= 2 ? 4 : 2);
+  const int qkv_units = ctx->dense_units ? ctx->dense_units : (few_strips ? 1 : (qkv_tiles >= 2 ? 4 : 2));
   auto dense_grid = [&](int units, int du, int tiles) { return (((units + du - 1) / du + 7) / 8) * 8 * tiles; };
   // Projection weights are fetched with non-temporal loads. (Measured on a 48-layer stack, where no weight is
   // read twice within an iteration: never slower than ordinary loads at 1, 2 and 4 token tiles per strip, 5 % faster
@@ -325,6 +329,14 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // operand of the workgroup in LDS (gemm_dense_strip_kernel) instead of the contraction split. Measured:
   // pays from 128 tokens on with two token tiles per workgroup (the operand of two tiles must fit in LDS), from
   // 256 tokens on with one.
+  // Between the two: the tiled kernel, as soon as the contraction split would need more than one round of workgroups with
+  // two token tiles each (us, contraction split -> tiled: 320 strips of 64 blocks 48 tokens 13.7 -> 10.3, 128 tokens
+  // 16.1 -> 12.2 against one strip per wavefront, 912 tokens 59 -> 39; 128 strips of 128 blocks 64 tokens 12.3 against
+  // 14.3, so not yet, 80 tokens 21.4 -> 14.3, 226 tokens 41 -> 15, 912 tokens 72 -> 30).
+  auto dense_tiled = [&](const GemmArgs& a, int epi) {
+    return ctx->dense_kernel == 2 && !ctx->dense_nt && !ctx->dense_ntw && !ctx->dense_units && m.dtype == EVICT_BF16 && T > 32 &&
+           a.n_strips * ((T + 31) / 32) > 256 && tile_dense_applies(a, epi);
+  };
   auto dense_strip_shape = [&](const GemmArgs& a, int* ntw) {
     if (ctx->dense_kernel == 0) return false;
     int nt = ctx->dense_ntw ? ctx->dense_ntw : (dense_strip_applies(a, 2) ? 2 : 1);
@@ -336,7 +348,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   {  // q, k, v projections + rotation (positions ctx_len + depth)
     GemmArgs a = {};
     a.W = (const u32x4*)w->wqkv_packed;
-    a.n_strips = (m.Hq + 2 * m.Hkv) * m.D / 16;
+    a.n_strips = qkv_strips;
     a.nkb = m.d * eb / 64;
     a.X = ctx->x_norm;
     a.ldx_bytes = (long long)m.d * eb;
@@ -349,8 +361,9 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.dense_units = qkv_units;
     a.nt_loads = dense_ntl;
     int ntw;
-    rc = dense_strip_shape(a, &ntw) ? launch_gemm_dense_strip(m.dtype, EPI_QKV, a, ntw, s)
-                                         : launch_gemm(m.dtype, EPI_QKV, a, nt_qkv, dense_grid(a.n_strips, qkv_units, qkv_tiles), s);
+    rc = dense_tiled(a, EPI_QKV)       ? launch_gemm_tile_dense(EPI_QKV, a, s)
+         : dense_strip_shape(a, &ntw) ? launch_gemm_dense_strip(m.dtype, EPI_QKV, a, ntw, s)
+                                      : launch_gemm(m.dtype, EPI_QKV, a, nt_qkv, dense_grid(a.n_strips, qkv_units, qkv_tiles), s);
     if (rc) return rc;
     if (aux && aux->q) EVICT_HIP_CHECK(hipMemcpyAsync(aux->q, ctx->q, (size_t)T * HqD * eb, hipMemcpyDeviceToDevice, s));
   }
@@ -375,8 +388,9 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.dense_units = 1;
     a.nt_loads = dense_ntl;
     int ntw;
-    rc = dense_strip_shape(a, &ntw) ? launch_gemm_dense_strip(m.dtype, EPI_RESID, a, ntw, s)
-                                         : launch_gemm(m.dtype, EPI_RESID, a, nt_dense, dense_grid(a.n_strips, 1, dense_tiles), s);
+    rc = dense_tiled(a, EPI_RESID)     ? launch_gemm_tile_dense(EPI_RESID, a, s)
+         : dense_strip_shape(a, &ntw) ? launch_gemm_dense_strip(m.dtype, EPI_RESID, a, ntw, s)
+                                      : launch_gemm(m.dtype, EPI_RESID, a, nt_dense, dense_grid(a.n_strips, 1, dense_tiles), s);
     if (rc) return rc;
     if (aux && aux->h) EVICT_HIP_CHECK(hipMemcpyAsync(aux->h, ctx->h, (size_t)T * m.d * eb, hipMemcpyDeviceToDevice, s));
   }

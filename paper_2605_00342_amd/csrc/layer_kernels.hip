@@ -1480,6 +1480,7 @@ int launch_gemm_tile_grouped(int epi, const GemmArgs& a, int grid, hipStream_t s
 // CUs), since a tile twice as large re-reads half as much but a workgroup's walk over the contraction costs the same
 // 10-20 us however few there are; the largest when none does. Measured (us): 320 strips x 64 blocks at 80 / 128 / 160 /
 // 226 / 400 / 912 tokens 10.5 / 12.1 / 15.7 / 17.6 / 25.6 / 38.9 by this rule; the next smaller or larger tile 0.5-5 more.
+// Weights by non-temporal loads as everywhere: within 1 us of ordinary ones alone, 1 % of a layer faster in sequence.
 constexpr int kTileRound = 256;
 bool tile_dense_applies(const GemmArgs& a, int epi) {
 #define EVICT_TILE_HAS(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_) \
@@ -1507,7 +1508,7 @@ int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
   if (i++ == fit) {                                                                                                          \
     a.dense_tiles = (a.T + 16 * NT_ - 1) / (16 * NT_);                                                                       \
     const int nsg = (a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_);                                                              \
-    hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, false>),                             \
+    hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>),                              \
                        dim3(((nsg + 7) / 8) * 8 * a.dense_tiles), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);           \
   }
   EVICT_TILE_DENSE(EVICT_TILE_LAUNCH)
@@ -1590,7 +1591,7 @@ int kernels_setup(const evict_model_desc& m) {
 #undef EVICT_DS_ATTR
 #define EVICT_TILE_ATTR(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                       \
   if (tile_lds_bytes(NT_, WS_) > 64 * 1024)                                                                                  \
-    EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, GROUPED_>, \
+    EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>, \
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(NT_, WS_)));
   EVICT_TILE_GROUPED(EVICT_TILE_ATTR)
   EVICT_TILE_DENSE(EVICT_TILE_ATTR)

@@ -28,3 +28,17 @@ def test_slot_edges(n, batch):
 def test_widths(d, F, n_shared, n, k):
     case = layer_case(n, 400 + n, d, F, 16, k, n_shared=n_shared)
     check_against_oracle(case, run_case(case))
+
+
+# dense projections: token counts that pick each tile of strips x tokens in turn, with ragged last tiles (320 strips of 64
+# blocks and 128 of 128 blocks; one rank's share: 80 strips of 128 and 256 of 32)
+@pytest.mark.parametrize("n,batch", [(33, 1), (49, 1), (81, 1), (113, 1), (128, 1), (80, 2), (113, 2), (100, 3), (100, 4), (101, 6)])
+def test_dense_tiles(n, batch):
+    case = layer_case(n, 500 + n, 2048, 64, 16, 2, batch=batch, Hq=32, Hkv=4, D=128, L=20)
+    check_against_oracle(case, run_case(case))
+
+
+@pytest.mark.parametrize("n,batch", [(1, 1), (48, 1), (65, 1), (113, 1), (100, 3), (100, 5)])
+def test_dense_tiles_of_a_share(n, batch):
+    case = layer_case(n, 600 + n, 4096, 64, 16, 2, batch=batch, Hq=8, Hkv=1, D=128, L=20)
+    check_against_oracle(case, run_case(case))
