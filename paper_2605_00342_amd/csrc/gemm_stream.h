@@ -908,7 +908,24 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       for (int i = 0; i < NS; ++i) {
         const f32x4 sum = acc[i][t];
         const bool ok = valid[t] && strip + i < a.n_strips;
-        if (EPI == EPI_F32) {
+        if (EPI == EPI_ARGMAX) {
+          // best of the strip's 16 rows (lowest row on equal values): this lane's four, then across the lanes of the token
+          float bv = sum[0];
+          int bi = (strip + i) * 16 + m0;
+#pragma unroll
+          for (int q = 1; q < 4; ++q)
+            if (sum[q] > bv) { bv = sum[q]; bi = (strip + i) * 16 + m0 + q; }
+#pragma unroll
+          for (int o = 16; o <= 32; o <<= 1) {
+            const float ov = __shfl_xor(bv, o);
+            const int oi = __shfl_xor(bi, o);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+          }
+          if (ok && lane < 16) {
+            ((float*)a.out0)[(long long)col * a.ldo + strip + i] = bv;
+            ((int*)a.out1)[(long long)col * a.ldo + strip + i] = bi;
+          }
+        } else if (EPI == EPI_F32) {
           if (ok) *reinterpret_cast<f32x4*>((float*)a.out0 + (long long)(p0 + col) * a.ldo + (strip + i) * 16 + m0) = sum;
         } else if (EPI == EPI_RESID) {
           if (ok) {
@@ -944,14 +961,15 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     }
   };
-  // the number of live token tiles is known per piece of work: one compiled body for each (for a token group of a dense
-  // projection, where all but the last are full: one for a single tile, one for more)
+  // the number of live token tiles is known per piece of work: one compiled body for each (for a token group of the layer's
+  // projections, where all but the last are full: one for a single tile, one for more)
+  constexpr bool kEach = GROUPED || EPI == EPI_F32 || EPI == EPI_ARGMAX;
   auto dispatch = [&](const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
     const int live = (ntok - tok0 + 15) >> 4;
     if (live <= 1) run(std::integral_constant<int, 1>{}, wbase, sg, p0, ntok, tok0);
-    else if (GROUPED && NT >= 3 && live == 2) run(std::integral_constant<int, (GROUPED && NT >= 3 ? 2 : 1)>{}, wbase, sg, p0, ntok, tok0);
-    else if (GROUPED && NT >= 4 && live == 3) run(std::integral_constant<int, (GROUPED && NT >= 4 ? 3 : 1)>{}, wbase, sg, p0, ntok, tok0);
-    else if (GROUPED && NT >= 5 && live == 4) run(std::integral_constant<int, (GROUPED && NT >= 5 ? 4 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else if (kEach && NT >= 3 && live == 2) run(std::integral_constant<int, (kEach && NT >= 3 ? 2 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else if (kEach && NT >= 4 && live == 3) run(std::integral_constant<int, (kEach && NT >= 4 ? 3 : 1)>{}, wbase, sg, p0, ntok, tok0);
+    else if (kEach && NT >= 5 && live == 4) run(std::integral_constant<int, (kEach && NT >= 5 ? 4 : 1)>{}, wbase, sg, p0, ntok, tok0);
     else run(std::integral_constant<int, NT>{}, wbase, sg, p0, ntok, tok0);
   };
 

@@ -1409,6 +1409,11 @@ constexpr size_t kDenseStripLdsMax = 128 * 1024;
   EVICT_TILE_DENSE_NKB(X, EPI_QKV, 64) X(EPI_QKV, 6, 2, 4, 8, 2, 64, false) X(EPI_QKV, 6, 2, 8, 8, 2, 64, false) \
   EVICT_TILE_DENSE_NKB(X, EPI_QKV, 128) X(EPI_QKV, 6, 2, 4, 8, 2, 128, false) X(EPI_QKV, 6, 2, 8, 8, 2, 128, false) \
   EVICT_TILE_DENSE_NKB(X, EPI_RESID, 32) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 64) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 128)
+// LM head (vocabulary rows x tokens, weights read once).
+#define EVICT_TILE_LM_NKB(X, EPI_, NKB_) \
+  X(EPI_, 2, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 8, 8, 2, NKB_, false) X(EPI_, 6, 2, 8, 8, 2, NKB_, false)
+#define EVICT_TILE_LM(X) \
+  EVICT_TILE_LM_NKB(X, EPI_F32, 64) EVICT_TILE_LM_NKB(X, EPI_F32, 128) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 64) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 128)
 constexpr size_t tile_lds_bytes(int nt, int ws) { return (size_t)2 * nt * ws * 1024; }
 
 }  // namespace
@@ -1520,6 +1525,35 @@ int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
   return launch_status("gemm_tile_kernel");
 }
 
+// LM head, 151936 rows (us, contraction split -> tiled). 64 blocks: 16 tokens 101 (not yet: 112), 32 tokens 116 (118),
+// 48 tokens 161 -> 124, 64 173 -> 129, 96 215 -> 142, 128 270 -> 176. 128 blocks, where the split kernel re-reads its token
+// operand for every strip: 8 tokens 192 (not yet), 16 240 -> 212, 32 382 -> 225, 64 714 -> 249, 128 1308 -> 342.
+bool tile_lm_applies(const GemmArgs& a) {
+  return a.n_strips % 2 == 0 && ((a.nkb == 64 && a.T > 32) || (a.nkb == 128 && a.T > 8));
+}
+
+// 2, 4 or 6 token tiles at once, whichever takes the fewest passes over the weights
+int launch_gemm_tile_lm(int epi, GemmArgs a, hipStream_t s) {
+  const int nt = a.T <= 32 ? 2 : ((a.T + 95) / 96 < (a.T + 63) / 64 ? 6 : 4);
+  const int ws = a.T <= 64 ? 4 : 8;
+  a.dense_tiles = (a.T + 16 * nt - 1) / (16 * nt);
+  bool launched = false;
+#define EVICT_TILE_LAUNCH(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                     \
+  if (epi == EPI_ && a.nkb == NKB_ && nt == NT_ && ws == WS_) {                                                              \
+    const int nsg = (a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_);                                                              \
+    hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>),                              \
+                       dim3(((nsg + 7) / 8) * 8 * a.dense_tiles), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);           \
+    launched = true;                                                                                                         \
+  }
+  EVICT_TILE_LM(EVICT_TILE_LAUNCH)
+#undef EVICT_TILE_LAUNCH
+  if (!launched) {
+    set_error("gemm_tile_kernel: no LM head variant for epilogue %d, %d contraction blocks, %d token tiles", epi, a.nkb, nt);
+    return EVICT_E_INVALID;
+  }
+  return launch_status("gemm_tile_kernel");
+}
+
 int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStream_t s) {
 #define EVICT_GEMM_CASE(E_)                                                   \
   case E_:                                                                    \
@@ -1595,6 +1629,7 @@ int kernels_setup(const evict_model_desc& m) {
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes(NT_, WS_)));
   EVICT_TILE_GROUPED(EVICT_TILE_ATTR)
   EVICT_TILE_DENSE(EVICT_TILE_ATTR)
+  EVICT_TILE_LM(EVICT_TILE_ATTR)
 #undef EVICT_TILE_ATTR
   EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_wave_gateup_kernel<BF16, 16, 16, 6, 64, 2>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));

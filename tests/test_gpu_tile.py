@@ -1,13 +1,17 @@
 """The tiled GEMM at the sizes where its tiles end, through the whole layer protocol (every stage against the CPU oracle):
 experts with 1, 15, 16, 17, ... tokens up to several slots, strips that do not fill the last workgroup, shared experts."""
 import pytest
+import torch
 
 import synth
 
 pytestmark = pytest.mark.gpu
 
-pytest.importorskip("paper_2605_00342_amd")
+ev = pytest.importorskip("paper_2605_00342_amd")
+from paper_2605_00342_amd import harness  # noqa: E402
 from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
+
+DEV = "cuda:0"
 
 
 def layer_case(n, seed, d, F, E, k, n_shared=0, batch=1, Hq=8, Hkv=2, D=64, L=40, sigma=0.5):
@@ -42,3 +46,40 @@ def test_dense_tiles(n, batch):
 def test_dense_tiles_of_a_share(n, batch):
     case = layer_case(n, 600 + n, 4096, 64, 16, 2, batch=batch, Hq=8, Hkv=1, D=128, L=20)
     check_against_oracle(case, run_case(case))
+
+
+# LM head: score rows and arg max at every tile choice, ragged last tiles, strips that leave wavefronts idle; the count in
+# device memory smaller than the bound
+@pytest.mark.parametrize("d,T", [(2048, 33), (2048, 64), (2048, 65), (2048, 96), (2048, 97), (2048, 200), (4096, 9), (4096, 31),
+                                 (4096, 50), (4096, 128)])
+def test_lm_head_tiles(d, T):
+    cfg = synth.ModelCfg("lm", "bf16", d=d, Hq=4, Hkv=4, D=64, E=16, k=2, F=32)
+    V = 1184  # 74 strips
+    ctx = ev.evict_create(harness.model_desc(cfg, V), T, 1, 16)
+    try:
+        g = torch.Generator().manual_seed(d + T)
+        x = torch.randn(T, d, generator=g).to(DEV, torch.bfloat16)
+        w = (0.02 * torch.randn(V, d, generator=g)).to(DEV, torch.bfloat16)
+        gain = (1 + 0.1 * torch.randn(d, generator=g)).to(DEV, torch.bfloat16)
+        packed = torch.empty(V * d, dtype=torch.bfloat16, device=DEV)
+        ev.evict_pack_dense(ev.EVICT_BF16, w, V, d, packed)
+        xn = torch.zeros_like(x)
+        logits = torch.full((T, V), -7.0, device=DEV)
+        nxt, best = torch.zeros(T, dtype=torch.int32, device=DEV), torch.zeros(T, device=DEV)
+        ev.evict_lm_head_logits(ctx, x, gain, packed, T, logits, xn)
+        ev.evict_lm_head_argmax(ctx, x, gain, packed, T, nxt, best)
+        want = xn.double() @ w.double().T
+        # fp32 sums of d products of |x w| ~ 0.02: a few d * 2^-24 of the largest partial sum at most
+        assert float((logits - want).abs().max()) < 2e-4
+        val, idx = logits.max(-1)
+        assert torch.equal(best, val) and torch.equal(nxt.long(), idx)
+        few = torch.tensor([min(T, 18)], dtype=torch.int32, device=DEV)
+        part = torch.full((T, V), -7.0, device=DEV)
+        ev.evict_dynamic_tokens(ctx, few.data_ptr())
+        ev.evict_lm_head_logits(ctx, x, gain, packed, T, part)
+        ev.evict_dynamic_tokens(ctx, None)
+        torch.cuda.synchronize()
+        n = int(few.item())
+        assert torch.equal(part[:n], logits[:n]) and bool((part[n:] == -7.0).all())
+    finally:
+        ev.evict_destroy(ctx)
