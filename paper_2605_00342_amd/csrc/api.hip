@@ -409,10 +409,11 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // at a time, but their workgroups run longer: they pay once experts mostly have several token tiles. Measured on whole
   // layers (us, before -> tiled): 128 experts 96 nodes 143 -> 131, 175 -> 173, 217 -> 211 (child noise 0.2, 0.5, 1.0) but
   // 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; 64 experts of width 1408 64 nodes 186 -> 163; 8 ranks' share of 128 experts
-  // 96 nodes 162 -> 163, 128 nodes 175 -> 166. So the line is an average of 6 tokens per expert.
+  // 96 nodes 162 -> 163, 128 nodes 175 -> 166. So the line is an average of 6 tokens per expert, 10 for the long contraction
+  // of 4096 columns, where the contraction-split kernel keeps its token operand.
   const bool moe_auto = ctx->moe_nt == 0 && ctx->moe_gateup_kernel == 2 && ctx->moe_down_kernel == 1 && ctx->moe_pair_down == 2 &&
                         ctx->moe_down_ws == 0;
-  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= 6 * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
+  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= (gu.nkb == 64 ? 6 : 10) * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
                      tile_grouped_applies(dn, EPI_F32);
   // expert weights fetched with non-temporal loads: they are read once per call (up to the further token tiles
   // of an expert, which run next to the first on the same XCD), and kept out of the caches they leave the
@@ -446,6 +447,8 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     // where its chunks line up with the XCDs, see gateup_waves, else from 128)
     a.wave_strip = ctx->moe_gateup_kernel == 2 ? (T >= (gateup_waves(a) != 4 ? 64 : 128) ? 1 : 0) : ctx->moe_gateup_kernel;
     a.chunk_units = ctx->moe_chunk_gateup;
+    // (two strip pairs per chunk where the token operand stays in registers across them; at 8 tokens 9.4 us with one, 14.2)
+    if (a.chunk_units == 1 && a.nkb % 128 == 0 && m.dtype == EVICT_BF16 && T > 8 && (m.F / 16) % 2 == 0) a.chunk_units = 2;
     rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }

@@ -80,7 +80,7 @@ constexpr int kGemmThreads = kGemmWaves * 64;
 // the last token tile of an expert, so that later tiles find the weights in L2, lose more in the following
 // kernels than they save in this one.)
 template <typename ST, int NT, int KBW, int PF, int EPI, bool EXACT, int IS = 1, int NS = 0, bool NTL = false>
-__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2))) void gemm_stream_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT == 1 && KBW <= 8 ? 4 : 2))) void gemm_stream_kernel(const GemmArgs a) {
   constexpr int SPU = (EPI == EPI_SWIGLU) ? 2 : 1;  // strips per unit of work
   static_assert(EPI != EPI_SWIGLU || IS == 1, "gate/up strips are exchanged one at a time");
   __shared__ f32x4 s_part[2][kGemmWaves][IS * NT][64];
@@ -89,7 +89,8 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, known uniform
   const int upg = a.n_strips / SPU;
   const int nkb = a.nkb;
-  const int nchunks = (nkb + 63) >> 6;
+  constexpr int CB = EXACT && KBW > 8 ? KBW * kGemmWaves : 64;  // contraction blocks per step of the workgroup
+  const int nchunks = (nkb + CB - 1) / CB;
   int parity = 0;
 
   // One segment = `nunits` consecutive units (strips, or gate/up strip pairs) of one weight
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
       // block range of this wavefront inside chunk c: [b0, b0 + nb)
       auto range = [&](int c, int& b0, int& nb) {
         if (EXACT) {
-          b0 = c * 64 + w * KBW;
+          b0 = c * CB + w * KBW;
           nb = KBW;
         } else {
           int cb = nkb - c * 64;
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
               // a step (same registers; the queue position of every load stays known at compile time)
               const bool more = step + 1 < nsteps;
               const int itn = (step + 1) / nchunks, cn = (step + 1) - itn * nchunks;
-              const long long boff = (long long)(cn * 64 + w * KBW);
+              const long long boff = (long long)(cn * CB + w * KBW);
 #pragma unroll
               for (int i = 0; i < IS; ++i) {
                 const u32x4* pn = wbase + ((long long)(strip0 + itn * IS + i) * nkb + boff) * 64 + lane;
