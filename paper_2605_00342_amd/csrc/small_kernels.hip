@@ -916,9 +916,10 @@ int union_mask_plan(int T, int k, int E, size_t* lds_bytes) {
   const int P = T * k;
   const size_t words = (size_t)(T + 63) / 64;
   size_t lds = sizeof(int) * union_lds_ints(P, E);
-  const size_t mask_bytes = 8 * (size_t)E * words;
-  const int use_masks = lds + mask_bytes <= 60 * 1024 ? 1 : 0;
+  const size_t mask_bytes = union_mask_bytes(E, (int)words), before_bytes = union_before_bytes(E, (int)words);
+  const int use_masks = lds + mask_bytes + before_bytes <= 60 * 1024 ? 2 : (lds + mask_bytes <= 60 * 1024 ? 1 : 0);
   if (use_masks) lds += mask_bytes;
+  if (use_masks == 2) lds += before_bytes;
   *lds_bytes = lds;
   return use_masks;
 }
