@@ -619,25 +619,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       f32x4 acc = {0, 0, 0, 0};
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) acc = mfma_block<BF16>(kf[kt & 1][kb], Qf[kb], acc);
-      // (scores stay unscaled here: the scale is positive, so the maximum commutes with it, and it is applied
-      // inside the one multiply-add that feeds the exponential below)
-      if (full) {  // a whole chunk of cache keys: every key is visible to every row
-        // (maximum as the median with +inf: one instruction each, where fmaxf first spends one per operand on
-        // quieting signalling NaNs, which matrix-core outputs of finite inputs cannot be)
-        const float m01 = __builtin_amdgcn_fmed3f(acc[0], acc[1], INFINITY), m23 = __builtin_amdgcn_fmed3f(acc[2], acc[3], INFINITY);
-        mx = __builtin_amdgcn_fmed3f(mx, __builtin_amdgcn_fmed3f(m01, m23, INFINITY), INFINITY);
-      } else {
+      S[kt] = acc;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // Row maxima once all tiles are on their way through the matrix cores: taken tile by tile they waited for each tile's
+    // last MFMA. (Scores stay unscaled: the scale is positive, so the maximum commutes with it, and it is applied inside
+    // the one multiply-add that feeds the exponential below.)
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      if (!full) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int key = kt * 16 + kq * 4 + j;  // (the draft-node split has a single chunk: key = node index)
           const uint64_t word = key < 64 ? a0 : a1;
           const bool vis = key < nkeys && ((word >> (key & 63)) & 1ull);
-          acc[j] = vis ? acc[j] : -INFINITY;
-          mx = fmaxf(mx, acc[j]);
+          S[kt][j] = vis ? S[kt][j] : -INFINITY;
         }
       }
-      S[kt] = acc;
-      __builtin_amdgcn_sched_barrier(0);
+      const f32x4 v = S[kt];
+      mx = fmaxf(fmaxf(fmaxf(v[0], v[1]), mx), fmaxf(v[2], v[3]));
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -674,14 +674,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     m_run = m_new;
 #pragma unroll
     for (int bk = 0; bk < KT / 2; ++bk) Lsum = mfma_block<BF16>(Pf[bk], ones, Lsum);  // the sums use the rounded weights
-    // V^T fragments of the next output tile are requested before the MFMAs of the current one
+    // V^T fragments of the next output tile are requested before the MFMAs of the current one. From output tile 4 on the
+    // XOR of the column swaps the two halves of a fragment: the halves of the weights are swapped to match, once for all
+    // tiles, instead of those of every fragment (48 register moves fewer per chunk).
+    u32x4 Ps[KT / 2];
+    if (DT > 4) {
+#pragma unroll
+      for (int bk = 0; bk < KT / 2; ++bk) Ps[bk] = u32x4{Pf[bk][2], Pf[bk][3], Pf[bk][0], Pf[bk][1]};
+    }
     auto load_v = [&](u32x4(&dst)[KT / 2], int dt) {
 #pragma unroll
       for (int bk = 0; bk < KT / 2; ++bk) {
         const uint32_t* vrow = s_vt + (dt * 16 + ln) * (LDV / 2);
         const uint2 lo2 = *reinterpret_cast<const uint2*>(vrow + ((bk * 16 + kq * 2) ^ (dt << 1)));
         const uint2 hi2 = *reinterpret_cast<const uint2*>(vrow + ((bk * 16 + kq * 2 + 8) ^ (dt << 1)));
-        dst[bk] = u32x4{lo2.x, lo2.y, hi2.x, hi2.y};
+        dst[bk] = dt & 4 ? u32x4{hi2.x, hi2.y, lo2.x, lo2.y} : u32x4{lo2.x, lo2.y, hi2.x, hi2.y};
       }
     };
     u32x4 vf[2][KT / 2];
@@ -692,7 +699,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       __builtin_amdgcn_sched_barrier(0);
       f32x4 acc = O[dt];
 #pragma unroll
-      for (int bk = 0; bk < KT / 2; ++bk) acc = mfma_block<BF16>(Pf[bk], vf[dt & 1][bk], acc);
+      for (int bk = 0; bk < KT / 2; ++bk) acc = mfma_block<BF16>(dt & 4 ? Ps[bk] : Pf[bk], vf[dt & 1][bk], acc);
       O[dt] = acc;
       __builtin_amdgcn_sched_barrier(0);
     }
