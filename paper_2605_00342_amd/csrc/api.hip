@@ -408,12 +408,13 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // The tiled kernels take up to 96 tokens of an expert through one weight stream where the kernels below take 16 (or 32)
   // at a time, but their workgroups run longer: they pay once experts mostly have several token tiles. Measured on whole
   // layers (us, before -> tiled): 128 experts 96 nodes 143 -> 131, 175 -> 173, 217 -> 211 (child noise 0.2, 0.5, 1.0) but
-  // 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; 64 experts of width 1408 64 nodes 186 -> 163; 8 ranks' share of 128 experts
-  // 96 nodes 162 -> 163, 128 nodes 175 -> 166. So the line is an average of 6 tokens per expert, 10 for the long contraction
-  // of 4096 columns, where the contraction-split kernel keeps its token operand.
+  // 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; 8 ranks' share of 128 experts 128 nodes 175 -> 150, 4 x 100 nodes
+  // 309 -> 212. So the line is an average of 6 tokens per expert; 8 where six wavefronts do not share out an expert's strip
+  // pairs evenly (width 1408: 64 nodes, 6 tokens per expert, between 2 % faster and 2 % slower by the routing); 10 for the
+  // long contraction of 4096 columns, where the contraction-split kernel keeps its token operand.
   const bool moe_auto = ctx->moe_nt == 0 && ctx->moe_gateup_kernel == 2 && ctx->moe_down_kernel == 1 && ctx->moe_pair_down == 2 &&
                         ctx->moe_down_ws == 0;
-  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= (gu.nkb == 64 ? 6 : 10) * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
+  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= (gu.nkb == 64 ? (gu.n_strips % 12 == 0 ? 6 : 8) : 10) * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
                      tile_grouped_applies(dn, EPI_F32);
   // expert weights fetched with non-temporal loads: they are read once per call (up to the further token tiles
   // of an expert, which run next to the first on the same XCD), and kept out of the caches they leave the
