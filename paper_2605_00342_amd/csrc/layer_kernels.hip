@@ -1819,13 +1819,12 @@ int launch_router(const evict_ctx* c, const void* gain, const void* wg, int T, c
   float* a_lg = aux ? aux->router_logits : nullptr;
   // One strip per workgroup spreads W_g over the chip; with so many token tiles that this takes more than one round of the
   // 256 CUs (a workgroup's LDS fills one), two or more: every workgroup normalises its 16 tokens again, so fewer is less
-  // work too. 912 tokens, 128 experts: 14.3 -> 9.0 us. (Strips x contraction slices stay 16, and with them the LDS.)
+  // work too. 912 tokens, 128 experts: 14.3 -> 9.0 us. (Strips x contraction slices stay what the LDS is sized for.)
   int spw = router_strips_per_wg(m);
+  const int items = spw * router_ksplit(m);
   const int tiles = (T + 15) / 16, nstrips = m.E / 16;
-  while (tiles * ((nstrips + spw - 1) / spw) > 256 && spw * 2 <= nstrips && spw * 2 <= kRouterWaves) spw *= 2;
-  int ksplit = kRouterWaves / spw;
-  const int nkb = m.d * (m.dtype == EVICT_BF16 ? 2 : 4) / 64;
-  ksplit = ksplit > nkb ? nkb : (ksplit < 1 ? 1 : ksplit);
+  while (tiles * ((nstrips + spw - 1) / spw) > 256 && spw * 2 <= nstrips && spw * 2 <= items) spw *= 2;
+  const int ksplit = items / spw;
   const dim3 grid(tiles, (nstrips + spw - 1) / spw);
   if (m.dtype == EVICT_BF16)
     hipLaunchKernelGGL(router_logits_kernel<BF16>, grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T, m.d,

@@ -83,3 +83,10 @@ def test_lm_head_tiles(d, T):
         assert torch.equal(part[:n], logits[:n]) and bool((part[n:] == -7.0).all())
     finally:
         ev.evict_destroy(ctx)
+
+
+# many tokens: the router takes several expert strips per workgroup; short contractions have fewer slices than wavefronts
+@pytest.mark.parametrize("d,E,n,batch", [(256, 128, 120, 5), (2048, 128, 120, 5), (512, 256, 100, 4), (96, 128, 128, 6)])
+def test_router_strips(d, E, n, batch):
+    case = layer_case(n, 900 + d, d, 32, E, 2, batch=batch, Hq=2, Hkv=2, D=64, L=5)
+    check_against_oracle(case, run_case(case))
