@@ -782,8 +782,15 @@ __global__ __launch_bounds__(WS * 64) void gemm_dense_strip_kernel(const GemmArg
 // stage ahead exposes the latency of memory in each). So LDS holds 2 * NT * WS KiB whatever the contraction length, an
 // expert's weights are fetched once for all of its (up to 16 * NT) tokens, and every LDS fragment feeds NS MFMAs, every
 // weight register one per token tile.
-// Sums run over the contraction in ascending order in one accumulator, as in the strip kernels above: same results bit
-// for bit. All loops are unrolled over the compile-time block count NKB so that every wait is by queue position.
+// Sums: chains of CH contraction blocks, added up in ascending order. Where this kernel stands in for a strip kernel (the
+// expert projections of up to 64 blocks) CH is the whole contraction, one chain, and the results are the strip kernel's bit
+// for bit. Where it stands in for the contraction split (the layer's projections, the LM head, gate / up of 128 blocks) CH is
+// NKB / 8: that kernel adds up eight chains, and one chain eight times as long loses nearly three times as much to rounding
+// (score rows against 64-bit sums of the same bf16 operands, relative: 2048 columns 1.02e-7 with eight chains, 2.70e-7 with
+// one; 4096 columns 1.37e-7, 3.96e-7); up to 64 blocks these are the same eight chains and the same results bit for bit. The total of the chains so far takes NS * NT more
+// fragments: with six token tiles there is room for it only with one set of operand fragments, each refilled behind its last
+// MFMA, in place of two (CH < NKB and NT > 4).
+// All loops are unrolled over the compile-time block count NKB so that every wait is by queue position.
 // Bound by memory up to a few tokens tiles per expert, by the L2 -> CU path beyond. Gate / up of 128 experts 2048 x 768,
 // 912 tokens (57 per expert): one 16-token tile at a time re-reads every expert four times, 312 us; this kernel 154 us
 // (5.2 TB/s of weights read once); 226 tokens over 111 experts 125 -> 109 us (6.4 TB/s). Down: 145 -> 91, 68 -> 61.5 us.
@@ -791,6 +798,8 @@ __global__ __launch_bounds__(WS * 64) void gemm_dense_strip_kernel(const GemmArg
 template <int EPI, int NT, int NS, int WS, int WIN, int D, int NKB, bool GROUPED, bool NTL>
 __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_tile_kernel(const GemmArgs a) {
   static_assert(EPI != EPI_SWIGLU || NS == 2, "a gate / up pair per wavefront");
+  constexpr int CH = !GROUPED || NKB > 64 ? NKB / 8 : NKB;  // contraction blocks per chain of sums
+  static_assert(NKB % CH == 0, "whole chains");
   constexpr int KC = WS;                        // contraction blocks per stage
   constexpr int NST = (NKB + KC - 1) / KC;      // stages
   static_assert(WIN <= NKB, "the window holds blocks of one strip");
@@ -847,12 +856,8 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     first = false;
     put(0);
     lds_barrier();
-    f32x4 acc[NS][NTT];
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-#pragma unroll
-      for (int t = 0; t < NTT; ++t) acc[i][t] = f32x4{0, 0, 0, 0};
-    const int m0 = (lane >> 4) * 4;  // first of this lane's 4 rows in a strip
+    f32x4 acc[NS][NTT], sum_of[NS][NTT];  // the chain being summed, the chains before it
+    const int m0 = (lane >> 4) * 4;       // first of this lane's 4 rows in a strip
     uint2 res[NS][NTT];              // residual values of this lane's elements, requested ahead of the stream
     if (EPI == EPI_RESID) {
 #pragma unroll
@@ -868,20 +873,30 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       const int kn = s * KC + KC <= NKB ? KC : NKB - s * KC;
       if (s + D < NST) fetch(s + D);
       const u32x4* sx = s_x + (s & 1) * NT * KC * 64 + lane;
-      u32x4 b[2][NTT];
+      constexpr bool kOneSet = CH < NKB && NTT > 4;
+      constexpr int NB = kOneSet ? 1 : 2;
+      u32x4 b[NB][NTT];
 #pragma unroll
       for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64];
 #pragma unroll
       for (int jj = 0; jj < kn; ++jj) {
         const int j = s * KC + jj;
-        if (jj + 1 < kn) {
+        if (!kOneSet && jj + 1 < kn) {
 #pragma unroll
-          for (int t = 0; t < NTT; ++t) b[(jj + 1) & 1][t] = sx[(t * KC + jj + 1) * 64];
+          for (int t = 0; t < NTT; ++t) b[(jj + 1) % NB][t] = sx[(t * KC + jj + 1) * 64];
         }
 #pragma unroll
-        for (int t = 0; t < NTT; ++t)
+        for (int t = 0; t < NTT; ++t) {
 #pragma unroll
-          for (int i = 0; i < NS; ++i) acc[i][t] = mfma_block<BF16>(A[i][j % WIN], b[jj & 1][t], acc[i][t]);
+          for (int i = 0; i < NS; ++i) {
+            if (j % CH == 0 && j > 0) {
+              sum_of[i][t] = j == CH ? acc[i][t] : sum_of[i][t] + acc[i][t];
+              asm volatile("" : "+v"(sum_of[i][t]));  // (added here and not at the end, which would keep every chain in registers)
+            }
+            acc[i][t] = mfma_block<BF16>(A[i][j % WIN], b[jj % NB][t], j % CH == 0 ? f32x4{0, 0, 0, 0} : acc[i][t]);
+          }
+          if (kOneSet && jj + 1 < kn) b[0][t] = sx[(t * KC + jj + 1) * 64];
+        }
         if (j + WIN < NKB) {
 #pragma unroll
           for (int i = 0; i < NS; ++i) A[i][j % WIN] = load_w(i, j + WIN);
@@ -892,6 +907,12 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         put(s + 1);  // (that buffer's last readers passed the barrier before this stage)
         lds_barrier();
       }
+    }
+    if (CH < NKB) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) acc[i][t] = sum_of[i][t] + acc[i][t];
     }
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {

@@ -1,5 +1,6 @@
 """The tiled GEMM at the sizes where its tiles end, through the whole layer protocol (every stage against the CPU oracle):
 experts with 1, 15, 16, 17, ... tokens up to several slots, strips that do not fill the last workgroup, shared experts."""
+import numpy as np
 import pytest
 import torch
 
@@ -83,6 +84,43 @@ def test_lm_head_tiles(d, T):
         assert torch.equal(part[:n], logits[:n]) and bool((part[n:] == -7.0).all())
     finally:
         ev.evict_destroy(ctx)
+
+
+# the tiled kernel adds up the same eight chains as the contraction split: the same score rows bit for bit up to 64 blocks;
+# of 128 blocks the chains hold other blocks, as many of them, so the error against 64 bits is the same but for chance
+@pytest.mark.parametrize("d,T", [(2048, 33), (2048, 64), (2048, 96), (2048, 128), (4096, 20), (4096, 64), (4096, 96), (4096, 128)])
+def test_lm_head_sums(d, T):
+    cfg = synth.ModelCfg("lm", "bf16", d=d, Hq=4, Hkv=4, D=64, E=16, k=2, F=32)
+    V = 32000
+    ctx = ev.evict_create(harness.model_desc(cfg, V), T, 1, 16)
+    try:
+        g = torch.Generator(device=DEV).manual_seed(d + T)
+        x = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+        w = (0.02 * torch.randn(V, d, generator=g, device=DEV)).to(torch.bfloat16)
+        gain = (1 + 0.1 * torch.randn(d, generator=g, device=DEV)).to(torch.bfloat16)
+        packed = torch.empty(V * d, dtype=torch.bfloat16, device=DEV)
+        ev.evict_pack_dense(ev.EVICT_BF16, w, V, d, packed)
+        xn, tiled, split = torch.zeros_like(x), torch.zeros(T, V, device=DEV), torch.zeros(T, V, device=DEV)
+        ev.evict_lm_head_logits(ctx, x, gain, packed, T, tiled, xn)
+        ev.evict_tune(ctx, "lm_nt", 2)
+        ev.evict_lm_head_logits(ctx, x, gain, packed, T, split)
+        torch.cuda.synchronize()
+        if d == 2048:
+            assert torch.equal(tiled, split)
+        want = xn.double() @ w.double().T
+        err = [float((a.double() - want).norm() / want.norm()) for a in (tiled, split)]
+        assert err[0] < 1.05 * err[1], err  # (one chain of 64 / 128 blocks: 2.6 / 2.9 times)
+    finally:
+        ev.evict_destroy(ctx)
+
+
+# the projections likewise, at the tiles of few and of many tokens (64 blocks: 512 QKV strips, 128 output strips)
+@pytest.mark.parametrize("n,batch", [(33, 1), (65, 1), (100, 1), (113, 2), (100, 4)])
+def test_dense_sums(n, batch):
+    case = layer_case(n, 550 + n, 2048, 64, 16, 2, batch=batch, Hq=32, Hkv=16, D=64, L=20)
+    tiled, split = run_case(case), run_case(case, tune={"dense_kernel": 0})
+    for key in ("q", "k_new", "v_new", "h", "router_logits", "out"):
+        assert np.array_equal(tiled[key], split[key]), key
 
 
 # many tokens: the router takes several expert strips per workgroup; short contractions have fewer slices than wavefronts
