@@ -811,7 +811,10 @@ constexpr int kRouterThreads = kRouterWaves * 64;
 constexpr int kFusedTopkTokens = 32;  // up to here TopK and the union share one workgroup (measured: no loss up to 32;
                                       // two tokens per wavefront at most, which topk_union_kernel relies on)
 
-template <typename ST>
+// M: contraction slices a wavefront takes of its strip. Strips x slices x M fill the wavefronts; every slice keeps a sum of
+// its own and the sums are added up in the same order whatever M is, so the scores do not depend on how many strips a
+// workgroup takes (one chain over two or four slices: error against 64-bit sums 1.15e-7 -> 1.38e-7 and 1.89e-7 at 4096 columns).
+template <typename ST, int M>
 __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
     const void* __restrict__ h, const void* __restrict__ gain, const u32x4* __restrict__ wg_packed, int T_max, int d, int E,
     int strips_per_wg, int ksplit, float eps, void* __restrict__ h_norm, float* __restrict__ logits,
@@ -823,7 +826,8 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
   const int nkb = d * EB / 64;
   u32x4* s_b = reinterpret_cast<u32x4*>(s_raw);                       // [nkb][64] token operand blocks
-  f32x4* s_p = reinterpret_cast<f32x4*>(s_raw + (size_t)nkb * 1024);  // [ksplit][strips_per_wg][64]
+  // [ksplit][strips_per_wg][64]; with several slices per wavefront over the token operand, once that has been read
+  f32x4* s_p = reinterpret_cast<f32x4*>(s_raw + (M == 1 ? (size_t)nkb * 1024 : 0));
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tok0 = blockIdx.x * 16;
@@ -892,18 +896,23 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
     }
   }
   __syncthreads();
-  // ---- scores: (expert strip, contraction slice) items round-robin over the wavefronts
+  // ---- scores: one (expert strip, M contraction slices) per wavefront
   const int nstrips = E >> 4;
   int my_strips = nstrips - strip_base;
   my_strips = my_strips > strips_per_wg ? strips_per_wg : my_strips;
   const int per = (nkb + ksplit - 1) / ksplit;  // blocks per slice
-  for (int item = w; item < my_strips * ksplit; item += kRouterWaves) {
-    const int sl = item / ksplit, ks = item - sl * ksplit;
-    const int kb_lo = ks * per;
-    int kb_hi = kb_lo + per;
+  const int groups = (ksplit + M - 1) / M;
+  // (host-checked: my_strips * groups <= kRouterWaves, so a wavefront has one item at most)
+  const int sl = w / groups, ks0 = (w - sl * groups) * M;
+  const bool mine = w < my_strips * groups;
+  f32x4 part[M];
+#pragma unroll
+  for (int q = 0; q < M; ++q) part[q] = f32x4{0, 0, 0, 0};
+  if (mine) {
+    const int kb_lo = ks0 * per;
+    int kb_hi = kb_lo + M * per;
     kb_hi = kb_hi > nkb ? nkb : kb_hi;
     const u32x4* wp = wg_packed + (size_t)(strip_base + sl) * nkb * 64 + lane;
-    f32x4 acc = {0, 0, 0, 0};
     for (int kb0 = kb_lo; kb0 < kb_hi; kb0 += 8) {
       u32x4 a[8];
 #pragma unroll
@@ -911,10 +920,19 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
         if (kb0 + j < kb_hi) a[j] = wp[(size_t)(kb0 + j) * 64];
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (kb0 + j < kb_hi)
-          acc = mfma_block<ST>(a[j], s_b[(kb0 + j) * 64 + (lane ^ ((lane >> 4) | (((kb0 + j) & 1) << 2)))], acc);
+        if (kb0 + j < kb_hi) {
+          const u32x4 b = s_b[(kb0 + j) * 64 + (lane ^ ((lane >> 4) | (((kb0 + j) & 1) << 2)))];
+#pragma unroll
+          for (int q = 0; q < M; ++q)
+            if (M == 1 || (kb0 + j >= kb_lo + q * per && kb0 + j < kb_lo + (q + 1) * per)) part[q] = mfma_block<ST>(a[j], b, part[q]);
+        }
     }
-    s_p[((size_t)ks * strips_per_wg + sl) * 64 + lane] = acc;
+  }
+  if (M > 1) __syncthreads();  // every wavefront is done with the token operand
+  if (mine) {
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+      if (ks0 + q < ksplit) s_p[((size_t)(ks0 + q) * strips_per_wg + sl) * 64 + lane] = part[q];
   }
   __syncthreads();
   // ---- sum the slices in a fixed order, publish the scores: lane holds 4 experts of one token
@@ -1720,10 +1738,11 @@ int kernels_setup(const evict_model_desc& m) {
   const size_t rl = router_lds_bytes(m);
   EVICT_REQUIRE(rl <= 152 * 1024, EVICT_E_UNSUPPORTED, "router needs %zu bytes of LDS (limit 152 KiB): d too large", rl);
   EVICT_REQUIRE(m.d <= 64 * 8 * (m.dtype == EVICT_BF16 ? 8 : 4), EVICT_E_UNSUPPORTED, "router keeps a token row in registers: d=%d too large", m.d);
-  if (m.dtype == EVICT_BF16)
-    EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)router_logits_kernel<BF16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rl));
-  else
-    EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)router_logits_kernel<F32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rl));
+#define EVICT_ROUTER_ATTR(ST_, M_) \
+  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)router_logits_kernel<ST_, M_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rl))
+  if (m.dtype == EVICT_BF16) { EVICT_ROUTER_ATTR(BF16, 1); EVICT_ROUTER_ATTR(BF16, 2); EVICT_ROUTER_ATTR(BF16, 4); }
+  else { EVICT_ROUTER_ATTR(F32, 1); EVICT_ROUTER_ATTR(F32, 2); EVICT_ROUTER_ATTR(F32, 4); }
+#undef EVICT_ROUTER_ATTR
   return EVICT_OK;
 }
 
@@ -1819,19 +1838,30 @@ int launch_router(const evict_ctx* c, const void* gain, const void* wg, int T, c
   float* a_lg = aux ? aux->router_logits : nullptr;
   // One strip per workgroup spreads W_g over the chip; with so many token tiles that this takes more than one round of the
   // 256 CUs (a workgroup's LDS fills one), two or more: every workgroup normalises its 16 tokens again, so fewer is less
-  // work too. 912 tokens, 128 experts: 14.3 -> 9.0 us. (Strips x contraction slices stay what the LDS is sized for.)
-  int spw = router_strips_per_wg(m);
-  const int items = spw * router_ksplit(m);
+  // work too (917 tokens, 128 experts, time of the stage: 15.8 -> 12.0 us; 256 experts 37 -> 25). The wavefronts then take 2 or 4 contraction slices each, whose sums
+  // must fit the LDS, and the items the wavefronts.
+  const int ksplit = router_ksplit(m);
+  int spw = router_strips_per_wg(m), mult = 1;
   const int tiles = (T + 15) / 16, nstrips = m.E / 16;
-  while (tiles * ((nstrips + spw - 1) / spw) > 256 && spw * 2 <= nstrips && spw * 2 <= items) spw *= 2;
-  const int ksplit = items / spw;
+  while (mult < 4 && tiles * ((nstrips + spw - 1) / spw) > 256 && spw * 2 <= nstrips &&
+         spw * 2 * ((ksplit + mult * 2 - 1) / (mult * 2)) <= kRouterWaves && (size_t)ksplit * spw * 2 * 64 * sizeof(f32x4) <= lds) {
+    spw *= 2;
+    mult *= 2;
+  }
   const dim3 grid(tiles, (nstrips + spw - 1) / spw);
-  if (m.dtype == EVICT_BF16)
-    hipLaunchKernelGGL(router_logits_kernel<BF16>, grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T, m.d,
-                       m.E, spw, ksplit, m.rms_eps, c->h_norm, c->logits, a_hn, a_lg, c->t_dev);
-  else
-    hipLaunchKernelGGL(router_logits_kernel<F32>, grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T, m.d,
-                       m.E, spw, ksplit, m.rms_eps, c->h_norm, c->logits, a_hn, a_lg, c->t_dev);
+#define EVICT_ROUTER(ST_, M_)                                                                                                \
+  hipLaunchKernelGGL((router_logits_kernel<ST_, M_>), grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T,    \
+                     m.d, m.E, spw, ksplit, m.rms_eps, c->h_norm, c->logits, a_hn, a_lg, c->t_dev)
+#define EVICT_ROUTER_M(ST_)                                                                                                  \
+  do {                                                                                                                       \
+    if (mult == 1) EVICT_ROUTER(ST_, 1);                                                                                     \
+    else if (mult == 2) EVICT_ROUTER(ST_, 2);                                                                                \
+    else EVICT_ROUTER(ST_, 4);                                                                                               \
+  } while (0)
+  if (m.dtype == EVICT_BF16) EVICT_ROUTER_M(BF16);
+  else EVICT_ROUTER_M(F32);
+#undef EVICT_ROUTER_M
+#undef EVICT_ROUTER
   return launch_status("router_logits_kernel");
 }
 

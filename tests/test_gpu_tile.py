@@ -128,3 +128,15 @@ def test_dense_sums(n, batch):
 def test_router_strips(d, E, n, batch):
     case = layer_case(n, 900 + d, d, 32, E, 2, batch=batch, Hq=2, Hkv=2, D=64, L=5)
     check_against_oracle(case, run_case(case))
+
+
+# ... whose scores are the same sums of slices then: no further from 64 bits than with one strip per workgroup (one, two and
+# four slices per wavefront; one chain over two or four of them: 1.2 and 1.6 times as far)
+def test_router_sums():
+    err = []
+    for batch in (1, 3, 8):
+        case = layer_case(128, 950, 4096, 32, 256, 2, batch=batch, Hq=2, Hkv=2, L=5)
+        got = run_case(case)
+        want = np.asarray(got["h_norm"], np.float64) @ np.asarray(case["W"]["wg"], np.float64).T
+        err.append(float(np.linalg.norm(got["router_logits"] - want) / np.linalg.norm(want)))
+    assert max(err) < 1.05 * err[0], err
