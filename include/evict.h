@@ -431,13 +431,15 @@ int evict_device_status(evict_ctx* ctx, int32_t* status_host, void* stream);
  *   "moe_grid"        workgroups of the grouped expert GEMMs (chunks are dealt round-robin)
  *   "moe_prefetch"    1: weight registers of the streaming GEMMs refilled right behind each MFMA where the
  *                     step count is known at compile time (default); 3: refilled per step (measurement knob)
- *   "moe_chunk_gateup", "moe_chunk_down"  units (16-row strips; strip pairs for gate/up) a
- *                     workgroup takes from the device-side work list at a time
+ *   "moe_chunk_gateup", "moe_chunk_down"  units (16-row strips; strip pairs for gate/up) a workgroup of the
+ *                     contraction-split kernel takes from the device-side work list at a time (until set: by size)
  *   "moe_gateup_kernel" 1: gate/up projections with one (gate, up) strip pair per wavefront and the token
  *                     operand in LDS; 0: contraction split over the wavefronts of a workgroup; 2 = auto
  *                     (the former from 64 tokens on where its chunks line up with the XCDs, else from 128; and
- *                     where experts have several token tiles on average, unless one of the "moe_" kernel, tile
- *                     or pairing knobs is set, the tiled kernel: up to 96 tokens of an expert at once)
+ *                     where experts have several token tiles on average, the tiled kernel for both expert
+ *                     projections: up to 96 tokens of an expert at once, weights by non-temporal loads. Setting any
+ *                     "moe_" knob but "moe_grid" away from its default, or a "moe_chunk_" knob at all, leaves the
+ *                     tiled kernel out; it is built for d of 2048 and 4096 and expert widths 192, 256, 768 and 1408)
  *   "moe_lds_dma"     1 (default): that kernel stages its token operand with direct global-to-LDS loads where
  *                     the shape allows (bf16, 64 contraction blocks); 0: through registers
  *   "moe_down_kernel" 1: down projections with one 16-row strip per wavefront over the whole
@@ -446,15 +448,17 @@ int evict_device_status(evict_ctx* ctx, int32_t* status_host, void* stream);
  *   "dense_nt"        16-token tiles a workgroup of the QKV / output projections takes: 1, 2, or 0 = auto
  *                     (the tiled kernel once two tiles per workgroup are more than one round of workgroups)
  *   "dense_units"     consecutive 16-row strips a workgroup of the QKV projection takes, 0 = auto
- *   "moe_nt_loads"    expert weights fetched with non-temporal loads: 1, 0 (ordinary loads), 2 = auto;
+ *   "moe_nt_loads"    expert weights fetched with non-temporal loads: 1, 0 (ordinary loads), 2 = auto (non-temporal,
+ *                     but ordinary in the down projection of expert width 256);
  *   "dense_nt_loads"  the same for the QKV / output projections and the LM head (auto: always for the
  *                     projections; for the LM head when every strip is read by a single workgroup)
  *   "dense_kernel"    QKV / output projections: 0 contraction split over the wavefronts of a workgroup,
  *                     1 one strip per wavefront with the token operand in LDS (where its shape conditions
- *                     hold), 2 = auto (bf16: the tiled kernel where its shapes are built and "dense_nt",
- *                     "dense_units" and "dense_ntw" are 0; the latter from 128 or 256 tokens on); "dense_ntw" its token tiles
- *                     per workgroup, 1, 2 or 0 = auto
- *   "lm_units", "lm_nt" LM head: consecutive 16-row strips and 16-token tiles a workgroup takes, 0 = auto
+ *                     hold), 2 = auto (bf16: the tiled kernel where it is built, contractions of 1024 (output projection),
+ *                     2048 and 4096, and "dense_nt", "dense_units" and "dense_ntw" are 0 and "dense_nt_loads" is not 0;
+ *                     the latter from 128 or 256 tokens on); "dense_ntw" its token tiles per workgroup, 1, 2 or 0 = auto
+ *   "lm_units", "lm_nt" LM head: consecutive 16-row strips and 16-token tiles a workgroup takes, 0 = auto (bf16, d of 2048
+ *                     and 4096, "dense_nt_loads" 2: the tiled kernel for many tokens or a long contraction)
  *   "attn_target_wgs" workgroups the bf16 attention kernel aims for when it cuts the context into splits
  *   "moe_nt"          16-token tiles per work-list slot of the grouped expert GEMMs: 1, 2, or 0 = auto (1)
  *   "attn_waves"      wavefronts per workgroup of that kernel: 4, 8 (two LDS buffers, next chunk fetched

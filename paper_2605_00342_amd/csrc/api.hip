@@ -8,6 +8,7 @@
 
 #include "ctx.h"
 #include "gemm_stream.h"
+#include "launch_rules.h"
 #include "layer_launch.h"
 
 using namespace evict;
@@ -149,9 +150,8 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
   c.lm_units = 0;
   c.lm_nt = 0;
   c.dense_ntw = 0;
-  c.moe_chunk_gateup = 1;
-  c.moe_chunk_down = 1;
-  for (int cu : {4, 2}) if ((m->d / 16) % cu == 0) { c.moe_chunk_down = cu; break; }
+  c.moe_chunk_gateup = 0;
+  c.moe_chunk_down = 0;
   c.attn_row_blocks = 0;
   c.timed_once = 0;
   c.capturing = 0;
@@ -334,7 +334,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // 16.1 -> 12.2 against one strip per wavefront, 912 tokens 59 -> 39; 128 strips of 128 blocks 64 tokens 12.3 against
   // 14.3, so not yet, 80 tokens 21.4 -> 14.3, 226 tokens 41 -> 15, 912 tokens 72 -> 30).
   auto dense_tiled = [&](const GemmArgs& a, int epi) {
-    return ctx->dense_kernel == 2 && !ctx->dense_nt && !ctx->dense_ntw && !ctx->dense_units && m.dtype == EVICT_BF16 && T > 32 &&
+    return dense_knobs_auto(ctx->dense_kernel, ctx->dense_nt, ctx->dense_ntw, ctx->dense_units, ctx->dense_nt_loads) && m.dtype == EVICT_BF16 && T > 32 &&
            a.n_strips * ((T + 31) / 32) > 256 && tile_dense_applies(a, epi);
   };
   auto dense_strip_shape = [&](const GemmArgs& a, int* ntw) {
@@ -412,8 +412,8 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // 309 -> 212. So the line is an average of 6 tokens per expert; 8 where six wavefronts do not share out an expert's strip
   // pairs evenly (width 1408: 64 nodes, 6 tokens per expert, between 2 % faster and 2 % slower by the routing); 10 for the
   // long contraction of 4096 columns, where the contraction-split kernel keeps its token operand.
-  const bool moe_auto = ctx->moe_nt == 0 && ctx->moe_gateup_kernel == 2 && ctx->moe_down_kernel == 1 && ctx->moe_pair_down == 2 &&
-                        ctx->moe_down_ws == 0;
+  const bool moe_auto = moe_knobs_auto({ctx->moe_nt, ctx->moe_gateup_kernel, ctx->moe_down_kernel, ctx->moe_pair_down, ctx->moe_down_ws,
+                                        ctx->moe_nt_loads, ctx->moe_lds_dma, ctx->moe_prefetch, ctx->moe_chunk_gateup, ctx->moe_chunk_down});
   const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= (gu.nkb == 64 ? (gu.n_strips % 12 == 0 ? 6 : 8) : 10) * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
                      tile_grouped_applies(dn, EPI_F32);
   // expert weights fetched with non-temporal loads: they are read once per call (up to the further token tiles
@@ -447,9 +447,9 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     // (one strip pair per wavefront pays once experts often have several token tiles: measured from 64 tokens on
     // where its chunks line up with the XCDs, see gateup_waves, else from 128)
     a.wave_strip = ctx->moe_gateup_kernel == 2 ? (T >= (gateup_waves(a) != 4 ? 64 : 128) ? 1 : 0) : ctx->moe_gateup_kernel;
-    a.chunk_units = ctx->moe_chunk_gateup;
     // (two strip pairs per chunk where the token operand stays in registers across them; at 8 tokens 9.4 us with one, 14.2)
-    if (a.chunk_units == 1 && a.nkb % 128 == 0 && m.dtype == EVICT_BF16 && T > 8 && (m.F / 16) % 2 == 0) a.chunk_units = 2;
+    a.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup
+                    : (a.nkb % 128 == 0 && m.dtype == EVICT_BF16 && T > 8 && (m.F / 16) % 2 == 0) ? 2 : 1;
     rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }
@@ -467,10 +467,10 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.x_by_token = 0;
     a.out0 = ctx->y;
     a.ldo = m.d;
-    a.chunk_units = ctx->moe_chunk_down;
+    a.chunk_units = ctx->moe_chunk_down ? ctx->moe_chunk_down : (a.n_strips % 4 == 0 ? 4 : (a.n_strips % 2 == 0 ? 2 : 1));
     a.prefetch = ctx->moe_prefetch;
     a.wave_strip = ctx->moe_down_kernel;
-    a.nt_loads = moe_nt;
+    a.nt_loads = down_nt_loads(ctx->moe_nt_loads, a.nkb);
     // An expert with more than 16 tokens has several 16-token slots. The strip-per-wavefront kernel can take two
     // consecutive ones of an expert through one weight stream (its operand of 32 tokens must fit the LDS budget of
     // that kernel); measured to pay once there are enough tokens for such experts to be common.

@@ -1402,9 +1402,9 @@ int launch_gemm_wave_strip(const GemmArgs& a, int grid, hipStream_t s) {
   else if (nkb == 44 && NTW == 1) EVICT_WS_LAUNCH_NT(11, 6, 44);
   else if (nkb == 44) EVICT_WS_LAUNCH(11, 6 / NTW, true);
   // narrow experts (a rank's share): the whole strip is one window, its length known at compile time (35 experts of width
-  // 192: 12.6 -> 9.0 us; 40 of width 256: 14.8 -> 13.8 us, where ordinary loads are the better from 64 tokens on)
+  // 192: 12.6 -> 9.0 us; 40 of width 256: 14.8 -> 13.8 us)
   else if (nkb == 6 && ST::kBytes == 2) EVICT_WS_LAUNCH_NT(6, 1, 6);
-  else if (nkb == 8 && ST::kBytes == 2) hipLaunchKernelGGL((gemm_wave_strip_kernel<ST, 8, 1, true, NTW, 8, 8, false>), dim3(grid), dim3(8 * 64), lds, s, a);
+  else if (nkb == 8 && ST::kBytes == 2) EVICT_WS_LAUNCH_NT(8, 1, 8);
   else if (nkb % 16 == 0) EVICT_WS_LAUNCH_NT(16, 4 / NTW, 0);
   else if (nkb % 8 == 0) EVICT_WS_LAUNCH(8, 2 / NTW, true);
   else EVICT_WS_LAUNCH(16, 4 / NTW, false);

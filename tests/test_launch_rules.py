@@ -1,0 +1,61 @@
+"""The rules that choose kernels by size and by the launch-shape knobs (csrc/launch_rules.h), compiled for the host."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++")
+SHIM = """
+#include "launch_rules.h"
+using namespace evict;
+extern "C" {
+int moe_auto(const int* k) {
+  return moe_knobs_auto(MoeKnobs{k[0], k[1], k[2], k[3], k[4], k[5], k[6], k[7], k[8], k[9]});
+}
+int dense_auto(int kernel, int nt, int ntw, int units, int nt_loads) { return dense_knobs_auto(kernel, nt, ntw, units, nt_loads); }
+int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
+}
+"""
+pytestmark = pytest.mark.skipif(CXX is None, reason="no host compiler")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "rules.so")
+    subprocess.run([CXX, "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2605_00342_amd", "csrc"),
+                    "-o", so, str(d / "shim.cpp")], check=True)
+    return ctypes.CDLL(so)
+
+
+# nt, gateup_kernel, down_kernel, pair_down, down_ws, nt_loads, lds_dma, prefetch, chunk_gateup, chunk_down as evict_create sets them
+DEFAULTS = dict(nt=0, gateup_kernel=2, down_kernel=1, pair_down=2, down_ws=0, nt_loads=2, lds_dma=1, prefetch=1, chunk_gateup=0, chunk_down=0)
+
+
+def moe_auto(rules, **knobs):
+    k = dict(DEFAULTS, **knobs)
+    return bool(rules.moe_auto((ctypes.c_int * 10)(*k.values())))
+
+
+def test_expert_knobs_ask_for_their_kernels(rules):
+    assert moe_auto(rules) and moe_auto(rules, nt_loads=1)
+    for name, values in (("nt", (1, 2)), ("gateup_kernel", (0, 1)), ("down_kernel", (0,)), ("pair_down", (0, 1)), ("down_ws", (8, 16)),
+                         ("nt_loads", (0,)), ("lds_dma", (0,)), ("prefetch", (3,)), ("chunk_gateup", (1, 2, 4)), ("chunk_down", (1, 4))):
+        for v in values:
+            assert not moe_auto(rules, **{name: v}), (name, v)
+
+
+def test_projection_knobs_ask_for_their_kernels(rules):
+    assert rules.dense_auto(2, 0, 0, 0, 2) and rules.dense_auto(2, 0, 0, 0, 1)
+    for args in ((0, 0, 0, 0, 2), (1, 0, 0, 0, 2), (2, 1, 0, 0, 2), (2, 0, 1, 0, 2), (2, 0, 0, 4, 2), (2, 0, 0, 0, 0)):
+        assert not rules.dense_auto(*args), args
+
+
+def test_down_loads_follow_the_knob(rules):
+    for nkb in (6, 8, 24, 44):
+        assert rules.down_nt(0, nkb) == 0 and rules.down_nt(1, nkb) == 1
+    assert [rules.down_nt(2, n) for n in (6, 8, 24, 44)] == [1, 0, 1, 1]
