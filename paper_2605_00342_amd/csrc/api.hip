@@ -447,9 +447,8 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     // (one strip pair per wavefront pays once experts often have several token tiles: measured from 64 tokens on
     // where its chunks line up with the XCDs, see gateup_waves, else from 128)
     a.wave_strip = ctx->moe_gateup_kernel == 2 ? (T >= (gateup_waves(a) != 4 ? 64 : 128) ? 1 : 0) : ctx->moe_gateup_kernel;
-    // (two strip pairs per chunk where the token operand stays in registers across them; at 8 tokens 9.4 us with one, 14.2)
-    a.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup
-                    : (a.nkb % 128 == 0 && m.dtype == EVICT_BF16 && T > 8 && (m.F / 16) % 2 == 0) ? 2 : 1;
+    // (the kernel with steps of 128 blocks keeps its token operand across a chunk's pairs and has its chunks cut by the slots)
+    a.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup : gateup_long_steps(m.dtype, a, nt_exp) ? 0 : 1;
     rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }

@@ -40,9 +40,9 @@ struct GemmArgs {
   const void* X;         // token operand rows, storage dtype
   long long ldx_bytes;   // bytes between rows of X
   int grouped;           // 0: one matrix, tokens 0..T-1; 1: one matrix per union expert
-  const int* union_count;  // grouped: number of work slots (expert x token tile)
+  const int* union_count;  // grouped: [0] number of work slots (expert x token tile), [2] units per chunk for them (gateup_chunk)
   const WorkRec* work;   // per union slot (see WorkRec)
-  int chunk_units;       // grouped: units per chunk (divides the units per expert)
+  int chunk_units;       // grouped: units per chunk (divides the units per expert); 0: as union_count[2] says (steps of 128 blocks)
   const int* tok_of_pos; // token of each grouped position (perm[p] / k)
   int x_by_token;        // grouped: 1 -> X row = tok_of_pos[p], 0 -> X row = p
   int T;                 // dense: token rows (upper bound when T_dev is set)
@@ -350,13 +350,15 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
     // Device-side work list: union experts x units, cut into chunks of `chunk_units` units that
     // never straddle an expert. Chunks are dealt round-robin to the workgroups; all chunks cost
     // the same, so this stays balanced for any union size without the host knowing it.
-    const int cpg = upg / a.chunk_units;
-    const int total = *a.union_count * cpg;
+    const int slots = *a.union_count;
+    const int cu = CB > 64 && a.chunk_units == 0 ? a.union_count[2] : a.chunk_units;
+    const int cpg = upg / cu;
+    const int total = slots * cpg;
     for (int chunk = blockIdx.x; chunk < total; chunk += gridDim.x) {
       // (the token tiles of one expert are consecutive slots: with cpg a multiple of 8 their
       // chunks land on the same XCD, whose L2 serves the second reader of the weights)
       const int slot = chunk / cpg, uc = chunk - slot * cpg;
-      run_segment(std::integral_constant<bool, NTL>{}, slot, uc * a.chunk_units, a.chunk_units, 0, 0x7fffffff);
+      run_segment(std::integral_constant<bool, NTL>{}, slot, uc * cu, cu, 0, 0x7fffffff);
     }
   } else {
     // one workgroup per (strip, token tile). Workgroup ids go round-robin over the 8 XCDs, so

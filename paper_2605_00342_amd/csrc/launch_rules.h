@@ -24,4 +24,33 @@ inline bool dense_knobs_auto(int kernel, int nt, int ntw, int units, int nt_load
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }
 
+// Strip pairs per chunk of the contraction-split gate/up kernel over 4096 columns, for `slots` slots of the work list and
+// `pairs` strip pairs per expert. A workgroup fills a CU, so what counts is how the slots * pairs / c chunks fall into rounds
+// of 256: a full round streams at the rate of memory, 10 us per pair of a chunk; the last takes at least a chunk's own walk,
+// 4 us per pair and 8 to start. (us for c = 1, 2, 3, 4, and the kernel with steps of 64 blocks that this one replaced; width
+// 192: 43 slots 34.0, 37.7, 29.2, 32.4, old 35.5; 46 slots 34.2, 37.4, 27.7, 34.6, old 37.8; 17 slots 14.1, 17.9, 22.3,
+// 26.3, old 16.0; 66 slots 42.0, 40.3, 49.6, 38.8, old 45.1. Width 256, c = 1, 2, 4: 35 slots 35.1, 37.6, 31.3, old 36.4;
+// 130 slots 90.3, 91.5, 103.3, old 97.8. Always two is slower than the old kernel at 16 of
+// ninety such points.)
+// Worked out on the device, with the slots, from the counts of chunks that the host has divided out.
+struct ChunkCounts {
+  int n[4];  // chunks of 1 .. 4 pairs an expert's pairs make, 0 where that does not divide them
+};
+constexpr ChunkCounts gateup_chunk_counts(int pairs) {
+  ChunkCounts k = {};
+  for (int c = 1; c <= 4; ++c) k.n[c - 1] = pairs % c == 0 ? pairs / c : 0;
+  return k;
+}
+constexpr int gateup_chunk(int slots, const ChunkCounts& counts) {
+  int best = 1, best_cost = 0x7fffffff;
+#pragma unroll
+  for (int c = 1; c <= 4; ++c) {
+    const int n = slots * counts.n[c - 1], rest = n & 255;
+    const int walk = 4 * c + 8, share = 10 * c * rest >> 8;
+    const int cost = (n >> 8) * 10 * c + (rest == 0 ? 0 : (walk > share ? walk : share));
+    if (counts.n[c - 1] > 0 && cost <= best_cost) { best_cost = cost; best = c; }
+  }
+  return best;
+}
+
 }  // namespace evict

@@ -1111,7 +1111,7 @@ __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
     int32_t* __restrict__ aux_idx, float* __restrict__ aux_w, int use_masks, int32_t* __restrict__ union_ids,
     int32_t* __restrict__ union_count, int32_t* __restrict__ hist, int32_t* __restrict__ offsets,
     int32_t* __restrict__ perm, int32_t* __restrict__ inv, int32_t* __restrict__ status, WorkRec* __restrict__ work,
-    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count, int n_shared, int tt, const int* __restrict__ t_dev) {
+    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count, int n_shared, int tt, const ChunkCounts counts, const int* __restrict__ t_dev) {
   extern __shared__ __attribute__((aligned(16))) int s_all[];
   const int T = dyn_tokens(t_dev, T_max);
   const int lane = threadIdx.x & 63;
@@ -1151,7 +1151,7 @@ __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
   }
   __syncthreads();
   expert_union_body(s_all, nullptr, T, k, E, use_masks, union_ids, union_count, hist, offsets, perm, inv, status, work,
-                    tok_of_pos, slot_count, n_shared, tt);
+                    tok_of_pos, slot_count, n_shared, tt, counts);
 }
 
 // expert union and grouping (Eq. 5) with the device-side work list, one workgroup
@@ -1159,11 +1159,11 @@ __global__ __launch_bounds__(kRouterThreads) void union_worklist_kernel(
     const int32_t* __restrict__ topk_idx, int T_max, int k, int E, int use_masks, int32_t* __restrict__ union_ids,
     int32_t* __restrict__ union_count, int32_t* __restrict__ hist, int32_t* __restrict__ offsets,
     int32_t* __restrict__ perm, int32_t* __restrict__ inv, int32_t* __restrict__ status, WorkRec* __restrict__ work,
-    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count, int n_shared, int tt, const int* __restrict__ t_dev) {
+    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count, int n_shared, int tt, const ChunkCounts counts, const int* __restrict__ t_dev) {
   extern __shared__ __attribute__((aligned(16))) int s_all[];
   const int T = dyn_tokens(t_dev, T_max);
   expert_union_body(s_all, topk_idx, T, k, E, use_masks, union_ids, union_count, hist, offsets, perm, inv, status, work,
-                    tok_of_pos, slot_count, n_shared, tt);
+                    tok_of_pos, slot_count, n_shared, tt, counts);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1319,6 +1319,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ h
   }
 }
 
+}  // namespace
+// gate/up projections by the contraction split in steps of 128 blocks (bf16, one token tile per slot)
+bool gateup_long_steps(int dtype, const GemmArgs& a, int nt) {
+  return dtype == EVICT_BF16 && a.grouped && nt == 1 && a.nkb % 128 == 0 && a.prefetch != 3;
+}
+namespace {
+
 template <typename ST, int NT, int EPI>
 int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
   // (non-temporal weight loads are a template parameter; they are built for the bf16 production shapes only)
@@ -1335,7 +1342,7 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
   const int need = ((nkb > 64 ? 64 : nkb) + kGemmWaves - 1) / kGemmWaves;
   constexpr bool bf16 = ST::kBytes == 2;
   if constexpr (bf16) {
-  if (EPI == EPI_SWIGLU && NT == 1 && a.grouped && nkb % 128 == 0 && a.prefetch != 3) {
+  if (EPI == EPI_SWIGLU && gateup_long_steps(EVICT_BF16, a, NT)) {
     // steps of 128 blocks: the token operand of a contraction of 4096 columns stays in registers for all strips of a chunk
     // instead of being fetched again for every strip, half of it at a time (35 experts of width 192: 23.4 -> 18.7 us
     // with two strip pairs per chunk; one workgroup per CU, as 16 blocks of weights and of tokens fill the registers)
@@ -1875,7 +1882,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   if (regs && T <= kFusedTopkTokens) {
     hipLaunchKernelGGL(topk_union_kernel, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx,
                        c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv,
-                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, c->t_dev);
+                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, gateup_chunk_counts(m.F / 16), c->t_dev);
     return launch_status("topk_union_kernel");
   }
   const dim3 tgrid((T + kRouterWaves - 1) / kRouterWaves);
@@ -1891,7 +1898,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   if (rc) return rc;
   hipLaunchKernelGGL(union_worklist_kernel, dim3(1), dim3(kRouterThreads), lds, s, c->topk_idx, T, m.k, m.E, use_masks,
                      c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv, c->status, c->work, c->tok_of_pos,
-                     c->sched, m.n_shared, tile_tokens, c->t_dev);
+                     c->sched, m.n_shared, tile_tokens, gateup_chunk_counts(m.F / 16), c->t_dev);
   return launch_status("union_worklist_kernel");
 }
 

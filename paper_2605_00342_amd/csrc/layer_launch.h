@@ -10,6 +10,7 @@ struct WorkRec;
 int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStream_t s);
 bool dense_strip_applies(const GemmArgs& a, int ntw);
 int gateup_waves(const GemmArgs& a);
+bool gateup_long_steps(int dtype, const GemmArgs& a, int nt);
 int launch_gemm_dense_strip(int dtype, int epi, GemmArgs a, int ntw, hipStream_t s);
 constexpr int kTileSlotTokens = 96;  // tokens per work-list slot of the grouped tiled GEMM
 bool tile_grouped_applies(const GemmArgs& a, int epi);

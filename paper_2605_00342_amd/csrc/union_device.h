@@ -1,6 +1,7 @@
 // Expert union (Eq. 5) and the token grouping it induces, as a device routine run by one
 // workgroup; shared by the stand-alone union kernel and the fused top-k + union kernel.
 #pragma once
+#include "launch_rules.h"
 #include "ctx.h"
 #include "gemm_stream.h"
 
@@ -74,12 +75,14 @@ __host__ __device__ inline size_t union_before_bytes(int E, int words) { return 
 // One workgroup: what bounds it is the chain of round trips, so a thread's expert indices are requested together, and both
 // scans share their barriers. (16 trees of 64 nodes, 8 experts each: 15 us with a load, a division and a walk over the
 // masks per pair one after the other, 12 us this way; 128 nodes 6.0 -> 5.2 us; TopK and union of 32 nodes 9.5 -> 8.9.)
-// topk_idx: global [T*k], or nullptr when s_mem[0..P) already holds the indices.
+// topk_idx: global [T*k], or nullptr when s_mem[0..P) already holds the indices. slot_count: [0] slots of the work list,
+// [1] running total of union sizes, [2] strip pairs per chunk that gateup_chunk gives for these slots and `counts`.
 __device__ inline void expert_union_body(
     int* s_mem, const int32_t* __restrict__ topk_idx, int T, int k, int E, int use_masks, int32_t* __restrict__ union_ids,
     int32_t* __restrict__ union_count, int32_t* __restrict__ hist, int32_t* __restrict__ offsets,
     int32_t* __restrict__ perm, int32_t* __restrict__ inv, int32_t* __restrict__ status, WorkRec* __restrict__ work,
-    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count = nullptr, int n_shared = 0, int tt = 16) {
+    int32_t* __restrict__ tok_of_pos, int32_t* __restrict__ slot_count = nullptr, int n_shared = 0, int tt = 16,
+    const ChunkCounts counts = {}) {
   const int P = T * k;
   const int words = (T + 63) >> 6;
   int* s_idx = s_mem;            // [P]
@@ -148,6 +151,8 @@ __device__ inline void expert_union_body(
     // (expert id E + s; positions T*k + s*T + t), one slot per tile of tt tokens
     const int ttiles = (T + tt - 1) / tt;
     if (tid == 0 && slot_count) slot_count[0] = tot_s + n_shared * ttiles;
+    // (by the last wavefront, which mostly has no expert: worked out at the start of the gate/up kernel it costs 1.3 us there)
+    if (tid == nthreads - 1 && slot_count) slot_count[2] = gateup_chunk(tot_s + n_shared * ttiles, counts);
     for (int q = tid; q < n_shared * ttiles; q += nthreads) {
       const int sh = q / ttiles, i = q - sh * ttiles;
       WorkRec* rec = work + tot_s + q;

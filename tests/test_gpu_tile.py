@@ -123,6 +123,15 @@ def test_dense_sums(n, batch):
         assert np.array_equal(tiled[key], split[key]), key
 
 
+# gate/up of 4096 columns: chunks cut by the slots on the device (about 35 slots of 16 pairs: four pairs each) or by the knob
+def test_gateup_chunks():
+    case = layer_case(40, 980, 4096, 256, 32, 4, n_shared=1)
+    got = run_case(case)
+    check_against_oracle(case, got)
+    for chunk in (1, 2, 4):
+        assert np.array_equal(got["out"], run_case(case, tune={"moe_chunk_gateup": chunk})["out"]), chunk
+
+
 # many tokens: the router takes several expert strips per workgroup; short contractions have fewer slices than wavefronts
 @pytest.mark.parametrize("d,E,n,batch", [(256, 128, 120, 5), (2048, 128, 120, 5), (512, 256, 100, 4), (96, 128, 128, 6)])
 def test_router_strips(d, E, n, batch):
