@@ -549,6 +549,36 @@ __global__ __launch_bounds__(kStatsThreads) void row_expsum_kernel(const float* 
   if (lane == 0) st[kSampWaves + part] = z;
 }
 
+// Short rows: both numbers by one workgroup per row in one launch, the same additions in the same order; maximum and sum go to
+// the first slot of the partial maxima and of the partial sums. Two launches cost more than they save there (256 rows: 1000
+// logits 2.9 us this way, 8.3 in two launches; 16000 logits 8.0 and 8.3).
+constexpr int kShortRow = 16384;
+__global__ __launch_bounds__(kSampThreads) void short_row_stats_kernel(const float* __restrict__ logits, int V, float inv_temp,
+                                                                       float* __restrict__ stats, const int* __restrict__ t_dev) {
+  __shared__ float s_red[2][kSampWaves];
+  if ((int)blockIdx.x >= dyn_tokens(t_dev, (int)gridDim.x)) return;  // (rows past the call's actual token count)
+  const float* row = logits + (size_t)blockIdx.x * V;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  float m = -INFINITY;
+  for (int i = tid; i < V; i += kSampThreads) m = fmaxf(m, row[i]);
+  m = wave_max(m);
+  if (lane == 0) s_red[0][w] = m;
+  __syncthreads();
+  m = s_red[0][0];
+  for (int i = 1; i < kSampWaves; ++i) m = fmaxf(m, s_red[0][i]);
+  float z = 0.0f;
+  for (int i = tid; i < V; i += kSampThreads) z += __expf((row[i] - m) * inv_temp);
+  z = wave_sum(z);
+  if (lane == 0) s_red[1][w] = z;
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.0f;
+    for (int i = 0; i < kSampWaves; ++i) t += s_red[1][i];
+    stats[(size_t)blockIdx.x * kSampStats] = m;
+    stats[(size_t)blockIdx.x * kSampStats + kSampWaves] = t;
+  }
+}
+
 __device__ __forceinline__ float wave_incl_scan_f32(float v, int lane) {
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -570,11 +600,14 @@ __device__ __forceinline__ float wave_incl_scan_f32(float v, int lane) {
 // What bounds step 3 is the latency of one workgroup's loads, so kStatsBatch of them are in flight per lane, and the
 // pieces, which a lane adds up element by element, come through LDS in chunks of 64 elements that all wavefronts fetch
 // coalesced (168 -> 31 us for four trees at a vocabulary of 151936; the additions and their order are unchanged).
+// SHORT: statistics of short_row_stats_kernel; a segment is at most 16 loads per lane, and the code walked through counts.
+template <bool SHORT>
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
     const float* __restrict__ u_node, const float* __restrict__ u_bonus, int32_t* __restrict__ path, int path_stride,
     int32_t* __restrict__ path_len, int32_t* __restrict__ bonus, int32_t* __restrict__ status) {
+  constexpr int kBatch = SHORT ? 4 : kStatsBatch;
   __shared__ int s_par[kMaxSel];
   __shared__ int s_tok[kMaxSel];
   __shared__ float s_p[kMaxSel];
@@ -601,10 +634,12 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
         const size_t prow = (size_t)(lo + pa);
         const float* st = stats + prow * kSampStats;
         const float logit = logits[prow * V + tk];
-        float z = 0.0f;
+        float z = SHORT ? st[kSampWaves] : 0.0f;
+        if (!SHORT) {
 #pragma unroll
-        for (int q = 0; q < kSampWaves; ++q) z += st[kSampWaves + q];
-        pr = __expf((logit - stats_max(st)) * inv_temp) / z;
+          for (int q = 0; q < kSampWaves; ++q) z += st[kSampWaves + q];
+        }
+        pr = __expf((logit - (SHORT ? st[0] : stats_max(st))) * inv_temp) / z;
       }
     }
     s_par[i] = i == 0 ? -1 : pa;
@@ -652,7 +687,8 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   __syncthreads();
   const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const float* row = logits + (size_t)(lo + cur) * V;
-  const float m = stats_max(stats + (size_t)(lo + cur) * kSampStats);
+  const float* st_cur = stats + (size_t)(lo + cur) * kSampStats;
+  const float m = SHORT ? st_cur[0] : stats_max(st_cur);
   auto mass = [&](float v, int i) {
     float e = __expf((v - m) * inv_temp);
     for (int r = 0; r < nrej; ++r)
@@ -664,28 +700,28 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   const int sb = w * seg;
   const int se = sb + seg < V ? sb + seg : V;
   float acc = 0.0f;
-  for (int i0 = sb; i0 < se; i0 += 64 * kStatsBatch) {
-    float e[kStatsBatch];
+  for (int i0 = sb; i0 < se; i0 += 64 * kBatch) {
+    float e[kBatch];
 #pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * 64 + lane;
       e[u] = i < se ? row[i] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * 64 + lane;
       e[u] = i < se ? __expf((e[u] - m) * inv_temp) : 0.0f;
     }
     for (int r = 0; r < nrej; ++r) {  // (the same for the whole wavefront, and rarely inside this batch)
       const int at = __builtin_amdgcn_readfirstlane(s_rej[r]) - i0;
-      if (at >= 0 && at < 64 * kStatsBatch) {
+      if (at >= 0 && at < 64 * kBatch) {
 #pragma unroll
-        for (int u = 0; u < kStatsBatch; ++u)
+        for (int u = 0; u < kBatch; ++u)
           if (u * 64 + lane == at) e[u] = 0.0f;
       }
     }
 #pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u) acc += e[u];  // (adding a zero leaves a sum of non-negative terms as it is)
+    for (int u = 0; u < kBatch; ++u) acc += e[u];  // (adding a zero leaves a sum of non-negative terms as it is)
   }
   acc = wave_sum(acc);
   if (lane == 0) s_segsum[w] = acc;
@@ -744,7 +780,8 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
       for (int c0 = 0; c0 < cl && !inside; c0 += 64) {
         const int i = pb + c0 + lane;
         const int ebits = __float_as_int((c0 + lane < cl && i < V) ? mass(row[i], i) : 0.0f);
-        for (int j = 0; j < 64 && !inside; ++j) {
+        const int jn = cl - c0 < 64 ? cl - c0 : 64;
+        for (int j = 0; j < jn && !inside; ++j) {
           const float e = __int_as_float(__builtin_amdgcn_readlane(ebits, j));
           if (e > 0.0f) {
             pick = pb + c0 + j;
@@ -762,12 +799,20 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
 int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const int32_t* tok, const float* logits, int V,
                           float inv_temp, float* stats, const float* u_node, const float* u_bonus, int B, int T, int32_t* path,
                           int path_stride, int32_t* path_len, int32_t* bonus, int32_t* status, const int32_t* t_dev, hipStream_t s) {
-  hipLaunchKernelGGL(row_max_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, stats, T, t_dev);
-  hipLaunchKernelGGL(row_expsum_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, inv_temp, stats, T, t_dev);
+  if (V <= kShortRow) {
+    hipLaunchKernelGGL(short_row_stats_kernel, dim3(T), dim3(kSampThreads), 0, s, logits, V, inv_temp, stats, t_dev);
+  } else {
+    hipLaunchKernelGGL(row_max_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, stats, T, t_dev);
+    hipLaunchKernelGGL(row_expsum_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, inv_temp, stats, T, t_dev);
+  }
   int rc = launch_status("softmax statistics kernels");
   if (rc) return rc;
-  hipLaunchKernelGGL(accept_sampled_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                     u_node, u_bonus, path, path_stride, path_len, bonus, status);
+  if (V <= kShortRow)
+    hipLaunchKernelGGL(accept_sampled_kernel<true>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                       u_node, u_bonus, path, path_stride, path_len, bonus, status);
+  else
+    hipLaunchKernelGGL(accept_sampled_kernel<false>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                       u_node, u_bonus, path, path_stride, path_len, bonus, status);
   return launch_status("accept_sampled_kernel");
 }
 

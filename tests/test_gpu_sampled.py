@@ -197,3 +197,12 @@ def test_vocabulary_edges(ctx_small, V):
         path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, u_bonus, max(sizes))
         assert np.all((bonus >= 0) & (bonus < V))
         check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus)
+
+
+@pytest.mark.parametrize("V", [16384, 16385])
+def test_short_and_long_rows_agree(ctx_small, V):
+    """Either side of the row length from which the statistics are spread over several workgroups: every decision as the
+    oracle's."""
+    parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(41, [1, 9, 16, 30], V)
+    path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.8, u_node, u_bonus, 30)
+    assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.8, path, plen, bonus) <= 1
