@@ -196,7 +196,7 @@ def test_vocabulary_edges(ctx_small, V):
         u_bonus[:] = u
         path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, u_bonus, max(sizes))
         assert np.all((bonus >= 0) & (bonus < V))
-        check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus)
+        assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus) == 0
 
 
 @pytest.mark.parametrize("V", [16384, 16385])
