@@ -209,7 +209,7 @@ constexpr int kAttnKeys = 64;
 typedef f32x4 __attribute__((aligned(4))) f32x4u;  // (a contiguous fp32 cache may have any head and sequence stride)
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_partial_f32_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_partial_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc, long long seq_stride,
     long long head_stride, const int32_t* __restrict__ ctx_len, int max_ctx, const int32_t* __restrict__ tree_off,
     const float* __restrict__ k_new, const float* __restrict__ v_new, const uint64_t* __restrict__ anc, int Hq, int Hkv,
@@ -287,6 +287,11 @@ __global__ __launch_bounds__(256) void attn_partial_f32_kernel(
   const float scale = 1.0f / sqrtf((float)D);
   const int ntiles = (R + 15) >> 4;
   for (int rt = w; rt < ntiles; rt += 4) {
+    // The compiler keeps the K and V fragments, the same for every tile, in registers across the tiles. That pays with many
+    // tiles at head dimension 64 (128 nodes of 8 heads per group: 142 -> 132 us); at 128 it takes 448 registers, one workgroup
+    // per CU, so there they are read again (114 registers; 1 node, 8 KV heads, 4000 positions: 76 -> 60 us, 128 nodes
+    // 152 -> 129; 128 nodes of 8 heads per group 180 -> 184).
+    if (D == 128) asm volatile("" ::: "memory");
     const int r = rt * 16 + ln < R ? rt * 16 + ln : R - 1;  // (rows past the end repeat the last; never stored)
     const int t = lo + r / G, h = g * G + r % G;
     u32x4 Qf[KB];
