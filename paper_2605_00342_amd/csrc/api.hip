@@ -405,17 +405,14 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   gu.nkb = m.d * eb / 64;
   dn.n_strips = m.d / 16;
   dn.nkb = m.F * eb / 64;
-  // The tiled kernels take up to 96 tokens of an expert through one weight stream where the kernels below take 16 (or 32)
-  // at a time, but their workgroups run longer: they pay once experts mostly have several token tiles. Measured on whole
-  // layers (us, before -> tiled): 128 experts 96 nodes 143 -> 131, 175 -> 173, 217 -> 211 (child noise 0.2, 0.5, 1.0) but
-  // 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; 8 ranks' share of 128 experts 128 nodes 175 -> 150, 4 x 100 nodes
-  // 309 -> 212. So the line is an average of 6 tokens per expert; 8 where six wavefronts do not share out an expert's strip
-  // pairs evenly (width 1408: 64 nodes, 6 tokens per expert, between 2 % faster and 2 % slower by the routing); 10 for the
-  // long contraction of 4096 columns, where the contraction-split kernel keeps its token operand.
   const bool moe_auto = moe_knobs_auto({ctx->moe_nt, ctx->moe_gateup_kernel, ctx->moe_down_kernel, ctx->moe_pair_down, ctx->moe_down_ws,
                                         ctx->moe_nt_loads, ctx->moe_lds_dma, ctx->moe_prefetch, ctx->moe_chunk_gateup, ctx->moe_chunk_down});
-  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && T * m.k >= (gu.nkb == 64 ? (gu.n_strips % 12 == 0 ? 6 : 8) : 10) * m.E && tile_grouped_applies(gu, EPI_SWIGLU) &&
-                     tile_grouped_applies(dn, EPI_F32);
+  // (one strip pair per wavefront pays once experts often have several token tiles: measured from 64 tokens on
+  // where its chunks line up with the XCDs, see gateup_waves, else from 128)
+  gu.lds_dma = ctx->moe_lds_dma;
+  const bool gu_strip = T >= (gateup_waves(gu) != 4 ? 64 : 128);
+  const bool tiled = m.dtype == EVICT_BF16 && moe_auto && experts_tiled(T, m.k, m.E, gu.nkb, gu.n_strips / 2, gu_strip) &&
+                     tile_grouped_applies(gu, EPI_SWIGLU) && tile_grouped_applies(dn, EPI_F32);
   // expert weights fetched with non-temporal loads: they are read once per call (up to the further token tiles
   // of an expert, which run next to the first on the same XCD), and kept out of the caches they leave the
   // activations and projection weights of the next kernels there
@@ -443,10 +440,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.ldo = m.F;
     a.prefetch = ctx->moe_prefetch;
     a.nt_loads = moe_nt;
-    a.lds_dma = ctx->moe_lds_dma;
-    // (one strip pair per wavefront pays once experts often have several token tiles: measured from 64 tokens on
-    // where its chunks line up with the XCDs, see gateup_waves, else from 128)
-    a.wave_strip = ctx->moe_gateup_kernel == 2 ? (T >= (gateup_waves(a) != 4 ? 64 : 128) ? 1 : 0) : ctx->moe_gateup_kernel;
+    a.wave_strip = ctx->moe_gateup_kernel == 2 ? (gu_strip ? 1 : 0) : ctx->moe_gateup_kernel;
     // (the kernel with steps of 128 blocks keeps its token operand across a chunk's pairs and has its chunks cut by the slots)
     a.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup : gateup_long_steps(m.dtype, a, nt_exp) ? 0 : 1;
     rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);

@@ -15,6 +15,26 @@ inline bool moe_knobs_auto(const MoeKnobs& k) {
          k.lds_dma == 1 && k.prefetch == 1 && k.chunk_gateup == 0 && k.chunk_down == 0;
 }
 
+// The tiled expert kernels (bf16, knobs as above, shapes that are built) for T tokens of k experts out of E; the gate/up
+// projection has nkb contraction blocks and `pairs` strip pairs; strip: the call would else take the strip kernels.
+// They take up to 96 tokens of an expert through one weight stream where the other kernels take 16 (or 32) at a time, but
+// their workgroups run longer. They pay once
+//  - experts mostly have several token tiles. Whole layers (us, before -> tiled): 128 experts 96 nodes 143 -> 131, 175 -> 173,
+//    217 -> 211 (child noise 0.2, 0.5, 1.0) but 64 nodes 115 -> 110, 149 -> 148, 180 -> 183; a rank's share of 128 experts
+//    128 nodes 175 -> 150, 4 x 100 nodes 309 -> 212. So from an average of 6 tokens per expert; 8 where six wavefronts do not
+//    share out an expert's strip pairs evenly (width 1408: 64 nodes, 6 tokens per expert, 2 % faster to 2 % slower by the
+//    routing; 86 nodes, 8 tokens, 170 -> 150, 223 -> 192, 255 -> 233); 10 over 4096 columns, where the contraction-split
+//    kernel keeps its token operand;
+//  - the experts' chunks of six strip pairs can fill the 256 CUs. 16 experts of width 256 are 48 workgroups: gate/up of 96
+//    nodes 17 -> 28 us; of width 768, 128 workgroups, 26 -> 30.
+// Over 2048 columns their sums are one chain, as those of the strip kernels, where the contraction split has eight: they stand
+// in for the strip kernels only.
+constexpr bool experts_tiled(int T, int k, int E, int nkb, int pairs, bool strip) {
+  if (nkb <= 64 && !strip) return false;
+  if (E * ((pairs + 5) / 6) < 256) return false;
+  return T * k >= (nkb <= 64 ? (pairs % 6 == 0 ? 6 : 8) : 10) * E;
+}
+
 // Knobs of the QKV / output projections, likewise.
 inline bool dense_knobs_auto(int kernel, int nt, int ntw, int units, int nt_loads) {
   return kernel == 2 && nt == 0 && ntw == 0 && units == 0 && nt_loads != 0;

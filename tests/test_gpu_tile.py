@@ -1,5 +1,6 @@
-"""The tiled GEMM at the sizes where its tiles end, through the whole layer protocol (every stage against the CPU oracle):
-experts with 1, 15, 16, 17, ... tokens up to several slots, strips that do not fill the last workgroup, shared experts."""
+"""The tiled GEMM of the projections and the LM head at the sizes where its tiles end, and the expert kernels of few experts with
+1, 15, 16, 17, ... tokens up to several slots (too few for the tiled ones, which test_gpu_tile_experts.py compares with these),
+through the whole layer protocol (every stage against the CPU oracle)."""
 import numpy as np
 import pytest
 import torch

@@ -17,6 +17,7 @@ int moe_auto(const int* k) {
 }
 int dense_auto(int kernel, int nt, int ntw, int units, int nt_loads) { return dense_knobs_auto(kernel, nt, ntw, units, nt_loads); }
 int chunk(int slots, int pairs) { return gateup_chunk(slots, gateup_chunk_counts(pairs)); }
+int tiled(int T, int k, int E, int nkb, int pairs, int strip) { return experts_tiled(T, k, E, nkb, pairs, strip); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
 """
@@ -72,3 +73,13 @@ def test_gateup_chunk(rules):
     # measured the best, or within 2 % of it
     assert [rules.chunk(s, 12) for s in (17, 22, 43, 46, 66)] == [1, 2, 3, 3, 4]
     assert rules.chunk(35, 16) == 4 and rules.chunk(130, 16) in (1, 2)
+
+
+def test_tiled_experts(rules):
+    # (T, k, E, blocks, strip pairs, strip kernels' size)
+    assert rules.tiled(96, 8, 128, 64, 48, 1) and not rules.tiled(95, 8, 128, 64, 48, 1)   # 6 tokens per expert
+    assert rules.tiled(86, 6, 64, 64, 88, 1) and not rules.tiled(85, 6, 64, 64, 88, 1)     # 8: 88 pairs are no multiple of 6
+    assert rules.tiled(160, 8, 128, 128, 12, 1) and not rules.tiled(159, 8, 128, 128, 12, 1)
+    assert rules.tiled(320, 8, 256, 128, 16, 0)                                            # (no strip kernel of 128 blocks)
+    assert not rules.tiled(63, 8, 64, 64, 48, 0)                                           # the contraction split's sums
+    assert not rules.tiled(512, 4, 16, 64, 16, 1) and not rules.tiled(512, 4, 16, 64, 48, 1)  # too few workgroups
