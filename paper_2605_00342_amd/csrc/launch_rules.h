@@ -40,6 +40,14 @@ inline bool dense_knobs_auto(int kernel, int nt, int ntw, int units, int nt_load
   return kernel == 2 && nt == 0 && ntw == 0 && units == 0 && nt_loads != 0;
 }
 
+// Workgroups of a tiled projection that takes `strips` of the n_strips strips and one of the token groups each. Ids go
+// round-robin over the 8 XCDs, a strip group's token groups on one XCD, so the strip groups are padded to a multiple of 8 and
+// the XCDs with one group more decide: 20 strip groups x 12 token groups are 36 workgroups for each of four XCDs of 32 CUs
+// and not one round (160 strips of 64 blocks, 370 tokens: 28 us, and 20 with the next larger tile).
+constexpr int tile_grid(int n_strips, int strips, int token_groups) {
+  return ((n_strips + strips - 1) / strips + 7) / 8 * 8 * token_groups;
+}
+
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }

@@ -1600,8 +1600,7 @@ int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
   int fit = -1, i = 0, last = -1;
 #define EVICT_TILE_FIT(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                        \
   if (epi == EPI_ && a.nkb == NKB_) {                                                                                        \
-    const int wgs = ((a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_)) * ((a.T + 16 * NT_ - 1) / (16 * NT_));                      \
-    if (fit < 0 && wgs <= kTileRound) fit = i;                                                                               \
+    if (fit < 0 && tile_grid(a.n_strips, WS_ * NS_, (a.T + 16 * NT_ - 1) / (16 * NT_)) <= kTileRound) fit = i;               \
     last = i;                                                                                                                \
   }                                                                                                                          \
   ++i;
@@ -1612,9 +1611,8 @@ int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
 #define EVICT_TILE_LAUNCH(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                     \
   if (i++ == fit) {                                                                                                          \
     a.dense_tiles = (a.T + 16 * NT_ - 1) / (16 * NT_);                                                                       \
-    const int nsg = (a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_);                                                              \
     hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>),                              \
-                       dim3(((nsg + 7) / 8) * 8 * a.dense_tiles), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);           \
+                       dim3(tile_grid(a.n_strips, WS_ * NS_, a.dense_tiles)), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);\
   }
   EVICT_TILE_DENSE(EVICT_TILE_LAUNCH)
 #undef EVICT_TILE_LAUNCH
@@ -1640,9 +1638,8 @@ int launch_gemm_tile_lm(int epi, GemmArgs a, hipStream_t s) {
   bool launched = false;
 #define EVICT_TILE_LAUNCH(EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_)                                                     \
   if (epi == EPI_ && a.nkb == NKB_ && nt == NT_ && ws == WS_) {                                                              \
-    const int nsg = (a.n_strips + WS_ * NS_ - 1) / (WS_ * NS_);                                                              \
     hipLaunchKernelGGL((gemm_tile_kernel<EPI_, NT_, NS_, WS_, WIN_, D_, NKB_, GROUPED_, true>),                              \
-                       dim3(((nsg + 7) / 8) * 8 * a.dense_tiles), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);           \
+                       dim3(tile_grid(a.n_strips, WS_ * NS_, a.dense_tiles)), dim3(WS_ * 64), tile_lds_bytes(NT_, WS_), s, a);\
     launched = true;                                                                                                         \
   }
   EVICT_TILE_LM(EVICT_TILE_LAUNCH)

@@ -18,6 +18,7 @@ int moe_auto(const int* k) {
 int dense_auto(int kernel, int nt, int ntw, int units, int nt_loads) { return dense_knobs_auto(kernel, nt, ntw, units, nt_loads); }
 int chunk(int slots, int pairs) { return gateup_chunk(slots, gateup_chunk_counts(pairs)); }
 int tiled(int T, int k, int E, int nkb, int pairs, int strip) { return experts_tiled(T, k, E, nkb, pairs, strip); }
+int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
 """
@@ -83,3 +84,14 @@ def test_tiled_experts(rules):
     assert rules.tiled(320, 8, 256, 128, 16, 0)                                            # (no strip kernel of 128 blocks)
     assert not rules.tiled(63, 8, 64, 64, 48, 0)                                           # the contraction split's sums
     assert not rules.tiled(512, 4, 16, 64, 16, 1) and not rules.tiled(512, 4, 16, 64, 48, 1)  # too few workgroups
+
+
+def test_tile_grid(rules):
+    assert rules.grid(320, 4, 3) == 240 and rules.grid(128, 8, 4) == 64
+    assert rules.grid(160, 8, 12) == 288 and rules.grid(160, 8, 10) == 240 and rules.grid(1, 8, 1) == 8
+    for n_strips in (1, 7, 80, 128, 160, 320, 384, 9496):
+        for strips in (4, 8, 16):
+            for groups in (1, 2, 11):
+                wgs = rules.grid(n_strips, strips, groups)
+                # the fullest XCD's share of the grid, eight times
+                assert wgs == 8 * groups * -(-(-(-n_strips // strips)) // 8)
