@@ -545,17 +545,16 @@ int evict_verify_stack_paged(evict_ctx* ctx, const evict_layer_weights* layers, 
 }
 
 // LM head GEMM (vocabulary rows x T tokens): launch shape. Many tokens, or a long contraction: the tiled kernel (see
-// tile_lm_applies). Else a workgroup of the contraction-split kernel takes several consecutive strips, so the token operand
+// lm_tiled). Else a workgroup of the contraction-split kernel takes several consecutive strips, so the token operand
 // is fetched once for all of them and the weight loads run ahead across strips, and two token tiles once there are more
-// than 16 tokens, so the weights are streamed once instead of once per tile.
-// Measured at 151936 x 2048, bf16 (us): one strip at a time 233 at 32 tokens, 8 strips 116; at 16 tokens 2 strips 108, 8
-// strips 101; at 8 tokens 2 strips 95, 8 strips 96.
+// than 16 tokens, so the weights are streamed once instead of once per tile (151936 x 2048, 32 tokens: one strip at a time
+// 233 us, 8 strips 116).
 static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream_t s) {
-  if (ctx->m.dtype == EVICT_BF16 && !ctx->lm_nt && !ctx->lm_units && ctx->dense_nt_loads == 2 && tile_lm_applies(a))
+  if (ctx->m.dtype == EVICT_BF16 && !ctx->lm_nt && !ctx->lm_units && ctx->dense_nt_loads == 2 && lm_tiled(T, a.n_strips, a.nkb))
     return launch_gemm_tile_lm(epi, a, s);
   const int nt = ctx->lm_nt ? ctx->lm_nt : (T > 16 ? 2 : 1);
   a.dense_tiles = (T + 16 * nt - 1) / (16 * nt);
-  a.dense_units = ctx->lm_units ? ctx->lm_units : (T > 8 ? 8 : 2);
+  a.dense_units = ctx->lm_units ? ctx->lm_units : lm_units(T, a.n_strips);
   a.nt_loads = ctx->dense_nt_loads == 2 ? (a.dense_tiles == 1 ? 1 : 0) : ctx->dense_nt_loads;  // every strip is read by one workgroup
   const int grid = (((a.n_strips + a.dense_units - 1) / a.dense_units + 7) / 8) * 8 * a.dense_tiles;
   return launch_gemm(ctx->m.dtype, epi, a, nt, grid, s);

@@ -48,6 +48,24 @@ constexpr int tile_grid(int n_strips, int strips, int token_groups) {
   return ((n_strips + strips - 1) / strips + 7) / 8 * 8 * token_groups;
 }
 
+// The LM head (bf16, auto knobs, shapes that are built): the tiled kernel for T tokens, n_strips 16-row strips and nkb
+// contraction blocks. It reads the weights once for up to 96 tokens, but a workgroup takes 8 or 16 strips, so it needs many.
+// 151936 rows (us, contraction split -> tiled). 64 blocks: 16 tokens 101 (not yet: 112), 32 tokens 116 (118), 48 tokens
+// 161 -> 124, 64 173 -> 129, 96 211 -> 135, 128 313 -> 171. 128 blocks, where the split kernel re-reads its token operand for
+// every strip: 9 tokens 209 (214), 12 229 -> 215, 16 254 -> 216, 33 690 -> 224, 64 743 -> 244, 128 1345 -> 323.
+// 64 blocks, 96 tokens: 32000 rows 46 -> 44, but 16000 rows 37 (43), 4096 rows 25 (40). 128 blocks: 16000 rows 16 tokens
+// 38 -> 35, but 8192 rows 26 (32); from 17 tokens on the tiled kernel is the better at 1024 rows already, 61 -> 30.
+constexpr bool lm_tiled(int T, int n_strips, int nkb) {
+  if (n_strips % 2 != 0) return false;
+  return (nkb == 64 && T > 32 && n_strips > 1024) || (nkb == 128 && (T > 16 || (T >= 12 && n_strips > 768)));
+}
+
+// Strips per workgroup of the contraction split for the LM head: 8 from 17 tokens on; for one token tile 2, but 8 from 13
+// tokens on if that leaves about a workgroup per CU. (64 blocks, 2 strips -> 8, us: 151936 rows 16 tokens 121 -> 111, 9 tokens
+// 109 -> 109; 32000 rows 16 tokens 33.7 -> 31.1; 102400 rows 12 tokens 81 -> 84, 9 tokens 76 -> 83; 16000 rows 16 tokens
+// 24.1 -> 24.8.)
+constexpr int lm_units(int T, int n_strips) { return T > 16 || (T > 12 && n_strips > 1024) ? 8 : 2; }
+
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }

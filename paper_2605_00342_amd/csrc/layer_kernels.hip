@@ -1623,13 +1623,6 @@ int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s) {
   return launch_status("gemm_tile_kernel");
 }
 
-// LM head, 151936 rows (us, contraction split -> tiled). 64 blocks: 16 tokens 101 (not yet: 112), 32 tokens 116 (118),
-// 48 tokens 161 -> 124, 64 173 -> 129, 96 215 -> 142, 128 270 -> 176. 128 blocks, where the split kernel re-reads its token
-// operand for every strip: 8 tokens 192 (not yet), 16 240 -> 212, 32 382 -> 225, 64 714 -> 249, 128 1308 -> 342.
-bool tile_lm_applies(const GemmArgs& a) {
-  return a.n_strips % 2 == 0 && ((a.nkb == 64 && a.T > 32) || (a.nkb == 128 && a.T > 8));
-}
-
 // 2, 4 or 6 token tiles at once, whichever takes the fewest passes over the weights
 int launch_gemm_tile_lm(int epi, GemmArgs a, hipStream_t s) {
   const int nt = a.T <= 32 ? 2 : ((a.T + 95) / 96 < (a.T + 63) / 64 ? 6 : 4);

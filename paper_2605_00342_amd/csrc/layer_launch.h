@@ -17,7 +17,6 @@ bool tile_grouped_applies(const GemmArgs& a, int epi);
 int launch_gemm_tile_grouped(int epi, const GemmArgs& a, int grid, hipStream_t s);
 bool tile_dense_applies(const GemmArgs& a, int epi);
 int launch_gemm_tile_dense(int epi, GemmArgs a, hipStream_t s);
-bool tile_lm_applies(const GemmArgs& a);
 int launch_gemm_tile_lm(int epi, GemmArgs a, hipStream_t s);
 int launch_pack(const void* src, long long src_group_bytes, int rows, int cols, int dtype, void* dst, int dst_strip0,
                 int dst_strip_step, long long dst_group_strips, int groups, int head_dim, hipStream_t s);

@@ -18,6 +18,8 @@ int moe_auto(const int* k) {
 int dense_auto(int kernel, int nt, int ntw, int units, int nt_loads) { return dense_knobs_auto(kernel, nt, ntw, units, nt_loads); }
 int chunk(int slots, int pairs) { return gateup_chunk(slots, gateup_chunk_counts(pairs)); }
 int tiled(int T, int k, int E, int nkb, int pairs, int strip) { return experts_tiled(T, k, E, nkb, pairs, strip); }
+int lm(int T, int n_strips, int nkb) { return lm_tiled(T, n_strips, nkb); }
+int units(int T, int n_strips) { return lm_units(T, n_strips); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
@@ -95,3 +97,14 @@ def test_tile_grid(rules):
                 wgs = rules.grid(n_strips, strips, groups)
                 # the fullest XCD's share of the grid, eight times
                 assert wgs == 8 * groups * -(-(-(-n_strips // strips)) // 8)
+
+
+def test_lm_head(rules):
+    big = 9496
+    assert [rules.lm(T, big, 64) for T in (16, 32, 33, 128)] == [0, 0, 1, 1]
+    assert [rules.lm(T, big, 128) for T in (8, 11, 12, 16, 128)] == [0, 0, 1, 1, 1]
+    assert not rules.lm(96, 1000, 64) and rules.lm(96, 2000, 64)          # few strips: too few workgroups
+    assert not rules.lm(16, 512, 128) and rules.lm(16, 1000, 128) and rules.lm(17, 64, 128)
+    assert not rules.lm(96, 2001, 64) and not rules.lm(96, 2000, 32)      # odd strip counts, lengths that are not built
+    assert [rules.units(T, big) for T in (1, 9, 12, 13, 16, 17)] == [2, 2, 2, 8, 8, 8]
+    assert rules.units(16, 1000) == 2 and rules.units(32, 64) == 8
