@@ -140,6 +140,14 @@ __device__ __forceinline__ int dyn_tokens(const int* t_dev, int t_max) {
   return v < 1 ? 1 : (v > t_max ? t_max : v);
 }
 
+// Between a lane's write to LDS and another lane's read of it in the same wavefront: LDS operations of one wavefront complete
+// in order, so no instruction is needed, but the compiler, which sees each lane by itself, must keep the two in order.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroup barrier that waits for LDS traffic only, so that global loads already in
 // flight (weight prefetch) stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

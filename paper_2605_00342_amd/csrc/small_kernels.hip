@@ -416,7 +416,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_batch_kernel(
         const bool keeps = i < tn && (int)(v & 0xFFFFu) < tks;
         const unsigned long long m = __ballot(keeps);
         const int ni = kept + __popcll(m & ((1ull << lane) - 1ull));
-        if (keeps) node[i] = (v & 0xFFFF0000u) | (uint32_t)ni;  // (LDS operations of one wavefront complete in order)
+        if (keeps) node[i] = (v & 0xFFFF0000u) | (uint32_t)ni;
+        wave_lds_fence();
         if (keeps) {
           const uint32_t p = v >> 16;
           keep[tout + ni] = i;
@@ -669,7 +670,8 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
             if (s_rej[r] == tk) pc = 0.0f;
           if (s_u[c] < pc / (1.0f - removed)) { nxt = c; break; }
           removed += pc;
-          if (lane == 0) s_rej[nrej] = tk;  // (LDS operations of one wavefront complete in order)
+          if (lane == 0) s_rej[nrej] = tk;
+          wave_lds_fence();
           ++nrej;
         }
       }
