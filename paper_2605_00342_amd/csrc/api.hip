@@ -417,7 +417,13 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   // of an expert, which run next to the first on the same XCD), and kept out of the caches they leave the
   // activations and projection weights of the next kernels there
   const int moe_nt = ctx->moe_nt_loads == 2 ? 1 : ctx->moe_nt_loads;
-  rc = launch_topk_union(ctx, T, aux, tiled ? kTileSlotTokens : 16 * nt_exp, s);
+  // units per chunk of the contraction-split gate/up kernel; 0: the union kernel cuts the chunks by the slots, for the kernel
+  // with steps of 128 blocks, which keeps its token operand across a chunk's pairs
+  gu.grouped = 1;
+  gu.prefetch = ctx->moe_prefetch;
+  gu.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup : !tiled && gateup_long_steps(m.dtype, gu, nt_exp) ? 0 : 1;
+  rc = launch_topk_union(ctx, T, aux, tiled ? kTileSlotTokens : 16 * nt_exp,
+                         gu.chunk_units == 0 ? gateup_chunk_counts(m.F / 16) : ChunkCounts{}, s);
   if (rc) return rc;
   if (aux) {
     if (aux->union_ids) EVICT_HIP_CHECK(hipMemcpyAsync(aux->union_ids, ctx->union_ids, (size_t)m.E * 4, hipMemcpyDeviceToDevice, s));
@@ -433,16 +439,12 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.group_stride = (long long)a.n_strips * a.nkb * 64;
     a.X = ctx->h_norm;
     a.ldx_bytes = (long long)m.d * eb;
-    a.grouped = 1;
     a.union_count = ctx->sched; a.work = ctx->work; a.tok_of_pos = ctx->tok_of_pos;
     a.x_by_token = 1;
     a.out0 = ctx->act;
     a.ldo = m.F;
-    a.prefetch = ctx->moe_prefetch;
     a.nt_loads = moe_nt;
     a.wave_strip = ctx->moe_gateup_kernel == 2 ? (gu_strip ? 1 : 0) : ctx->moe_gateup_kernel;
-    // (the kernel with steps of 128 blocks keeps its token operand across a chunk's pairs and has its chunks cut by the slots)
-    a.chunk_units = ctx->moe_chunk_gateup ? ctx->moe_chunk_gateup : gateup_long_steps(m.dtype, a, nt_exp) ? 0 : 1;
     rc = tiled ? launch_gemm_tile_grouped(EPI_SWIGLU, a, ctx->moe_grid, s) : launch_gemm(m.dtype, EPI_SWIGLU, a, nt_exp, ctx->moe_grid, s);
     if (rc) return rc;
   }

@@ -1867,7 +1867,7 @@ int launch_router(const evict_ctx* c, const void* gain, const void* wg, int T, c
   return launch_status("router_logits_kernel");
 }
 
-int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int tile_tokens, hipStream_t s) {
+int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int tile_tokens, const ChunkCounts& counts, hipStream_t s) {
   const evict_model_desc& m = c->m;
   int32_t* a_idx = aux ? aux->topk_idx : nullptr;
   float* a_w = aux ? aux->topk_w : nullptr;
@@ -1877,7 +1877,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   if (regs && T <= kFusedTopkTokens) {
     hipLaunchKernelGGL(topk_union_kernel, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx,
                        c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv,
-                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, gateup_chunk_counts(m.F / 16), c->t_dev);
+                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, counts, c->t_dev);
     return launch_status("topk_union_kernel");
   }
   const dim3 tgrid((T + kRouterWaves - 1) / kRouterWaves);
@@ -1893,7 +1893,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   if (rc) return rc;
   hipLaunchKernelGGL(union_worklist_kernel, dim3(1), dim3(kRouterThreads), lds, s, c->topk_idx, T, m.k, m.E, use_masks,
                      c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv, c->status, c->work, c->tok_of_pos,
-                     c->sched, m.n_shared, tile_tokens, gateup_chunk_counts(m.F / 16), c->t_dev);
+                     c->sched, m.n_shared, tile_tokens, counts, c->t_dev);
   return launch_status("union_worklist_kernel");
 }
 
