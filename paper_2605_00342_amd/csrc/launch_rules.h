@@ -77,7 +77,9 @@ inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 :
 // 192: 43 slots 34.0, 37.7, 29.2, 32.4, old 35.5; 46 slots 34.2, 37.4, 27.7, 34.6, old 37.8; 17 slots 14.1, 17.9, 22.3,
 // 26.3, old 16.0; 66 slots 42.0, 40.3, 49.6, 38.8, old 45.1. Width 256, c = 1, 2, 4: 35 slots 35.1, 37.6, 31.3, old 36.4;
 // 130 slots 90.3, 91.5, 103.3, old 97.8. Always two is slower than the old kernel at 16 of
-// ninety such points.)
+// ninety such points.) From two full rounds of two pairs on the rounds no longer decide but the operand traffic and, where experts
+// have several slots, the weights that these find in L2: two pairs there (width 256, 4 x 80 nodes: 170 us, 183 by rounds; 2 x 100
+// nodes 77, 90).
 // Worked out on the device, with the slots, from the counts of chunks that the host has divided out.
 struct ChunkCounts {
   int n[4];  // chunks of 1 .. 4 pairs an expert's pairs make, 0 where that does not divide them
@@ -88,13 +90,14 @@ constexpr ChunkCounts gateup_chunk_counts(int pairs) {
   return k;
 }
 constexpr int gateup_chunk(int slots, const ChunkCounts& counts) {
+  if (counts.n[1] > 0 && slots * counts.n[1] >= 512) return 2;
   int best = 1, best_cost = 0x7fffffff;
 #pragma unroll
   for (int c = 1; c <= 4; ++c) {
     const int n = slots * counts.n[c - 1], rest = n & 255;
     const int walk = 4 * c + 8, share = 10 * c * rest >> 8;
     const int cost = (n >> 8) * 10 * c + (rest == 0 ? 0 : (walk > share ? walk : share));
-    if (counts.n[c - 1] > 0 && cost <= best_cost) { best_cost = cost; best = c; }
+    if (counts.n[c - 1] > 0 && cost < best_cost) { best_cost = cost; best = c; }
   }
   return best;
 }

@@ -151,9 +151,6 @@ __device__ inline void expert_union_body(
     // (expert id E + s; positions T*k + s*T + t), one slot per tile of tt tokens
     const int ttiles = (T + tt - 1) / tt;
     if (tid == 0 && slot_count) slot_count[0] = tot_s + n_shared * ttiles;
-    // (by the last wavefront, which mostly has no expert: worked out at the start of the gate/up kernel it costs 1.3 us there;
-    // no counts: not asked for)
-    if (counts.n[0] > 0 && tid == nthreads - 1 && slot_count) slot_count[2] = gateup_chunk(tot_s + n_shared * ttiles, counts);
     for (int q = tid; q < n_shared * ttiles; q += nthreads) {
       const int sh = q / ttiles, i = q - sh * ttiles;
       WorkRec* rec = work + tot_s + q;
@@ -192,6 +189,10 @@ __device__ inline void expert_union_body(
     if (slot_count) slot_count[1] = (int)((unsigned)union_total + (unsigned)tot_f);  // (wraps; the profiler resets it)
   }
   __syncthreads();
+  // (by the last wavefront, which has no pair in small calls, behind the last barrier: worked out at the start of the gate/up
+  // kernel it costs 1.3 us there; no counts: not asked for)
+  if (counts.n[0] > 0 && tid == nthreads - 1 && slot_count)
+    slot_count[2] = gateup_chunk(tot_s + n_shared * ((T + tt - 1) / tt), counts);
   if (use_masks && !s_dup) {
     // position of pair (t, slot) inside its expert = number of earlier tokens routed there
     for (int p = tid; p < P; p += nthreads) {

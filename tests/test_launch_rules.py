@@ -75,7 +75,8 @@ def test_gateup_chunk(rules):
                 assert c == 1  # all in one round already
     # measured the best, or within 2 % of it
     assert [rules.chunk(s, 12) for s in (17, 22, 43, 46, 66)] == [1, 2, 3, 3, 4]
-    assert rules.chunk(35, 16) == 4 and rules.chunk(130, 16) in (1, 2)
+    assert [rules.chunk(57, 12), rules.chunk(35, 16), rules.chunk(36, 16)] == [3, 4, 4]
+    assert [rules.chunk(s, 16) for s in (64, 69, 130, 144, 300)] == [2] * 5  # two full rounds of two pairs and more
 
 
 def test_tiled_experts(rules):
