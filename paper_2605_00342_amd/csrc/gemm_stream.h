@@ -817,7 +817,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int strip_raw = (sg * WS + w) * NS;
     const bool active = strip_raw < a.n_strips;  // the last group may be short: its idle wavefronts still stage and wait
     const int strip = active ? strip_raw : a.n_strips - NS;
-    const char* xrow[NTT];
+    uint32_t xrow[NTT];  // byte offset of the token's row (at most 8192 + shared rows of 8 KiB)
     bool valid[NTT];
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
@@ -825,7 +825,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       valid[t] = active && col < ntok;
       col = col < ntok ? col : ntok - 1;  // padded columns repeat the last token; never stored
       const long long xr = GROUPED ? (a.x_by_token ? a.tok_of_pos[p0 + col] : p0 + col) : col;
-      xrow[t] = (const char*)a.X + xr * a.ldx_bytes + (lane >> 4) * 16;
+      xrow[t] = (uint32_t)(xr * a.ldx_bytes) + (lane >> 4) * 16;
     }
     const u32x4* wp = wbase + (long long)strip * NKB * 64 + lane;
     auto load_w = [&](int i, int j) __attribute__((always_inline)) {
@@ -836,7 +836,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     auto fetch = [&](int s) __attribute__((always_inline)) {
       if (s * KC + KC <= NKB || s * KC + w < NKB) {
 #pragma unroll
-        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>(xrow[t] + (s * KC + w) * 64);
+        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>((const char*)a.X + (s * KC + w) * 64 + xrow[t]);
       }
     };
     auto put = [&](int s) __attribute__((always_inline)) {
@@ -988,8 +988,12 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // the number of live token tiles is known per piece of work: one compiled body for each (for a token group of the layer's
   // projections, where all but the last are full: one for a single tile, one for more)
   constexpr bool kEach = GROUPED || EPI == EPI_F32 || EPI == EPI_ARGMAX;
-  auto dispatch = [&](const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
-    const int live = (ntok - tok0 + 15) >> 4;
+  // In step: the token groups of a strip group run side by side and share its weights through L2 as long as neither gets
+  // ahead, so the last group of several goes at the pace of the full ones where it has more than half as many tiles (LM head,
+  // 151936 x 2048, score rows of 104 tokens: 193 us with 4 and 3 tiles, 184 with 4 and 4).
+  auto dispatch = [&](const u32x4* wbase, int sg, int p0, int ntok, int tok0, bool in_step) __attribute__((always_inline)) {
+    int live = (ntok - tok0 + 15) >> 4;
+    if (in_step && live * 2 > NT) live = NT;
     if (live <= 1) run(std::integral_constant<int, 1>{}, wbase, sg, p0, ntok, tok0);
     else if (kEach && NT >= 3 && live == 2) run(std::integral_constant<int, (kEach && NT >= 3 ? 2 : 1)>{}, wbase, sg, p0, ntok, tok0);
     else if (kEach && NT >= 4 && live == 3) run(std::integral_constant<int, (kEach && NT >= 4 ? 3 : 1)>{}, wbase, sg, p0, ntok, tok0);
@@ -1005,7 +1009,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       const int ex = rec->expert;
       const u32x4* wbase = ex < a.n_routed ? a.W + (long long)ex * a.group_stride
                                            : a.W_shared + (long long)(ex - a.n_routed) * a.group_stride;
-      dispatch(wbase, chunk - slot * nsg, rec->p0, rec->ntok, 0);
+      dispatch(wbase, chunk - slot * nsg, rec->p0, rec->ntok, 0, false);
     }
   } else {
     // workgroup ids go round-robin over the 8 XCDs: the token groups of a strip group are 8 apart and share an L2
@@ -1015,7 +1019,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     const unsigned tg = q % ntg, sg = (q / ntg) * 8u + xcd;
     if (sg >= (unsigned)nsg || (int)tg * NT * 16 >= T) return;  // (whole workgroup, before any barrier)
     const int tok0 = (int)tg * NT * 16;
-    dispatch(a.W, (int)sg, 0, T < tok0 + NT * 16 ? T : tok0 + NT * 16, tok0);
+    dispatch(a.W, (int)sg, 0, T < tok0 + NT * 16 ? T : tok0 + NT * 16, tok0, T > NT * 16);
   }
 }
 
