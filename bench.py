@@ -680,6 +680,8 @@ def main():
     gateup_ms = max(stage_ms["gateup"] - ev_overhead_ms, 1e-6)
     gateup_s = gateup_ms * 1e-3
     achieved = gateup_bytes / gateup_s / 1e9
+    # (larger calls and other widths take other kernels, chosen by size inside the library)
+    gateup_name = GATEUP_KERNEL if T < 64 and cfg.d == 2048 and cfg.dtype == "bf16" and not args.tune else "the kernel chosen for this size"
     # HBM bytes per launch of that kernel by hardware counters: not measurable from inside this process; taken from the
     # committed rocprofv3 --pmc summary of this same command when it was made for this workload and this kernel
     traffic, traffic_source = None, None
@@ -716,7 +718,7 @@ def main():
                           "hbm_frac_north_star": round(north_star_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                           "hbm_frac_all_required": round(all_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
         "stage_us": {n: round(v * 1e3, 2) for n, v in stage_ms.items()},
-        "roofline": {"bound": "hbm", "kernel": GATEUP_KERNEL + " (gate/up grouped GEMM + SiLU gating)",
+        "roofline": {"bound": "hbm", "kernel": gateup_name + " (gate/up grouped GEMM + SiLU gating)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_source": traffic_source,
                      "bytes_per_launch": gateup_bytes, "avg_launch_us": round(gateup_ms * 1e3, 2),
