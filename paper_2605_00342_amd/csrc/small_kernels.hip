@@ -476,9 +476,11 @@ __global__ __launch_bounds__(64) void accept_path_kernel(
 // ------------------------------------------------------------------------------------
 constexpr int kSampThreads = 1024;
 constexpr int kSampWaves = kSampThreads / 64;
-// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials.
+// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials; for the
+// root of a tree also the kSampWaves segment sums of the draw, the last node of the walk (bits of an int) and its row's maximum.
 constexpr int kSampStats = EVICT_SAMP_STATS;
-static_assert(kSampStats == 2 * kSampWaves, "one partial maximum and one partial sum per column group");
+constexpr int kSampSeg = 2 * kSampWaves, kSampCur = 3 * kSampWaves, kSampMax = kSampCur + 1;
+static_assert(kSampStats > kSampMax, "maxima, sums, segment sums, last node, its maximum");
 
 // Per node, the two numbers that turn any logit of the row into a probability -- the maximum and the sum of
 // exp((logit - max) / temperature) over the vocabulary -- as kSampWaves partial results each, one wavefront per
@@ -589,42 +591,26 @@ __device__ __forceinline__ float wave_incl_scan_f32(float v, int lane) {
   return v;
 }
 
-// One workgroup per tree. Step 1, all threads: the target probability of every node's token
-// under its parent's distribution. Step 2, one wavefront: the walk of Eq. 3 on values in LDS --
-// child c of the surviving node is accepted when u_node[c] < p(c) / (1 - mass rejected so
-// far at this node), which is what the repeated renormalisation amounts to; a token already
-// rejected at this node has no mass left. The children of a node are found 64 nodes at a time by a
-// ballot. Step 3, all threads: the final draw from the
-// distribution at the last node with the rejected tokens removed, by inverting the cumulative
-// sum at u_bonus: 16 contiguous vocabulary segments are summed (one per wavefront), the
-// segment holding the target mass is cut into 64 contiguous pieces, the piece is walked.
-// What bounds step 3 is the latency of one workgroup's loads, so kStatsBatch of them are in flight per lane, and the
-// pieces, which a lane adds up element by element, come through LDS in chunks of 64 elements that all wavefronts fetch
-// coalesced (168 -> 31 us for four trees at a vocabulary of 151936; the additions and their order are unchanged).
-// SHORT: statistics of short_row_stats_kernel; a segment is at most 16 loads per lane, and the code walked through counts.
+// The walk of Eq. 3 over one tree by the whole workgroup. All threads: the target probability of every node's token under its
+// parent's distribution. Then one wavefront, on values in LDS: child c of the surviving node is accepted when
+// u_node[c] < p(c) / (1 - mass rejected so far at this node), which is what the repeated renormalisation amounts to; a token
+// already rejected at this node has no mass left. The children of a node are found 64 nodes at a time by a ballot.
+// Leaves the last node in *s_cur and the tokens rejected there, its children's, in s_rej[0 .. *s_nrej). `writer`: this
+// workgroup writes the path (several may walk the same tree). Ends behind a barrier.
+struct SampTree {
+  int par[kMaxSel], tok[kMaxSel];
+  float p[kMaxSel], u[kMaxSel];
+};
+
 template <bool SHORT>
-__global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
-    const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
-    const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
-    const float* __restrict__ u_node, const float* __restrict__ u_bonus, int32_t* __restrict__ path, int path_stride,
-    int32_t* __restrict__ path_len, int32_t* __restrict__ bonus, int32_t* __restrict__ status) {
-  constexpr int kBatch = SHORT ? 4 : kStatsBatch;
-  __shared__ int s_par[kMaxSel];
-  __shared__ int s_tok[kMaxSel];
-  __shared__ float s_p[kMaxSel];
-  __shared__ float s_u[kMaxSel];
-  __shared__ int s_rej[kMaxSel];
-  __shared__ float s_piece[64][65];  // chunk of 64 elements of each of the 64 pieces (rows one bank apart)
-  __shared__ int s_cur, s_nrej, s_seg;
-  __shared__ float s_segsum[kSampWaves];
-  __shared__ float s_rem;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lo = tree_off[b];
-  int n = tree_off[b + 1] - lo;
-  n = n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
+__device__ __forceinline__ void sampled_walk(
+    SampTree& s, int* s_rej, int* s_cur, int* s_nrej, bool writer, int lo, int n, const int32_t* __restrict__ parent,
+    const int32_t* __restrict__ tok, const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
+    const float* __restrict__ u_node, int32_t* __restrict__ my, int path_stride, int32_t* __restrict__ my_len,
+    int32_t* __restrict__ status) {
+  const int tid = threadIdx.x, lane = tid & 63, nthreads = blockDim.x;
   bool bad = false;
-  for (int i = tid; i < n; i += kSampThreads) {
+  for (int i = tid; i < n; i += nthreads) {
     int pa = parent[lo + i];
     int tk = tok[lo + i];
     if (i > 0 && (pa < 0 || pa >= i)) { bad = true; pa = 0; }
@@ -643,16 +629,16 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
         pr = __expf((logit - (SHORT ? st[0] : stats_max(st))) * inv_temp) / z;
       }
     }
-    s_par[i] = i == 0 ? -1 : pa;
-    s_tok[i] = tk;
-    s_p[i] = pr;
-    s_u[i] = u_node[lo + i];
+    s.par[i] = i == 0 ? -1 : pa;
+    s.tok[i] = tk;
+    s.p[i] = pr;
+    s.u[i] = u_node[lo + i];
   }
-  if (bad && status) atomicOr(status, ST_BAD_PARENT);
-  int32_t* my = path + (size_t)b * path_stride;
-  for (int i = tid; i < path_stride; i += kSampThreads) my[i] = i == 0 ? 0 : -1;
+  if (bad && writer && status) atomicOr(status, ST_BAD_PARENT);
+  if (writer)
+    for (int i = tid; i < path_stride; i += nthreads) my[i] = i == 0 ? 0 : -1;
   __syncthreads();
-  if (w == 0) {
+  if (tid < 64) {
     int cur = 0, len = 1, nrej = 0;
     while (true) {
       float removed = 0.0f;
@@ -660,15 +646,15 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
       int nxt = -1;
       for (int base = cur + 1; base < n && nxt < 0; base += 64) {
         const int c0 = base + lane;
-        unsigned long long kids = __ballot(c0 < n && s_par[c0] == cur);
+        unsigned long long kids = __ballot(c0 < n && s.par[c0] == cur);
         while (kids) {  // children in ascending order
           const int c = base + __ffsll((long long)kids) - 1;
           kids &= kids - 1;
-          const int tk = s_tok[c];
-          float pc = s_p[c];
+          const int tk = s.tok[c];
+          float pc = s.p[c];
           for (int r = 0; r < nrej; ++r)
             if (s_rej[r] == tk) pc = 0.0f;
-          if (s_u[c] < pc / (1.0f - removed)) { nxt = c; break; }
+          if (s.u[c] < pc / (1.0f - removed)) { nxt = c; break; }
           removed += pc;
           if (lane == 0) s_rej[nrej] = tk;
           wave_lds_fence();
@@ -677,30 +663,198 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
       }
       if (nxt < 0) break;
       cur = nxt;  // strictly increasing: the walk ends
-      if (lane == 0 && len < path_stride) my[len] = cur;
+      if (writer && lane == 0 && len < path_stride) my[len] = cur;
       ++len;
     }
     if (lane == 0) {
-      path_len[b] = len;
-      s_cur = cur;
-      s_nrej = nrej;
+      if (writer) *my_len = len;
+      *s_cur = cur;
+      *s_nrej = nrej;
     }
   }
   __syncthreads();
+}
+
+__device__ __forceinline__ int tree_nodes(int lo, int hi) {
+  const int n = hi - lo;
+  return n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
+}
+
+// The final draw from the distribution at the last node with the rejected tokens removed, by inverting the cumulative sum at
+// u_bonus: kSampWaves contiguous vocabulary segments are summed, the segment holding the target mass is cut into 64 contiguous
+// pieces, the piece is walked. Lane l of a segment adds up elements 64j + l in ascending j, lane p of the pieces its own
+// elements in ascending order: the order of every addition is fixed by the vocabulary size alone.
+
+// segments start at multiples of 64
+__device__ __forceinline__ int samp_segment(int V) { return (((V + kSampWaves - 1) / kSampWaves) + 63) & ~63; }
+
+// which segment holds the target mass, and what of the target is left in it
+__device__ __forceinline__ void pick_segment(const float* segsum, float u, int* segment, float* rem) {
+  float total = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kSampWaves; ++i) total += segsum[i];
+  const float target = u * total;
+  float before = 0.0f, last = 0.0f;
+  int pick = -1;
+  bool inside = false;
+#pragma unroll
+  for (int i = 0; i < kSampWaves; ++i) {
+    if (!inside && segsum[i] > 0.0f) {
+      pick = i;
+      last = segsum[i];
+      inside = target < before + last;
+      if (!inside) before += last;
+    }
+  }
+  // (rounding may leave the target past the last sum: the last non-empty segment takes it)
+  if (pick >= 0 && !inside) before -= last;
+  *segment = pick < 0 ? 0 : pick;
+  *rem = target - before;
+}
+
+// Pieces of the segment at `base`, cl elements each, by a workgroup of 1024 threads: their exponentials go through LDS,
+// LEN elements of every piece at a time, the first wavefront adds up one piece per lane and walks the one that holds
+// `rem`. Returns the drawn token, in the first wavefront.
+constexpr int kPieceLong = 150;                                   // a vocabulary of 151936 has pieces of 149: one round trip
+constexpr int piece_row(int len) { return len | 1; }                // odd: 64 lanes read 64 pieces without bank conflicts
+template <int LEN>
+__device__ __forceinline__ int draw_from_segment(float* s_piece, const int* s_rej, int nrej, const float* __restrict__ row, int V,
+                                                 float m, float inv_temp, int base, int cl, float rem) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  constexpr int ROW = piece_row(LEN);
+  // running sums of every piece behind each kMark elements, so that the walk of the drawn piece need not start at its front
+  constexpr int kMark = 16, kMarks = (LEN + kMark - 1) / kMark;
+  static_assert(kMarks <= 64, "one mark per lane");
+  __shared__ float s_mark[kMarks][64];
+  constexpr int kLoads = (64 * LEN + kSampThreads - 1) / kSampThreads;
+  float psum = 0.0f;
+  for (int c0 = 0; c0 < cl; c0 += LEN) {
+    const int cn = cl - c0 < LEN ? cl - c0 : LEN;
+    const float per = 1.0f / (float)cn;
+    float v[kLoads];
+    int slot[kLoads];  // place in s_piece, -1: none
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      const int f = tid + q * kSampThreads;  // (consecutive threads, consecutive elements where one round takes whole pieces)
+      int piece = (int)((float)f * per);     // f / cn: below 2^14, so off by one at most
+      if (piece * cn > f) --piece;
+      if ((piece + 1) * cn <= f) ++piece;
+      const int j = f - piece * cn, i = base + piece * cl + c0 + j;
+      const bool in = f < 64 * cn;
+      slot[q] = in ? (piece * ROW + j) | (i < V ? 0 : 1 << 30) : -1;
+      v[q] = in && i < V ? row[i] : 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q)
+      if (slot[q] >= 0) s_piece[slot[q] & ~(1 << 30)] = slot[q] >> 30 ? 0.0f : __expf((v[q] - m) * inv_temp);
+    __syncthreads();
+    for (int r = tid; r < nrej; r += kSampThreads) {
+      const int at = s_rej[r] - base;
+      if (at >= 0 && at < 64 * cl) {
+        const int piece = at / cl, j = at - piece * cl - c0;
+        if (j >= 0 && j < cn) s_piece[piece * ROW + j] = 0.0f;
+      }
+    }
+    __syncthreads();
+    if (tid < 64) {
+      const float* mine = s_piece + lane * ROW;
+      for (int j0 = 0, q = 0; j0 < cn; j0 += kMark, ++q) {
+        float e[kMark];
+#pragma unroll
+        for (int u = 0; u < kMark; ++u) e[u] = j0 + u < cn ? mine[j0 + u] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < kMark; ++u) psum += e[u];  // (trailing zeros leave a sum of non-negative terms as it is)
+        if (cl <= LEN) s_mark[q][lane] = psum;
+      }
+    }
+    if (cl > LEN) __syncthreads();
+  }
+  if (tid >= 64) return 0;
+  const float incl = wave_incl_scan_f32(psum, lane);
+  const unsigned long long hit = __ballot(psum > 0.0f && rem < incl);
+  const unsigned long long any = __ballot(psum > 0.0f);
+  int owner = -1;
+  if (hit) owner = __ffsll((long long)hit) - 1;
+  else if (any) owner = 63 - __clzll((long long)any);  // rounding: the last piece with mass takes it
+  if (owner < 0) return 0;
+  const float r2 = __shfl(rem - (incl - psum), owner);
+  const int pb = base + owner * cl;
+  int pick = -1;
+  float run = 0.0f;
+  bool inside = false;
+  int first = 0;  // element the walk starts at, behind the last mark that the target lies past
+  if (cl <= LEN) {
+    wave_lds_fence();
+    const int marks = (cl + kMark - 1) / kMark;
+    const float mk = lane < marks ? s_mark[lane][owner] : 0.0f;
+    const unsigned long long past = __ballot(lane < marks && mk > 0.0f && r2 < mk);
+    if (past) {
+      const int q = __ffsll((long long)past) - 1;
+      first = q * kMark;
+      if (q > 0) run = __shfl(mk, q - 1);
+    }
+  }
+  for (int c0 = 0; c0 < cl && !inside; c0 += LEN) {
+    const int cn = cl - c0 < LEN ? cl - c0 : LEN;
+    const float* src = s_piece + owner * ROW;
+    if (cl > LEN) {  // (LDS holds the last round: the owner's elements of this one again, by this wavefront)
+      for (int j = lane; j < cn; j += 64) {
+        const int i = pb + c0 + j;
+        float e = i < V ? __expf((row[i] - m) * inv_temp) : 0.0f;
+        for (int r = 0; r < nrej; ++r)
+          if (s_rej[r] == i) e = 0.0f;
+        s_piece[j] = e;
+      }
+      wave_lds_fence();
+      src = s_piece;
+    }
+    for (int j0 = first; j0 < cn && !inside; j0 += 8) {
+      float e[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) e[u] = j0 + u < cn ? src[j0 + u] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const bool take = !inside && e[u] > 0.0f;
+        pick = take ? pb + c0 + j0 + u : pick;
+        run = take ? run + e[u] : run;
+        inside = take ? r2 < run : inside;
+      }
+    }
+    if (cl > LEN) wave_lds_fence();
+  }
+  return pick < 0 ? 0 : pick;
+}
+
+// Rows of up to kOneDrawRow logits: one workgroup per tree walks, sums the segments, one per wavefront, and draws.
+// SHORT: statistics of short_row_stats_kernel; a segment is at most 16 loads per lane, and the code walked through counts.
+// (One tree of 8 nodes, four of 32, eight of 64, all launches, us, one workgroup -> spread as below: 16385 logits 15.9 -> 18.4,
+// 18.0 -> 20.1, 28.5 -> 29.5; 32000 logits 16.9 -> 18.8, 19.9 -> 20.7, 37.3 -> 36.9; 65536 logits 25.2 -> 22.2, 30.3 -> 27.7,
+// 57.2 -> 55.8.)
+constexpr int kOneDrawRow = 49152;
+template <bool SHORT>
+__global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
+    const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
+    const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
+    const float* __restrict__ u_node, const float* __restrict__ u_bonus, int32_t* __restrict__ path, int path_stride,
+    int32_t* __restrict__ path_len, int32_t* __restrict__ bonus, int32_t* __restrict__ status) {
+  constexpr int kBatch = SHORT ? 4 : kStatsBatch;
+  constexpr int kPiece = (SHORT ? kShortRow : kOneDrawRow) / (kSampWaves * 64);
+  __shared__ SampTree s_tree;
+  __shared__ int s_rej[kMaxSel];
+  __shared__ float s_piece[64 * piece_row(kPiece)];
+  __shared__ int s_cur, s_nrej;
+  __shared__ float s_segsum[kSampWaves];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
+  sampled_walk<SHORT>(s_tree, s_rej, &s_cur, &s_nrej, true, lo, n, parent, tok, logits, V, inv_temp, stats, u_node,
+                     path + (size_t)b * path_stride, path_stride, path_len + b, status);
   const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const float* row = logits + (size_t)(lo + cur) * V;
   const float* st_cur = stats + (size_t)(lo + cur) * kSampStats;
   const float m = SHORT ? st_cur[0] : stats_max(st_cur);
-  auto mass = [&](float v, int i) {
-    float e = __expf((v - m) * inv_temp);
-    for (int r = 0; r < nrej; ++r)
-      if (s_rej[r] == i) e = 0.0f;
-    return e;
-  };
-  // segment sums: segment w = [w * seg, (w + 1) * seg) with seg a multiple of 64
-  const int seg = (((V + kSampWaves - 1) / kSampWaves) + 63) & ~63;
-  const int sb = w * seg;
-  const int se = sb + seg < V ? sb + seg : V;
+  const int seg = samp_segment(V);
+  const int sb = w * seg, se = sb + seg < V ? sb + seg : V;
   float acc = 0.0f;
   for (int i0 = sb; i0 < se; i0 += 64 * kBatch) {
     float e[kBatch];
@@ -728,73 +882,117 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   acc = wave_sum(acc);
   if (lane == 0) s_segsum[w] = acc;
   __syncthreads();
-  if (tid == 0) {
-    float total = 0.0f;
-    for (int i = 0; i < kSampWaves; ++i) total += s_segsum[i];
-    const float target = u_bonus[b] * total;
-    float before = 0.0f;
-    int pick = -1;
-    bool inside = false;
-    for (int i = 0; i < kSampWaves && !inside; ++i) {
-      if (s_segsum[i] > 0.0f) {
-        pick = i;
-        inside = target < before + s_segsum[i];
-        if (!inside) before += s_segsum[i];
-      }
-    }
-    // (rounding may leave the target past the last sum: the last non-empty segment takes it)
-    if (pick >= 0 && !inside) before -= s_segsum[pick];
-    s_seg = pick < 0 ? 0 : pick;
-    s_rem = target - before;
-  }
-  __syncthreads();
-  const int cl = seg >> 6;  // contiguous piece per lane of the first wavefront
-  const int base = __builtin_amdgcn_readfirstlane(s_seg) * seg;
-  float psum = 0.0f;
-  for (int c0 = 0; c0 < cl; c0 += 64) {
-    const int cn = cl - c0 < 64 ? cl - c0 : 64;
+  int segment;
+  float rem;
+  pick_segment(s_segsum, u_bonus[b], &segment, &rem);
+  segment = __builtin_amdgcn_readfirstlane(segment);
+  const int pick = draw_from_segment<kPiece>(s_piece, s_rej, nrej, row, V, m, inv_temp, segment * seg, seg >> 6, rem);
+  if (tid == 0) bonus[b] = pick;
+}
+
+// Longer rows, in two launches. First one workgroup per (tree, segment): what bounds the sums is instruction issue, 149
+// exponentials per lane and segment at a vocabulary of 151936, so they are spread over 16 CUs per tree instead of one, and
+// over the four wavefronts of a workgroup, each a quarter of the 64-element blocks; the first wavefront then adds them up
+// from LDS in order. Every workgroup walks the tree for itself, which costs no hand-off; the first one of a tree writes the
+// path. What the draw needs goes to the statistics of the tree's root (kSampSeg, kSampCur, kSampMax).
+constexpr int kSegThreads = 256;
+constexpr int kSegBlocks = 152;  // blocks of 64 elements per round: one round up to a vocabulary of 155648
+__global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
+    const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
+    const float* __restrict__ logits, int V, float inv_temp, float* stats, const float* __restrict__ u_node,
+    int32_t* __restrict__ path, int path_stride, int32_t* __restrict__ path_len, int32_t* __restrict__ status) {
+  constexpr int kWaves = kSegThreads / 64, kPer = kSegBlocks / kWaves;
+  static_assert(kSegBlocks % kWaves == 0, "whole blocks per wavefront");
+  __shared__ SampTree s_tree;
+  __shared__ int s_rej[kMaxSel];
+  __shared__ float s_e[kSegBlocks * 64];
+  __shared__ int s_cur, s_nrej;
+  const int b = (int)blockIdx.x / kSampWaves, part = (int)blockIdx.x % kSampWaves;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
+  sampled_walk<false>(s_tree, s_rej, &s_cur, &s_nrej, part == 0, lo, n, parent, tok, logits, V, inv_temp, stats, u_node,
+                      path + (size_t)b * path_stride, path_stride, path_len + b, status);
+  const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
+  const float* row = logits + (size_t)(lo + cur) * V;
+  const float m = stats_max(stats + (size_t)(lo + cur) * kSampStats);
+  const int seg = samp_segment(V);
+  const int sb = part * seg, se = sb + seg < V ? sb + seg : V;
+  float acc = 0.0f;
+  for (int c0 = sb; c0 < se; c0 += kSegBlocks * 64) {
+    const int cn = se - c0 < kSegBlocks * 64 ? se - c0 : kSegBlocks * 64;
+    float v[kPer];
 #pragma unroll
-    for (int q = 0; q < 64 / kSampWaves; ++q) {
-      const int piece = w * (64 / kSampWaves) + q;
-      const int i = base + piece * cl + c0 + lane;
-      if (lane < cn) s_piece[piece][lane] = i < V ? mass(row[i], i) : 0.0f;
+    for (int u = 0; u < kPer; ++u) {
+      const int i = (u * kWaves + w) * 64 + lane;
+      v[u] = i < cn ? row[c0 + i] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = (u * kWaves + w) * 64 + lane;
+      s_e[i] = i < cn ? __expf((v[u] - m) * inv_temp) : 0.0f;
     }
     __syncthreads();
-    if (w == 0)
-      for (int j = 0; j < cn; ++j) psum += s_piece[lane][j];
+    for (int r = tid; r < nrej; r += kSegThreads) {
+      const int at = s_rej[r] - c0;
+      if (at >= 0 && at < cn) s_e[at] = 0.0f;
+    }
+    __syncthreads();
+    if (w == 0) {
+      const int blocks = (cn + 63) >> 6;
+#pragma unroll 8
+      for (int q = 0; q < blocks; ++q) acc += s_e[q * 64 + lane];
+    }
     __syncthreads();
   }
   if (w == 0) {
-    const float incl = wave_incl_scan_f32(psum, lane);
-    const float rem = s_rem;
-    const unsigned long long hit = __ballot(psum > 0.0f && rem < incl);
-    const unsigned long long any = __ballot(psum > 0.0f);
-    int owner = -1;
-    if (hit) owner = __ffsll((long long)hit) - 1;
-    else if (any) owner = 63 - __clzll((long long)any);  // rounding: the last piece with mass takes it
-    int pick = -1;
-    if (owner >= 0) {
-      // the owner's piece, element by element, 64 of them fetched at a time
-      const float r2 = __shfl(rem - (incl - psum), owner);
-      const int pb = base + owner * cl;
-      float run = 0.0f;
-      bool inside = false;
-      for (int c0 = 0; c0 < cl && !inside; c0 += 64) {
-        const int i = pb + c0 + lane;
-        const int ebits = __float_as_int((c0 + lane < cl && i < V) ? mass(row[i], i) : 0.0f);
-        const int jn = cl - c0 < 64 ? cl - c0 : 64;
-        for (int j = 0; j < jn && !inside; ++j) {
-          const float e = __int_as_float(__builtin_amdgcn_readlane(ebits, j));
-          if (e > 0.0f) {
-            pick = pb + c0 + j;
-            run += e;
-            inside = r2 < run;
-          }
-        }
+    acc = wave_sum(acc);
+    float* out = stats + (size_t)lo * kSampStats;
+    if (lane == 0) {
+      out[kSampSeg + part] = acc;
+      if (part == 0) {
+        out[kSampCur] = __int_as_float(cur);
+        out[kSampMax] = m;
       }
     }
-    if (lane == 0) bonus[b] = pick < 0 ? 0 : pick;
   }
+}
+
+// Second: one workgroup per tree draws from the segment that the sums pick. (Four trees of 32 nodes, vocabulary 151936: the
+// walk and the draw 31 us in one workgroup per tree, 18 in these two launches; 8 and 9 us, of which 3 each are the launch.)
+__global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
+    const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
+    const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats, const float* __restrict__ u_bonus,
+    int32_t* __restrict__ bonus) {
+  __shared__ int s_rej[kMaxSel];
+  __shared__ float s_piece[64 * piece_row(kPieceLong)];
+  __shared__ int s_nrej;
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
+  const float* root = stats + (size_t)lo * kSampStats;
+  const int cur = __builtin_amdgcn_readfirstlane(__float_as_int(root[kSampCur]));
+  if (tid == 0) s_nrej = 0;
+  __syncthreads();
+  for (int i = tid; i < n; i += kSampThreads) {  // the tokens rejected at the last node are its children's
+    int pa = i == 0 ? -1 : parent[lo + i];
+    if (i > 0 && (pa < 0 || pa >= i)) pa = 0;
+    const int tk = tok[lo + i];
+    if (pa == cur) s_rej[atomicAdd(&s_nrej, 1)] = tk < 0 || tk >= V ? -1 : tk;
+  }
+  float segsum[kSampWaves];
+#pragma unroll
+  for (int i = 0; i < kSampWaves; ++i) segsum[i] = root[kSampSeg + i];
+  int segment;
+  float rem;
+  pick_segment(segsum, u_bonus[b], &segment, &rem);
+  segment = __builtin_amdgcn_readfirstlane(segment);
+  const float m = root[kSampMax];
+  __syncthreads();
+  const int nrej = __builtin_amdgcn_readfirstlane(s_nrej);
+  const int seg = samp_segment(V);
+  const int pick = draw_from_segment<kPieceLong>(s_piece, s_rej, nrej, logits + (size_t)(lo + cur) * V, V, m, inv_temp,
+                                                 segment * seg, seg >> 6, rem);
+  if (tid == 0) bonus[b] = pick;
 }
 
 // the launches of acceptance under sampling on `stats`, [T][kSampStats] floats of scratch
@@ -809,13 +1007,20 @@ int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const 
   }
   int rc = launch_status("softmax statistics kernels");
   if (rc) return rc;
-  if (V <= kShortRow)
-    hipLaunchKernelGGL(accept_sampled_kernel<true>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                       u_node, u_bonus, path, path_stride, path_len, bonus, status);
-  else
-    hipLaunchKernelGGL(accept_sampled_kernel<false>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                       u_node, u_bonus, path, path_stride, path_len, bonus, status);
-  return launch_status("accept_sampled_kernel");
+  if (V <= kOneDrawRow) {
+    if (V <= kShortRow)
+      hipLaunchKernelGGL(accept_sampled_kernel<true>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                         u_node, u_bonus, path, path_stride, path_len, bonus, status);
+    else
+      hipLaunchKernelGGL(accept_sampled_kernel<false>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                         u_node, u_bonus, path, path_stride, path_len, bonus, status);
+    return launch_status("accept_sampled_kernel");
+  }
+  hipLaunchKernelGGL(accept_sampled_walk_kernel, dim3(B * kSampWaves), dim3(kSegThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp,
+                     stats, u_node, path, path_stride, path_len, status);
+  hipLaunchKernelGGL(accept_sampled_draw_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
+                     u_bonus, bonus);
+  return launch_status("accept_sampled_draw_kernel");
 }
 
 constexpr int kUnionThreads = 1024;  // >= the largest supported E: one expert per thread in the scan

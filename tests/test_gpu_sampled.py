@@ -206,3 +206,14 @@ def test_short_and_long_rows_agree(ctx_small, V):
     parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(41, [1, 9, 16, 30], V)
     path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.8, u_node, u_bonus, 30)
     assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.8, path, plen, bonus) <= 1
+
+
+@pytest.mark.parametrize("V", [49152, 49153, 151936, 16 * 64 * 150, 16 * 64 * 150 + 1, 16 * 64 * 152, 16 * 64 * 152 + 1])
+@pytest.mark.parametrize("u", [0.0, 0.37, 1.0 - 2.0 ** -24])
+def test_draw_rounds(ctx_small, V, u):
+    """The longest row of one workgroup and the next; rows of one round and of one round more, of the pieces (150 elements)
+    and of the segments (152 blocks of 64); the target at both ends of the cumulative sum, where the first and the last token with mass take it."""
+    parents, tree_off, parent, logits, tok, u_node, _ = make_sampling_case(77, [5, 1], V, spread=2.0)
+    logits[:, -200:] += 6.0  # (mass in the last segment and piece)
+    path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, np.full(2, u, np.float32), 8)
+    assert check_against_oracle(parents, tree_off, logits, tok, u_node, np.full(2, u, np.float32), 0.9, path, plen, bonus) < 2
