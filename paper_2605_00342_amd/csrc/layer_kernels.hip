@@ -1,6 +1,8 @@
 // Kernels of one verification pass through an MoE decoder layer (Sec. 2.1-2.2) other than
 // the streaming GEMM: weight packing, tree preparation + RMSNorm, tree-masked attention
 // (split over the context) and its merge, router top-k, un-permute/combine.
+#include <utility>
+
 #include "ctx.h"
 #include "gemm_stream.h"
 #include "layer_launch.h"
@@ -743,57 +745,91 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   }
 }
 
-// merge of the per-split partial softmaxes. D/4 lanes per (token, head) row, each with four
-// consecutive output columns; blockDim / (D/4) rows per workgroup (D is 64 or 128, so the lanes of a
-// row sit in one wavefront; one-wavefront workgroups when there are few rows, so that the serial walk
-// over the splits is spread over more CUs). Empty splits carry max = -inf and their partial rows are never read
-// into the sum. The partial rows of the first splits are requested before the (max, sum) pairs
-// are reduced, so the two round trips overlap.
-constexpr int kMergeBatch = 17;  // 16 context splits + the draft-node split: the default shape of a 2048-key context
+// merge of the per-split partial softmaxes. D/4 lanes (LPR: 16 or 32) per (token, head) row, each with four
+// consecutive output columns; blockDim / LPR rows per workgroup (one-wavefront workgroups when there are few rows, so that
+// the serial walk over the splits is spread over more CUs). Empty splits carry max = -inf and their partial rows are never
+// read into the sum. The partial rows of the first MB splits are requested before the (max, sum) pairs are reduced, so the
+// two round trips overlap.
+// What bounds it with few tokens is the code a wavefront walks through (with a cold instruction cache), not the bytes, so
+// that is kept short: every 16 lanes hold the pairs of all splits, turn each into its split's factor once and hand the
+// factors round by DPP; partial rows are requested from a base that is the same for all lanes; as many splits are unrolled
+// as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.8 -> 3.5, 32
+// tokens of 8 heads 4.9 -> 2.8, of 32 heads 5.1 -> 4.0; 5 splits, 917 tokens 13.0 -> 8.2.)
+constexpr int kMergeHeld = 3;                     // splits a lane of 16 holds the pairs of
+constexpr int kMergePairs = 16 * kMergeHeld;      // further ones (fp32 storage, long contexts) are walked one by one
+static_assert(kMergePairs >= kAttnMfmaMaxSplits, "the bf16 kernel's splits are all held");
 
-template <typename ST>
+// factor of split S of the lane's row
+template <int S>
+__device__ __forceinline__ float merge_factor(const float (&sc)[kMergeHeld]) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sc[S >> 4]), 0x150 + (S & 15), 0xF, 0xF, false));  // row_newbcast
+}
+template <int S0, int... I>
+__device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const float (&sc)[kMergeHeld], std::integer_sequence<int, I...>) {
+  const float f[] = {merge_factor<S0 + I>(sc)...};
+#pragma unroll
+  for (int i = 0; i < (int)sizeof...(I); ++i) {
+    const f32x4 x = f[i] != 0.0f ? v[i] : f32x4{0, 0, 0, 0};  // rows of empty splits hold no data
+    acc += x * f[i];
+  }
+}
+
+template <typename ST, int LPR, int MB>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                         int nsplits, int rows, int D, void* __restrict__ out,
+                                                         int nsplits, int rows, void* __restrict__ out,
                                                          void* __restrict__ aux_out, int Hq, const int* __restrict__ t_dev) {
-  const int lpr = D >> 2;  // lanes per row: 16 or 32
+  constexpr int D = 4 * LPR;
   const int tid = threadIdx.x;
-  const int row = blockIdx.x * ((int)blockDim.x / lpr) + tid / lpr;
-  const int c4 = tid & (lpr - 1);
+  const int row = blockIdx.x * ((int)blockDim.x / LPR) + tid / LPR;
+  const int c4 = tid & (LPR - 1), l16 = tid & 15;
   // (`rows` = tokens x heads the partials were laid out for; rows past the call's actual token count hold nothing)
   if (row >= rows || row >= dyn_tokens(t_dev, rows / Hq) * Hq) return;  // (no barrier follows)
-  const size_t sstride = (size_t)rows * D;
-  const float* po = part_o + (size_t)row * D + c4 * 4;
-  const float* pml = part_ml + (size_t)row * 2;
-  f32x4 v[kMergeBatch];
+  float2 ml[kMergeHeld];
 #pragma unroll
-  for (int i = 0; i < kMergeBatch; ++i)
-    v[i] = i < nsplits ? *reinterpret_cast<const f32x4*>(po + (size_t)i * sstride) : f32x4{0, 0, 0, 0};
-  // global maximum and normaliser: the lanes of a row share the splits between them
+  for (int q = 0; q < kMergeHeld; ++q) {
+    const int sp = l16 + 16 * q;
+    ml[q] = make_float2(-INFINITY, 0.0f);
+    if (q * 16 < nsplits && sp < nsplits) ml[q] = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
+  }
+  const size_t sstride = (size_t)rows * D, off = (size_t)row * D + c4 * 4;
+  const float* base = part_o;  // of the split to request next
+  f32x4 v[MB];
+  auto request = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      v[i] = *reinterpret_cast<const f32x4*>(base + off);  // (past the last split: the last one again, at a factor of zero)
+      if (s0 + i + 1 < nsplits) base += sstride;
+    }
+  };
+  request(0);
+  // global maximum and normaliser: the lanes share the splits between them
   float M = -INFINITY;
-  for (int sp = c4; sp < nsplits; sp += lpr) M = fmaxf(M, pml[(size_t)sp * rows * 2]);
-  M = row16_max(M);  // lpr is 16 or 32: DPP inside the rows of 16, one shuffle across the pair
-  if (lpr == 32) M = fmaxf(M, __shfl_xor(M, 16));
+#pragma unroll
+  for (int q = 0; q < kMergeHeld; ++q) M = fmaxf(M, ml[q].x);
+  for (int sp = l16 + kMergePairs; sp < nsplits; sp += 16) M = fmaxf(M, part_ml[((size_t)sp * rows + row) * 2]);
+  M = row16_max(M);
+  auto factor = [&](float m) { return m == -INFINITY ? 0.0f : __expf(m - M); };
   float l = 0.0f;
-  for (int sp = c4; sp < nsplits; sp += lpr) {
-    const float2 ml = *reinterpret_cast<const float2*>(pml + (size_t)sp * rows * 2);
-    l += ml.x == -INFINITY ? 0.0f : ml.y * __expf(ml.x - M);
+  float sc[kMergeHeld];
+#pragma unroll
+  for (int q = 0; q < kMergeHeld; ++q) {
+    sc[q] = factor(ml[q].x);
+    l += ml[q].y * sc[q];
+  }
+  for (int sp = l16 + kMergePairs; sp < nsplits; sp += 16) {
+    const float2 x = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
+    l += x.x == -INFINITY ? 0.0f : x.y * factor(x.x);
   }
   l = row16_sum(l);
-  if (lpr == 32) l += __shfl_xor(l, 16);
   f32x4 acc = {0, 0, 0, 0};
-  for (int s0 = 0; s0 < nsplits; s0 += kMergeBatch) {
-    if (s0 > 0) {
-#pragma unroll
-      for (int i = 0; i < kMergeBatch; ++i)
-        v[i] = s0 + i < nsplits ? *reinterpret_cast<const f32x4*>(po + (size_t)(s0 + i) * sstride) : f32x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) {
-      if (s0 + i < nsplits) {
-        const float ms = pml[(size_t)(s0 + i) * rows * 2];
-        const float sc = ms == -INFINITY ? 0.0f : __expf(ms - M);
-        if (sc != 0.0f) acc += v[i] * sc;  // rows of empty splits hold no data
-      }
+  merge_add<0>(acc, v, sc, std::make_integer_sequence<int, MB>{});
+  if (MB == 17 && nsplits > MB) {
+    request(MB);
+    merge_add<MB>(acc, v, sc, std::make_integer_sequence<int, MB>{});
+    for (int sp = 2 * MB; sp < nsplits; ++sp) {
+      const float f = factor(part_ml[((size_t)sp * rows + row) * 2]);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(part_o + (size_t)sp * sstride + off);
+      if (f != 0.0f) acc += x * f;
     }
   }
 #pragma unroll
@@ -1824,12 +1860,19 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
   const int mthreads = (long long)mrows * (m.D / 4) >= 256 * 256 ? 256 : 64;  // at least ~256 workgroups, or one wavefront each
   const int rows_per_wg = mthreads / (m.D / 4);
   const dim3 mgrid((mrows + rows_per_wg - 1) / rows_per_wg);
-  if (m.dtype == EVICT_BF16)
-    hipLaunchKernelGGL(attn_merge_kernel<BF16>, mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows, m.D,
-                       c->attn_o, aux_out, m.Hq, c->t_dev);
-  else
-    hipLaunchKernelGGL(attn_merge_kernel<F32>, mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows, m.D,
-                       c->attn_o, aux_out, m.Hq, c->t_dev);
+#define EVICT_MERGE(ST_, LPR_, MB_)                                                                                             \
+  hipLaunchKernelGGL((attn_merge_kernel<ST_, LPR_, MB_>), mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows,   \
+                     c->attn_o, aux_out, m.Hq, c->t_dev)
+#define EVICT_MERGE_D(ST_, LPR_)                        \
+  do {                                                  \
+    if (nsplits <= 5) EVICT_MERGE(ST_, LPR_, 5);        \
+    else if (nsplits <= 9) EVICT_MERGE(ST_, LPR_, 9);   \
+    else EVICT_MERGE(ST_, LPR_, 17);                    \
+  } while (0)
+  if (m.dtype == EVICT_BF16) { if (m.D == 128) EVICT_MERGE_D(BF16, 32); else EVICT_MERGE_D(BF16, 16); }
+  else { if (m.D == 128) EVICT_MERGE_D(F32, 32); else EVICT_MERGE_D(F32, 16); }
+#undef EVICT_MERGE_D
+#undef EVICT_MERGE
   return launch_status("attn_merge_kernel");
 }
 

@@ -1,0 +1,26 @@
+"""The merge of the attention's partial softmaxes where its unrolling changes: up to 5, 9 and 17 splits in one go, a second batch of
+17, pairs held by the lanes up to 48 and walked one by one beyond; with splits that are empty for the shorter sequence."""
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+pytest.importorskip("paper_2605_00342_amd")
+from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
+
+
+@pytest.mark.parametrize("splits", [3, 5, 6, 9, 10, 17, 18, 34, 35, 48, 49, 60])
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_counts(splits, D):
+    L = 64 * (splits - 2)  # 64 keys a split, two splits of draft nodes
+    cfg = synth.ModelCfg("f32merge", "f32", d=128, Hq=2, Hkv=1, D=D, E=16, k=2, F=64, theta=1e4)
+    case = synth.make_case(cfg.name, n=5, L=L, seed=splits, sigma=0.5, tree="random", batch=2, L_list=[L, 70], cfg=cfg)
+    check_against_oracle(case, run_case(case))
+
+
+@pytest.mark.parametrize("chunks", [4, 5, 8, 9, 16, 17, 31, 32])
+def test_bf16_split_counts(chunks):
+    cfg = synth.ModelCfg("bf16merge", "bf16", d=256, Hq=4, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    case = synth.make_case(cfg.name, n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random", cfg=cfg)
+    check_against_oracle(case, run_case(case))
