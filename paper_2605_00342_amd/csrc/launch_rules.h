@@ -66,6 +66,15 @@ constexpr bool lm_tiled(int T, int n_strips, int nkb) {
 // 24.1 -> 24.8.)
 constexpr int lm_units(int T, int n_strips) { return T > 16 || (T > 12 && n_strips > 1024) ? 8 : 2; }
 
+// With two token tiles a workgroup fills a CU, and as long as there are enough strips they are dealt out in one round of 256
+// workgroups: three rounds of 8 strips leave the last a third full (151936 rows of 64 blocks, us, 8 strips per workgroup -> 38:
+// 32 tokens 118.3 -> 113.7, 24 tokens 112.4 -> 109.7; with one token tile two workgroups share a CU and 8 stay the best,
+// 16 tokens 103.3, 104.3).
+constexpr int lm_strips(int T, int n_strips) {
+  const int units = lm_units(T, n_strips), round = (n_strips + 255) / 256;
+  return T > 16 && round > units ? round : units;
+}
+
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }

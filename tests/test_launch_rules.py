@@ -20,6 +20,7 @@ int chunk(int slots, int pairs) { return gateup_chunk(slots, gateup_chunk_counts
 int tiled(int T, int k, int E, int nkb, int pairs, int strip) { return experts_tiled(T, k, E, nkb, pairs, strip); }
 int lm(int T, int n_strips, int nkb) { return lm_tiled(T, n_strips, nkb); }
 int units(int T, int n_strips) { return lm_units(T, n_strips); }
+int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
@@ -109,3 +110,10 @@ def test_lm_head(rules):
     assert not rules.lm(96, 2001, 64) and not rules.lm(96, 2000, 32)      # odd strip counts, lengths that are not built
     assert [rules.units(T, big) for T in (1, 9, 12, 13, 16, 17)] == [2, 2, 2, 8, 8, 8]
     assert rules.units(16, 1000) == 2 and rules.units(32, 64) == 8
+
+
+def test_lm_head_rounds(rules):
+    assert [rules.strips(T, 9496) for T in (1, 13, 16, 17, 32)] == [2, 8, 8, 38, 38]
+    for n in (64, 1024, 2048, 2049, 6400, 9496, 12504):
+        s = rules.strips(32, n)
+        assert s >= 8 and -(-n // s) <= 256
