@@ -753,7 +753,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // What bounds it with few tokens is the code a wavefront walks through (with a cold instruction cache), not the bytes, so
 // that is kept short: every 16 lanes hold the pairs of all splits, turn each into its split's factor once and hand the
 // factors round by DPP; partial rows are requested from a base that is the same for all lanes; as many splits are unrolled
-// as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.8 -> 3.5, 32
+// as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.8 -> 2.9, 32
 // tokens of 8 heads 4.9 -> 2.8, of 32 heads 5.1 -> 4.0; 5 splits, 917 tokens 13.0 -> 8.2.)
 constexpr int kMergeHeld = 3;                     // splits a lane of 16 holds the pairs of
 constexpr int kMergePairs = 16 * kMergeHeld;      // further ones (fp32 storage, long contexts) are walked one by one
@@ -1211,11 +1211,13 @@ __global__ __launch_bounds__(kRouterThreads) void union_worklist_kernel(
 // LM head, second step: per token, the best (value, row) over the per-strip candidates;
 // equal values go to the lower row (vocabulary) index. One workgroup per token.
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void argmax_reduce_kernel(const float* __restrict__ val, const int32_t* __restrict__ idx,
+// (1024 threads: a vocabulary of 151936 is two round trips of eight candidates a thread, five with 256; 32 tokens 7.3 -> 6.4 us)
+constexpr int kArgmaxThreads = 1024;
+__global__ __launch_bounds__(kArgmaxThreads) void argmax_reduce_kernel(const float* __restrict__ val, const int32_t* __restrict__ idx,
                                                             int nstrips, int ld, int32_t* __restrict__ next,
                                                             float* __restrict__ best_out, const int* __restrict__ t_dev) {
-  __shared__ float s_v[4];
-  __shared__ int s_i[4];
+  __shared__ float s_v[kArgmaxThreads / 64];
+  __shared__ int s_i[kArgmaxThreads / 64];
   const int t = blockIdx.x, tid = threadIdx.x;
   if (t >= dyn_tokens(t_dev, (int)gridDim.x)) return;  // (rows past the call's actual token count)
   float bv = -INFINITY;
@@ -1223,12 +1225,12 @@ __global__ __launch_bounds__(256) void argmax_reduce_kernel(const float* __restr
   // candidates of a token are contiguous ([T][ld] with ld >= nstrips): eight loads in flight per thread
   const float* vrow = val + (size_t)t * ld;
   const int32_t* irow = idx + (size_t)t * ld;
-  for (int s0 = tid; s0 < nstrips; s0 += 256 * 8) {
+  for (int s0 = tid; s0 < nstrips; s0 += kArgmaxThreads * 8) {
     float v[8];
     int i[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int s = s0 + 256 * u;
+      const int s = s0 + kArgmaxThreads * u;
       v[u] = s < nstrips ? vrow[s] : -INFINITY;
       i[u] = s < nstrips ? irow[s] : 0x7fffffff;
     }
@@ -1245,7 +1247,7 @@ __global__ __launch_bounds__(256) void argmax_reduce_kernel(const float* __restr
   if ((tid & 63) == 0) { s_v[tid >> 6] = bv; s_i[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 4; ++w)
+    for (int w = 1; w < kArgmaxThreads / 64; ++w)
       if (s_v[w] > bv || (s_v[w] == bv && s_i[w] < bi)) { bv = s_v[w]; bi = s_i[w]; }
     next[t] = bi;
     if (best_out) best_out[t] = bv;
@@ -1944,7 +1946,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
 
 int launch_argmax_reduce(const float* val, const int32_t* idx, int nstrips, int ld, int T, int32_t* next, float* best_out,
                          const int32_t* t_dev, hipStream_t s) {
-  hipLaunchKernelGGL(argmax_reduce_kernel, dim3(T), dim3(256), 0, s, val, idx, nstrips, ld, next, best_out, t_dev);
+  hipLaunchKernelGGL(argmax_reduce_kernel, dim3(T), dim3(kArgmaxThreads), 0, s, val, idx, nstrips, ld, next, best_out, t_dev);
   return launch_status("argmax_reduce_kernel");
 }
 
