@@ -89,11 +89,12 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
   A(&c.seq_of, T * 4);
   A(&c.rope_cs, T * m->D * 4);
   A(&c.rope_rev, (size_t)(m->D / 2) * 8);
-  A(&c.x_norm, T * d * eb);
+  const size_t T16 = (T + 15) / 16 * 16;  // (operand blocks are of 16 tokens)
+  A(&c.x_norm, T16 * d * eb);
   A(&c.q, T * HqD * eb);
   A(&c.part_o, (size_t)c.max_splits * T * HqD * 4);
   A(&c.part_ml, (size_t)c.max_splits * T * m->Hq * 2 * 4);
-  A(&c.attn_o, T * HqD * eb);
+  A(&c.attn_o, T16 * HqD * eb);
   A(&c.h, T * d * eb);
   A(&c.h_norm, T * d * eb);
   A(&c.logits, T * E * 4);
@@ -299,7 +300,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
   EVICT_MARK(0);
   // (in a stack the previous layer's combine has already normalised this layer's input)
   int rc = (tree_ready && x_norm_ready) ? EVICT_OK
-                                        : launch_prep(ctx, tree_off, parent, B, T, ctx_len, max_ctx_host, x_in, w->g_attn, tree_ready, s);
+                                        : launch_prep(ctx, tree_off, parent, B, T, ctx_len, max_ctx_host, x_in, w->g_attn, tree_ready, nullptr, s);
   if (rc) return rc;
   EVICT_MARK(1);
 
@@ -351,7 +352,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.n_strips = qkv_strips;
     a.nkb = m.d * eb / 64;
     a.X = ctx->x_norm;
-    a.ldx_bytes = (long long)m.d * eb;
+    a.x_shift = operand_shift(T);
     a.T = T;
     a.T_dev = ctx->t_dev;
     a.out0 = ctx->q; a.out1 = k_new; a.out2 = v_new;
@@ -378,7 +379,7 @@ static int verify_layer_impl(evict_ctx* ctx, const evict_layer_weights* w, const
     a.n_strips = m.d / 16;
     a.nkb = HqD * eb / 64;
     a.X = ctx->attn_o;
-    a.ldx_bytes = (long long)HqD * eb;
+    a.x_shift = operand_shift(T);
     a.T = T;
     a.T_dev = ctx->t_dev;
     a.out0 = ctx->h;
@@ -571,15 +572,14 @@ int evict_lm_head_argmax(evict_ctx* ctx, const void* x, const void* g_final, con
   EVICT_REQUIRE(aligned16(x) && aligned16(wlm_packed), EVICT_E_INVALID, "evict_lm_head_argmax: pointers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const int eb = elem_bytes(m.dtype);
-  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, s);  // final RMSNorm only
+  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, x_norm_out, s);  // final RMSNorm only
   if (rc) return rc;
-  if (x_norm_out) EVICT_HIP_CHECK(hipMemcpyAsync(x_norm_out, ctx->x_norm, (size_t)T * m.d * eb, hipMemcpyDeviceToDevice, s));
   GemmArgs a = {};
   a.W = (const u32x4*)wlm_packed;
   a.n_strips = m.vocab / 16;
   a.nkb = m.d * eb / 64;
   a.X = ctx->x_norm;
-  a.ldx_bytes = (long long)m.d * eb;
+  a.x_shift = operand_shift(T);
   a.T = T;
   a.T_dev = ctx->t_dev;
   a.out0 = ctx->lm_val;
@@ -600,15 +600,14 @@ int evict_lm_head_logits(evict_ctx* ctx, const void* x, const void* g_final, con
                 "evict_lm_head_logits: pointers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const int eb = elem_bytes(m.dtype);
-  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, s);  // final RMSNorm only
+  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, x_norm_out, s);  // final RMSNorm only
   if (rc) return rc;
-  if (x_norm_out) EVICT_HIP_CHECK(hipMemcpyAsync(x_norm_out, ctx->x_norm, (size_t)T * m.d * eb, hipMemcpyDeviceToDevice, s));
   GemmArgs a = {};
   a.W = (const u32x4*)wlm_packed;
   a.n_strips = m.vocab / 16;
   a.nkb = m.d * eb / 64;
   a.X = ctx->x_norm;
-  a.ldx_bytes = (long long)m.d * eb;
+  a.x_shift = operand_shift(T);
   a.T = T;
   a.T_dev = ctx->t_dev;
   a.out0 = logits;

@@ -34,11 +34,11 @@ struct evict_ctx {
   int32_t* seq_of;       // [T] sequence index of each token
   float* rope_cs;        // [T][D] cos (first half) and sin (second half) per token
   double* rope_rev;      // [D/2] rotary frequencies in revolutions per position
-  void* x_norm;          // [T][d] storage dtype
+  void* x_norm;          // [T][d] storage dtype, in operand blocks (operand_at)
   void* q;               // [T][Hq*D]
   float* part_o;         // [splits+1][T][Hq][D]
   float* part_ml;        // [splits+1][T][Hq][2]
-  void* attn_o;          // [T][Hq*D]
+  void* attn_o;          // [T][Hq*D], in operand blocks
   void* h;               // [T][d]
   void* h_norm;          // [T][d]
   float* logits;         // [T][E]

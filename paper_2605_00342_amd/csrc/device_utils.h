@@ -59,6 +59,25 @@ template <> __device__ __forceinline__ f32x4 load4<BF16>(const void* p, size_t i
   return v;
 }
 
+// Token operands of the dense projections and the LM head are kept in operand blocks: 64 bytes of the rows of 16 tokens, in the
+// order the lanes of a wavefront hold them (below), the blocks of 16 tokens one after the other. A wavefront then fetches a block
+// as 1 KiB in a row instead of half a cache line of each of 16 rows (us, rows -> blocks: output projection of 32 tokens, 4096
+// columns 8.9 -> 7.1, of 64 tokens, 2048 columns 7.5 -> 5.1; QKV of 32 tokens, 4096 columns 8.9 -> 7.1, of 917 tokens, 2048
+// columns 38.7 -> 34.1). Calls of up to 8 tokens have blocks of 8, 4, 2 or 1 (rows as they are), as the other lanes' tokens
+// would only spread them (blocks of 16 at one token: layer 56.9 -> 57.8 us).
+__host__ __device__ constexpr int operand_shift(int T) { return T > 8 ? 4 : T > 4 ? 3 : T > 2 ? 2 : T > 1 ? 1 : 0; }  // log2 of the tokens of a block
+// Byte offset of the 16 bytes at chunk c of token t's row of nkb blocks; the last tokens take a whole set of blocks.
+__device__ __forceinline__ unsigned operand_at(int t, int c, int nkb, int shift) {
+  return (((unsigned)(t >> shift) * nkb + (c >> 2)) * 64 << shift) + ((c & 3) * 16 << shift) + (t & ((1 << shift) - 1)) * 16;
+}
+// Kernels that write such rows, one workgroup per token, take 8 consecutive tokens on one XCD (workgroup ids go round-robin over
+// the 8), so that the pieces of a cache line, 16 bytes per token, meet in its L2 (16 trees of 64 nodes, layer: 465.5 -> 459.7 us).
+// Grids are padded to whole groups of 64 tokens; up to 8 tokens are left as they are.
+__device__ __forceinline__ int token_of_workgroup(int id, int shift) {
+  return shift < 4 ? id : (((id >> 6) * 8 + (id & 7)) << 3) + ((id >> 3) & 7);
+}
+__host__ __device__ constexpr int token_grid(int T) { return T > 8 ? (T + 63) / 64 * 64 : T; }
+
 // One 1 KiB operand block: each lane holds 16 bytes. With A[m][k] (16 rows) and B[k][n]
 // (16 columns), lane l carries row/column l%16 and the (l/16)-th quarter of the block's
 // contraction range; both operands use the same mapping so any k order cancels out.

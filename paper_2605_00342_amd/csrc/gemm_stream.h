@@ -37,8 +37,9 @@ struct GemmArgs {
   long long group_stride;  // u32x4 elements between experts
   int n_strips;          // 16-row strips per matrix (gate/up interleaved: 2 per 16 rows of F)
   int nkb;               // 1 KiB blocks per strip
-  const void* X;         // token operand rows, storage dtype
-  long long ldx_bytes;   // bytes between rows of X
+  const void* X;         // token operand, storage dtype; grouped: rows, dense: operand blocks (operand_at)
+  long long ldx_bytes;   // grouped: bytes between rows of X
+  int x_shift;           // dense: operand_shift of the call's tokens
   int grouped;           // 0: one matrix, tokens 0..T-1; 1: one matrix per union expert
   const int* union_count;  // grouped: [0] number of work slots (expert x token tile), [2] units per chunk for them (gateup_chunk)
   const WorkRec* work;   // per union slot (see WorkRec)
@@ -159,8 +160,10 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
       for (int r = 0; r < PF; ++r)
         if (r < nsteps) issue(A[r], r);
 
-      // token operand rows of this lane's column in each tile
+      // token operand of this lane's column in each tile
+      constexpr bool kDense = EPI != EPI_F32 && EPI != EPI_SWIGLU;  // (EPI_F32: a.grouped tells)
       const char* xrow[NT];
+      uint32_t xoff[NT];  // dense: offset from a base that is the same for all lanes
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         int col = tok0 + t * 16 + (lane & 15);
@@ -170,17 +173,21 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
           if (!a.x_by_token) row = p0 + col;
           else row = (t == 0 && tok0 == 0 && (lane & 15) < kWorkToks) ? tok_early : a.tok_of_pos[p0 + col];
         }
-        xrow[t] = (const char*)a.X + row * a.ldx_bytes + (lane >> 4) * 16;
+        xoff[t] = operand_at(col, lane >> 4, nkb, a.x_shift);
+        xrow[t] = (const char*)a.X + (a.grouped ? row * a.ldx_bytes + (lane >> 4) * 16 : (long long)xoff[t]);
       }
+      const int xstep = kDense || !a.grouped ? 64 << a.x_shift : 64;  // bytes between a row's blocks
       auto load_b = [&](int c) {
         int b0, nb;
         range(c, b0, nb);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const char* bp = xrow[t] + (long long)b0 * 64;  // one base per tile, constant offsets below
+          const char* base = (const char*)a.X + (long long)b0 * xstep;
+          const char* bp = xrow[t] + (long long)b0 * xstep;
 #pragma unroll
           for (int j = 0; j < KBW; ++j)
-            if (EXACT || j < nb) Bf[t][j] = *reinterpret_cast<const u32x4*>(bp + j * 64);
+            if (EXACT || j < nb)
+              Bf[t][j] = *reinterpret_cast<const u32x4*>(kDense ? base + j * xstep + xoff[t] : bp + j * (EPI == EPI_SWIGLU ? 64 : xstep));
         }
       };
       if (nchunks == 1) load_b(0);
@@ -664,7 +671,7 @@ __global__ __launch_bounds__(WS * 64) void gemm_dense_strip_kernel(const GemmArg
     int col = tok0 + t * 16 + lc;
     valid[t] = active && col < T;
     col = col < T ? col : T - 1;  // padded columns repeat the last token; never stored
-    xrow[t] = (const char*)a.X + (long long)col * a.ldx_bytes + (lane >> 4) * 16;
+    xrow[t] = (const char*)a.X + operand_at(col, lane >> 4, nkb, a.x_shift);
   }
   constexpr int BMAX = 4;  // operand blocks a wavefront stages per pass and token tile
   const u32x4* wp = a.W + (long long)strip * nkb * 64 + lane;
@@ -677,7 +684,7 @@ __global__ __launch_bounds__(WS * 64) void gemm_dense_strip_kernel(const GemmArg
 #pragma unroll
       for (int q = 0; q < BMAX; ++q) {
         const int kb = kb0 + q * WS + w;
-        if (kb < nkb) bst[t][q] = *reinterpret_cast<const u32x4*>(xrow[t] + (long long)kb * 64);
+        if (kb < nkb) bst[t][q] = *reinterpret_cast<const u32x4*>(xrow[t] + ((long long)kb * 64 << a.x_shift));
       }
     if (kb0 == 0) {
 #pragma unroll
@@ -804,6 +811,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   static_assert(NKB % CH == 0, "whole chains");
   constexpr int KC = WS;                        // contraction blocks per stage
   constexpr int NST = (NKB + KC - 1) / KC;      // stages
+  constexpr int kShift = 4;                     // dense: blocks of 16 tokens (dense_tiled and lm_tiled ask for more than 8)
   static_assert(WIN <= NKB, "the window holds blocks of one strip");
   extern __shared__ __attribute__((aligned(16))) u32x4 s_x[];  // [2][NT][KC][64]
   const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15;
@@ -817,7 +825,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int strip_raw = (sg * WS + w) * NS;
     const bool active = strip_raw < a.n_strips;  // the last group may be short: its idle wavefronts still stage and wait
     const int strip = active ? strip_raw : a.n_strips - NS;
-    uint32_t xrow[NTT];  // byte offset of the token's row (at most 8192 + shared rows of 8 KiB)
+    uint32_t xrow[NTT];  // byte offset of the token's row (at most 8192 + shared rows of 8 KiB), or of its part of the first operand block
     bool valid[NTT];
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
@@ -825,7 +833,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       valid[t] = active && col < ntok;
       col = col < ntok ? col : ntok - 1;  // padded columns repeat the last token; never stored
       const long long xr = GROUPED ? (a.x_by_token ? a.tok_of_pos[p0 + col] : p0 + col) : col;
-      xrow[t] = (uint32_t)(xr * a.ldx_bytes) + (lane >> 4) * 16;
+      xrow[t] = GROUPED ? (uint32_t)(xr * a.ldx_bytes) + (lane >> 4) * 16 : operand_at(col, lane >> 4, NKB, kShift);
     }
     const u32x4* wp = wbase + (long long)strip * NKB * 64 + lane;
     auto load_w = [&](int i, int j) __attribute__((always_inline)) {
@@ -836,7 +844,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     auto fetch = [&](int s) __attribute__((always_inline)) {
       if (s * KC + KC <= NKB || s * KC + w < NKB) {
 #pragma unroll
-        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>((const char*)a.X + (s * KC + w) * 64 + xrow[t]);
+        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>((const char*)a.X + (s * KC + w) * (GROUPED ? 64 : 64 << kShift) + xrow[t]);
       }
     };
     auto put = [&](int s) __attribute__((always_inline)) {

@@ -42,8 +42,10 @@ __global__ void pack_kernel(const char* __restrict__ src, long long src_group_by
 }
 
 // ------------------------------------------------------------------------------------
-// tree preparation + pre-attention RMSNorm: one workgroup per token
+// tree preparation + pre-attention RMSNorm: one workgroup per token; the normalised rows go out in operand blocks, and of the
+// final norm also as rows if the caller wants them (rows_out, at any address)
 // ------------------------------------------------------------------------------------
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
 template <typename ST>
 __global__ __launch_bounds__(256) void prep_kernel(const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent,
                                                    int B, const int32_t* __restrict__ ctx_len, int max_ctx,
@@ -52,6 +54,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const int32_t* __restrict__ t
                                                    int32_t* __restrict__ depth, int32_t* __restrict__ seq_of,
                                                    float* __restrict__ rope_cs, void* __restrict__ x_norm,
                                                    int32_t* __restrict__ status, int n_single, int norm_only,
+                                                   void* __restrict__ rows_out, int block_shift, int T_max,
                                                    const int* __restrict__ t_dev) {
   constexpr int EB = ST::kBytes;
   constexpr int CE = 16 / EB;
@@ -59,8 +62,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const int32_t* __restrict__ t
   __shared__ int s_par[EVICT_MAX_TREE_NODES];
   __shared__ int s_b, s_depth;
   __shared__ float s_red[4];
-  const int t = blockIdx.x, tid = threadIdx.x;
-  if (t >= dyn_tokens(t_dev, (int)gridDim.x)) return;  // (rows past the call's actual token count)
+  const int t = token_of_workgroup(blockIdx.x, block_shift), tid = threadIdx.x;
+  if (t >= dyn_tokens(t_dev, T_max)) return;  // (rows past the call's actual token count)
   // the row and the gain do not depend on the tree: fetch them first
   u32x4 raw[MAXC], graw[MAXC];
 #pragma unroll
@@ -107,7 +110,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const int32_t* __restrict__ t
             packed[u] = __float_as_uint(__uint_as_float(raw[k][u]) * rinv * __uint_as_float(graw[k][u]));
           }
         }
-        *reinterpret_cast<u32x4*>((char*)x_norm + ((size_t)t * d + c) * EB) = packed;
+        *reinterpret_cast<u32x4*>((char*)x_norm + operand_at(t, tid + 256 * k, d * EB / 64, block_shift)) = packed;
+        if (rows_out) *reinterpret_cast<u32x4_any*>((char*)rows_out + ((size_t)t * d + c) * EB) = packed;
       }
     }
     return;
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const int32_t* __restrict__ t
           packed[u] = __float_as_uint(__uint_as_float(raw[k][u]) * rinv * __uint_as_float(graw[k][u]));
         }
       }
-      *reinterpret_cast<u32x4*>((char*)x_norm + ((size_t)t * d + c) * EB) = packed;
+      *reinterpret_cast<u32x4*>((char*)x_norm + operand_at(t, tid + 256 * k, d * EB / 64, block_shift)) = packed;
     }
   }
   __syncthreads();
@@ -777,13 +781,19 @@ __device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const floa
 template <typename ST, int LPR, int MB>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplits, int rows, void* __restrict__ out,
-                                                         void* __restrict__ aux_out, int Hq, const int* __restrict__ t_dev) {
+                                                         void* __restrict__ aux_out, int Hq, int T_max, int block_shift,
+                                                         const int* __restrict__ t_dev) {
   constexpr int D = 4 * LPR;
   const int tid = threadIdx.x;
-  const int row = blockIdx.x * ((int)blockDim.x / LPR) + tid / LPR;
+  // rows in the order 8 tokens of a head, the next head: a workgroup of 256 threads writes whole cache lines of operand blocks
+  // (fewer tokens: as many as a block has)
+  const int at = blockIdx.x * ((int)blockDim.x / LPR) + tid / LPR, gs = block_shift < 3 ? block_shift : 3;
+  const int group = (at >> gs) / Hq, head = (at >> gs) - group * Hq;
+  const int t = (group << gs) + (at & ((1 << gs) - 1));
   const int c4 = tid & (LPR - 1), l16 = tid & 15;
   // (`rows` = tokens x heads the partials were laid out for; rows past the call's actual token count hold nothing)
-  if (row >= rows || row >= dyn_tokens(t_dev, rows / Hq) * Hq) return;  // (no barrier follows)
+  if (t >= dyn_tokens(t_dev, T_max)) return;  // (no barrier follows)
+  const int row = t * Hq + head;
   float2 ml[kMergeHeld];
 #pragma unroll
   for (int q = 0; q < kMergeHeld; ++q) {
@@ -834,10 +844,12 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const float r = acc[j] / l;
-    store_elem<ST>(out, (size_t)row * D + c4 * 4 + j, r);
-    if (aux_out) store_elem<ST>(aux_out, (size_t)row * D + c4 * 4 + j, r);
+    acc[j] /= l;
+    if (aux_out) store_elem<ST>(aux_out, (size_t)row * D + c4 * 4 + j, acc[j]);
   }
+  // (the output projection reads operand blocks of its tokens' rows of Hq * D)
+  const int byte = (head * D + c4 * 4) * ST::kBytes;
+  store4<ST>((char*)out + operand_at(t, byte >> 4, Hq * D * ST::kBytes / 64, block_shift) + (byte & 15), 0, acc);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1266,14 +1278,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ h
                                                       const float* __restrict__ w, const int32_t* __restrict__ inv,
                                                       int k, int d, int n_shared, int T_max,
                                                       void* __restrict__ out, const void* __restrict__ next_gain, float eps,
-                                                      void* __restrict__ x_norm, const int* __restrict__ t_dev) {
+                                                      void* __restrict__ x_norm, int block_shift, const int* __restrict__ t_dev) {
   constexpr int EB = ST::kBytes;
   constexpr int CE = 16 / EB;
   constexpr int MAXC = 4;  // 16-byte chunks of the row per thread (d <= 256*CE*MAXC, as in prep_kernel)
   __shared__ float s_w[64];
   __shared__ int s_inv[64];
   __shared__ float s_red[4];
-  const int t = blockIdx.x, tid = threadIdx.x;
+  const int t = token_of_workgroup(blockIdx.x, block_shift), tid = threadIdx.x;
   const int T = dyn_tokens(t_dev, T_max);
   if (t >= T) return;  // (rows past the call's actual token count: whole workgroup, before any barrier)
   const float* y_sh = y + (size_t)T * k * d;  // shared experts' rows follow the T * k routed pairs
@@ -1357,7 +1369,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ h
           packed[u] = __float_as_uint(__uint_as_float(raw[kk][u]) * rinv * __uint_as_float(graw[u]));
         }
       }
-      *reinterpret_cast<u32x4*>((char*)x_norm + ((size_t)t * d + c) * EB) = packed;
+      *reinterpret_cast<u32x4*>((char*)x_norm + operand_at(t, tid + 256 * kk, d * EB / 64, block_shift)) = packed;
     }
   }
 }
@@ -1715,14 +1727,14 @@ int launch_pack(const void* src, long long src_group_bytes, int rows, int cols, 
 }
 
 int launch_prep(const evict_ctx* c, const int32_t* tree_off, const int32_t* parent, int B, int T, const int32_t* ctx_len,
-                int max_ctx, const void* x, const void* gain, int norm_only, hipStream_t s) {
+                int max_ctx, const void* x, const void* gain, int norm_only, void* rows_out, hipStream_t s) {
   const evict_model_desc& m = c->m;
   if (m.dtype == EVICT_BF16)
-    hipLaunchKernelGGL(prep_kernel<BF16>, dim3(T), dim3(256), 0, s, tree_off, parent, B, ctx_len, max_ctx, x, gain, m.d,
-                       m.rms_eps, c->rope_rev, m.D, c->anc, c->depth, c->seq_of, c->rope_cs, c->x_norm, c->status, (B == 1 && !c->t_dev) ? T : 0, norm_only, c->t_dev);
+    hipLaunchKernelGGL(prep_kernel<BF16>, dim3(token_grid(T)), dim3(256), 0, s, tree_off, parent, B, ctx_len, max_ctx, x, gain, m.d,
+                       m.rms_eps, c->rope_rev, m.D, c->anc, c->depth, c->seq_of, c->rope_cs, c->x_norm, c->status, (B == 1 && !c->t_dev) ? T : 0, norm_only, rows_out, operand_shift(T), T, c->t_dev);
   else
-    hipLaunchKernelGGL(prep_kernel<F32>, dim3(T), dim3(256), 0, s, tree_off, parent, B, ctx_len, max_ctx, x, gain, m.d,
-                       m.rms_eps, c->rope_rev, m.D, c->anc, c->depth, c->seq_of, c->rope_cs, c->x_norm, c->status, (B == 1 && !c->t_dev) ? T : 0, norm_only, c->t_dev);
+    hipLaunchKernelGGL(prep_kernel<F32>, dim3(token_grid(T)), dim3(256), 0, s, tree_off, parent, B, ctx_len, max_ctx, x, gain, m.d,
+                       m.rms_eps, c->rope_rev, m.D, c->anc, c->depth, c->seq_of, c->rope_cs, c->x_norm, c->status, (B == 1 && !c->t_dev) ? T : 0, norm_only, rows_out, operand_shift(T), T, c->t_dev);
   return launch_status("prep_kernel");
 }
 
@@ -1861,10 +1873,11 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
   const int mrows = T * m.Hq;
   const int mthreads = (long long)mrows * (m.D / 4) >= 256 * 256 ? 256 : 64;  // at least ~256 workgroups, or one wavefront each
   const int rows_per_wg = mthreads / (m.D / 4);
-  const dim3 mgrid((mrows + rows_per_wg - 1) / rows_per_wg);
+  const int group = T > 8 ? 8 : 1 << operand_shift(T);  // tokens whose rows of a head lie together
+  const dim3 mgrid(((T + group - 1) / group * group * m.Hq + rows_per_wg - 1) / rows_per_wg);
 #define EVICT_MERGE(ST_, LPR_, MB_)                                                                                             \
   hipLaunchKernelGGL((attn_merge_kernel<ST_, LPR_, MB_>), mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows,   \
-                     c->attn_o, aux_out, m.Hq, c->t_dev)
+                     c->attn_o, aux_out, m.Hq, T, operand_shift(T), c->t_dev)
 #define EVICT_MERGE_D(ST_, LPR_)                        \
   do {                                                  \
     if (nsplits <= 5) EVICT_MERGE(ST_, LPR_, 5);        \
@@ -1953,11 +1966,11 @@ int launch_argmax_reduce(const float* val, const int32_t* idx, int nstrips, int 
 int launch_combine(const evict_ctx* c, int T, void* out, const void* next_gain, hipStream_t s) {
   const evict_model_desc& m = c->m;
   if (m.dtype == EVICT_BF16)
-    hipLaunchKernelGGL(combine_kernel<BF16>, dim3(T), dim3(256), 0, s, c->h, c->y, c->topk_w, c->inv, m.k, m.d,
-                       m.n_shared, T, out, next_gain, m.rms_eps, c->x_norm, c->t_dev);
+    hipLaunchKernelGGL(combine_kernel<BF16>, dim3(token_grid(T)), dim3(256), 0, s, c->h, c->y, c->topk_w, c->inv, m.k, m.d,
+                       m.n_shared, T, out, next_gain, m.rms_eps, c->x_norm, operand_shift(T), c->t_dev);
   else
-    hipLaunchKernelGGL(combine_kernel<F32>, dim3(T), dim3(256), 0, s, c->h, c->y, c->topk_w, c->inv, m.k, m.d,
-                       m.n_shared, T, out, next_gain, m.rms_eps, c->x_norm, c->t_dev);
+    hipLaunchKernelGGL(combine_kernel<F32>, dim3(token_grid(T)), dim3(256), 0, s, c->h, c->y, c->topk_w, c->inv, m.k, m.d,
+                       m.n_shared, T, out, next_gain, m.rms_eps, c->x_norm, operand_shift(T), c->t_dev);
   return launch_status("combine_kernel");
 }
 

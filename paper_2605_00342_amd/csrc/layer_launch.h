@@ -22,7 +22,7 @@ int launch_gemm_tile_lm(int epi, GemmArgs a, hipStream_t s);
 int launch_pack(const void* src, long long src_group_bytes, int rows, int cols, int dtype, void* dst, int dst_strip0,
                 int dst_strip_step, long long dst_group_strips, int groups, int head_dim, hipStream_t s);
 int launch_prep(const evict_ctx* c, const int32_t* tree_off, const int32_t* parent, int B, int T, const int32_t* ctx_len,
-                int max_ctx, const void* x, const void* gain, int norm_only, hipStream_t s);
+                int max_ctx, const void* x, const void* gain, int norm_only, void* rows_out, hipStream_t s);
 int kernels_setup(const evict_model_desc& m);
 int attn_splits_for(int max_ctx);
 constexpr int kAttnMfmaMaxSplits = 34;  // bf16 attention: at most 32 context splits + the draft-node split (+ 1 spare)

@@ -1,0 +1,50 @@
+"""Token operands kept in blocks of 16 tokens: counts around whole blocks, and the final norm's rows that a caller asks for, at any
+address."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+ev = pytest.importorskip("paper_2605_00342_amd")
+from paper_2605_00342_amd import harness  # noqa: E402
+from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("config", ["mini_bf16", "tiny"])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 49, 113])
+def test_layer_token_counts(config, n):
+    case = synth.make_case(config, n=n, L=90, seed=n, sigma=0.5, tree="random")
+    for tune in ({}, {"dense_kernel": 1}):  # (contraction split and strip per wavefront)
+        check_against_oracle(case, run_case(case, tune=tune))
+
+
+@pytest.mark.parametrize("T", [1, 16, 17, 40])
+@pytest.mark.parametrize("shift", [0, 1, 4])
+def test_rows_of_the_final_norm(T, shift):
+    """x_norm_out, `shift` elements past a 16-byte boundary, holds the rows that the scores were formed from."""
+    d, V = 256, 1024
+    cfg = synth.ModelCfg("lmrows", "bf16", d=d, Hq=2, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    g = torch.Generator().manual_seed(T)
+    x = torch.randn(T, d, generator=g).bfloat16()
+    gain = (1 + 0.1 * torch.randn(d, generator=g)).bfloat16()
+    w = (0.05 * torch.randn(V, d, generator=g)).bfloat16()
+    ctx = ev.evict_create(harness.model_desc(cfg, V), T, 1, 16)
+    head = harness.pack_lm_head(cfg, w.float().numpy())
+    logits = torch.zeros(T, V, device=DEV)
+    buf = torch.full((T * d + 32,), 7.0, dtype=torch.bfloat16, device=DEV)
+    ev.evict_lm_head_logits(ctx, x.to(DEV), gain.to(DEV), head, T, logits, buf[shift:])
+    torch.cuda.synchronize()
+    ev.evict_destroy(ctx)
+    rows = buf[shift:shift + T * d].view(T, d).float().cpu()
+    xf = x.double()
+    want = xf / torch.sqrt((xf * xf).mean(-1, keepdim=True) + cfg.eps) * gain.double()
+    np.testing.assert_allclose(rows.numpy(), want.numpy(), rtol=2 ** -8 * 1.01, atol=0)  # one bf16 rounding
+    assert (buf[:shift] == 7.0).all() and (buf[shift + T * d:] == 7.0).all()
+    # 256 products of rounded values in fp32 sums: 256 * 2^-24 of the sum of magnitudes
+    got, ref = logits.double().cpu(), rows.double() @ w.double().T
+    assert ((got - ref).abs() <= 256 * 2.0 ** -24 * (rows.double().abs() @ w.double().abs().T)).all()
