@@ -818,6 +818,15 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nsg = (a.n_strips + WS * NS - 1) / (WS * NS);  // strip groups
   bool first = true;
+  // Grouped: the rows of an expert's tokens lie anywhere, so a wavefront fetches whole cache lines, 128 bytes (two blocks) of 8
+  // rows, and a pair of wavefronts two blocks of 16 rows, instead of half a line of each of 16. In a block in LDS the token is
+  // XORed with the 16-byte piece of the line it belongs to, so that the 8 lanes of a line write to 8 bank groups; the readers
+  // undo it.
+  static_assert(!GROUPED || (WS % 2 == 0 && NKB % 2 == 0), "whole lines");
+  const int wb = GROUPED ? w & ~1 : w;                            // first block of a stage that this wavefront fetches
+  const int lrow = (lane >> 3) + 8 * (w & 1), piece = lane & 7;   // grouped: token of the tile, piece of its line
+  const int lput = GROUPED ? (piece >> 2) * 64 + (piece & 3) * 16 + (lrow ^ piece) : lane;
+  const int lget[2] = {GROUPED ? lane ^ (lane >> 4) : lane, GROUPED ? lane ^ ((lane >> 4) | 4) : lane};  // even, odd block
 
   // NTL_: live token tiles of this piece of work
   auto run = [&](auto ntl_tag, const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
@@ -829,11 +838,11 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     bool valid[NTT];
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
-      int col = tok0 + t * 16 + lc;
-      valid[t] = active && col < ntok;
+      valid[t] = active && tok0 + t * 16 + lc < ntok;
+      int col = tok0 + t * 16 + (GROUPED ? lrow : lc);
       col = col < ntok ? col : ntok - 1;  // padded columns repeat the last token; never stored
       const long long xr = GROUPED ? (a.x_by_token ? a.tok_of_pos[p0 + col] : p0 + col) : col;
-      xrow[t] = GROUPED ? (uint32_t)(xr * a.ldx_bytes) + (lane >> 4) * 16 : operand_at(col, lane >> 4, NKB, kShift);
+      xrow[t] = GROUPED ? (uint32_t)(xr * a.ldx_bytes) + (lane & 7) * 16 : operand_at(col, lane >> 4, NKB, kShift);
     }
     const u32x4* wp = wbase + (long long)strip * NKB * 64 + lane;
     auto load_w = [&](int i, int j) __attribute__((always_inline)) {
@@ -842,15 +851,15 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
     u32x4 st[D][NTT], A[NS][WIN];
     auto fetch = [&](int s) __attribute__((always_inline)) {
-      if (s * KC + KC <= NKB || s * KC + w < NKB) {
+      if (s * KC + KC <= NKB || s * KC + wb < NKB) {
 #pragma unroll
-        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>((const char*)a.X + (s * KC + w) * (GROUPED ? 64 : 64 << kShift) + xrow[t]);
+        for (int t = 0; t < NTT; ++t) st[s % D][t] = *reinterpret_cast<const u32x4*>((const char*)a.X + (s * KC + wb) * (GROUPED ? 64 : 64 << kShift) + xrow[t]);
       }
     };
     auto put = [&](int s) __attribute__((always_inline)) {
-      if (s * KC + KC <= NKB || s * KC + w < NKB) {
+      if (s * KC + KC <= NKB || s * KC + wb < NKB) {
 #pragma unroll
-        for (int t = 0; t < NTT; ++t) s_x[(((s & 1) * NT + t) * KC + w) * 64 + lane] = st[s % D][t];
+        for (int t = 0; t < NTT; ++t) s_x[(((s & 1) * NT + t) * KC + wb) * 64 + lput] = st[s % D][t];
       }
     };
     // token operand first, weights behind it: the in-order load counter lets the operand be consumed while the weights fly
@@ -882,18 +891,18 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int s = 0; s < NST; ++s) {
       const int kn = s * KC + KC <= NKB ? KC : NKB - s * KC;
       if (s + D < NST) fetch(s + D);
-      const u32x4* sx = s_x + (s & 1) * NT * KC * 64 + lane;
+      const u32x4* sx = s_x + (s & 1) * NT * KC * 64;
       constexpr bool kOneSet = CH < NKB && NTT > 4;
       constexpr int NB = kOneSet ? 1 : 2;
       u32x4 b[NB][NTT];
 #pragma unroll
-      for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64];
+      for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64 + lget[0]];
 #pragma unroll
       for (int jj = 0; jj < kn; ++jj) {
         const int j = s * KC + jj;
         if (!kOneSet && jj + 1 < kn) {
 #pragma unroll
-          for (int t = 0; t < NTT; ++t) b[(jj + 1) % NB][t] = sx[(t * KC + jj + 1) * 64];
+          for (int t = 0; t < NTT; ++t) b[(jj + 1) % NB][t] = sx[(t * KC + jj + 1) * 64 + lget[(jj + 1) & 1]];
         }
 #pragma unroll
         for (int t = 0; t < NTT; ++t) {
@@ -905,7 +914,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
             }
             acc[i][t] = mfma_block<BF16>(A[i][j % WIN], b[jj % NB][t], j % CH == 0 ? f32x4{0, 0, 0, 0} : acc[i][t]);
           }
-          if (kOneSet && jj + 1 < kn) b[0][t] = sx[(t * KC + jj + 1) * 64];
+          if (kOneSet && jj + 1 < kn) b[0][t] = sx[(t * KC + jj + 1) * 64 + lget[(jj + 1) & 1]];
         }
         if (j + WIN < NKB) {
 #pragma unroll
