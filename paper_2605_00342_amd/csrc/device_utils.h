@@ -150,6 +150,16 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Maximum over each row of 16 lanes, result in every lane of the row.
+__device__ __forceinline__ unsigned row16_max_u32(unsigned v) {
+  auto mx = [](unsigned a, unsigned b) { return a > b ? a : b; };
+  v = mx(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
+  v = mx(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
+  v = mx(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
+  v = mx(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
+  return v;
+}
+
 // Token count of a call: the host's T, or -- when the caller has pointed the context at a device word
 // (evict_dynamic_tokens) -- the value found there when the kernel runs, clamped to [1, T] (T is then the
 // upper bound every grid and buffer was sized for).

@@ -1129,6 +1129,73 @@ __device__ __forceinline__ void topk_wave_regs(const float (&raw)[NR], int E, in
   *my_w = ex / denom;
 }
 
+// TopK of four tokens by one wavefront, one per row of 16 lanes, with the scores held in registers (E <= 16 * NR, k <= 16): the
+// same selection rule as topk_kernel, without the LDS round trips. Lane l of a row holds the NR consecutive experts
+// l*NR .. l*NR + NR - 1; lane j ends up with the j-th pick and its weight.
+// With a token per wavefront the work of 32 tokens is all instruction issue (16 wavefronts share 4 SIMDs, two tokens each, 40
+// instructions a pick); four tokens share about 50 here. A single token's chain of dependent instructions is longer, so calls
+// of up to 8 tokens stay with one per wavefront (TopK and union, us, one token per wavefront -> four: 32 tokens 9.1 -> 7.3, one
+// token 5.3 -> 6.6).
+template <int NR>
+__device__ __forceinline__ void topk_load_four(const float* __restrict__ row, int E, int l16, bool live, f32x4 (&raw)[NR / 4]) {
+#pragma unroll
+  for (int i = 0; i < NR / 4; ++i) {  // (E is a multiple of 16: four experts are all there or none is)
+    const int e = l16 * NR + 4 * i;
+    raw[i] = live && e < E ? *reinterpret_cast<const f32x4*>(row + e) : f32x4{0, 0, 0, 0};
+  }
+}
+
+template <int NR>
+__device__ __forceinline__ void topk_rows(const f32x4 (&raw)[NR / 4], int E, int k, int norm, int l16, int* my_idx, float* my_w) {
+  unsigned key[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    unsigned bits = __float_as_uint(raw[i >> 2][i & 3]);
+    bits = bits == 0x80000000u ? 0u : bits;  // -0 and +0 compare equal
+    unsigned o = bits ^ ((bits >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+    o = o == 0u ? 1u : o;  // 0 marks "taken" (below every key)
+    key[i] = l16 * NR + i < E ? o : 0u;
+  }
+  unsigned mine = 0u;
+  int mine_idx = 0;
+#pragma unroll 1
+  for (int j = 0; j < k; ++j) {
+    // the lane's largest key and its register by a tournament, the lower register on equal keys: a short chain of dependent
+    // instructions, which is what a single wavefront waits for
+    unsigned top[NR / 2];
+    int reg[NR / 2];
+#pragma unroll
+    for (int i = 0; i < NR / 2; ++i) {
+      const bool up = key[2 * i + 1] > key[2 * i];
+      top[i] = up ? key[2 * i + 1] : key[2 * i];
+      reg[i] = up ? 2 * i + 1 : 2 * i;
+    }
+#pragma unroll
+    for (int h = NR / 4; h >= 1; h >>= 1)
+#pragma unroll
+      for (int i = 0; i < h; ++i) {
+        const bool up = top[2 * i + 1] > top[2 * i];
+        top[i] = up ? top[2 * i + 1] : top[2 * i];
+        reg[i] = up ? reg[2 * i + 1] : reg[2 * i];
+      }
+    const unsigned best = row16_max_u32(top[0]);
+    // lowest expert of the row holding the maximum (every key is above 0, the marker of those taken)
+    const unsigned at = top[0] == best ? (unsigned)(l16 * NR + reg[0]) : 0xFFFFFFFFu;
+    const unsigned sel = ~row16_max_u32(~at);
+    const int hit = at == sel ? reg[0] : NR;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) key[i] = i == hit ? 0u : key[i];
+    if (l16 == j) { mine = best; mine_idx = (int)sel; }
+  }
+  const float val = __uint_as_float(mine ^ ((mine >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+  const float first = __shfl(val, threadIdx.x & 48);
+  const float ex = l16 < k ? (norm ? 1.0f / (1.0f + __expf(-val)) : __expf(val - first)) : 0.0f;
+  *my_idx = mine_idx;
+  *my_w = ex / row16_sum(ex);
+}
+
+constexpr int kTopkRowsK = 16;        // picks a row of lanes has room for
+constexpr int kTopkRowsTokens = 9;    // from here on four tokens per wavefront
 // Register variant of topk_kernel for E <= 256: grid over groups of 16 tokens, one per wavefront.
 __global__ __launch_bounds__(kRouterThreads) void topk_regs_kernel(
     const float* __restrict__ logits, int T_max, int E, int k, int norm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
@@ -1159,6 +1226,8 @@ __global__ __launch_bounds__(kRouterThreads) void topk_regs_kernel(
 
 // Small token counts: TopK (register variant) and the expert union in one workgroup, the
 // wavefronts taking the tokens in turn; saves a launch when there are few tokens to share out.
+// ROWS: four tokens per wavefront.
+template <bool ROWS>
 __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
     const float* __restrict__ logits, int T_max, int E, int k, int norm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
     int32_t* __restrict__ aux_idx, float* __restrict__ aux_w, int use_masks, int32_t* __restrict__ union_ids,
@@ -1169,37 +1238,63 @@ __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
   const int T = dyn_tokens(t_dev, T_max);
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the scores of both tokens a wavefront may have (T <= 32) are requested before either is ranked
-  float raw[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-    if (w + r * kRouterWaves < T) {
+  if constexpr (ROWS) {
+    const int l16 = lane & 15, t = threadIdx.x >> 4;
+    if ((t & ~3) < T) {  // (whole wavefronts)
+      const bool live = t < T;
+      const float* row = logits + (size_t)t * E;
+      int idx;
+      float wv;
       if (E <= 128) {
-        float r2[2];
-        topk_load_row<2>(logits + (size_t)(w + r * kRouterWaves) * E, E, lane, r2);
-        raw[r][0] = r2[0]; raw[r][1] = r2[1];
+        f32x4 raw[2];
+        topk_load_four<8>(row, E, l16, live, raw);
+        topk_rows<8>(raw, E, k, norm, l16, &idx, &wv);
       } else {
-        topk_load_row<4>(logits + (size_t)(w + r * kRouterWaves) * E, E, lane, raw[r]);
+        f32x4 raw[4];
+        topk_load_four<16>(row, E, l16, live, raw);
+        topk_rows<16>(raw, E, k, norm, l16, &idx, &wv);
+      }
+      if (live && l16 < k) {
+        s_all[t * k + l16] = idx;  // where expert_union_body expects the pairs
+        topk_idx[(size_t)t * k + l16] = idx;
+        topk_w[(size_t)t * k + l16] = wv;
+        if (aux_idx) aux_idx[(size_t)t * k + l16] = idx;
+        if (aux_w) aux_w[(size_t)t * k + l16] = wv;
       }
     }
+  } else {
+    // the scores of both tokens a wavefront may have (T <= 32) are requested before either is ranked
+    float raw[2][4];
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int t = w + r * kRouterWaves;
-    if (t >= T) break;
-    int idx;
-    float wv;
-    if (E <= 128) {
-      const float r2[2] = {raw[r][0], raw[r][1]};
-      topk_wave_regs<2>(r2, E, k, norm, lane, &idx, &wv);
-    } else {
-      topk_wave_regs<4>(raw[r], E, k, norm, lane, &idx, &wv);
-    }
-    if (lane < k) {
-      s_all[t * k + lane] = idx;  // where expert_union_body expects the pairs
-      topk_idx[(size_t)t * k + lane] = idx;
-      topk_w[(size_t)t * k + lane] = wv;
-      if (aux_idx) aux_idx[(size_t)t * k + lane] = idx;
-      if (aux_w) aux_w[(size_t)t * k + lane] = wv;
+    for (int r = 0; r < 2; ++r)
+      if (w + r * kRouterWaves < T) {
+        if (E <= 128) {
+          float r2[2];
+          topk_load_row<2>(logits + (size_t)(w + r * kRouterWaves) * E, E, lane, r2);
+          raw[r][0] = r2[0]; raw[r][1] = r2[1];
+        } else {
+          topk_load_row<4>(logits + (size_t)(w + r * kRouterWaves) * E, E, lane, raw[r]);
+        }
+      }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int t = w + r * kRouterWaves;
+      if (t >= T) break;
+      int idx;
+      float wv;
+      if (E <= 128) {
+        const float r2[2] = {raw[r][0], raw[r][1]};
+        topk_wave_regs<2>(r2, E, k, norm, lane, &idx, &wv);
+      } else {
+        topk_wave_regs<4>(raw[r], E, k, norm, lane, &idx, &wv);
+      }
+      if (lane < k) {
+        s_all[t * k + lane] = idx;  // where expert_union_body expects the pairs
+        topk_idx[(size_t)t * k + lane] = idx;
+        topk_w[(size_t)t * k + lane] = wv;
+        if (aux_idx) aux_idx[(size_t)t * k + lane] = idx;
+        if (aux_w) aux_w[(size_t)t * k + lane] = wv;
+      }
     }
   }
   __syncthreads();
@@ -1935,9 +2030,13 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   const int use_masks = union_mask_plan(T, m.k, m.E, &lds);
   const bool regs = m.E <= 256;
   if (regs && T <= kFusedTopkTokens) {
-    hipLaunchKernelGGL(topk_union_kernel, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx,
-                       c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv,
-                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, counts, c->t_dev);
+#define EVICT_TOPK_UNION(ROWS_) \
+    hipLaunchKernelGGL(topk_union_kernel<ROWS_>, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx, \
+                       c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv, \
+                       c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, counts, c->t_dev)
+    if (T >= kTopkRowsTokens && m.k <= kTopkRowsK) EVICT_TOPK_UNION(true);
+    else EVICT_TOPK_UNION(false);
+#undef EVICT_TOPK_UNION
     return launch_status("topk_union_kernel");
   }
   const dim3 tgrid((T + kRouterWaves - 1) / kRouterWaves);

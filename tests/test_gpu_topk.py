@@ -1,0 +1,35 @@
+"""TopK and the expert union behind it where the kernels change: one token per wavefront up to 8 tokens and from 33 on, a row of 16
+lanes per token between, with 8 or 16 experts per lane and up to 16 picks; equal scores go to the lower expert."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import evict_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+pytest.importorskip("paper_2605_00342_amd")
+from test_gpu_layer import run_case  # noqa: E402
+
+
+@pytest.mark.parametrize("E,k", [(16, 1), (16, 16), (48, 3), (64, 8), (80, 8), (128, 16), (128, 17), (144, 8), (256, 16), (272, 4)])
+@pytest.mark.parametrize("T", [1, 8, 9, 11, 16, 31, 32, 33, 65])
+def test_topk_rule(E, k, T):
+    cfg = synth.ModelCfg(f"topk{E}", "bf16", d=256, Hq=2, Hkv=1, D=64, E=E, k=k, F=32, theta=1e4,
+                         router_norm="sigmoid" if E == 144 else "softmax")
+    case = synth.make_case(cfg.name, n=T, L=20, seed=T + E, sigma=1.0, tree="random", cfg=cfg)
+    wg = case["W"]["wg"]
+    wg[E // 2:] = wg[: E - E // 2]  # every score twice, half the experts apart
+    if T > 3:
+        wg[3:7] = wg[3]             # and four neighbours alike
+    got = run_case(case)
+    s = np.asarray(got["router_logits"], np.float32)
+    want = np.argsort(-s, axis=1, kind="stable")[:, :k]
+    assert np.array_equal(got["topk_idx"], want)
+    top = np.take_along_axis(s, want, 1).astype(np.float64)
+    w = 1 / (1 + np.exp(-top)) if cfg.router_norm == "sigmoid" else np.exp(top - top[:, :1])
+    np.testing.assert_allclose(got["topk_w"], w / w.sum(1, keepdims=True), rtol=0, atol=2e-6)  # (as test_gpu_layer.py)
+    un = orc.expert_union(want, E)
+    n = un["union_count"]
+    assert got["union_count"] == n and np.array_equal(got["union_ids"][:n], un["union_ids"][:n])
+    assert np.array_equal(got["hist"], un["hist"])
