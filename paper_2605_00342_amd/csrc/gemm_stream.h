@@ -822,11 +822,12 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // rows, and a pair of wavefronts two blocks of 16 rows, instead of half a line of each of 16. In a block in LDS the token is
   // XORed with the 16-byte piece of the line it belongs to, so that the 8 lanes of a line write to 8 bank groups; the readers
   // undo it.
-  static_assert(!GROUPED || (WS % 2 == 0 && NKB % 2 == 0), "whole lines");
-  const int wb = GROUPED ? w & ~1 : w;                            // first block of a stage that this wavefront fetches
+  constexpr bool kLines = GROUPED && NKB <= 64;  // (128 blocks: no registers left for it)
+  static_assert(!kLines || (WS % 2 == 0 && NKB % 2 == 0), "whole lines");
+  const int wb = kLines ? w & ~1 : w;                            // first block of a stage that this wavefront fetches
   const int lrow = (lane >> 3) + 8 * (w & 1), piece = lane & 7;   // grouped: token of the tile, piece of its line
-  const int lput = GROUPED ? (piece >> 2) * 64 + (piece & 3) * 16 + (lrow ^ piece) : lane;
-  const int lget[2] = {GROUPED ? lane ^ (lane >> 4) : lane, GROUPED ? lane ^ ((lane >> 4) | 4) : lane};  // even, odd block
+  const int lput = kLines ? (piece >> 2) * 64 + (piece & 3) * 16 + (lrow ^ piece) : lane;
+  const int lget[2] = {kLines ? lane ^ (lane >> 4) : lane, kLines ? lane ^ ((lane >> 4) | 4) : lane};  // even, odd block
 
   // NTL_: live token tiles of this piece of work
   auto run = [&](auto ntl_tag, const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
@@ -839,10 +840,10 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
       valid[t] = active && tok0 + t * 16 + lc < ntok;
-      int col = tok0 + t * 16 + (GROUPED ? lrow : lc);
+      int col = tok0 + t * 16 + (kLines ? lrow : lc);
       col = col < ntok ? col : ntok - 1;  // padded columns repeat the last token; never stored
       const long long xr = GROUPED ? (a.x_by_token ? a.tok_of_pos[p0 + col] : p0 + col) : col;
-      xrow[t] = GROUPED ? (uint32_t)(xr * a.ldx_bytes) + (lane & 7) * 16 : operand_at(col, lane >> 4, NKB, kShift);
+      xrow[t] = GROUPED ? (uint32_t)(xr * a.ldx_bytes) + (kLines ? lane & 7 : lane >> 4) * 16 : operand_at(col, lane >> 4, NKB, kShift);
     }
     const u32x4* wp = wbase + (long long)strip * NKB * 64 + lane;
     auto load_w = [&](int i, int j) __attribute__((always_inline)) {
