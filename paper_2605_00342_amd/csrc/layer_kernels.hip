@@ -1644,7 +1644,7 @@ constexpr size_t kDenseStripLdsMax = 128 * 1024;
 // same strips of an expert's consecutive slots share an XCD; fewer token tiles re-read the weights of busy experts (912
 // tokens, 128 experts: 172 us with four tiles, 153 with six), more spill.
 #define EVICT_TILE_GROUPED(X) \
-  X(EPI_SWIGLU, 6, 2, 6, 8, 1, 64, true) X(EPI_SWIGLU, 6, 2, 6, 5, 1, 128, true) \
+  X(EPI_SWIGLU, 6, 2, 6, 8, 1, 64, true) X(EPI_SWIGLU, 6, 2, 6, 4, 1, 128, true) \
   X(EPI_F32, 6, 2, 4, 8, 1, 24, true) X(EPI_F32, 6, 2, 4, 8, 1, 44, true) X(EPI_F32, 6, 2, 4, 6, 1, 6, true) X(EPI_F32, 6, 2, 4, 8, 1, 8, true)
 // Dense: from the smallest tile of strips x tokens to the largest.
 #define EVICT_TILE_DENSE_NKB(X, EPI_, NKB_) \
@@ -1652,7 +1652,7 @@ constexpr size_t kDenseStripLdsMax = 128 * 1024;
   X(EPI_, 3, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 4, 8, 2, NKB_, false)
 #define EVICT_TILE_DENSE(X) \
   EVICT_TILE_DENSE_NKB(X, EPI_QKV, 64) X(EPI_QKV, 6, 2, 4, 7, 1, 64, false) X(EPI_QKV, 6, 2, 8, 7, 1, 64, false) \
-  EVICT_TILE_DENSE_NKB(X, EPI_QKV, 128) X(EPI_QKV, 6, 2, 4, 7, 1, 128, false) X(EPI_QKV, 6, 2, 8, 6, 1, 128, false) \
+  EVICT_TILE_DENSE_NKB(X, EPI_QKV, 128) X(EPI_QKV, 6, 2, 4, 7, 1, 128, false) X(EPI_QKV, 6, 2, 8, 4, 1, 128, false) \
   EVICT_TILE_DENSE_NKB(X, EPI_RESID, 32) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 64) EVICT_TILE_DENSE_NKB(X, EPI_RESID, 128)
 // LM head (vocabulary rows x tokens, weights read once).
 // (six tiles: the arg max streams the better from a window of 6 blocks, 4096 columns, 66 tokens 249 -> 242 us; score rows, whose
