@@ -57,7 +57,7 @@ struct evict_ctx {
   float* y;              // [T*k + n_shared*T][d]
   float* lm_val;         // [T][vocab/16] best logit per token and strip
   int32_t* lm_idx;       // [T][vocab/16]
-  float* samp_stats;     // [T][EVICT_SAMP_STATS] per node: partial maxima of the logits, partial sums of exp((logit - max) / temperature); of a root: what the draw hands over
+  float* samp_stats;     // [T][EVICT_SAMP_STATS] per node: partial maxima of the logits, partial sums of exp((logit - max) / temperature); of node b also what the walk of tree b hands to its draw
   void* stack_buf[2];    // [T][d] ping-pong hidden states of evict_verify_stack
   hipEvent_t prof_ev[2]; // evict_profile_cost
 };

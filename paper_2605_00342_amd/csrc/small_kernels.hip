@@ -476,8 +476,9 @@ __global__ __launch_bounds__(64) void accept_path_kernel(
 // ------------------------------------------------------------------------------------
 constexpr int kSampThreads = 1024;
 constexpr int kSampWaves = kSampThreads / 64;
-// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials; for the
-// root of a tree also the kSampWaves segment sums of the draw, the last node of the walk (bits of an int) and its row's maximum.
+// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials. Behind those
+// of node b lies what the walk of tree b hands to its draw: the kSampWaves segment sums, the last node of the walk (bits of an int)
+// and its row's maximum. (By the tree's number, not at its root: an empty tree's offset is the next tree's root, or past the end.)
 constexpr int kSampStats = EVICT_SAMP_STATS;
 constexpr int kSampSeg = 2 * kSampWaves, kSampCur = 3 * kSampWaves, kSampMax = kSampCur + 1;
 static_assert(kSampStats > kSampMax, "maxima, sums, segment sums, last node, its maximum");
@@ -675,9 +676,14 @@ __device__ __forceinline__ void sampled_walk(
   __syncthreads();
 }
 
-__device__ __forceinline__ int tree_nodes(int lo, int hi) {
-  const int n = hi - lo;
-  return n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n);
+// First node and size of tree b. An empty tree is taken for the one node at its offset; either way the nodes lie within the T of
+// the call.
+struct TreeSpan { int lo, n; };
+__device__ __forceinline__ TreeSpan tree_span(const int32_t* __restrict__ tree_off, int b, int T) {
+  int lo = tree_off[b], n = tree_off[b + 1] - lo;
+  lo = lo < 0 ? 0 : (lo < T ? lo : T - 1);
+  n = n < T - lo ? n : T - lo;
+  return {lo, n < 1 ? 1 : (n > kMaxSel ? kMaxSel : n)};
 }
 
 // The final draw from the distribution at the last node with the rejected tokens removed, by inverting the cumulative sum at
@@ -835,7 +841,7 @@ template <bool SHORT>
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
-    const float* __restrict__ u_node, const float* __restrict__ u_bonus, int32_t* __restrict__ path, int path_stride,
+    const float* __restrict__ u_node, const float* __restrict__ u_bonus, int T, int32_t* __restrict__ path, int path_stride,
     int32_t* __restrict__ path_len, int32_t* __restrict__ bonus, int32_t* __restrict__ status) {
   constexpr int kBatch = SHORT ? 4 : kStatsBatch;
   constexpr int kPiece = (SHORT ? kShortRow : kOneDrawRow) / (kSampWaves * 64);
@@ -846,7 +852,8 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   __shared__ float s_segsum[kSampWaves];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
+  const TreeSpan span = tree_span(tree_off, b, T);
+  const int lo = span.lo, n = span.n;
   sampled_walk<SHORT>(s_tree, s_rej, &s_cur, &s_nrej, true, lo, n, parent, tok, logits, V, inv_temp, stats, u_node,
                      path + (size_t)b * path_stride, path_stride, path_len + b, status);
   const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
@@ -894,13 +901,13 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
 // exponentials per lane and segment at a vocabulary of 151936, so they are spread over 16 CUs per tree instead of one, and
 // over the four wavefronts of a workgroup, each a quarter of the 64-element blocks; the first wavefront then adds them up
 // from LDS in order. Every workgroup walks the tree for itself, which costs no hand-off; the first one of a tree writes the
-// path. What the draw needs goes to the statistics of the tree's root (kSampSeg, kSampCur, kSampMax).
+// path. What the draw needs goes behind the statistics of node b (kSampSeg, kSampCur, kSampMax).
 constexpr int kSegThreads = 256;
 constexpr int kSegBlocks = 152;  // blocks of 64 elements per round: one round up to a vocabulary of 155648
 __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, float* stats, const float* __restrict__ u_node,
-    int32_t* __restrict__ path, int path_stride, int32_t* __restrict__ path_len, int32_t* __restrict__ status) {
+    int T, int32_t* __restrict__ path, int path_stride, int32_t* __restrict__ path_len, int32_t* __restrict__ status) {
   constexpr int kWaves = kSegThreads / 64, kPer = kSegBlocks / kWaves;
   static_assert(kSegBlocks % kWaves == 0, "whole blocks per wavefront");
   __shared__ SampTree s_tree;
@@ -910,7 +917,8 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
   const int b = (int)blockIdx.x / kSampWaves, part = (int)blockIdx.x % kSampWaves;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
+  const TreeSpan span = tree_span(tree_off, b, T);
+  const int lo = span.lo, n = span.n;
   sampled_walk<false>(s_tree, s_rej, &s_cur, &s_nrej, part == 0, lo, n, parent, tok, logits, V, inv_temp, stats, u_node,
                       path + (size_t)b * path_stride, path_stride, path_len + b, status);
   const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
@@ -947,7 +955,7 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
   }
   if (w == 0) {
     acc = wave_sum(acc);
-    float* out = stats + (size_t)lo * kSampStats;
+    float* out = stats + (size_t)b * kSampStats;
     if (lane == 0) {
       out[kSampSeg + part] = acc;
       if (part == 0) {
@@ -963,14 +971,15 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats, const float* __restrict__ u_bonus,
-    int32_t* __restrict__ bonus) {
+    int T, int32_t* __restrict__ bonus) {
   __shared__ int s_rej[kMaxSel];
   __shared__ float s_piece[64 * piece_row(kPieceLong)];
   __shared__ int s_nrej;
   const int b = blockIdx.x, tid = threadIdx.x;
-  const int lo = tree_off[b], n = tree_nodes(lo, tree_off[b + 1]);
-  const float* root = stats + (size_t)lo * kSampStats;
-  const int cur = __builtin_amdgcn_readfirstlane(__float_as_int(root[kSampCur]));
+  const TreeSpan span = tree_span(tree_off, b, T);
+  const int lo = span.lo, n = span.n;
+  const float* walked = stats + (size_t)b * kSampStats;
+  const int cur = __builtin_amdgcn_readfirstlane(__float_as_int(walked[kSampCur]));
   if (tid == 0) s_nrej = 0;
   __syncthreads();
   for (int i = tid; i < n; i += kSampThreads) {  // the tokens rejected at the last node are its children's
@@ -981,12 +990,12 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
   }
   float segsum[kSampWaves];
 #pragma unroll
-  for (int i = 0; i < kSampWaves; ++i) segsum[i] = root[kSampSeg + i];
+  for (int i = 0; i < kSampWaves; ++i) segsum[i] = walked[kSampSeg + i];
   int segment;
   float rem;
   pick_segment(segsum, u_bonus[b], &segment, &rem);
   segment = __builtin_amdgcn_readfirstlane(segment);
-  const float m = root[kSampMax];
+  const float m = walked[kSampMax];
   __syncthreads();
   const int nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const int seg = samp_segment(V);
@@ -1007,19 +1016,19 @@ int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const 
   }
   int rc = launch_status("softmax statistics kernels");
   if (rc) return rc;
-  if (V <= kOneDrawRow) {
+  if (V <= kOneDrawRow || B > T) {  // (more trees than nodes, so some of them empty: no room to hand over)
     if (V <= kShortRow)
       hipLaunchKernelGGL(accept_sampled_kernel<true>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                         u_node, u_bonus, path, path_stride, path_len, bonus, status);
+                         u_node, u_bonus, T, path, path_stride, path_len, bonus, status);
     else
       hipLaunchKernelGGL(accept_sampled_kernel<false>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                         u_node, u_bonus, path, path_stride, path_len, bonus, status);
+                         u_node, u_bonus, T, path, path_stride, path_len, bonus, status);
     return launch_status("accept_sampled_kernel");
   }
   hipLaunchKernelGGL(accept_sampled_walk_kernel, dim3(B * kSampWaves), dim3(kSegThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp,
-                     stats, u_node, path, path_stride, path_len, status);
+                     stats, u_node, T, path, path_stride, path_len, status);
   hipLaunchKernelGGL(accept_sampled_draw_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                     u_bonus, bonus);
+                     u_bonus, T, bonus);
   return launch_status("accept_sampled_draw_kernel");
 }
 

@@ -217,3 +217,31 @@ def test_draw_rounds(ctx_small, V, u):
     logits[:, -200:] += 6.0  # (mass in the last segment and piece)
     path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, np.full(2, u, np.float32), 8)
     assert check_against_oracle(parents, tree_off, logits, tok, u_node, np.full(2, u, np.float32), 0.9, path, plen, bonus) < 2
+
+
+@pytest.mark.parametrize("V", [1000, 32000, 49153, 151936])
+@pytest.mark.parametrize("empty", [(1,), (0, 2), (3,), (0, 1, 2, 3, 4, 5)])
+def test_empty_trees_leave_their_neighbours_alone(ctx_small, V, empty):
+    """Trees without nodes, between others (their offset is the next tree's root), at the end (past the last node) and in greater
+    number than there are nodes: the other trees' paths and tokens are what they are without them, bit for bit, and an empty tree
+    accepts its root alone."""
+    parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(7, [2, 1] if len(empty) > 4 else [6, 9, 5], V)
+    B, T = len(parents), int(tree_off[-1])
+    want = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, u_bonus, 16)
+    assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, *want) == 0
+    off, u, live = [0], [], []
+    for b in range(B + 1):
+        for _ in range(empty.count(b) if len(empty) <= 4 else 2):
+            off.append(off[-1])
+            u.append(0.999)
+        if b < B:
+            live.append(len(u))
+            off.append(int(tree_off[b + 1]))
+            u.append(u_bonus[b])
+    assert off[-1] == T and (len(u) > T) == (len(empty) > 4)
+    got = run_gpu(ctx_small, np.array(off, np.int32), parent, tok, logits, V, 0.9, u_node, np.array(u, np.float32), 16)
+    for w, g in zip(want, got):
+        assert np.array_equal(w, g[live])
+    none = [b for b in range(len(u)) if b not in live]
+    assert np.all(got[1][none] == 1) and np.all(got[0][none, 0] == 0) and np.all(got[0][none, 1:] == -1)
+    assert np.all((got[2][none] >= 0) & (got[2][none] < V))
