@@ -65,7 +65,7 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
                 (long long)max_tokens * m->k);
   // attention scratch: the bf16 kernel cuts any context into at most 32 splits (+ the draft-node split); the
   // fp32 kernel takes 64 keys per split and is kept to 192 splits
-  EVICT_REQUIRE(m->dtype == EVICT_BF16 || attn_splits_for(max_ctx) <= 192, EVICT_E_UNSUPPORTED,
+  EVICT_REQUIRE(m->dtype == EVICT_BF16 || attn_splits_for(max_ctx) <= kAttnF32MaxSplits, EVICT_E_UNSUPPORTED,
                 "max_ctx=%d needs more than 192 attention splits (fp32 storage: at most 12160 positions)", max_ctx);
   EVICT_REQUIRE(max_ctx <= (1 << 20), EVICT_E_UNSUPPORTED, "max_ctx=%d exceeds 1048576", max_ctx);
   EVICT_REQUIRE(m->d * (m->dtype == EVICT_BF16 ? 2 : 4) <= 16384, EVICT_E_UNSUPPORTED, "d=%d: rows above 16 KiB are not supported", m->d);

@@ -1,6 +1,7 @@
 // Kernels of one verification pass through an MoE decoder layer (Sec. 2.1-2.2) other than
 // the streaming GEMM: weight packing, tree preparation + RMSNorm, tree-masked attention
 // (split over the context) and its merge, router top-k, un-permute/combine.
+#include <type_traits>
 #include <utility>
 
 #include "ctx.h"
@@ -759,17 +760,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // factors round by DPP; partial rows are requested from a base that is the same for all lanes; as many splits are unrolled
 // as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.8 -> 2.9, 32
 // tokens of 8 heads 4.9 -> 2.8, of 32 heads 5.1 -> 4.0; 5 splits, 917 tokens 13.0 -> 8.2.)
+// Contexts of 32-bit storage, a split per 64 keys, have more: the second 17 follow, the other held ones, then 16 at a time whose
+// factors are worked out again from their pairs, rows and pairs of a batch in one trip to memory (FAR: more than 48 splits).
+// (Layers of 32-bit storage, us, splits past 34 one by one -> so: 4 heads of 64, 1 node, 4000 positions 56 -> 48, 12000
+// 100 -> 56; 8 heads of 128, 100 nodes 122 -> 112, 216 -> 149.)
 constexpr int kMergeHeld = 3;                     // splits a lane of 16 holds the pairs of
-constexpr int kMergePairs = 16 * kMergeHeld;      // further ones (fp32 storage, long contexts) are walked one by one
-static_assert(kMergePairs >= kAttnMfmaMaxSplits, "the bf16 kernel's splits are all held");
+constexpr int kMergePairs = 16 * kMergeHeld;
+constexpr int kMergeFar = kAttnF32MaxSplits / 16;  // the same with FAR
+static_assert(kMergePairs >= kAttnMfmaMaxSplits && 16 * kMergeFar >= kAttnF32MaxSplits, "the pairs of all splits are held");
 
 // factor of split S of the lane's row
-template <int S>
-__device__ __forceinline__ float merge_factor(const float (&sc)[kMergeHeld]) {
+template <int S, int N>
+__device__ __forceinline__ float merge_factor(const float (&sc)[N]) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sc[S >> 4]), 0x150 + (S & 15), 0xF, 0xF, false));  // row_newbcast
 }
-template <int S0, int... I>
-__device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const float (&sc)[kMergeHeld], std::integer_sequence<int, I...>) {
+template <int S0, int N, int... I>
+__device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const float (&sc)[N], std::integer_sequence<int, I...>) {
   const float f[] = {merge_factor<S0 + I>(sc)...};
 #pragma unroll
   for (int i = 0; i < (int)sizeof...(I); ++i) {
@@ -778,12 +784,12 @@ __device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const floa
   }
 }
 
-template <typename ST, int LPR, int MB>
+template <typename ST, int LPR, int MB, bool FAR = false>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplits, int rows, void* __restrict__ out,
                                                          void* __restrict__ aux_out, int Hq, int T_max, int block_shift,
                                                          const int* __restrict__ t_dev) {
-  constexpr int D = 4 * LPR;
+  constexpr int D = 4 * LPR, HELD = FAR ? kMergeFar : kMergeHeld;
   const int tid = threadIdx.x;
   // rows in the order 8 tokens of a head, the next head: a workgroup of 256 threads writes whole cache lines of operand blocks
   // (fewer tokens: as many as a block has)
@@ -794,9 +800,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   // (`rows` = tokens x heads the partials were laid out for; rows past the call's actual token count hold nothing)
   if (t >= dyn_tokens(t_dev, T_max)) return;  // (no barrier follows)
   const int row = t * Hq + head;
-  float2 ml[kMergeHeld];
+  float2 ml[HELD];
 #pragma unroll
-  for (int q = 0; q < kMergeHeld; ++q) {
+  for (int q = 0; q < HELD; ++q) {
     const int sp = l16 + 16 * q;
     ml[q] = make_float2(-INFINITY, 0.0f);
     if (q * 16 < nsplits && sp < nsplits) ml[q] = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
@@ -804,43 +810,46 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   const size_t sstride = (size_t)rows * D, off = (size_t)row * D + c4 * 4;
   const float* base = part_o;  // of the split to request next
   f32x4 v[MB];
-  auto request = [&](int s0) __attribute__((always_inline)) {
+  auto request = [&](int s0, auto count) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
+    for (int i = 0; i < decltype(count)::value; ++i) {
       v[i] = *reinterpret_cast<const f32x4*>(base + off);  // (past the last split: the last one again, at a factor of zero)
       if (s0 + i + 1 < nsplits) base += sstride;
     }
   };
-  request(0);
+  request(0, std::integral_constant<int, MB>{});
   // global maximum and normaliser: the lanes share the splits between them
   float M = -INFINITY;
 #pragma unroll
-  for (int q = 0; q < kMergeHeld; ++q) M = fmaxf(M, ml[q].x);
-  for (int sp = l16 + kMergePairs; sp < nsplits; sp += 16) M = fmaxf(M, part_ml[((size_t)sp * rows + row) * 2]);
+  for (int q = 0; q < HELD; ++q) M = fmaxf(M, ml[q].x);
   M = row16_max(M);
   auto factor = [&](float m) { return m == -INFINITY ? 0.0f : __expf(m - M); };
   float l = 0.0f;
-  float sc[kMergeHeld];
+  float sc[HELD];
 #pragma unroll
-  for (int q = 0; q < kMergeHeld; ++q) {
+  for (int q = 0; q < HELD; ++q) {
     sc[q] = factor(ml[q].x);
     l += ml[q].y * sc[q];
-  }
-  for (int sp = l16 + kMergePairs; sp < nsplits; sp += 16) {
-    const float2 x = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
-    l += x.x == -INFINITY ? 0.0f : x.y * factor(x.x);
   }
   l = row16_sum(l);
   f32x4 acc = {0, 0, 0, 0};
   merge_add<0>(acc, v, sc, std::make_integer_sequence<int, MB>{});
   if (MB == 17 && nsplits > MB) {
-    request(MB);
+    request(MB, std::integral_constant<int, MB>{});
     merge_add<MB>(acc, v, sc, std::make_integer_sequence<int, MB>{});
-    for (int sp = 2 * MB; sp < nsplits; ++sp) {
-      const float f = factor(part_ml[((size_t)sp * rows + row) * 2]);
-      const f32x4 x = *reinterpret_cast<const f32x4*>(part_o + (size_t)sp * sstride + off);
-      if (f != 0.0f) acc += x * f;
+    constexpr int kRest = kMergePairs - 2 * MB;
+    if (!std::is_same<ST, BF16>::value && nsplits > 2 * MB) {
+      request(2 * MB, std::integral_constant<int, kRest>{});
+      merge_add<2 * MB>(acc, v, sc, std::make_integer_sequence<int, kRest>{});
     }
+    if (FAR)
+      for (int s0 = kMergePairs; s0 < nsplits; s0 += 16) {
+        const int sp = s0 + l16;
+        const float m = sp < nsplits ? part_ml[((size_t)sp * rows + row) * 2] : -INFINITY;
+        request(s0, std::integral_constant<int, 16>{});
+        const float f[1] = {factor(m)};
+        merge_add<0>(acc, v, f, std::make_integer_sequence<int, 16>{});
+      }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -1970,14 +1979,15 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
   const int rows_per_wg = mthreads / (m.D / 4);
   const int group = T > 8 ? 8 : 1 << operand_shift(T);  // tokens whose rows of a head lie together
   const dim3 mgrid(((T + group - 1) / group * group * m.Hq + rows_per_wg - 1) / rows_per_wg);
-#define EVICT_MERGE(ST_, LPR_, MB_)                                                                                             \
-  hipLaunchKernelGGL((attn_merge_kernel<ST_, LPR_, MB_>), mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows,   \
+#define EVICT_MERGE(ST_, LPR_, ...)                                                                                             \
+  hipLaunchKernelGGL((attn_merge_kernel<ST_, LPR_, __VA_ARGS__>), mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows,   \
                      c->attn_o, aux_out, m.Hq, T, operand_shift(T), c->t_dev)
 #define EVICT_MERGE_D(ST_, LPR_)                        \
   do {                                                  \
     if (nsplits <= 5) EVICT_MERGE(ST_, LPR_, 5);        \
     else if (nsplits <= 9) EVICT_MERGE(ST_, LPR_, 9);   \
-    else EVICT_MERGE(ST_, LPR_, 17);                    \
+    else if (nsplits <= kMergePairs || std::is_same<ST_, BF16>::value) EVICT_MERGE(ST_, LPR_, 17); \
+    else EVICT_MERGE(ST_, LPR_, 17, !std::is_same<ST_, BF16>::value); \
   } while (0)
   if (m.dtype == EVICT_BF16) { if (m.D == 128) EVICT_MERGE_D(BF16, 32); else EVICT_MERGE_D(BF16, 16); }
   else { if (m.D == 128) EVICT_MERGE_D(F32, 32); else EVICT_MERGE_D(F32, 16); }

@@ -1,5 +1,5 @@
 """The merge of the attention's partial softmaxes where its unrolling changes: up to 5, 9 and 17 splits in one go, a second batch of
-17, pairs held by the lanes up to 48 and walked one by one beyond; with splits that are empty for the shorter sequence."""
+17, the other held pairs up to 48 and batches of 16 beyond; with splits that are empty for the shorter sequence."""
 import pytest
 
 import synth
@@ -10,7 +10,7 @@ pytest.importorskip("paper_2605_00342_amd")
 from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
 
 
-@pytest.mark.parametrize("splits", [3, 5, 6, 9, 10, 17, 18, 34, 35, 48, 49, 60])
+@pytest.mark.parametrize("splits", [3, 5, 6, 9, 10, 17, 18, 34, 35, 48, 49, 60, 64, 65, 191, 192])
 @pytest.mark.parametrize("D", [64, 128])
 def test_f32_split_counts(splits, D):
     L = 64 * (splits - 2)  # 64 keys a split, two splits of draft nodes
