@@ -784,8 +784,9 @@ __device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const floa
   }
 }
 
+// (at most 5 wavefronts per SIMD with 17 splits, so that the compiler keeps all 17 rows in flight instead of 8 wavefronts' registers)
 template <typename ST, int LPR, int MB, bool FAR = false>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17 ? 5 : 8))) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplits, int rows, void* __restrict__ out,
                                                          void* __restrict__ aux_out, int Hq, int T_max, int block_shift,
                                                          const int* __restrict__ t_dev) {
