@@ -557,7 +557,9 @@ static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream
     return launch_gemm_tile_lm(epi, a, s);
   const int nt = ctx->lm_nt ? ctx->lm_nt : (T > 16 ? 2 : 1);
   a.dense_tiles = (T + 16 * nt - 1) / (16 * nt);
-  a.dense_units = ctx->lm_units ? ctx->lm_units : lm_strips(T, a.n_strips);
+  a.dense_units = ctx->lm_units                                                    ? ctx->lm_units
+                  : lm_one_round(T, a.n_strips, a.nkb, ctx->m.dtype == EVICT_BF16) ? lm_strips(T, a.n_strips)
+                                                                                   : lm_units(T, a.n_strips);
   a.nt_loads = ctx->dense_nt_loads == 2 ? (a.dense_tiles == 1 ? 1 : 0) : ctx->dense_nt_loads;  // every strip is read by one workgroup
   const int grid = (((a.n_strips + a.dense_units - 1) / a.dense_units + 7) / 8) * 8 * a.dense_tiles;
   return launch_gemm(ctx->m.dtype, epi, a, nt, grid, s);

@@ -66,13 +66,22 @@ constexpr bool lm_tiled(int T, int n_strips, int nkb) {
 // 24.1 -> 24.8.)
 constexpr int lm_units(int T, int n_strips) { return T > 16 || (T > 12 && n_strips > 1024) ? 8 : 2; }
 
-// With two token tiles a workgroup fills a CU, and as long as there are enough strips they are dealt out in one round of 256
-// workgroups: three rounds of 8 strips leave the last a third full (151936 rows of 64 blocks, us, 8 strips per workgroup -> 38:
-// 32 tokens 118.3 -> 113.7, 24 tokens 112.4 -> 109.7; with one token tile two workgroups share a CU and 8 stay the best,
-// 16 tokens 103.3, 104.3).
+// With two token tiles a workgroup fills a CU, so the strips can be dealt out in one round of 256 workgroups instead of 8 at a
+// time, whose last round may be partly empty and whose every workgroup fetches the token operand.
 constexpr int lm_strips(int T, int n_strips) {
   const int units = lm_units(T, n_strips), round = (n_strips + 255) / 256;
   return T > 16 && round > units ? round : units;
+}
+
+// Where that pays: bf16, strips of up to 64 blocks, and not with so much for each workgroup that the last ones to end cost more
+// than is saved: 2048 blocks, from 25 tokens on, whose operand is the larger, 2432. (T of 17 .. 32, arg max and score rows, time
+// against 8 strips each: 2560 strips of 32 blocks 0.79 .. 0.82, 9496 of 32 0.88 .. 0.96, 9496 of 48 0.95 .. 1.00, 6400 of 64 0.94 .. 0.98,
+// 8016 of 64 0.97 .. 1.03, most below 1, 3142 of 24 1.00 .. 1.03, 9496 of 64, the weights of three heads in turn, T up to 24
+// 1.00 .. 1.02, 26 to 30 0.98 .. 1.00, 32 0.97 .. 0.99; but 8016 of 96 0.99 .. 1.06, 2049 and 4097 of 128 1.03 .. 1.07; 32-bit storage, 4096
+// of 64, 0.98 .. 1.03.) Several groups of 32 tokens are no longer one round: only with short strips, whose workgroups are all
+// start (33 to 128 tokens, 2560 to 15625 strips of 16 to 48 blocks 0.75 .. 1.01; 4097 of 64 0.94 .. 1.04).
+constexpr bool lm_one_round(int T, int n_strips, int nkb, bool bf16) {
+  return bf16 && nkb <= 64 && (n_strips + 255) / 256 * nkb <= (T > 24 ? 2432 : 2048) && (T <= 32 || nkb <= 48);
 }
 
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks

@@ -21,6 +21,7 @@ int tiled(int T, int k, int E, int nkb, int pairs, int strip) { return experts_t
 int lm(int T, int n_strips, int nkb) { return lm_tiled(T, n_strips, nkb); }
 int units(int T, int n_strips) { return lm_units(T, n_strips); }
 int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
+int one_round(int T, int n_strips, int nkb, int bf16) { return lm_one_round(T, n_strips, nkb, bf16); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
@@ -117,3 +118,12 @@ def test_lm_head_rounds(rules):
     for n in (64, 1024, 2048, 2049, 6400, 9496, 12504):
         s = rules.strips(32, n)
         assert s >= 8 and -(-n // s) <= 256
+
+
+def test_lm_head_rounds_where_they_were_measured_faster(rules):
+    for T in (17, 24, 32):
+        assert rules.one_round(T, 9496, 32, 1) and rules.one_round(T, 9496, 48, 1) and rules.one_round(T, 6400, 64, 1)
+        assert bool(rules.one_round(T, 9496, 64, 1)) == (T > 24)
+        # slower, or not faster: 32 strips of 96 blocks each, 9 of 128; 32-bit storage
+        assert not (rules.one_round(T, 8016, 96, 1) or rules.one_round(T, 2049, 128, 1) or rules.one_round(T, 4096, 64, 0))
+    assert rules.one_round(96, 9496, 32, 1) and not rules.one_round(33, 4097, 64, 1)  # several groups of 32 tokens
