@@ -167,7 +167,8 @@ int evict_dynamic_tokens(evict_ctx* ctx, const int32_t* count_dev);
  * temperature 0; feeds evict_accept_path).
  *   x [dev] [T, d]; g_final [dev] [d]; wlm_packed [dev] from evict_pack_dense(W_lm [vocab, d]);
  *   next [dev] int32[T]; best_logit [dev] float[T], nullable; x_norm_out [dev] [T, d] storage
- *   dtype, nullable: the normalised input the logits were formed from. Needs vocab > 0 in the
+ *   dtype, nullable, at any address: the normalised input the logits were formed from (it may
+ *   lie over x or g_final, which are then overwritten). Needs vocab > 0 in the
  *   model description given to evict_create. */
 int evict_lm_head_argmax(evict_ctx* ctx, const void* x, const void* g_final, const void* wlm_packed, int T,
                          int32_t* next, float* best_logit, void* x_norm_out, void* stream);

@@ -565,6 +565,24 @@ static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream
   return launch_gemm(ctx->m.dtype, epi, a, nt, grid, s);
 }
 
+// Final RMSNorm of the LM head. It writes the rows the caller asks for while it still reads others: where they lie over its
+// inputs, these are read from a copy (h and h_norm are free outside a layer).
+static int launch_final_norm(evict_ctx* ctx, const void* x, const void* g_final, int T, void* x_norm_out, hipStream_t s) {
+  const size_t row = (size_t)ctx->m.d * elem_bytes(ctx->m.dtype);
+  auto overlaps = [&](const void* in, size_t bytes) {
+    return x_norm_out && (uintptr_t)in < (uintptr_t)x_norm_out + T * row && (uintptr_t)x_norm_out < (uintptr_t)in + bytes;
+  };
+  if (overlaps(x, T * row)) {
+    EVICT_HIP_CHECK(hipMemcpyAsync(ctx->h, x, T * row, hipMemcpyDeviceToDevice, s));
+    x = ctx->h;
+  }
+  if (overlaps(g_final, row)) {
+    EVICT_HIP_CHECK(hipMemcpyAsync(ctx->h_norm, g_final, row, hipMemcpyDeviceToDevice, s));
+    g_final = ctx->h_norm;
+  }
+  return launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, x_norm_out, s);
+}
+
 int evict_lm_head_argmax(evict_ctx* ctx, const void* x, const void* g_final, const void* wlm_packed, int T, int32_t* next,
                          float* best_logit, void* x_norm_out, void* stream) {
   EVICT_REQUIRE(ctx && x && g_final && wlm_packed && next, EVICT_E_INVALID, "evict_lm_head_argmax: null pointer argument");
@@ -574,7 +592,7 @@ int evict_lm_head_argmax(evict_ctx* ctx, const void* x, const void* g_final, con
   EVICT_REQUIRE(aligned16(x) && aligned16(wlm_packed), EVICT_E_INVALID, "evict_lm_head_argmax: pointers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const int eb = elem_bytes(m.dtype);
-  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, x_norm_out, s);  // final RMSNorm only
+  int rc = launch_final_norm(ctx, x, g_final, T, x_norm_out, s);
   if (rc) return rc;
   GemmArgs a = {};
   a.W = (const u32x4*)wlm_packed;
@@ -602,7 +620,7 @@ int evict_lm_head_logits(evict_ctx* ctx, const void* x, const void* g_final, con
                 "evict_lm_head_logits: pointers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const int eb = elem_bytes(m.dtype);
-  int rc = launch_prep(ctx, nullptr, nullptr, 1, T, nullptr, 0, x, g_final, 1, x_norm_out, s);  // final RMSNorm only
+  int rc = launch_final_norm(ctx, x, g_final, T, x_norm_out, s);
   if (rc) return rc;
   GemmArgs a = {};
   a.W = (const u32x4*)wlm_packed;

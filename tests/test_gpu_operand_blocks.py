@@ -48,3 +48,32 @@ def test_rows_of_the_final_norm(T, shift):
     # 256 products of rounded values in fp32 sums: 256 * 2^-24 of the sum of magnitudes
     got, ref = logits.double().cpu(), rows.double() @ w.double().T
     assert ((got - ref).abs() <= 256 * 2.0 ** -24 * (rows.double().abs() @ w.double().abs().T)).all()
+
+
+@pytest.mark.parametrize("T,d", [(1, 256), (9, 256), (40, 256), (700, 2048)])
+@pytest.mark.parametrize("over", ["x", "x+1", "x-1", "x+8", "gain"])
+def test_rows_of_the_final_norm_over_its_inputs(T, d, over):
+    """x_norm_out over the rows (the same, one or eight further on, one before) or the gain that the norm reads: what it is and
+    what the scores are elsewhere."""
+    V = 1024
+    cfg = synth.ModelCfg("lmover", "bf16", d=d, Hq=2, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x = torch.randn(T, d, generator=g, device=DEV).bfloat16()
+    gain = (1 + 0.1 * torch.randn(d, generator=g, device=DEV)).bfloat16()
+    ctx = ev.evict_create(harness.model_desc(cfg, V), T, 1, 16)
+    head = harness.pack_lm_head(cfg, (0.05 * np.random.default_rng(T).standard_normal((V, d))).astype(np.float32))
+    want_rows, want, got = torch.zeros_like(x), torch.zeros(T, V, device=DEV), torch.zeros(T, V, device=DEV)
+    ev.evict_lm_head_logits(ctx, x, gain, head, T, want, want_rows)
+    buf = torch.zeros((T + 16) * d, dtype=torch.bfloat16, device=DEV)
+    at = 8 * d
+    xin = buf[at:at + T * d].view(T, d)
+    xin.copy_(x)
+    if over == "gain":
+        gain = buf[at + T * d - d // 2:at + T * d + d - d // 2].copy_(gain)  # (half under the rows, half behind)
+        xin, out = x, buf[at:]
+    else:
+        out = buf[at + d * int(over[1:] or 0):]
+    ev.evict_lm_head_logits(ctx, xin, gain, head, T, got, out)
+    torch.cuda.synchronize()
+    ev.evict_destroy(ctx)
+    assert torch.equal(out[:T * d].view(T, d), want_rows) and torch.equal(got, want)
