@@ -827,7 +827,9 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int wb = kLines ? w & ~1 : w;                            // first block of a stage that this wavefront fetches
   const int lrow = (lane >> 3) + 8 * (w & 1), piece = lane & 7;   // grouped: token of the tile, piece of its line
   const int lput = kLines ? (piece >> 2) * 64 + (piece & 3) * 16 + (lrow ^ piece) : lane;
-  const int lget[2] = {kLines ? lane ^ (lane >> 4) : lane, kLines ? lane ^ ((lane >> 4) | 4) : lane};  // even, odd block
+  const int even = lane ^ (lane >> 4), odd = lane ^ ((lane >> 4) | 4);
+  // where a lane reads in a block; without kLines its own place, which the base holds (an offset of its own there costs two registers)
+  auto lget = [&](int block) __attribute__((always_inline)) { return kLines ? (block & 1 ? odd : even) : 0; };
 
   // NTL_: live token tiles of this piece of work
   auto run = [&](auto ntl_tag, const u32x4* wbase, int sg, int p0, int ntok, int tok0) __attribute__((always_inline)) {
@@ -892,18 +894,18 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int s = 0; s < NST; ++s) {
       const int kn = s * KC + KC <= NKB ? KC : NKB - s * KC;
       if (s + D < NST) fetch(s + D);
-      const u32x4* sx = s_x + (s & 1) * NT * KC * 64;
+      const u32x4* sx = s_x + (s & 1) * NT * KC * 64 + (kLines ? 0 : lane);
       constexpr bool kOneSet = CH < NKB && NTT > 4;
       constexpr int NB = kOneSet ? 1 : 2;
       u32x4 b[NB][NTT];
 #pragma unroll
-      for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64 + lget[0]];
+      for (int t = 0; t < NTT; ++t) b[0][t] = sx[t * KC * 64 + lget(0)];
 #pragma unroll
       for (int jj = 0; jj < kn; ++jj) {
         const int j = s * KC + jj;
         if (!kOneSet && jj + 1 < kn) {
 #pragma unroll
-          for (int t = 0; t < NTT; ++t) b[(jj + 1) % NB][t] = sx[(t * KC + jj + 1) * 64 + lget[(jj + 1) & 1]];
+          for (int t = 0; t < NTT; ++t) b[(jj + 1) % NB][t] = sx[(t * KC + jj + 1) * 64 + lget(jj + 1)];
         }
 #pragma unroll
         for (int t = 0; t < NTT; ++t) {
@@ -915,7 +917,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
             }
             acc[i][t] = mfma_block<BF16>(A[i][j % WIN], b[jj % NB][t], j % CH == 0 ? f32x4{0, 0, 0, 0} : acc[i][t]);
           }
-          if (kOneSet && jj + 1 < kn) b[0][t] = sx[(t * KC + jj + 1) * 64 + lget[(jj + 1) & 1]];
+          if (kOneSet && jj + 1 < kn) b[0][t] = sx[(t * KC + jj + 1) * 64 + lget(jj + 1)];
         }
         if (j + WIN < NKB) {
 #pragma unroll

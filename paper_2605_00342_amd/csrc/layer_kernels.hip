@@ -1653,10 +1653,13 @@ constexpr size_t kDenseStripLdsMax = 128 * 1024;
 // Grouped: slots of kTileSlotTokens tokens. Six wavefronts make 8 chunks of the 48 strip pairs of expert width 768, so the
 // same strips of an expert's consecutive slots share an XCD; fewer token tiles re-read the weights of busy experts (912
 // tokens, 128 experts: 172 us with four tiles, 153 with six), more spill.
+// 128 blocks: a window of 5, as many as the registers hold (4 x 100 and 4 x 120 nodes, 128 experts of width 192, us: window of 4 81 and 83,
+// 5 79.5 and 81.6; 256 of width 256, 4 x 120 nodes 178 and 178).
 #define EVICT_TILE_GROUPED(X) \
-  X(EPI_SWIGLU, 6, 2, 6, 8, 1, 64, true) X(EPI_SWIGLU, 6, 2, 6, 4, 1, 128, true) \
+  X(EPI_SWIGLU, 6, 2, 6, 8, 1, 64, true) X(EPI_SWIGLU, 6, 2, 6, 5, 1, 128, true) \
   X(EPI_F32, 6, 2, 4, 8, 1, 24, true) X(EPI_F32, 6, 2, 4, 8, 1, 44, true) X(EPI_F32, 6, 2, 4, 6, 1, 6, true) X(EPI_F32, 6, 2, 4, 8, 1, 8, true)
-// Dense: from the smallest tile of strips x tokens to the largest.
+// Dense: from the smallest tile of strips x tokens to the largest. (The largest of 128 blocks streams as well from a window of 4 blocks
+// as from one of 7: 640 strips, 195, 370 and 649 tokens 45, 58 and 106 us, 44, 58 and 108.)
 #define EVICT_TILE_DENSE_NKB(X, EPI_, NKB_) \
   X(EPI_, 2, 1, 4, 16, 4, NKB_, false) X(EPI_, 3, 1, 4, 8, 2, NKB_, false) X(EPI_, 2, 2, 4, 8, 2, NKB_, false) \
   X(EPI_, 3, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 4, 8, 2, NKB_, false)
