@@ -20,8 +20,10 @@ def test_f32_split_counts(splits, D):
 
 
 @pytest.mark.parametrize("chunks", [4, 5, 8, 9, 16, 17, 31, 32])
-def test_bf16_split_counts(chunks):
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_split_counts(chunks, D):
     # (experts of the usual width: 64 columns make a contribution of 50 roundings of the stored output, and half a rounding each
     # way, 1/100 to 6/100 of it seen, is what the protocol's bound of 5e-2 on the contribution is to tell from a wrong expert)
-    case = synth.make_case("mini_bf16", n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random")
+    cfg = synth.ModelCfg("bf16merge", "bf16", d=512, Hq=8, Hkv=2, D=D, E=32, k=4, F=192)
+    case = synth.make_case(cfg.name, n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random", cfg=cfg)
     check_against_oracle(case, run_case(case))

@@ -1,5 +1,5 @@
-"""Token operands kept in blocks of 16 tokens: counts around whole blocks, and the final norm's rows that a caller asks for, at any
-address."""
+"""Token operands kept in blocks of 16 tokens, of 1, 2, 4 or 8 in calls of up to 8: counts around whole blocks, and the final norm's
+rows that a caller asks for, at any address."""
 import numpy as np
 import pytest
 import torch
@@ -15,15 +15,20 @@ from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("config", ["mini_bf16", "tiny"])
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 49, 113])
+CONFIGS = {"mini_bf16": synth.CONFIGS["mini_bf16"], "tiny": synth.CONFIGS["tiny"],  # heads of 128 and of 64 columns
+           "bf16_64": synth.ModelCfg("bf16_64", "bf16", d=512, Hq=8, Hkv=2, D=64, E=32, k=4, F=192),
+           "f32_128": synth.ModelCfg("f32_128", "f32", d=256, Hq=4, Hkv=2, D=128, E=16, k=2, F=128, theta=1e4)}
+
+
+@pytest.mark.parametrize("config", list(CONFIGS))
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 33, 49, 113])
 def test_layer_token_counts(config, n):
-    case = synth.make_case(config, n=n, L=90, seed=n, sigma=0.5, tree="random")
+    case = synth.make_case(config, n=n, L=90, seed=n, sigma=0.5, tree="random", cfg=CONFIGS[config])
     for tune in ({}, {"dense_kernel": 1}):  # (contraction split and strip per wavefront)
         check_against_oracle(case, run_case(case, tune=tune))
 
 
-@pytest.mark.parametrize("T", [1, 16, 17, 40])
+@pytest.mark.parametrize("T", [1, 2, 3, 6, 9, 16, 17, 40])
 @pytest.mark.parametrize("shift", [0, 1, 4])
 def test_rows_of_the_final_norm(T, shift):
     """x_norm_out, `shift` elements past a 16-byte boundary, holds the rows that the scores were formed from."""

@@ -212,11 +212,17 @@ def test_short_and_long_rows_agree(ctx_small, V):
 @pytest.mark.parametrize("u", [0.0, 0.37, 1.0 - 2.0 ** -24])
 def test_draw_rounds(ctx_small, V, u):
     """The longest row of one workgroup and the next; rows of one round and of one round more, of the pieces (150 elements)
-    and of the segments (152 blocks of 64); the target at both ends of the cumulative sum, where the first and the last token with mass take it."""
+    and of the segments (152 blocks of 64); the target at both ends of the cumulative sum: at 0 the first token that is not rejected
+    takes it (every one has mass), just below 1 one of the last within the margin."""
     parents, tree_off, parent, logits, tok, u_node, _ = make_sampling_case(77, [5, 1], V, spread=2.0)
     logits[:, -200:] += 6.0  # (mass in the last segment and piece)
     path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, np.full(2, u, np.float32), 8)
-    assert check_against_oracle(parents, tree_off, logits, tok, u_node, np.full(2, u, np.float32), 0.9, path, plen, bonus) < 2
+    assert check_against_oracle(parents, tree_off, logits, tok, u_node, np.full(2, u, np.float32), 0.9, path, plen, bonus) == 0
+    if u == 0.0:
+        for b, par in enumerate(parents):
+            lo, last = int(tree_off[b]), path[b, plen[b] - 1]
+            rejected = {int(tok[lo + c]) for c in range(len(par)) if par[c] == last}
+            assert bonus[b] == min(set(range(len(par) + 1)) - rejected)
 
 
 @pytest.mark.parametrize("V", [1000, 32000, 49153, 151936])
