@@ -831,23 +831,25 @@ __device__ __forceinline__ int draw_from_segment(float* s_piece, const int* s_re
   return pick < 0 ? 0 : pick;
 }
 
-// Rows of up to kOneDrawRow logits: one workgroup per tree walks, sums the segments, one per wavefront, and draws.
+// Rows of up to kOneDrawRow logits: one workgroup per tree walks, sums the segments, one per wavefront, and draws. PIECE: elements
+// of a piece that one round takes, for rows of up to 1024 * PIECE logits.
 // SHORT: statistics of short_row_stats_kernel; a segment is at most 16 loads per lane, and the code walked through counts.
-// (One tree of 8 nodes, four of 32, eight of 64, all launches, us, one workgroup -> spread as below: 16385 logits 15.9 -> 18.4,
-// 18.0 -> 20.1, 28.5 -> 29.5; 32000 logits 16.9 -> 18.8, 19.9 -> 20.7, 37.3 -> 36.9; 65536 logits 25.2 -> 22.2, 30.3 -> 27.7,
-// 57.2 -> 55.8.)
-constexpr int kOneDrawRow = 49152;
-template <bool SHORT>
+// (One tree of 2 nodes, one of 32, four of 32, eight of 64, all launches, us, one workgroup -> spread as below: 50272 logits 20.4 -> 22.0,
+// 22.1 -> 22.6, 26.1 -> 26.5, 46.8 -> 47.2; 65536 logits 21.0 -> 21.9, 22.9 -> 23.4, 29.0 -> 29.1, 55.5 -> 55.0; past that a lane takes a
+// third batch of loads: 65537 logits 26.1 -> 23.7, 28.0 -> 25.8, 34.8 -> 31.3, 62.2 -> 59.6. Shorter pieces make shorter code: 32000
+// logits, a tree of 32 nodes, 16.6 with pieces of 48, 17.0 with 64.)
+constexpr int kOneDrawRow = 65536, kMidRow = 49152;
+template <int PIECE>
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats,
     const float* __restrict__ u_node, const float* __restrict__ u_bonus, int T, int32_t* __restrict__ path, int path_stride,
     int32_t* __restrict__ path_len, int32_t* __restrict__ bonus, int32_t* __restrict__ status) {
+  constexpr bool SHORT = PIECE * kSampWaves * 64 <= kShortRow;
   constexpr int kBatch = SHORT ? 4 : kStatsBatch;
-  constexpr int kPiece = (SHORT ? kShortRow : kOneDrawRow) / (kSampWaves * 64);
   __shared__ SampTree s_tree;
   __shared__ int s_rej[kMaxSel];
-  __shared__ float s_piece[64 * piece_row(kPiece)];
+  __shared__ float s_piece[64 * piece_row(PIECE)];
   __shared__ int s_cur, s_nrej;
   __shared__ float s_segsum[kSampWaves];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
@@ -893,7 +895,7 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
   float rem;
   pick_segment(s_segsum, u_bonus[b], &segment, &rem);
   segment = __builtin_amdgcn_readfirstlane(segment);
-  const int pick = draw_from_segment<kPiece>(s_piece, s_rej, nrej, row, V, m, inv_temp, segment * seg, seg >> 6, rem);
+  const int pick = draw_from_segment<PIECE>(s_piece, s_rej, nrej, row, V, m, inv_temp, segment * seg, seg >> 6, rem);
   if (tid == 0) bonus[b] = pick;
 }
 
@@ -1016,15 +1018,16 @@ int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const 
   }
   int rc = launch_status("softmax statistics kernels");
   if (rc) return rc;
+#define EVICT_ONE_DRAW(ROW_)                                                                                                       \
+  hipLaunchKernelGGL(accept_sampled_kernel<(ROW_) / (kSampWaves * 64)>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok,   \
+                     logits, V, inv_temp, stats, u_node, u_bonus, T, path, path_stride, path_len, bonus, status)
   if (V <= kOneDrawRow || B > T) {  // (more trees than nodes, so some of them empty: no room to hand over)
-    if (V <= kShortRow)
-      hipLaunchKernelGGL(accept_sampled_kernel<true>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                         u_node, u_bonus, T, path, path_stride, path_len, bonus, status);
-    else
-      hipLaunchKernelGGL(accept_sampled_kernel<false>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,
-                         u_node, u_bonus, T, path, path_stride, path_len, bonus, status);
+    if (V <= kShortRow) EVICT_ONE_DRAW(kShortRow);
+    else if (V <= kMidRow) EVICT_ONE_DRAW(kMidRow);
+    else EVICT_ONE_DRAW(kOneDrawRow);
     return launch_status("accept_sampled_kernel");
   }
+#undef EVICT_ONE_DRAW
   hipLaunchKernelGGL(accept_sampled_walk_kernel, dim3(B * kSampWaves), dim3(kSegThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp,
                      stats, u_node, T, path, path_stride, path_len, status);
   hipLaunchKernelGGL(accept_sampled_draw_kernel, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok, logits, V, inv_temp, stats,

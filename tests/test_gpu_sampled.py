@@ -208,10 +208,10 @@ def test_short_and_long_rows_agree(ctx_small, V):
     assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.8, path, plen, bonus) <= 1
 
 
-@pytest.mark.parametrize("V", [49152, 49153, 151936, 16 * 64 * 150, 16 * 64 * 150 + 1, 16 * 64 * 152, 16 * 64 * 152 + 1])
+@pytest.mark.parametrize("V", [49152, 49153, 65536, 65537, 151936, 16 * 64 * 150, 16 * 64 * 150 + 1, 16 * 64 * 152, 16 * 64 * 152 + 1])
 @pytest.mark.parametrize("u", [0.0, 0.37, 1.0 - 2.0 ** -24])
 def test_draw_rounds(ctx_small, V, u):
-    """The longest row of one workgroup and the next; rows of one round and of one round more, of the pieces (150 elements)
+    """The longest rows of one workgroup, with pieces of 48 and 64, and the next; rows of one round and of one round more, of the pieces (150 elements)
     and of the segments (152 blocks of 64); the target at both ends of the cumulative sum: at 0 the first token that is not rejected
     takes it (every one has mass), just below 1 one of the last within the margin."""
     parents, tree_off, parent, logits, tok, u_node, _ = make_sampling_case(77, [5, 1], V, spread=2.0)
@@ -225,7 +225,7 @@ def test_draw_rounds(ctx_small, V, u):
             assert bonus[b] == min(set(range(len(par) + 1)) - rejected)
 
 
-@pytest.mark.parametrize("V", [1000, 32000, 49153, 151936])
+@pytest.mark.parametrize("V", [1000, 32000, 49153, 65537, 151936])
 @pytest.mark.parametrize("empty", [(1,), (0, 2), (3,), (0, 1, 2, 3, 4, 5)])
 def test_empty_trees_leave_their_neighbours_alone(ctx_small, V, empty):
     """Trees without nodes, between others (their offset is the next tree's root), at the end (past the last node) and in greater
