@@ -1328,13 +1328,16 @@ __global__ __launch_bounds__(kRouterThreads) void union_worklist_kernel(
 // LM head, second step: per token, the best (value, row) over the per-strip candidates;
 // equal values go to the lower row (vocabulary) index. One workgroup per token.
 // ------------------------------------------------------------------------------------
-// (1024 threads: a vocabulary of 151936 is two round trips of eight candidates a thread, five with 256; 32 tokens 7.3 -> 6.4 us)
-constexpr int kArgmaxThreads = 1024;
-__global__ __launch_bounds__(kArgmaxThreads) void argmax_reduce_kernel(const float* __restrict__ val, const int32_t* __restrict__ idx,
-                                                            int nstrips, int ld, int32_t* __restrict__ next,
-                                                            float* __restrict__ best_out, const int* __restrict__ t_dev) {
-  __shared__ float s_v[kArgmaxThreads / 64];
-  __shared__ int s_i[kArgmaxThreads / 64];
+// Up to kArgmaxFew candidates 256 threads, two trips of eight each; beyond, 1024 threads. (1024 columns, head and arg max, us, 256 ->
+// 1024 threads: 2000 strips, 1 token 20.3 -> 22.0, 32 tokens 22.3 -> 24.2; 4096 strips 31.8 -> 32.5, 32.0 -> 32.5; 6400 strips 46.3 -> 45.4,
+// 44.0 -> 42.9; 9496 strips 68.1 -> 67.1, 76.5 -> 75.5.)
+constexpr int kArgmaxFew = 4096;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void argmax_reduce_kernel(const float* __restrict__ val, const int32_t* __restrict__ idx, int nstrips,
+                                                                int ld, int32_t* __restrict__ next, float* __restrict__ best_out,
+                                                                const int* __restrict__ t_dev) {
+  __shared__ float s_v[THREADS / 64];
+  __shared__ int s_i[THREADS / 64];
   const int t = blockIdx.x, tid = threadIdx.x;
   if (t >= dyn_tokens(t_dev, (int)gridDim.x)) return;  // (rows past the call's actual token count)
   float bv = -INFINITY;
@@ -1342,12 +1345,12 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_reduce_kernel(const flo
   // candidates of a token are contiguous ([T][ld] with ld >= nstrips): eight loads in flight per thread
   const float* vrow = val + (size_t)t * ld;
   const int32_t* irow = idx + (size_t)t * ld;
-  for (int s0 = tid; s0 < nstrips; s0 += kArgmaxThreads * 8) {
+  for (int s0 = tid; s0 < nstrips; s0 += THREADS * 8) {
     float v[8];
     int i[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int s = s0 + kArgmaxThreads * u;
+      const int s = s0 + THREADS * u;
       v[u] = s < nstrips ? vrow[s] : -INFINITY;
       i[u] = s < nstrips ? irow[s] : 0x7fffffff;
     }
@@ -1364,7 +1367,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_reduce_kernel(const flo
   if ((tid & 63) == 0) { s_v[tid >> 6] = bv; s_i[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < kArgmaxThreads / 64; ++w)
+    for (int w = 1; w < THREADS / 64; ++w)
       if (s_v[w] > bv || (s_v[w] == bv && s_i[w] < bi)) { bv = s_v[w]; bi = s_i[w]; }
     next[t] = bi;
     if (best_out) best_out[t] = bv;
@@ -2072,7 +2075,10 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
 
 int launch_argmax_reduce(const float* val, const int32_t* idx, int nstrips, int ld, int T, int32_t* next, float* best_out,
                          const int32_t* t_dev, hipStream_t s) {
-  hipLaunchKernelGGL(argmax_reduce_kernel, dim3(T), dim3(kArgmaxThreads), 0, s, val, idx, nstrips, ld, next, best_out, t_dev);
+  if (nstrips <= kArgmaxFew)
+    hipLaunchKernelGGL(argmax_reduce_kernel<256>, dim3(T), dim3(256), 0, s, val, idx, nstrips, ld, next, best_out, t_dev);
+  else
+    hipLaunchKernelGGL(argmax_reduce_kernel<1024>, dim3(T), dim3(1024), 0, s, val, idx, nstrips, ld, next, best_out, t_dev);
   return launch_status("argmax_reduce_kernel");
 }
 

@@ -151,3 +151,32 @@ def test_router_sums():
         want = np.asarray(got["h_norm"], np.float64) @ np.asarray(case["W"]["wg"], np.float64).T
         err.append(float(np.linalg.norm(got["router_logits"] - want) / np.linalg.norm(want)))
     assert max(err) < 1.05 * err[0], err
+
+
+@pytest.mark.parametrize("vocab", [16, 65536, 65552, 131072, 131088])
+@pytest.mark.parametrize("T", [1, 40])
+def test_argmax_over_strips(vocab, T):
+    """The arg max where its workgroup changes (4096 strips) and takes another trip (8192): every row of the head stands there twice,
+    half the vocabulary apart, and the lower one is the answer; the greatest score sits in the first, the last and other strips."""
+    d = 256
+    cfg = synth.ModelCfg("lmargmax", "bf16", d=d, Hq=2, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    g = torch.Generator(device=DEV).manual_seed(vocab + T)
+    w = (0.02 * torch.randn(vocab // 2, d, generator=g, device=DEV)).bfloat16()
+    x = torch.randn(T, d, generator=g, device=DEV).bfloat16()
+    where = torch.linspace(0, vocab // 2 - 1, T, device=DEV).long() if T > 1 else torch.tensor([vocab // 2 - 1], device=DEV)
+    if vocab > T * 32:
+        w[where] = x  # far above every other score
+    w = torch.cat([w, w]).contiguous()
+    ctx = ev.evict_create(harness.model_desc(cfg, vocab), T, 1, 16)
+    head = torch.empty_like(w).reshape(-1)
+    ev.evict_pack_dense(ev.EVICT_BF16, w, vocab, d, head)
+    nxt, best = torch.zeros(T, dtype=torch.int32, device=DEV), torch.zeros(T, device=DEV)
+    logits = torch.zeros(T, vocab, device=DEV)
+    gain = torch.ones(d, dtype=torch.bfloat16, device=DEV)
+    ev.evict_lm_head_argmax(ctx, x, gain, head, T, nxt, best)
+    ev.evict_lm_head_logits(ctx, x, gain, head, T, logits)
+    torch.cuda.synchronize()
+    ev.evict_destroy(ctx)
+    top = logits.max(dim=1).values
+    assert torch.equal(best, top) and torch.equal(nxt.long(), (logits == top[:, None]).int().argmax(1))
+    assert (nxt < vocab // 2).all() and (vocab <= T * 32 or torch.equal(nxt.long(), where))
