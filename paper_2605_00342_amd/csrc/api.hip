@@ -632,7 +632,7 @@ int evict_lm_head_logits(evict_ctx* ctx, const void* x, const void* g_final, con
   a.T_dev = ctx->t_dev;
   a.out0 = logits;
   a.ldo = m.vocab;
-  return launch_lm_gemm(ctx, EPI_F32, a, T, s);
+  return launch_lm_gemm(ctx, EPI_ROWS, a, T, s);
 }
 
 int evict_profile_cost_union(evict_ctx* ctx, const evict_layer_weights* layers, int n_layers, const int32_t* tree_off,

@@ -18,7 +18,10 @@
 
 namespace evict {
 
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_ARGMAX = 4 };
+// SWIGLU and F32 (fp32 rows, the down projection) are grouped by expert, the others dense; ROWS: fp32 rows of a dense matrix (score
+// rows). What the operand is must be known at compile time: with one instance for both kinds of fp32 rows and a stride chosen
+// when it runs, score rows took up to 14 % longer (128256 rows of 96 blocks, 1 token, us: 150 -> 131; 32-bit storage, 32000 of 64 34.6 -> 30.8).
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_ARGMAX = 4, EPI_ROWS = 5 };
 
 // One slot of the device-side work list = one activated expert and one tile of up to 16 of its
 // tokens: the expert, where the tile sits in the grouped order, how many tokens it has, how many
@@ -56,10 +59,10 @@ struct GemmArgs {
   int lds_dma;           // 1: strip-pair gate/up kernel stages its token operand with direct global-to-LDS loads
   int down_ws;           // gemm_wave_strip_kernel: strips (wavefronts) per workgroup, 8 or 16
   int pair_tiles;        // 1: gemm_wave_strip_kernel with two token tiles takes them from two consecutive 16-token records
-  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ARGMAX: best value per (token, strip), [T][ldo]
+  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per (token, strip), [T][ldo]
   void* out1;            // QKV: k_new; ARGMAX: row index of the best value per (strip, token)
   void* out2;            // QKV: v_new
-  long long ldo;         // elements between output rows (RESID / SWIGLU / F32)
+  long long ldo;         // elements between output rows (RESID / SWIGLU / F32 / ROWS)
   const void* resid;     // RESID: residual rows, same layout as out0
   const float* rope_cs;  // QKV: [T][D] cos | sin
   int Hq, Hkv, D;
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
         if (r < nsteps) issue(A[r], r);
 
       // token operand of this lane's column in each tile
-      constexpr bool kDense = EPI != EPI_F32 && EPI != EPI_SWIGLU;  // (EPI_F32: a.grouped tells)
+      constexpr bool kDense = EPI != EPI_F32 && EPI != EPI_SWIGLU;
       const char* xrow[NT];
       uint32_t xoff[NT];  // dense: offset from a base that is the same for all lanes
 #pragma unroll
@@ -173,21 +176,20 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
           if (!a.x_by_token) row = p0 + col;
           else row = (t == 0 && tok0 == 0 && (lane & 15) < kWorkToks) ? tok_early : a.tok_of_pos[p0 + col];
         }
-        xoff[t] = operand_at(col, lane >> 4, nkb, a.x_shift);
-        xrow[t] = (const char*)a.X + (a.grouped ? row * a.ldx_bytes + (lane >> 4) * 16 : (long long)xoff[t]);
+        if (kDense) xoff[t] = operand_at(col, lane >> 4, nkb, a.x_shift);
+        else xrow[t] = (const char*)a.X + row * a.ldx_bytes + (lane >> 4) * 16;
       }
-      const int xstep = kDense || !a.grouped ? 64 << a.x_shift : 64;  // bytes between a row's blocks
+      const int xstep = kDense ? 64 << a.x_shift : 64;  // bytes between a row's blocks
       auto load_b = [&](int c) {
         int b0, nb;
         range(c, b0, nb);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const char* base = (const char*)a.X + (long long)b0 * xstep;
-          const char* bp = xrow[t] + (long long)b0 * xstep;
+          const char* base = (kDense ? (const char*)a.X : xrow[t]) + (long long)b0 * xstep;
 #pragma unroll
           for (int j = 0; j < KBW; ++j)
             if (EXACT || j < nb)
-              Bf[t][j] = *reinterpret_cast<const u32x4*>(kDense ? base + j * xstep + xoff[t] : bp + j * (EPI == EPI_SWIGLU ? 64 : xstep));
+              Bf[t][j] = *reinterpret_cast<const u32x4*>(kDense ? base + j * xstep + xoff[t] : base + j * 64);
         }
       };
       if (nchunks == 1) load_b(0);
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
                       ((float*)a.out0)[(long long)col * a.ldo + strip] = bv;
                       ((int*)a.out1)[(long long)col * a.ldo + strip] = bi;
                     }
-                  } else if (EPI == EPI_F32) {
+                  } else if (EPI == EPI_F32 || EPI == EPI_ROWS) {
                     if (valid) {
                       const long long orow = a.grouped ? (p0 + col) : col;
                       *reinterpret_cast<f32x4*>((float*)a.out0 + orow * a.ldo + strip * 16 + m0) = sum;
@@ -969,7 +971,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
             ((float*)a.out0)[(long long)col * a.ldo + strip + i] = bv;
             ((int*)a.out1)[(long long)col * a.ldo + strip + i] = bi;
           }
-        } else if (EPI == EPI_F32) {
+        } else if (EPI == EPI_F32 || EPI == EPI_ROWS) {
           if (ok) *reinterpret_cast<f32x4*>((float*)a.out0 + (long long)(p0 + col) * a.ldo + (strip + i) * 16 + m0) = sum;
         } else if (EPI == EPI_RESID) {
           if (ok) {
@@ -1007,7 +1009,7 @@ __global__ __launch_bounds__(WS * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   };
   // the number of live token tiles is known per piece of work: one compiled body for each (for a token group of the layer's
   // projections, where all but the last are full: one for a single tile, one for more)
-  constexpr bool kEach = GROUPED || EPI == EPI_F32 || EPI == EPI_ARGMAX;
+  constexpr bool kEach = GROUPED || EPI == EPI_ROWS || EPI == EPI_ARGMAX;
   // In step: the token groups of a strip group run side by side and share its weights through L2 as long as neither gets
   // ahead, so the last group of several goes at the pace of the full ones where it has more than half as many tiles (LM head,
   // 151936 x 2048, score rows of 104 tokens: 193 us with 4 and 3 tiles, 184 with 4 and 4).

@@ -1676,7 +1676,7 @@ constexpr size_t kDenseStripLdsMax = 128 * 1024;
 #define EVICT_TILE_LM_NKB(X, EPI_, NKB_) \
   X(EPI_, 2, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 4, 8, 2, NKB_, false) X(EPI_, 4, 2, 8, 8, 2, NKB_, false) X(EPI_, 6, 2, 8, (EPI_ == EPI_ARGMAX ? 6 : 8), 1, NKB_, false)
 #define EVICT_TILE_LM(X) \
-  EVICT_TILE_LM_NKB(X, EPI_F32, 64) EVICT_TILE_LM_NKB(X, EPI_F32, 128) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 64) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 128)
+  EVICT_TILE_LM_NKB(X, EPI_ROWS, 64) EVICT_TILE_LM_NKB(X, EPI_ROWS, 128) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 64) EVICT_TILE_LM_NKB(X, EPI_ARGMAX, 128)
 constexpr size_t tile_lds_bytes(int nt, int ws) { return (size_t)2 * nt * ws * 1024; }
 
 }  // namespace
@@ -1818,6 +1818,7 @@ int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStre
     EVICT_GEMM_CASE(EPI_SWIGLU)
     EVICT_GEMM_CASE(EPI_F32)
     EVICT_GEMM_CASE(EPI_ARGMAX)
+    EVICT_GEMM_CASE(EPI_ROWS)
   }
 #undef EVICT_GEMM_CASE
   set_error("unknown epilogue %d", epi);

@@ -180,3 +180,25 @@ def test_argmax_over_strips(vocab, T):
     top = logits.max(dim=1).values
     assert torch.equal(best, top) and torch.equal(nxt.long(), (logits == top[:, None]).int().argmax(1))
     assert (nxt < vocab // 2).all() and (vocab <= T * 32 or torch.equal(nxt.long(), where))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 256), ("bf16", 768), ("bf16", 1536), ("bf16", 3072), ("f32", 256), ("f32", 1024)])
+@pytest.mark.parametrize("T", [1, 3, 16, 17, 40])
+def test_score_rows_of_other_lengths(dtype, d, T):
+    """Score rows by the contraction split (strips of 8 to 96 blocks, none of them 64 in bf16): products of the rows the head reports
+    in 64 bits. An fp32 sum of d products is off by at most d * 2^-24 of the sum of their magnitudes."""
+    V = 528
+    cfg = synth.ModelCfg("lmrows", dtype, d=d, Hq=2, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=DEV).manual_seed(d + T)
+    w = (0.05 * torch.randn(V, d, generator=g, device=DEV)).to(td)
+    x = torch.randn(T, d, generator=g, device=DEV).to(td)
+    ctx = ev.evict_create(harness.model_desc(cfg, V), T, 1, 16)
+    head = torch.empty_like(w).reshape(-1)
+    ev.evict_pack_dense(ev.EVICT_BF16 if dtype == "bf16" else ev.EVICT_F32, w, V, d, head)
+    rows, logits = torch.zeros_like(x), torch.full((T, V), float("nan"), device=DEV)
+    ev.evict_lm_head_logits(ctx, x, torch.ones(d, dtype=td, device=DEV), head, T, logits, rows)
+    torch.cuda.synchronize()
+    ev.evict_destroy(ctx)
+    got, rows, w = logits.double().cpu(), rows.double().cpu(), w.double().cpu()
+    assert ((got - rows @ w.T).abs() <= d * 2.0 ** -24 * (rows.abs() @ w.abs().T)).all()
