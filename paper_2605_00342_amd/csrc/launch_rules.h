@@ -84,6 +84,13 @@ constexpr bool lm_one_round(int T, int n_strips, int nkb, bool bf16) {
   return bf16 && nkb <= 64 && (n_strips + 255) / 256 * nkb <= (T > 24 ? 2432 : 2048) && (T <= 32 || nkb <= 48);
 }
 
+// TopK beside the union (up to 32 tokens): four tokens per wavefront, in rows of 16 lanes with room for a pick each, once some of
+// the 16 wavefronts would have two tokens. (TopK and union, us, one -> four: 32 tokens 9.1 -> 7.3, one token 5.3 -> 6.6. Whole layers: 8 picks
+// of 128 experts, 9 tokens 41.5 -> 42.1, 17 43.3 -> 43.3, 24 44.2 -> 43.8, 32 45.5 -> 44.1; 16 picks, 9 tokens 43.9 -> 44.8, 17 46.6 -> 46.9, 24
+// 48.0 -> 47.5. With 16 scores in a lane instead of 8 the chain of a pick is longer: 8 of 256, 9 tokens 42.8 -> 44.2, 24 46.1 -> 46.7, 28
+// 47.4 -> 46.9; 16 of 256 45.7 -> 49.3, 52.5 -> 54.1, 54.4 -> 54.4; 4 of 160, 24 tokens 43.7 -> 43.8, 28 44.7 -> 44.1.)
+constexpr bool topk_by_rows(int T, int E, int k) { return k <= 16 && T >= (E > 128 ? 28 : 17); }
+
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }

@@ -1143,9 +1143,8 @@ __device__ __forceinline__ void topk_wave_regs(const float (&raw)[NR], int E, in
 // same selection rule as topk_kernel, without the LDS round trips. Lane l of a row holds the NR consecutive experts
 // l*NR .. l*NR + NR - 1; lane j ends up with the j-th pick and its weight.
 // With a token per wavefront the work of 32 tokens is all instruction issue (16 wavefronts share 4 SIMDs, two tokens each, 40
-// instructions a pick); four tokens share about 50 here. A single token's chain of dependent instructions is longer, so calls
-// of up to 8 tokens stay with one per wavefront (TopK and union, us, one token per wavefront -> four: 32 tokens 9.1 -> 7.3, one
-// token 5.3 -> 6.6).
+// instructions a pick); four tokens share about 50 here. A single token's chain of dependent instructions is longer, so smaller calls
+// stay with one per wavefront (topk_by_rows).
 template <int NR>
 __device__ __forceinline__ void topk_load_four(const float* __restrict__ row, int E, int l16, bool live, f32x4 (&raw)[NR / 4]) {
 #pragma unroll
@@ -1204,8 +1203,6 @@ __device__ __forceinline__ void topk_rows(const f32x4 (&raw)[NR / 4], int E, int
   *my_w = ex / row16_sum(ex);
 }
 
-constexpr int kTopkRowsK = 16;        // picks a row of lanes has room for
-constexpr int kTopkRowsTokens = 9;    // from here on four tokens per wavefront
 // Register variant of topk_kernel for E <= 256: grid over groups of 16 tokens, one per wavefront.
 __global__ __launch_bounds__(kRouterThreads) void topk_regs_kernel(
     const float* __restrict__ logits, int T_max, int E, int k, int norm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
@@ -2052,7 +2049,7 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
     hipLaunchKernelGGL(topk_union_kernel<ROWS_>, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx, \
                        c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv, \
                        c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, counts, c->t_dev)
-    if (T >= kTopkRowsTokens && m.k <= kTopkRowsK) EVICT_TOPK_UNION(true);
+    if (topk_by_rows(T, m.E, m.k)) EVICT_TOPK_UNION(true);
     else EVICT_TOPK_UNION(false);
 #undef EVICT_TOPK_UNION
     return launch_status("topk_union_kernel");

@@ -22,6 +22,7 @@ int lm(int T, int n_strips, int nkb) { return lm_tiled(T, n_strips, nkb); }
 int units(int T, int n_strips) { return lm_units(T, n_strips); }
 int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
 int one_round(int T, int n_strips, int nkb, int bf16) { return lm_one_round(T, n_strips, nkb, bf16); }
+int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
@@ -127,3 +128,9 @@ def test_lm_head_rounds_where_they_were_measured_faster(rules):
         # slower, or not faster: 32 strips of 96 blocks each, 9 of 128; 32-bit storage
         assert not (rules.one_round(T, 8016, 96, 1) or rules.one_round(T, 2049, 128, 1) or rules.one_round(T, 4096, 64, 0))
     assert rules.one_round(96, 9496, 32, 1) and not rules.one_round(33, 4097, 64, 1)  # several groups of 32 tokens
+
+
+def test_topk_rows_where_they_were_measured_faster(rules):
+    for E, k, first in ((16, 2, 17), (64, 6, 17), (128, 8, 17), (128, 1, 17), (64, 16, 17), (144, 4, 28), (256, 8, 28), (256, 16, 28)):
+        assert [T for T in range(1, 33) if rules.topk(T, E, k)] == list(range(first, 33))
+    assert not any(rules.topk(T, 64, 17) for T in range(1, 33))  # (a row of 16 lanes has no room for 17 picks)
