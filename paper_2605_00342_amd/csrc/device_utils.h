@@ -63,8 +63,8 @@ template <> __device__ __forceinline__ f32x4 load4<BF16>(const void* p, size_t i
 // order the lanes of a wavefront hold them (below), the blocks of 16 tokens one after the other. A wavefront then fetches a block
 // as 1 KiB in a row instead of half a cache line of each of 16 rows (us, rows -> blocks: output projection of 32 tokens, 4096
 // columns 8.9 -> 7.1, of 64 tokens, 2048 columns 7.5 -> 5.1; QKV of 32 tokens, 4096 columns 8.9 -> 7.1, of 917 tokens, 2048
-// columns 38.7 -> 34.1). Calls of up to 8 tokens have blocks of 8, 4, 2 or 1 (rows as they are), as the other lanes' tokens
-// would only spread them (blocks of 16 at one token: layer 56.9 -> 57.8 us).
+// columns 38.7 -> 34.1; of the kernels that write them the norm of 917 tokens takes 6.0 instead of 5.9). Calls of up to 8 tokens have
+// blocks of 8, 4, 2 or 1 (rows as they are), as the other lanes' tokens would only spread them (blocks of 16 at one token: layer 56.9 -> 57.8 us).
 __host__ __device__ constexpr int operand_shift(int T) { return T > 8 ? 4 : T > 4 ? 3 : T > 2 ? 2 : T > 1 ? 1 : 0; }  // log2 of the tokens of a block
 // Byte offset of the 16 bytes at chunk c of token t's row of nkb blocks; the last tokens take a whole set of blocks.
 __device__ __forceinline__ unsigned operand_at(int t, int c, int nkb, int shift) {

@@ -755,11 +755,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // the serial walk over the splits is spread over more CUs). Empty splits carry max = -inf and their partial rows are never
 // read into the sum. The partial rows of the first MB splits are requested before the (max, sum) pairs are reduced, so the
 // two round trips overlap.
-// What bounds it with few tokens is the code a wavefront walks through (with a cold instruction cache), not the bytes, so
-// that is kept short: every 16 lanes hold the pairs of all splits, turn each into its split's factor once and hand the
+// With few tokens it is bound by its chain of instructions and trips to memory, not by the bytes (16 wavefronts, 62 % of their time spent
+// waiting, at one token), so both are kept short: every 16 lanes hold the pairs of all splits, turn each into its split's factor once and hand the
 // factors round by DPP; partial rows are requested from a base that is the same for all lanes; as many splits are unrolled
-// as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.8 -> 2.9, 32
-// tokens of 8 heads 4.9 -> 2.8, of 32 heads 5.1 -> 4.0; 5 splits, 917 tokens 13.0 -> 8.2.)
+// as there are, 5, 9 or 17 (16 context splits + the draft-node split: a 2048-key context). (us: 17 splits, 1 token of 32 heads 4.9 -> 3.0, 32
+// tokens of 32 heads 5.4 -> 4.0; 5 splits, 917 tokens 13.0 -> 8.6.)
 // Contexts of 32-bit storage, a split per 64 keys, have more: the second 17 follow, the other held ones, then 16 at a time whose
 // factors are worked out again from their pairs, rows and pairs of a batch in one trip to memory (FAR: more than 48 splits).
 // (Layers of 32-bit storage, us, splits past 34 one by one -> so: 4 heads of 64, 1 node, 4000 positions 56 -> 48, 12000
@@ -1028,8 +1028,8 @@ __global__ __launch_bounds__(kRouterThreads) void topk_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   float* s_sel = reinterpret_cast<float*>(s_all) + w * 64;                                   // [k] per wavefront
   unsigned* s_ord = reinterpret_cast<unsigned*>(s_all) + kRouterWaves * 64 + (size_t)w * E;  // [E] per wavefront
-  // The loops below are deliberately not unrolled: with a cold instruction cache the cost of
-  // this small kernel follows the size of the code it walks through.
+  // The loops below are deliberately not unrolled: every line of code is fetched once per launch, which counts in a kernel
+  // this small.
   const int t = blockIdx.x * kRouterWaves + w;  // one token per wavefront
   if (t >= T) return;
   const float* row = logits + (size_t)t * E;

@@ -721,7 +721,10 @@ __device__ __forceinline__ void pick_segment(const float* segsum, float u, int* 
 // Pieces of the segment at `base`, cl elements each, by a workgroup of 1024 threads: their exponentials go through LDS,
 // LEN elements of every piece at a time, the first wavefront adds up one piece per lane and walks the one that holds
 // `rem`. Returns the drawn token, in the first wavefront.
-constexpr int kPieceLong = 150;                                   // a vocabulary of 151936 has pieces of 149: one round trip
+// A vocabulary of 151936 has pieces of 149: one round. Past 153600 logits there is a second one, and the drawn piece is evaluated again (all
+// launches, four trees of 32 nodes, us, one workgroup per tree -> spread: 128256 logits 51.5 -> 38.6, 153600 60.6 -> 44.4, 153601 65.4 -> 56.0,
+// 200064 76.9 -> 64.9, 262144 94.6 -> 81.1).
+constexpr int kPieceLong = 150;
 constexpr int piece_row(int len) { return len | 1; }                // odd: 64 lanes read 64 pieces without bank conflicts
 template <int LEN>
 __device__ __forceinline__ int draw_from_segment(float* s_piece, const int* s_rej, int nrej, const float* __restrict__ row, int V,
