@@ -1233,8 +1233,10 @@ __global__ __launch_bounds__(kRouterThreads) void topk_regs_kernel(
 
 // Small token counts: TopK (register variant) and the expert union in one workgroup, the
 // wavefronts taking the tokens in turn; saves a launch when there are few tokens to share out.
-// ROWS: four tokens per wavefront.
-template <bool ROWS>
+// BY: a token per wavefront, four (rows of lanes), or as topk_by_rows says for the count found in device memory, of which the call
+// knows the upper bound only (a single token of at most 32, 256 experts: layer 60.3 us by rows of lanes, 58.7 by wavefronts).
+enum { TOPK_WAVES, TOPK_ROWS, TOPK_BY_COUNT };
+template <int BY>
 __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
     const float* __restrict__ logits, int T_max, int E, int k, int norm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
     int32_t* __restrict__ aux_idx, float* __restrict__ aux_w, int use_masks, int32_t* __restrict__ union_ids,
@@ -1245,7 +1247,7 @@ __global__ __launch_bounds__(kRouterThreads) void topk_union_kernel(
   const int T = dyn_tokens(t_dev, T_max);
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if constexpr (ROWS) {
+  if (BY == TOPK_ROWS || (BY == TOPK_BY_COUNT && topk_by_rows(T, E, k))) {
     const int l16 = lane & 15, t = threadIdx.x >> 4;
     if ((t & ~3) < T) {  // (whole wavefronts)
       const bool live = t < T;
@@ -2045,12 +2047,13 @@ int launch_topk_union(const evict_ctx* c, int T, const evict_layer_aux* aux, int
   const int use_masks = union_mask_plan(T, m.k, m.E, &lds);
   const bool regs = m.E <= 256;
   if (regs && T <= kFusedTopkTokens) {
-#define EVICT_TOPK_UNION(ROWS_) \
-    hipLaunchKernelGGL(topk_union_kernel<ROWS_>, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx, \
+#define EVICT_TOPK_UNION(BY_) \
+    hipLaunchKernelGGL(topk_union_kernel<BY_>, dim3(1), dim3(kRouterThreads), lds, s, c->logits, T, m.E, m.k, m.router_norm, c->topk_idx, \
                        c->topk_w, a_idx, a_w, use_masks, c->union_ids, c->union_count, c->hist, c->offsets, c->perm, c->inv, \
                        c->status, c->work, c->tok_of_pos, c->sched, m.n_shared, tile_tokens, counts, c->t_dev)
-    if (topk_by_rows(T, m.E, m.k)) EVICT_TOPK_UNION(true);
-    else EVICT_TOPK_UNION(false);
+    if (!topk_by_rows(T, m.E, m.k)) EVICT_TOPK_UNION(TOPK_WAVES);
+    else if (c->t_dev) EVICT_TOPK_UNION(TOPK_BY_COUNT);
+    else EVICT_TOPK_UNION(TOPK_ROWS);
 #undef EVICT_TOPK_UNION
     return launch_status("topk_union_kernel");
   }
