@@ -55,6 +55,37 @@ def test_rows_of_the_final_norm(T, shift):
     assert ((got - ref).abs() <= 256 * 2.0 ** -24 * (rows.double().abs() @ w.double().abs().T)).all()
 
 
+@pytest.mark.parametrize("dtype,d,bound", [("bf16", 512, 8), ("bf16", 512, 16), ("bf16", 512, 40), ("f32", 256, 32), ("bf16", 2048, 64)])
+@pytest.mark.parametrize("live", [1, 2, 3, 5, 8, 9, 64])
+def test_head_of_a_count_in_device_memory(dtype, d, bound, live):
+    """A head that knows an upper bound of its tokens only (and has the operand blocks of that bound) gives the rows of the live ones,
+    their scores and arg max as the products of the rows in 64 bits (d * 2^-24 of the sum of magnitudes) and touches no others; a
+    count above the bound is the bound."""
+    V, n = 32768, min(live, bound)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = synth.ModelCfg("lmcount", dtype, d=d, Hq=2, Hkv=1, D=64, E=16, k=2, F=64, theta=1e4)
+    g = torch.Generator(device=DEV).manual_seed(bound + live)
+    x = torch.randn(bound, d, generator=g, device=DEV).to(td)
+    w = (0.05 * torch.randn(V, d, generator=g, device=DEV)).to(td)
+    ctx = ev.evict_create(harness.model_desc(cfg, V), bound, 1, 16)
+    head = torch.empty_like(w).reshape(-1)
+    ev.evict_pack_dense(ev.EVICT_BF16 if dtype == "bf16" else ev.EVICT_F32, w, V, d, head)
+    gain, count = torch.ones(d, dtype=td, device=DEV), torch.tensor([live], dtype=torch.int32, device=DEV)
+    rows, logits = torch.zeros_like(x), torch.full((bound, V), -7.0, device=DEV)
+    nxt, best = torch.full((bound,), -1, dtype=torch.int32, device=DEV), torch.zeros(bound, device=DEV)
+    ev.evict_dynamic_tokens(ctx, count.data_ptr())
+    ev.evict_lm_head_logits(ctx, x, gain, head, bound, logits, rows)
+    ev.evict_lm_head_argmax(ctx, x, gain, head, bound, nxt, best)
+    ev.evict_dynamic_tokens(ctx, None)
+    torch.cuda.synchronize()
+    ev.evict_destroy(ctx)
+    ref, mag = rows[:n].double() @ w.double().T, rows[:n].double().abs() @ w.double().abs().T
+    assert ((logits[:n].double() - ref).abs() <= d * 2.0 ** -24 * mag).all() and bool((logits[n:] == -7.0).all())
+    val, idx = logits[:n].max(-1)
+    assert torch.equal(best[:n], val) and torch.equal(nxt[:n].long(), idx)
+    assert not rows[n:].any() and bool((nxt[n:] == -1).all())
+
+
 @pytest.mark.parametrize("T,d", [(1, 256), (9, 256), (40, 256), (700, 2048)])
 @pytest.mark.parametrize("over", ["x", "x+1", "x-1", "x+8", "gain"])
 def test_rows_of_the_final_norm_over_its_inputs(T, d, over):
