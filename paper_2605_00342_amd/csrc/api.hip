@@ -94,6 +94,7 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
   A(&c.q, T * HqD * eb);
   A(&c.part_o, (size_t)c.max_splits * T * HqD * 4);
   A(&c.part_ml, (size_t)c.max_splits * T * m->Hq * 2 * 4);
+  A(&c.row_splits, T * 4);
   A(&c.attn_o, T16 * HqD * eb);
   A(&c.h, T * d * eb);
   A(&c.h_norm, T * d * eb);
@@ -142,7 +143,7 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
   c.moe_nt_loads = 2;
   c.dense_nt_loads = 2;
   c.dense_nt = 0;
-  c.attn_target_wgs = 512;
+  c.attn_target_wgs = kAttnTargetWgs;
   c.attn_waves = 0;
   c.moe_nt = 0;
   c.dense_units = 0;

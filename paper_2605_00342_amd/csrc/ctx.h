@@ -38,6 +38,7 @@ struct evict_ctx {
   void* q;               // [T][Hq*D]
   float* part_o;         // [splits+1][T][Hq][D]
   float* part_ml;        // [splits+1][T][Hq][2]
+  int32_t* row_splits;   // [T] splits of a token's sequence, where the attention kernel chose them itself
   void* attn_o;          // [T][Hq*D], in operand blocks
   void* h;               // [T][d]
   void* h_norm;          // [T][d]

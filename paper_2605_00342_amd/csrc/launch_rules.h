@@ -91,6 +91,32 @@ constexpr bool lm_one_round(int T, int n_strips, int nkb, bool bf16) {
 // 47.4 -> 46.9; 16 of 256 45.7 -> 49.3, 52.5 -> 54.1, 54.4 -> 54.4; 4 of 160, 24 tokens 43.7 -> 43.8, 28 44.7 -> 44.1.)
 constexpr bool topk_by_rows(int T, int E, int k) { return k <= 16 && T >= (E > 128 ? 28 : 17); }
 
+// bf16 attention with 32 query rows per wavefront (attn_rows_kernel) instead of 16 (attn_partial_mfma_kernel), for B trees of T nodes together
+// and contexts of up to max_ctx positions. Its workgroups take 128 rows of a KV head and run through chunks of 64 keys.
+constexpr int kAttnRowsKeys = 64, kAttnRowsPerWg = 128, kAttnRowsMaxSeqs = 64;
+// Chunks of all row blocks, KV heads and sequences, by the longest context.
+constexpr long long attn_rows_work(int B, int T, int Hq, int Hkv, int max_ctx) {
+  const long long rbs = ((long long)T * (Hq / Hkv) + kAttnRowsPerWg - 1) / kAttnRowsPerWg;
+  return (rbs > B ? rbs : B) * Hkv * ((max_ctx + kAttnRowsKeys - 1) / kAttnRowsKeys + 1);
+}
+// Attention and merge, us, 16 rows -> 32. Many chunks: 1 x 64 nodes of 4 KV heads of 8, ctx 2048 18.4 -> 17.8, ctx 6000 25.0 -> 21.2, 1 x 128 ctx 16000
+// 70.3 -> 50.0, 4 x 64 ctx 6000 56.6 -> 37.8, 16 x 64 ctx 2048 101.5 -> 46.6; one KV head of 8, 2 x 128 ctx 2048 20.4 -> 19.0; 16 heads of one, 4 x 64
+// ctx 600 19.4 -> 14.2. Many small trees, whose empty row blocks the 16-row kernel deals out between the others (half to three quarters of
+// the CUs get none): 16 x 16 ctx 600 51.4 -> 17.9, 64 x 8 ctx 100 45.2 -> 22.7. One tree that fills at most two wavefronts, which then take a
+// chunk of 64 keys each where the other kernel takes 128: 1 x 8 ctx 600 10.0 -> 9.2, 16 heads of one, 1 x 64 ctx 2048 16.2 -> 13.2.
+// Not where few chunks leave most of a workgroup's time to its start and its end: 1 x 64 ctx 600 13.4 (14.9), 1 x 32 ctx 600 11.5 (13.0), one KV
+// head, 2 x 128 ctx 600 12.8 (17.1), 1 x 64 ctx 6000 15.8 (16.7).
+constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_ctx) {
+  if (D != 128 || B > kAttnRowsMaxSeqs) return false;
+  return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 400 || B >= 16 || (B == 1 && T * (Hq / Hkv) <= 64);
+}
+// Workgroups to cut the splits for: one per CU, or two, which overlap each other's phases but leave twice the partial rows to the
+// merge, once they have 16 chunks and more (one, two per CU: 8 x 32 nodes, 16 heads of one, ctx 2048 28.8, 22.6; 16 x 64 ctx 2048 57.6, 46.6; but
+// 4 x 64 ctx 2048 21.8, 24.8, 1 x 128 ctx 6000 29.4, 31.7).
+constexpr int attn_rows_wgs(int B, int T, int Hq, int Hkv, int max_ctx) {
+  return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 16 * 256 ? 512 : 256;
+}
+
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).
 inline int down_nt_loads(int knob, int nkb) { return knob == 2 ? (nkb == 8 ? 0 : 1) : knob; }

@@ -784,12 +784,13 @@ __device__ __forceinline__ void merge_add(f32x4& acc, const f32x4* v, const floa
   }
 }
 
+// (PLANNED: 5 splits first, which is what a batch of many rows has, then 12 more, then 17: us, 917 tokens with 2 splits 14 -> 10.)
 // (at most 5 wavefronts per SIMD with 17 splits, so that the compiler keeps all 17 rows in flight instead of 8 wavefronts' registers)
-template <typename ST, int LPR, int MB, bool FAR = false>
+template <typename ST, int LPR, int MB, bool FAR = false, bool PLANNED = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17 ? 5 : 8))) void attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                          int nsplits, int rows, void* __restrict__ out,
                                                          void* __restrict__ aux_out, int Hq, int T_max, int block_shift,
-                                                         const int* __restrict__ t_dev) {
+                                                         const int* __restrict__ t_dev, const int32_t* __restrict__ row_splits) {
   constexpr int D = 4 * LPR, HELD = FAR ? kMergeFar : kMergeHeld;
   const int tid = threadIdx.x;
   // rows in the order 8 tokens of a head, the next head: a workgroup of 256 threads writes whole cache lines of operand blocks
@@ -799,14 +800,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17
   const int t = (group << gs) + (at & ((1 << gs) - 1));
   const int c4 = tid & (LPR - 1), l16 = tid & 15;
   // (`rows` = tokens x heads the partials were laid out for; rows past the call's actual token count hold nothing)
-  if (t >= dyn_tokens(t_dev, T_max)) return;  // (no barrier follows)
+  const int T = dyn_tokens(t_dev, T_max);
+  // (PLANNED: the attention kernel cut every sequence into splits of its own number; a wavefront goes by the most of its rows')
+  int mine = nsplits;
+  if (PLANNED) {
+    mine = t < T ? row_splits[t] : 0;  // (tokens of a tree that was too large have none)
+    mine = mine < 0 ? 0 : (mine > nsplits ? nsplits : mine);
+    nsplits = (int)wave_max_u32((unsigned)mine);
+  }
+  if (t >= T) return;  // (no barrier follows)
   const int row = t * Hq + head;
   float2 ml[HELD];
 #pragma unroll
   for (int q = 0; q < HELD; ++q) {
     const int sp = l16 + 16 * q;
     ml[q] = make_float2(-INFINITY, 0.0f);
-    if (q * 16 < nsplits && sp < nsplits) ml[q] = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
+    if (q * 16 < nsplits && sp < mine) ml[q] = *reinterpret_cast<const float2*>(part_ml + ((size_t)sp * rows + row) * 2);
   }
   const size_t sstride = (size_t)rows * D, off = (size_t)row * D + c4 * 4;
   const float* base = part_o;  // of the split to request next
@@ -818,7 +827,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17
       if (s0 + i + 1 < nsplits) base += sstride;
     }
   };
-  request(0, std::integral_constant<int, MB>{});
+  constexpr int FIRST = PLANNED ? 5 : MB;
+  request(0, std::integral_constant<int, FIRST>{});
   // global maximum and normaliser: the lanes share the splits between them
   float M = -INFINITY;
 #pragma unroll
@@ -834,7 +844,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17
   }
   l = row16_sum(l);
   f32x4 acc = {0, 0, 0, 0};
-  merge_add<0>(acc, v, sc, std::make_integer_sequence<int, MB>{});
+  merge_add<0>(acc, v, sc, std::make_integer_sequence<int, FIRST>{});
+  if (PLANNED && nsplits > FIRST) {
+    request(FIRST, std::integral_constant<int, MB - FIRST>{});
+    merge_add<FIRST>(acc, v, sc, std::make_integer_sequence<int, MB - FIRST>{});
+  }
   if (MB == 17 && nsplits > MB) {
     request(MB, std::integral_constant<int, MB>{});
     merge_add<MB>(acc, v, sc, std::make_integer_sequence<int, MB>{});
@@ -1916,6 +1930,7 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
                      const void* v_new, void* aux_out, hipStream_t s) {
   const evict_model_desc& m = c->m;
   int ctx_splits, nsplits, keys;
+  const int32_t* planned = nullptr;
   if (m.dtype == EVICT_BF16) {
     // one 16-row query tile per wavefront; enough context splits to cover the chip, each a whole
     // number of 128-key chunks (more chunks per split = fewer partial results to merge)
@@ -1926,46 +1941,52 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
     // those past a sequence's own tiles leave at once; the split count goes by the average tree)
     const int avg_nodes = (T + B - 1) / B < max_nodes ? (T + B - 1) / B : max_nodes;
     const int avg_tiles = (avg_nodes * G + 15) / 16;
-    const int chunks = (max_ctx_host + kMfmaKeys - 1) / kMfmaKeys;
-    // 8-wavefront workgroups with two LDS buffers (the next chunk is fetched during the matrix work) once
-    // there is more than one round of 4-wavefront workgroups to run. With fewer than 8 row tiles some of the
-    // 8 wavefronts only stage; measured to pay down to 4 tiles (many KV heads, few rows per head).
-    const long long chunk_wgs4 = (long long)chunks * m.Hkv * B * ((avg_tiles + 3) / 4);
-    int nw = (avg_tiles >= 4 && chunk_wgs4 > c->attn_target_wgs) ? 8 : 4;
-    if (c->attn_waves == 4 || c->attn_waves == 8) nw = c->attn_waves;
-    const int rb = c->attn_row_blocks > 0 ? c->attn_row_blocks : (ntiles + nw - 1) / nw;
-    const int rb_avg = (avg_tiles + nw - 1) / nw;
-    // context splits: two workgroups of 4 wavefronts per CU overlap each other; one of 8 fills it. The
-    // draft-node split of every unit comes on top, so one split of the budget is kept for it: a grid a
-    // few workgroups above what the chip holds at once would run a nearly empty second round. (Not in a
-    // batch: splits past a shorter sequence's context leave at once, so the grid is not what runs.)
-    int want = (nw == 8 ? c->attn_target_wgs / 2 : c->attn_target_wgs) / (m.Hkv * B * rb_avg) - (B == 1 ? 1 : 0);
-    want = want < 1 ? 1 : want;
-    // (the merge walks the splits of a row in batches of 17, one round trip each: beyond about 32 splits a
-    // second chunk per workgroup costs less than the extra batches; measured at 8 nodes, ctx 8192)
-    want = want > 32 ? 32 : want;
-    int cps = (chunks + want - 1) / want;  // chunks per split
-    cps = cps < 1 ? 1 : cps;
-    keys = cps * kMfmaKeys;
-    ctx_splits = (max_ctx_host + keys - 1) / keys;
-    nsplits = ctx_splits + 1;
-    EVICT_REQUIRE(rb * nw >= ntiles, EVICT_E_INVALID, "attn_row_blocks=%d is too small for %d query tiles", rb, ntiles);
-    EVICT_REQUIRE(nsplits <= c->max_splits, EVICT_E_INVALID, "attention: %d splits exceed the scratch of %d", nsplits, c->max_splits);
-    const int units = nsplits * m.Hkv * B;
-    const dim3 grid(((units + 7) / 8) * 8 * rb);
-    const size_t lds = attn_mfma_lds_bytes(m.D) * (nw == 8 ? 2 : 1);
+    if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == kAttnTargetWgs && attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host)) {
+      if (B > 1) planned = c->row_splits;
+      const int rc = launch_attn_rows(c, kc, vc, seq_stride, head_stride, ctx_len, max_ctx_host, tree_off, B, T, k_new, v_new, &nsplits, s);
+      if (rc) return rc;
+    } else {
+      const int chunks = (max_ctx_host + kMfmaKeys - 1) / kMfmaKeys;
+      // 8-wavefront workgroups with two LDS buffers (the next chunk is fetched during the matrix work) once
+      // there is more than one round of 4-wavefront workgroups to run. With fewer than 8 row tiles some of the
+      // 8 wavefronts only stage; measured to pay down to 4 tiles (many KV heads, few rows per head).
+      const long long chunk_wgs4 = (long long)chunks * m.Hkv * B * ((avg_tiles + 3) / 4);
+      int nw = (avg_tiles >= 4 && chunk_wgs4 > c->attn_target_wgs) ? 8 : 4;
+      if (c->attn_waves == 4 || c->attn_waves == 8) nw = c->attn_waves;
+      const int rb = c->attn_row_blocks > 0 ? c->attn_row_blocks : (ntiles + nw - 1) / nw;
+      const int rb_avg = (avg_tiles + nw - 1) / nw;
+      // context splits: two workgroups of 4 wavefronts per CU overlap each other; one of 8 fills it. The
+      // draft-node split of every unit comes on top, so one split of the budget is kept for it: a grid a
+      // few workgroups above what the chip holds at once would run a nearly empty second round. (Not in a
+      // batch: splits past a shorter sequence's context leave at once, so the grid is not what runs.)
+      int want = (nw == 8 ? c->attn_target_wgs / 2 : c->attn_target_wgs) / (m.Hkv * B * rb_avg) - (B == 1 ? 1 : 0);
+      want = want < 1 ? 1 : want;
+      // (the merge walks the splits of a row in batches of 17, one round trip each: beyond about 32 splits a
+      // second chunk per workgroup costs less than the extra batches; measured at 8 nodes, ctx 8192)
+      want = want > 32 ? 32 : want;
+      int cps = (chunks + want - 1) / want;  // chunks per split
+      cps = cps < 1 ? 1 : cps;
+      keys = cps * kMfmaKeys;
+      ctx_splits = (max_ctx_host + keys - 1) / keys;
+      nsplits = ctx_splits + 1;
+      EVICT_REQUIRE(rb * nw >= ntiles, EVICT_E_INVALID, "attn_row_blocks=%d is too small for %d query tiles", rb, ntiles);
+      EVICT_REQUIRE(nsplits <= c->max_splits, EVICT_E_INVALID, "attention: %d splits exceed the scratch of %d", nsplits, c->max_splits);
+      const int units = nsplits * m.Hkv * B;
+      const dim3 grid(((units + 7) / 8) * 8 * rb);
+      const size_t lds = attn_mfma_lds_bytes(m.D) * (nw == 8 ? 2 : 1);
 #define EVICT_ATTN_ARGS (const uint16_t*)c->q, (const uint16_t*)kc, (const uint16_t*)vc, seq_stride, head_stride, ctx_len, \
                         max_ctx_host, tree_off, (const uint16_t*)k_new, (const uint16_t*)v_new, c->anc, m.Hq, m.Hkv,       \
                         ctx_splits, keys, rb, T, c->part_o, c->part_ml, (B == 1 && !c->t_dev) ? T : 0, B, c->paging, c->status,   \
                         (B == 1 && c->t_dev) ? 1 : 0
 #define EVICT_ATTN_LAUNCH(PAGED_)                                                                                              \
-    if (m.D == 128 && nw == 4) hipLaunchKernelGGL((attn_partial_mfma_kernel<128, 4, PAGED_>), grid, dim3(256), lds, s, EVICT_ATTN_ARGS); \
-    else if (m.D == 128) hipLaunchKernelGGL((attn_partial_mfma_kernel<128, 8, PAGED_>), grid, dim3(512), lds, s, EVICT_ATTN_ARGS);       \
-    else if (nw == 4) hipLaunchKernelGGL((attn_partial_mfma_kernel<64, 4, PAGED_>), grid, dim3(256), lds, s, EVICT_ATTN_ARGS);           \
-    else hipLaunchKernelGGL((attn_partial_mfma_kernel<64, 8, PAGED_>), grid, dim3(512), lds, s, EVICT_ATTN_ARGS)
-    if (c->paging.table) { EVICT_ATTN_LAUNCH(true); } else { EVICT_ATTN_LAUNCH(false); }
+      if (m.D == 128 && nw == 4) hipLaunchKernelGGL((attn_partial_mfma_kernel<128, 4, PAGED_>), grid, dim3(256), lds, s, EVICT_ATTN_ARGS); \
+      else if (m.D == 128) hipLaunchKernelGGL((attn_partial_mfma_kernel<128, 8, PAGED_>), grid, dim3(512), lds, s, EVICT_ATTN_ARGS);       \
+      else if (nw == 4) hipLaunchKernelGGL((attn_partial_mfma_kernel<64, 4, PAGED_>), grid, dim3(256), lds, s, EVICT_ATTN_ARGS);           \
+      else hipLaunchKernelGGL((attn_partial_mfma_kernel<64, 8, PAGED_>), grid, dim3(512), lds, s, EVICT_ATTN_ARGS)
+      if (c->paging.table) { EVICT_ATTN_LAUNCH(true); } else { EVICT_ATTN_LAUNCH(false); }
 #undef EVICT_ATTN_LAUNCH
 #undef EVICT_ATTN_ARGS
+    }
   } else {
     keys = kAttnKeys;
     ctx_splits = (max_ctx_host + keys - 1) / keys;
@@ -1988,7 +2009,7 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
   const dim3 mgrid(((T + group - 1) / group * group * m.Hq + rows_per_wg - 1) / rows_per_wg);
 #define EVICT_MERGE(ST_, LPR_, ...)                                                                                             \
   hipLaunchKernelGGL((attn_merge_kernel<ST_, LPR_, __VA_ARGS__>), mgrid, dim3(mthreads), 0, s, c->part_o, c->part_ml, nsplits, mrows,   \
-                     c->attn_o, aux_out, m.Hq, T, operand_shift(T), c->t_dev)
+                     c->attn_o, aux_out, m.Hq, T, operand_shift(T), c->t_dev, planned)
 #define EVICT_MERGE_D(ST_, LPR_)                        \
   do {                                                  \
     if (nsplits <= 5) EVICT_MERGE(ST_, LPR_, 5);        \
@@ -1996,7 +2017,9 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
     else if (nsplits <= kMergePairs || std::is_same<ST_, BF16>::value) EVICT_MERGE(ST_, LPR_, 17); \
     else EVICT_MERGE(ST_, LPR_, 17, !std::is_same<ST_, BF16>::value); \
   } while (0)
-  if (m.dtype == EVICT_BF16) { if (m.D == 128) EVICT_MERGE_D(BF16, 32); else EVICT_MERGE_D(BF16, 16); }
+  if (planned) {  // (bf16, head dimension 128)
+    EVICT_MERGE(BF16, 32, 17, false, true);
+  } else if (m.dtype == EVICT_BF16) { if (m.D == 128) EVICT_MERGE_D(BF16, 32); else EVICT_MERGE_D(BF16, 16); }
   else { if (m.D == 128) EVICT_MERGE_D(F32, 32); else EVICT_MERGE_D(F32, 16); }
 #undef EVICT_MERGE_D
 #undef EVICT_MERGE

@@ -1,0 +1,96 @@
+"""bf16 tree attention with 32 query rows per wavefront: one tree around the edges of a wavefront's rows, a chunk of 64 keys and a
+split, batches whose splits the kernel plans itself (uneven trees and contexts, empty contexts), every page size class bit for bit
+against the contiguous caches, and a count of nodes in device memory below the host's bound."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+ev = pytest.importorskip("paper_2605_00342_amd")
+from paper_2605_00342_amd import harness  # noqa: E402
+from test_gpu_layer import check_against_oracle, run_case  # noqa: E402
+import test_gpu_paged as paged  # noqa: E402
+
+
+def cfg_of(Hq, Hkv):
+    return synth.ModelCfg("wide", "bf16", d=256, Hq=Hq, Hkv=Hkv, D=128, E=16, k=2, F=64, theta=1e4)
+
+
+def batch(cfg, sizes, Ls, seed):
+    """Trees of different sizes as one case."""
+    parts = [synth.make_case(cfg.name, n=n, L=L, seed=seed + i, sigma=0.5, tree="random", cfg=cfg) for i, (n, L) in enumerate(zip(sizes, Ls))]
+    out = dict(parts[0])
+    out["tree_off"] = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    for key in ("parent", "q", "x"):
+        out[key] = np.concatenate([p[key] for p in parts])
+    for key in ("parents", "K", "V"):
+        out[key] = [p[key][0] for p in parts]
+    out["ctx_len"] = np.asarray(Ls, dtype=np.int32)
+    return out
+
+
+@pytest.mark.parametrize("n,L,Hq,Hkv", [
+    (1, 0, 8, 1), (1, 1, 8, 1), (8, 63, 16, 2), (8, 64, 8, 1), (7, 65, 8, 1), (64, 129, 4, 4), (33, 700, 2, 2), (63, 4200, 2, 2),
+    (128, 6400, 8, 1), (100, 3333, 16, 2),
+])
+def test_one_tree(n, L, Hq, Hkv):
+    cfg = cfg_of(Hq, Hkv)
+    check_against_oracle(*(lambda c: (c, run_case(c)))(synth.make_case(cfg.name, n=n, L=L, seed=900 + n, sigma=0.5, tree="random", cfg=cfg)))
+
+
+@pytest.mark.parametrize("sizes,Ls,Hq,Hkv", [
+    ([1] * 16, [0] * 16, 8, 1),
+    ([17, 1, 33, 16, 5, 64, 2, 3, 9, 40, 1, 1, 15, 16, 17, 8], [65, 0, 900, 64, 1, 128, 0, 2000, 63, 7, 500, 31, 129, 640, 77, 256], 8, 1),
+    ([3, 65, 20] * 6, [100, 33, 1500] * 6, 8, 2),
+    ([128, 40], [4000, 10], 16, 2),
+    ([5] * 33, [17 + 40 * (i % 7) for i in range(33)], 4, 4),
+])
+def test_batches(sizes, Ls, Hq, Hkv):
+    case = batch(cfg_of(Hq, Hkv), sizes, Ls, 950)
+    check_against_oracle(case, run_case(case))
+
+
+@pytest.mark.parametrize("n,Ls,P", [(8, [300], 1), (8, [301], 2), (8, [1037], 4), (5, [130 + 61 * (i % 5) for i in range(16)], 8), (6, [40 * i for i in range(17)], 64)])
+def test_pages(n, Ls, P):
+    case, cfg, Ws, Ks, Vs, pools, table, n_pages = paged.build("mini_bf16", n, Ls, P, 97, 0)
+    dev = paged.Dev(case, cfg, Ws, Ks, Vs, pools, table, n_pages, P, max(Ls))
+    try:
+        ctx_len = harness.dev_i32(case["ctx_len"])
+        a = dev.run_contiguous(case["tree_off"], case["parent"], ctx_len, max(Ls), case["x"])
+        b = dev.run_paged(case["tree_off"], case["parent"], ctx_len, max(Ls), case["x"])
+        torch.cuda.synchronize()
+        assert ev.evict_device_status(dev.ctx) == 0
+        assert torch.equal(a[0], b[0]) and all(torch.equal(x, y) for x, y in zip(a[1] + a[2], b[1] + b[2]))
+    finally:
+        dev.close()
+
+
+@pytest.mark.parametrize("n,bound,L,cap", [(1, 64, 2500, 2500), (14, 41, 3000, 3000), (40, 41, 100, 6000)])
+def test_count_in_device_memory(n, bound, L, cap):
+    """The rows of the actual nodes, a bound above them and a context below the host's."""
+    cfg = cfg_of(16, 2)
+    case = synth.make_case(cfg.name, n=n, L=L, seed=970, sigma=0.5, tree="random", cfg=cfg)
+    layer = harness.DeviceLayer(cfg, case["W"], bound, 1, cap)
+    dc = harness.DeviceCase(case)
+    x = torch.zeros(bound, cfg.d, dtype=torch.bfloat16, device="cuda:0")
+    x[:n] = dc.x
+    parent = harness.dev_i32(np.concatenate([case["parent"], np.zeros(bound - n, np.int32)]))
+    kc = torch.zeros(1, cfg.Hkv, cap, cfg.D, dtype=torch.bfloat16, device="cuda:0")
+    vc = torch.full_like(kc, float("nan"))  # positions past the context are never weighted, and never read either
+    kc[:, :, :L], vc[:, :, :L] = dc.k_cache[:, :, :L], dc.v_cache[:, :, :L]
+    out = torch.zeros_like(x)
+    kn = torch.zeros(bound, cfg.Hkv, cfg.D, dtype=torch.bfloat16, device="cuda:0")
+    vn = torch.zeros_like(kn)
+    try:
+        ev.evict_dynamic_tokens(layer.ctx, dc.tree_off.data_ptr() + 4)
+        ev.evict_verify_layer(layer.ctx, layer.weights, dc.tree_off, parent, 1, bound, kc, vc, kc.stride(0), kc.stride(1), dc.ctx_len, cap, x, out, kn, vn)
+        ev.evict_dynamic_tokens(layer.ctx, None)
+        torch.cuda.synchronize()
+        from oracle import evict_oracle as orc
+        ref = orc.verify_layer(cfg, case["W"], case["tree_off"], case["parent"], case["x"], case["K"], case["V"], case["ctx_len"])
+        assert paged.rel_l2(out[:n].float().cpu().numpy(), ref["out"]) < paged.TOL["bf16"]
+    finally:
+        layer.close()

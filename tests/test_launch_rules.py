@@ -24,6 +24,8 @@ int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
 int one_round(int T, int n_strips, int nkb, int bf16) { return lm_one_round(T, n_strips, nkb, bf16); }
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
+int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
+int rows_wgs(int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_wgs(B, T, Hq, Hkv, ctx); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
 """
@@ -134,3 +136,13 @@ def test_topk_rows_where_they_were_measured_faster(rules):
     for E, k, first in ((16, 2, 17), (64, 6, 17), (128, 8, 17), (128, 1, 17), (64, 16, 17), (144, 4, 28), (256, 8, 28), (256, 16, 28)):
         assert [T for T in range(1, 33) if rules.topk(T, E, k)] == list(range(first, 33))
     assert not any(rules.topk(T, 64, 17) for T in range(1, 33))  # (a row of 16 lanes has no room for 17 picks)
+
+
+def test_attention_rows(rules):
+    f = rules.rows_applies
+    assert not f(64, 16, 256, 32, 4, 6000) and not f(128, 65, 520, 32, 4, 2048)  # other head dimension, too many sequences
+    assert f(128, 1, 8, 32, 4, 0) and f(128, 1, 64, 16, 16, 1 << 20) and f(128, 16, 16, 8, 1, 0) and f(128, 64, 64, 8, 1, 100)
+    assert not f(128, 1, 9, 32, 4, 100) and not f(128, 15, 120, 32, 4, 100)
+    edge = [L for L in range(64, 8192, 64) if f(128, 1, 64, 32, 4, L)][0]  # 4 row blocks x 4 heads x (chunks + 1)
+    assert edge == 24 * 64 and not f(128, 1, 64, 32, 4, edge - 64) and f(128, 1, 64, 32, 4, edge - 63)
+    assert rules.rows_wgs(16, 900, 32, 4, 2048) == 512 and rules.rows_wgs(1, 128, 32, 4, 4096) == 256
