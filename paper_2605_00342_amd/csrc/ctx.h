@@ -4,7 +4,7 @@
 
 namespace evict { struct WorkRec; }
 
-#define EVICT_SAMP_STATS 64  // floats of scratch per node of acceptance under sampling
+#define EVICT_SAMP_STATS 80  // floats of scratch per node of acceptance under sampling
 
 // Addressing of a paged KV cache: position p of sequence b lives in page table[b][p >> page_shift]
 // at row p & (page size - 1). table == nullptr: contiguous caches.
@@ -58,7 +58,7 @@ struct evict_ctx {
   float* y;              // [T*k + n_shared*T][d]
   float* lm_val;         // [T][vocab/16] best logit per token and strip
   int32_t* lm_idx;       // [T][vocab/16]
-  float* samp_stats;     // [T][EVICT_SAMP_STATS] per node: partial maxima of the logits, partial sums of exp((logit - max) / temperature); of node b also what the walk of tree b hands to its draw
+  float* samp_stats;     // [T][EVICT_SAMP_STATS] per node: maxima of the logits of each part of the row, sums of exp((logit - that maximum) / temperature); of node b also what the walk of tree b hands to its draw
   void* stack_buf[2];    // [T][d] ping-pong hidden states of evict_verify_stack
   hipEvent_t prof_ev[2]; // evict_profile_cost
 };

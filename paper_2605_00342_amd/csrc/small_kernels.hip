@@ -476,81 +476,103 @@ __global__ __launch_bounds__(64) void accept_path_kernel(
 // ------------------------------------------------------------------------------------
 constexpr int kSampThreads = 1024;
 constexpr int kSampWaves = kSampThreads / 64;
-// Floats of scratch per node: kSampWaves partial maxima of the row, then kSampWaves partial sums of its exponentials. Behind those
-// of node b lies what the walk of tree b hands to its draw: the kSampWaves segment sums, the last node of the walk (bits of an int)
-// and its row's maximum. (By the tree's number, not at its root: an empty tree's offset is the next tree's root, or past the end.)
+// Floats of scratch per node: the maxima of kSampWaves parts of the row, then their sums of exponentials. Behind those of node b
+// lies what the walk of tree b hands to its draw: the kSampWaves segment sums, the segments' maxima that they are relative to, and
+// the last node of the walk (bits of an int). (By the tree's number, not at its root: an empty tree's offset is the next tree's root, or past the end.)
 constexpr int kSampStats = EVICT_SAMP_STATS;
-constexpr int kSampSeg = 2 * kSampWaves, kSampCur = 3 * kSampWaves, kSampMax = kSampCur + 1;
-static_assert(kSampStats > kSampMax, "maxima, sums, segment sums, last node, its maximum");
+constexpr int kSampSeg = 2 * kSampWaves, kSampSegMax = 3 * kSampWaves, kSampCur = 4 * kSampWaves;
+static_assert(kSampStats > kSampCur, "maxima, sums; segment sums, their maxima, last node");
 
-// Per node, the two numbers that turn any logit of the row into a probability -- the maximum and the sum of
-// exp((logit - max) / temperature) over the vocabulary -- as kSampWaves partial results each, one wavefront per
-// (row, part), so that a few rows still fill the chip: a row is 0.6 MB at a vocabulary of 151936, and one workgroup
-// walking it alone is bound by the latency of its loads (89 us for 128 rows; this way the two launches take 12 and 13 us,
-// 78 MB read by each, 6 TB/s).
-// The maxima come first, in a launch of their own: each sum needs the whole row's. Parts of the maximum are contiguous
-// ranges. Part w of the sum is what wavefront w of a 1024-thread workgroup striding over the row would add up: lane l
-// takes elements 64w + l + 1024j in ascending j, and the row's sum is the parts' in ascending w. The order of every
-// addition is fixed by the vocabulary size alone.
+// Per node, what turns any logit of the row into a probability: for each of kSampWaves contiguous parts of the vocabulary its maximum
+// and its sum of exp((logit - that maximum) / temperature), one wavefront per (row, part), so that a few rows still fill the
+// chip: a row is 0.6 MB at a vocabulary of 151936, and one workgroup walking it alone is bound by the latency of its loads.
+// One pass: every lane keeps the maximum of what it has seen and rescales its sum when that grows; the sums of rows of 151936 drawn
+// with deviations of 1 to 5 are off from those in 64 bits by 1.05e-7 relative in the mean, 4.4e-7 at most (with the row's maximum found
+// first, in a pass of its own, 1.25e-7 and 9.4e-7). `skip_leaves`: a node without children needs neither number, as the walk ends
+// there, and the draw takes maxima and sums of its own; that is about half of the nodes of a tree. (113 rows of 151936, us: two passes
+// over all rows 12.2 + 13.5, this way 11.3, about 38 MB; what is left is the launch, two trips for the tree and the parents, and one
+// workgroup per CU of loads.) The order of every addition is fixed by the vocabulary size alone.
 constexpr int kStatsThreads = 256;
 constexpr int kStatsWgs = kSampThreads / kStatsThreads;  // workgroups per row
 constexpr int kStatsBatch = 32;                          // loads in flight per lane
 
-__global__ __launch_bounds__(kStatsThreads) void row_max_kernel(const float* __restrict__ logits, int V, float* __restrict__ stats,
-                                                                int T, const int* __restrict__ t_dev) {
+// exp((v - m) / temperature), zero while nothing but -inf has been seen
+__device__ __forceinline__ float samp_exp(float v, float m, float inv_temp) { return __expf((v - (m == -INFINITY ? 0.0f : m)) * inv_temp); }
+
+__global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(const float* __restrict__ logits, int V, float inv_temp, float* __restrict__ stats,
+                                                                  int T, const int* __restrict__ t_dev, const int32_t* __restrict__ tree_off,
+                                                                  const int32_t* __restrict__ parent, int B, int skip_leaves) {
   const int r = (int)blockIdx.x / kStatsWgs;
   if (r >= dyn_tokens(t_dev, T)) return;  // (rows past the call's actual token count)
   const int lane = threadIdx.x & 63;
+  if (skip_leaves) {
+    // the tree of row r: the first that ends past it
+    int b = 0;
+    for (; b < B; b += 64) {
+      const unsigned long long past = __ballot(b + lane < B && tree_off[b + lane + 1] > r);
+      if (past) { b += __ffsll((long long)past) - 1; break; }
+    }
+    if (b < B) {
+      const int lo = tree_off[b], node = r - lo;
+      int end = tree_off[b + 1];
+      end = end < T ? end : T;
+      bool parent_of = node <= 0;  // (the root also takes nodes whose parent is invalid)
+      for (int c0 = r + 1; c0 < end && !parent_of; c0 += 64) parent_of = __ballot(c0 + lane < end && parent[c0 + lane] == node) != 0;
+      if (!parent_of) return;
+    }
+  }
   const int part = ((int)blockIdx.x % kStatsWgs) * (kStatsThreads / 64) + (threadIdx.x >> 6);
   const float* row = logits + (size_t)r * V;
   const int seg = (V + kSampWaves - 1) / kSampWaves;
   const int lo = part * seg, hi = lo + seg < V ? lo + seg : V;
-  float m = -INFINITY;
-  for (int i0 = lo; i0 < hi; i0 += 64 * kStatsBatch) {
-    float v[kStatsBatch];
+  float m = -INFINITY, z = 0.0f;
+  float v[2][kStatsBatch];  // one batch is on its way while the other is added up
+  auto request = [&](float(&to)[kStatsBatch], int i0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kStatsBatch; ++u) {
       const int i = i0 + u * 64 + lane;
-      v[u] = i < hi ? row[i] : -INFINITY;
+      to[u] = i < hi ? row[i] : -INFINITY;
     }
+  };
+  auto add = [&](const float(&of)[kStatsBatch]) __attribute__((always_inline)) {
+    float top = m;
 #pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u) m = fmaxf(m, v[u]);
+    for (int u = 0; u < kStatsBatch; ++u) top = fmaxf(top, of[u]);
+    z *= samp_exp(m, top, inv_temp);
+    m = top;
+#pragma unroll
+    for (int u = 0; u < kStatsBatch; ++u) z += samp_exp(of[u], m, inv_temp);
+  };
+  constexpr int kStep = 64 * kStatsBatch;
+  request(v[0], lo);
+  for (int i0 = lo; i0 < hi; i0 += 2 * kStep) {
+    if (i0 + kStep < hi) request(v[1], i0 + kStep);
+    add(v[0]);
+    if (i0 + kStep >= hi) break;
+    if (i0 + 2 * kStep < hi) request(v[0], i0 + 2 * kStep);
+    add(v[1]);
   }
-  m = wave_max(m);
-  if (lane == 0) stats[(size_t)r * kSampStats + part] = m;
+  const float top = wave_max(m);
+  z = wave_sum(z * samp_exp(m, top, inv_temp));
+  if (lane == 0) {
+    stats[(size_t)r * kSampStats + part] = top;
+    stats[(size_t)r * kSampStats + kSampWaves + part] = z;
+  }
 }
 
-// maximum of a row from its partial maxima
+// maximum of a row from those of its parts
 __device__ __forceinline__ float stats_max(const float* __restrict__ st) {
   float m = -INFINITY;
 #pragma unroll
   for (int i = 0; i < kSampWaves; ++i) m = fmaxf(m, st[i]);
   return m;
 }
-
-__global__ __launch_bounds__(kStatsThreads) void row_expsum_kernel(const float* __restrict__ logits, int V, float inv_temp,
-                                                                   float* __restrict__ stats, int T, const int* __restrict__ t_dev) {
-  const int r = (int)blockIdx.x / kStatsWgs;
-  if (r >= dyn_tokens(t_dev, T)) return;
-  const int lane = threadIdx.x & 63;
-  const int part = ((int)blockIdx.x % kStatsWgs) * (kStatsThreads / 64) + (threadIdx.x >> 6);
-  const float* row = logits + (size_t)r * V;
-  float* st = stats + (size_t)r * kSampStats;
-  const float m = stats_max(st);
+// its sum, relative to that maximum
+__device__ __forceinline__ float stats_sum(const float* __restrict__ st, float m, float inv_temp) {
   float z = 0.0f;
-  for (int i0 = part * 64; i0 < V; i0 += kSampThreads * kStatsBatch) {
-    float v[kStatsBatch];
 #pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u) {
-      const int i = i0 + u * kSampThreads + lane;
-      v[u] = i < V ? row[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kStatsBatch; ++u)
-      if (i0 + u * kSampThreads + lane < V) z += __expf((v[u] - m) * inv_temp);
-  }
-  z = wave_sum(z);
-  if (lane == 0) st[kSampWaves + part] = z;
+  for (int i = 0; i < kSampWaves; ++i) z += st[kSampWaves + i] * samp_exp(st[i], m, inv_temp);
+  return z;
 }
 
 // Short rows: both numbers by one workgroup per row in one launch, the same additions in the same order; maximum and sum go to
@@ -622,12 +644,8 @@ __device__ __forceinline__ void sampled_walk(
         const size_t prow = (size_t)(lo + pa);
         const float* st = stats + prow * kSampStats;
         const float logit = logits[prow * V + tk];
-        float z = SHORT ? st[kSampWaves] : 0.0f;
-        if (!SHORT) {
-#pragma unroll
-          for (int q = 0; q < kSampWaves; ++q) z += st[kSampWaves + q];
-        }
-        pr = __expf((logit - (SHORT ? st[0] : stats_max(st))) * inv_temp) / z;
+        const float m = SHORT ? st[0] : stats_max(st);
+        pr = __expf((logit - m) * inv_temp) / (SHORT ? st[kSampWaves] : stats_sum(st, m, inv_temp));
       }
     }
     s.par[i] = i == 0 ? -1 : pa;
@@ -906,7 +924,8 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_kernel(
 // exponentials per lane and segment at a vocabulary of 151936, so they are spread over 16 CUs per tree instead of one, and
 // over the four wavefronts of a workgroup, each a quarter of the 64-element blocks; the first wavefront then adds them up
 // from LDS in order. Every workgroup walks the tree for itself, which costs no hand-off; the first one of a tree writes the
-// path. What the draw needs goes behind the statistics of node b (kSampSeg, kSampCur, kSampMax).
+// path. A segment is summed relative to its own maximum, as nobody knows the row's where the walk ends in a leaf. What the draw
+// needs goes behind the statistics of node b (kSampSeg, kSampSegMax, kSampCur).
 constexpr int kSegThreads = 256;
 constexpr int kSegBlocks = 152;  // blocks of 64 elements per round: one round up to a vocabulary of 155648
 __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
@@ -917,7 +936,7 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
   static_assert(kSegBlocks % kWaves == 0, "whole blocks per wavefront");
   __shared__ SampTree s_tree;
   __shared__ int s_rej[kMaxSel];
-  __shared__ float s_e[kSegBlocks * 64];
+  __shared__ float s_e[kSegBlocks * 64], s_top[kWaves];
   __shared__ int s_cur, s_nrej;
   const int b = (int)blockIdx.x / kSampWaves, part = (int)blockIdx.x % kSampWaves;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -928,23 +947,29 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
                       path + (size_t)b * path_stride, path_stride, path_len + b, status);
   const int cur = __builtin_amdgcn_readfirstlane(s_cur), nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const float* row = logits + (size_t)(lo + cur) * V;
-  const float m = stats_max(stats + (size_t)(lo + cur) * kSampStats);
   const int seg = samp_segment(V);
   const int sb = part * seg, se = sb + seg < V ? sb + seg : V;
-  float acc = 0.0f;
+  float m = -INFINITY, acc = 0.0f;  // of this segment: its own maximum, and the sum relative to it
   for (int c0 = sb; c0 < se; c0 += kSegBlocks * 64) {
     const int cn = se - c0 < kSegBlocks * 64 ? se - c0 : kSegBlocks * 64;
     float v[kPer];
+    float top = m;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
       const int i = (u * kWaves + w) * 64 + lane;
-      v[u] = i < cn ? row[c0 + i] : 0.0f;
+      v[u] = i < cn ? row[c0 + i] : -INFINITY;
     }
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = (u * kWaves + w) * 64 + lane;
-      s_e[i] = i < cn ? __expf((v[u] - m) * inv_temp) : 0.0f;
-    }
+    for (int u = 0; u < kPer; ++u) top = fmaxf(top, v[u]);
+    top = wave_max(top);
+    if (lane == 0) s_top[w] = top;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kWaves; ++u) top = fmaxf(top, s_top[u]);
+    acc *= samp_exp(m, top, inv_temp);
+    m = top;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) s_e[(u * kWaves + w) * 64 + lane] = samp_exp(v[u], m, inv_temp);
     __syncthreads();
     for (int r = tid; r < nrej; r += kSegThreads) {
       const int at = s_rej[r] - c0;
@@ -963,16 +988,14 @@ __global__ __launch_bounds__(kSegThreads) void accept_sampled_walk_kernel(
     float* out = stats + (size_t)b * kSampStats;
     if (lane == 0) {
       out[kSampSeg + part] = acc;
-      if (part == 0) {
-        out[kSampCur] = __int_as_float(cur);
-        out[kSampMax] = m;
-      }
+      out[kSampSegMax + part] = m;
+      if (part == 0) out[kSampCur] = __int_as_float(cur);
     }
   }
 }
 
 // Second: one workgroup per tree draws from the segment that the sums pick. (Four trees of 32 nodes, vocabulary 151936: the
-// walk and the draw 31 us in one workgroup per tree, 18 in these two launches; 8 and 9 us, of which 3 each are the launch.)
+// walk and the draw 31 us in one workgroup per tree, 18 in these two launches; 8 and 10 us, of which 3 each are the launch.)
 __global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
     const int32_t* __restrict__ tree_off, const int32_t* __restrict__ parent, const int32_t* __restrict__ tok,
     const float* __restrict__ logits, int V, float inv_temp, const float* __restrict__ stats, const float* __restrict__ u_bonus,
@@ -993,14 +1016,14 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
     const int tk = tok[lo + i];
     if (pa == cur) s_rej[atomicAdd(&s_nrej, 1)] = tk < 0 || tk >= V ? -1 : tk;
   }
+  const float m = stats_max(walked + kSampSegMax);
   float segsum[kSampWaves];
 #pragma unroll
-  for (int i = 0; i < kSampWaves; ++i) segsum[i] = walked[kSampSeg + i];
+  for (int i = 0; i < kSampWaves; ++i) segsum[i] = walked[kSampSeg + i] * samp_exp(walked[kSampSegMax + i], m, inv_temp);
   int segment;
   float rem;
   pick_segment(segsum, u_bonus[b], &segment, &rem);
   segment = __builtin_amdgcn_readfirstlane(segment);
-  const float m = walked[kSampMax];
   __syncthreads();
   const int nrej = __builtin_amdgcn_readfirstlane(s_nrej);
   const int seg = samp_segment(V);
@@ -1013,18 +1036,19 @@ __global__ __launch_bounds__(kSampThreads) void accept_sampled_draw_kernel(
 int launch_accept_sampled(const int32_t* tree_off, const int32_t* parent, const int32_t* tok, const float* logits, int V,
                           float inv_temp, float* stats, const float* u_node, const float* u_bonus, int B, int T, int32_t* path,
                           int path_stride, int32_t* path_len, int32_t* bonus, int32_t* status, const int32_t* t_dev, hipStream_t s) {
+  const bool one_draw = V <= kOneDrawRow || B > T;  // (more trees than nodes, so some of them empty: no room to hand over)
   if (V <= kShortRow) {
     hipLaunchKernelGGL(short_row_stats_kernel, dim3(T), dim3(kSampThreads), 0, s, logits, V, inv_temp, stats, t_dev);
   } else {
-    hipLaunchKernelGGL(row_max_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, stats, T, t_dev);
-    hipLaunchKernelGGL(row_expsum_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, inv_temp, stats, T, t_dev);
+    hipLaunchKernelGGL(row_stats_kernel, dim3(T * kStatsWgs), dim3(kStatsThreads), 0, s, logits, V, inv_temp, stats, T, t_dev, tree_off,
+                       parent, B, one_draw ? 0 : 1);
   }
   int rc = launch_status("softmax statistics kernels");
   if (rc) return rc;
 #define EVICT_ONE_DRAW(ROW_)                                                                                                       \
   hipLaunchKernelGGL(accept_sampled_kernel<(ROW_) / (kSampWaves * 64)>, dim3(B), dim3(kSampThreads), 0, s, tree_off, parent, tok,   \
                      logits, V, inv_temp, stats, u_node, u_bonus, T, path, path_stride, path_len, bonus, status)
-  if (V <= kOneDrawRow || B > T) {  // (more trees than nodes, so some of them empty: no room to hand over)
+  if (one_draw) {
     if (V <= kShortRow) EVICT_ONE_DRAW(kShortRow);
     else if (V <= kMidRow) EVICT_ONE_DRAW(kMidRow);
     else EVICT_ONE_DRAW(kOneDrawRow);
