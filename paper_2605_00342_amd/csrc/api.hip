@@ -562,8 +562,9 @@ static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream
                   : lm_one_round(T, a.n_strips, a.nkb, ctx->m.dtype == EVICT_BF16) ? lm_strips(T, a.n_strips)
                                                                                    : lm_units(T, a.n_strips);
   a.nt_loads = ctx->dense_nt_loads == 2 ? (a.dense_tiles == 1 ? 1 : 0) : ctx->dense_nt_loads;  // every strip is read by one workgroup
-  const int grid = (((a.n_strips + a.dense_units - 1) / a.dense_units + 7) / 8) * 8 * a.dense_tiles;
-  return launch_gemm(ctx->m.dtype, epi, a, nt, grid, s);
+  const int wgs = (a.n_strips + a.dense_units - 1) / a.dense_units;
+  if (epi == EPI_ARGMAX) a.ldo = wgs;  // candidates per token
+  return launch_gemm(ctx->m.dtype, epi, a, nt, (wgs + 7) / 8 * 8 * a.dense_tiles, s);
 }
 
 // Final RMSNorm of the LM head. It writes the rows the caller asks for while it still reads others: where they lie over its
@@ -608,7 +609,7 @@ int evict_lm_head_argmax(evict_ctx* ctx, const void* x, const void* g_final, con
   a.ldo = a.n_strips;
   rc = launch_lm_gemm(ctx, EPI_ARGMAX, a, T, s);
   if (rc) return rc;
-  return launch_argmax_reduce(ctx->lm_val, ctx->lm_idx, a.n_strips, a.n_strips, T, next, best_logit, ctx->t_dev, s);
+  return launch_argmax_reduce(ctx->lm_val, ctx->lm_idx, (int)a.ldo, (int)a.ldo, T, next, best_logit, ctx->t_dev, s);
 }
 
 int evict_lm_head_logits(evict_ctx* ctx, const void* x, const void* g_final, const void* wlm_packed, int T, float* logits,

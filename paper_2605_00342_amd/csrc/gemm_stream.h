@@ -59,8 +59,8 @@ struct GemmArgs {
   int lds_dma;           // 1: strip-pair gate/up kernel stages its token operand with direct global-to-LDS loads
   int down_ws;           // gemm_wave_strip_kernel: strips (wavefronts) per workgroup, 8 or 16
   int pair_tiles;        // 1: gemm_wave_strip_kernel with two token tiles takes them from two consecutive 16-token records
-  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per (token, strip), [T][ldo]
-  void* out1;            // QKV: k_new; ARGMAX: row index of the best value per (strip, token)
+  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per token and workgroup (tiled kernel: and strip), [T][ldo]
+  void* out1;            // QKV: k_new; ARGMAX: row index of the best value
   void* out2;            // QKV: v_new
   long long ldo;         // elements between output rows (RESID / SWIGLU / F32 / ROWS)
   const void* resid;     // RESID: residual rows, same layout as out0
@@ -125,6 +125,10 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
       f32x4 acc[IS][NT];
       f32x4 gate[NT];
       f32x4 pre0[IS * NT], pre1[IS * NT];  // epilogue operands requested ahead (QKV / RESID)
+      float best_v[NT];  // ARGMAX
+      int best_i[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) { best_v[t] = -INFINITY; best_i[t] = 0x7fffffff; }
 #pragma unroll
       for (int q = 0; q < IS * NT; ++q) pre0[q] = pre1[q] = f32x4{0, 0, 0, 0};
 #pragma unroll
@@ -281,22 +285,11 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
                   const bool valid = col < ntok;
                   const int m0 = (lane >> 4) * 4;  // first of this lane's 4 rows in the strip
                   if (EPI == EPI_ARGMAX) {
-                    // best of this lane's 4 rows (lowest row on equal values), then across the 4
-                    // lanes that hold the other rows of the same token
-                    float bv = sum[0];
-                    int bi = strip * 16 + m0;
+                    // best of this lane's rows in all strips of this wavefront, the lowest row on equal values
 #pragma unroll
-                    for (int i = 1; i < 4; ++i)
-                      if (sum[i] > bv) { bv = sum[i]; bi = strip * 16 + m0 + i; }
-#pragma unroll
-                    for (int o = 16; o <= 32; o <<= 1) {
-                      const float ov = __shfl_xor(bv, o);
-                      const int oi = __shfl_xor(bi, o);
-                      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-                    }
-                    if (valid && lane < 16) {
-                      ((float*)a.out0)[(long long)col * a.ldo + strip] = bv;
-                      ((int*)a.out1)[(long long)col * a.ldo + strip] = bi;
+                    for (int i = 0; i < 4; ++i) {
+                      const int row = strip * 16 + m0 + i;
+                      if (sum[i] > best_v[t] || (sum[i] == best_v[t] && row < best_i[t])) { best_v[t] = sum[i]; best_i[t] = row; }
                     }
                   } else if (EPI == EPI_F32 || EPI == EPI_ROWS) {
                     if (valid) {
@@ -351,6 +344,35 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
             }
           }
         }
+      }
+      if (EPI == EPI_ARGMAX) {
+        // one candidate per token and workgroup: the wavefronts' bests, then those of the 4 lanes that hold other rows of a token.
+        // (151936 rows of 64 blocks, 32 tokens, us: with an exchange between lanes and a store at every strip 102, 6.1 TB/s, and 6.4
+        // for the best of 9496 candidates; this way 91, 6.8 TB/s, and 4.8 for the best of 256)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) s_part[parity][w][t][lane] = f32x4{best_v[t], __int_as_float(best_i[t]), 0.0f, 0.0f};
+        lds_barrier();
+        if (w < NT) {
+          float bv = -INFINITY;
+          int bi = 0x7fffffff;
+          auto take = [&](float ov, int oi) {
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+          };
+#pragma unroll
+          for (int ww = 0; ww < kGemmWaves; ++ww) {
+            const f32x4 o = s_part[parity][ww][w][lane];
+            take(o[0], __float_as_int(o[1]));
+          }
+#pragma unroll
+          for (int o = 16; o <= 32; o <<= 1) take(__shfl_xor(bv, o), __shfl_xor(bi, o));
+          const int col = tok0 + w * 16 + lane;
+          if (lane < 16 && col < ntok) {
+            const long long at = (long long)col * a.ldo + unit_in_grp / a.dense_units;
+            ((float*)a.out0)[at] = bv;
+            ((int*)a.out1)[at] = bi;
+          }
+        }
+        parity ^= 1;
       }
     }
   };
