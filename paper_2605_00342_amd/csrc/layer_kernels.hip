@@ -891,7 +891,12 @@ constexpr int kFusedTopkTokens = 32;  // up to here TopK and the union share one
 // M: contraction slices a wavefront takes of its strip. Strips x slices x M fill the wavefronts; every slice keeps a sum of
 // its own and the sums are added up in the same order whatever M is, so the scores do not depend on how many strips a
 // workgroup takes (one chain over two or four slices: error against 64-bit sums 1.15e-7 -> 1.38e-7 and 1.89e-7 at 4096 columns).
-template <typename ST, int M>
+// PER > 0: rows of 16 * PER blocks, 16 contraction slices of PER. Everything is then loaded without a condition, the row first, then the
+// first blocks of the wavefront's part of the weights, which are on their way during the norm (with conditions on the loads the
+// compiler waits for all of them before the first use of one), and the code is half as long, which counts where every CU fetches
+// it anew. (us, 128 experts of 2048 columns: 1 token 5.4 -> 4.4, 32 tokens 6.3 -> 4.9, 128 tokens 6.7 -> 5.2, 917
+// tokens, two strips per workgroup, 9.5 -> 7.4; of 4096 columns, 32 tokens 8.8 -> 7.4. All 8 blocks of 4096 columns ahead: 10.6, spilled.)
+template <typename ST, int M, int PER = 0>
 __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
     const void* __restrict__ h, const void* __restrict__ gain, const u32x4* __restrict__ wg_packed, int T_max, int d, int E,
     int strips_per_wg, int ksplit, float eps, void* __restrict__ h_norm, float* __restrict__ logits,
@@ -899,9 +904,10 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
   const int T = dyn_tokens(t_dev, T_max);
   constexpr int EB = ST::kBytes;
   constexpr int CE = 16 / EB;   // elements per 16-byte chunk
-  constexpr int MAXC = 8;       // 16-byte chunks a lane keeps of its token row (d <= 64*CE*MAXC)
+  constexpr int MAXC = PER > 0 ? PER : 8;  // 16-byte chunks a lane keeps of its token row (d <= 64*CE*MAXC)
+  constexpr int AHEAD = M * PER < 4 ? M * PER : 4;  // blocks of weights requested before the norm; the others once its registers are free
   extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-  const int nkb = d * EB / 64;
+  const int nkb = PER > 0 ? PER * kRouterWaves : d * EB / 64;
   u32x4* s_b = reinterpret_cast<u32x4*>(s_raw);                       // [nkb][64] token operand blocks
   // [ksplit][strips_per_wg][64]; with several slices per wavefront over the token operand, once that has been read
   f32x4* s_p = reinterpret_cast<f32x4*>(s_raw + (M == 1 ? (size_t)nkb * 1024 : 0));
@@ -910,12 +916,33 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
   const int tok0 = blockIdx.x * 16;
   const int strip_base = blockIdx.y * strips_per_wg;
   const bool writer = blockIdx.y == 0;
+  const int nstrips = E >> 4;
+  int my_strips = nstrips - strip_base;
+  my_strips = my_strips > strips_per_wg ? strips_per_wg : my_strips;
+  const int per = PER > 0 ? PER : (nkb + ksplit - 1) / ksplit;  // blocks per slice
+  const int groups = PER > 0 ? kRouterWaves / M : (ksplit + M - 1) / M;
+  // one (expert strip, M contraction slices) per wavefront
+  // (host-checked: my_strips * groups <= kRouterWaves, so a wavefront has one item at most)
+  const int sl = w / groups, ks0 = (w - sl * groups) * M;
+  const bool mine = w < my_strips * groups;
+  u32x4 ahead[PER > 0 ? M * PER : 1];
+  const u32x4* wahead = wg_packed + ((size_t)(strip_base + (mine ? sl : 0)) * nkb + ks0 * per) * 64 + lane;
   // ---- one token per wavefront: the row stays in registers between the two passes
   {
     const int n = w, t = tok0 + n;
     const bool live = t < T;
     u32x4 raw[MAXC], graw[MAXC];
     float ss = 0.0f;
+    if (PER > 0) {
+      const char* hrow = (const char*)h + (size_t)(live ? t : T - 1) * d * EB;
+#pragma unroll
+      for (int i = 0; i < MAXC; ++i) raw[i] = *reinterpret_cast<const u32x4*>(hrow + (lane + 64 * i) * 16);
+#pragma unroll
+      for (int i = 0; i < MAXC; ++i) graw[i] = *reinterpret_cast<const u32x4*>((const char*)gain + (lane + 64 * i) * 16);
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) ahead[j] = wahead[j * 64];
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = (lane + 64 * i) * CE;
@@ -925,6 +952,7 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
         if (live) raw[i] = *reinterpret_cast<const u32x4*>((const char*)h + ((size_t)t * d + c) * EB);
         graw[i] = *reinterpret_cast<const u32x4*>((const char*)gain + (size_t)c * EB);
       }
+    }
     }
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
@@ -944,7 +972,7 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = (lane + 64 * i) * CE;
-      if (c < d) {
+      if (PER > 0 || c < d) {
         u32x4 packed = {0, 0, 0, 0};
         if (live) {
 #pragma unroll
@@ -972,20 +1000,24 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_kernel(
       }
     }
   }
-  __syncthreads();
-  // ---- scores: one (expert strip, M contraction slices) per wavefront
-  const int nstrips = E >> 4;
-  int my_strips = nstrips - strip_base;
-  my_strips = my_strips > strips_per_wg ? strips_per_wg : my_strips;
-  const int per = (nkb + ksplit - 1) / ksplit;  // blocks per slice
-  const int groups = (ksplit + M - 1) / M;
-  // (host-checked: my_strips * groups <= kRouterWaves, so a wavefront has one item at most)
-  const int sl = w / groups, ks0 = (w - sl * groups) * M;
-  const bool mine = w < my_strips * groups;
+  if (PER > 0) {
+#pragma unroll
+    for (int j = AHEAD; j < M * PER; ++j) ahead[j] = wahead[j * 64];
+    lds_barrier();
+  } else {
+    __syncthreads();
+  }
+  // ---- scores
   f32x4 part[M];
 #pragma unroll
   for (int q = 0; q < M; ++q) part[q] = f32x4{0, 0, 0, 0};
-  if (mine) {
+  if (PER > 0) {
+#pragma unroll
+    for (int j = 0; j < M * PER; ++j) {
+      const int kb = ks0 * PER + j;
+      part[j / PER] = mfma_block<ST>(ahead[j], s_b[kb * 64 + (lane ^ ((lane >> 4) | ((kb & 1) << 2)))], part[j / PER]);
+    }
+  } else if (mine) {
     const int kb_lo = ks0 * per;
     int kb_hi = kb_lo + M * per;
     kb_hi = kb_hi > nkb ? nkb : kb_hi;
@@ -1917,10 +1949,10 @@ int kernels_setup(const evict_model_desc& m) {
   const size_t rl = router_lds_bytes(m);
   EVICT_REQUIRE(rl <= 152 * 1024, EVICT_E_UNSUPPORTED, "router needs %zu bytes of LDS (limit 152 KiB): d too large", rl);
   EVICT_REQUIRE(m.d <= 64 * 8 * (m.dtype == EVICT_BF16 ? 8 : 4), EVICT_E_UNSUPPORTED, "router keeps a token row in registers: d=%d too large", m.d);
-#define EVICT_ROUTER_ATTR(ST_, M_) \
-  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)router_logits_kernel<ST_, M_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rl))
-  if (m.dtype == EVICT_BF16) { EVICT_ROUTER_ATTR(BF16, 1); EVICT_ROUTER_ATTR(BF16, 2); EVICT_ROUTER_ATTR(BF16, 4); }
-  else { EVICT_ROUTER_ATTR(F32, 1); EVICT_ROUTER_ATTR(F32, 2); EVICT_ROUTER_ATTR(F32, 4); }
+#define EVICT_ROUTER_ATTR(ST_, ...) \
+  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)router_logits_kernel<ST_, __VA_ARGS__>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rl))
+  if (m.dtype == EVICT_BF16) { EVICT_ROUTER_ATTR(BF16, 1); EVICT_ROUTER_ATTR(BF16, 1, 4); EVICT_ROUTER_ATTR(BF16, 2, 4); EVICT_ROUTER_ATTR(BF16, 4, 4); EVICT_ROUTER_ATTR(BF16, 1, 8); EVICT_ROUTER_ATTR(BF16, 2, 8); EVICT_ROUTER_ATTR(BF16, 2); EVICT_ROUTER_ATTR(BF16, 4); }
+  else { EVICT_ROUTER_ATTR(F32, 1); EVICT_ROUTER_ATTR(F32, 1, 4); EVICT_ROUTER_ATTR(F32, 2, 4); EVICT_ROUTER_ATTR(F32, 4, 4); EVICT_ROUTER_ATTR(F32, 1, 8); EVICT_ROUTER_ATTR(F32, 2, 8); EVICT_ROUTER_ATTR(F32, 2); EVICT_ROUTER_ATTR(F32, 4); }
 #undef EVICT_ROUTER_ATTR
   return EVICT_OK;
 }
@@ -2046,12 +2078,21 @@ int launch_router(const evict_ctx* c, const void* gain, const void* wg, int T, c
     mult *= 2;
   }
   const dim3 grid(tiles, (nstrips + spw - 1) / spw);
-#define EVICT_ROUTER(ST_, M_)                                                                                                \
-  hipLaunchKernelGGL((router_logits_kernel<ST_, M_>), grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T,    \
+  const int nkb = m.d * (m.dtype == EVICT_BF16 ? 2 : 4) / 64;
+#define EVICT_ROUTER(ST_, ...)                                                                                               \
+  hipLaunchKernelGGL((router_logits_kernel<ST_, __VA_ARGS__>), grid, dim3(kRouterThreads), lds, s, c->h, gain, (const u32x4*)wg, T,    \
                      m.d, m.E, spw, ksplit, m.rms_eps, c->h_norm, c->logits, a_hn, a_lg, c->t_dev)
 #define EVICT_ROUTER_M(ST_)                                                                                                  \
   do {                                                                                                                       \
-    if (mult == 1) EVICT_ROUTER(ST_, 1);                                                                                     \
+    if (spw == mult && ksplit == kRouterWaves && nkb == 4 * kRouterWaves) {                                                  \
+      if (mult == 1) EVICT_ROUTER(ST_, 1, 4);                                                                                \
+      else if (mult == 2) EVICT_ROUTER(ST_, 2, 4);                                                                           \
+      else EVICT_ROUTER(ST_, 4, 4);                                                                                          \
+    } else if (spw == mult && ksplit == kRouterWaves && nkb == 8 * kRouterWaves && mult <= 2) {                              \
+      if (mult == 1) EVICT_ROUTER(ST_, 1, 8);                                                                                \
+      else EVICT_ROUTER(ST_, 2, 8);                                                                                          \
+    }                                                                                                                        \
+    else if (mult == 1) EVICT_ROUTER(ST_, 1);                                                                                \
     else if (mult == 2) EVICT_ROUTER(ST_, 2);                                                                                \
     else EVICT_ROUTER(ST_, 4);                                                                                               \
   } while (0)
