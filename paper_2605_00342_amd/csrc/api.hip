@@ -558,12 +558,13 @@ static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream
     return launch_gemm_tile_lm(epi, a, s);
   const int nt = ctx->lm_nt ? ctx->lm_nt : (T > 16 ? 2 : 1);
   a.dense_tiles = (T + 16 * nt - 1) / (16 * nt);
-  a.dense_units = ctx->lm_units                                                    ? ctx->lm_units
-                  : lm_one_round(T, a.n_strips, a.nkb, ctx->m.dtype == EVICT_BF16) ? lm_strips(T, a.n_strips)
-                                                                                   : lm_units(T, a.n_strips);
+  a.dense_units = ctx->lm_units ? ctx->lm_units : lm_deal(T, a.n_strips, a.nkb, ctx->m.dtype == EVICT_BF16);
   a.nt_loads = ctx->dense_nt_loads == 2 ? (a.dense_tiles == 1 ? 1 : 0) : ctx->dense_nt_loads;  // every strip is read by one workgroup
   const int wgs = (a.n_strips + a.dense_units - 1) / a.dense_units;
-  if (epi == EPI_ARGMAX) a.ldo = wgs;  // candidates per token
+  const bool exact = ctx->m.dtype == EVICT_BF16 && (a.nkb % 64 == 0 || a.nkb == 24);  // (the instances launch_gemm_nt takes for these)
+  if (epi == EPI_ARGMAX && (exact || nt == 2)) a.ldo = wgs;  // candidates per token
+  const int rows_lds = a.dense_units * nt * 1024;
+  if (epi == EPI_ROWS && ctx->m.dtype == EVICT_BF16 && a.nkb % 64 == 0 && rows_lds <= kRowsLdsMax) a.rows_lds = rows_lds;
   return launch_gemm(ctx->m.dtype, epi, a, nt, (wgs + 7) / 8 * 8 * a.dense_tiles, s);
 }
 

@@ -59,7 +59,8 @@ struct GemmArgs {
   int lds_dma;           // 1: strip-pair gate/up kernel stages its token operand with direct global-to-LDS loads
   int down_ws;           // gemm_wave_strip_kernel: strips (wavefronts) per workgroup, 8 or 16
   int pair_tiles;        // 1: gemm_wave_strip_kernel with two token tiles takes them from two consecutive 16-token records
-  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per token and workgroup (tiled kernel: and strip), [T][ldo]
+  int rows_lds;          // ROWS: bytes of LDS for the scores of all strips of a workgroup, 0: they are stored strip by strip
+  void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per token and strip, or workgroup (best_kept), [T][ldo]
   void* out1;            // QKV: k_new; ARGMAX: row index of the best value
   void* out2;            // QKV: v_new
   long long ldo;         // elements between output rows (RESID / SWIGLU / F32 / ROWS)
@@ -70,6 +71,19 @@ struct GemmArgs {
 
 constexpr int kGemmWaves = 8;
 constexpr int kGemmThreads = kGemmWaves * 64;
+
+// ARGMAX: candidates kept by the wavefronts until a workgroup's strips are done. Not with short strips of one token tile, of which a
+// workgroup takes two: its end then takes longer than two exchanges (1 token, us: 9496 strips of 32 blocks 69 against 107, 2000 of 32
+// 20 against 27; but 64 blocks 96.7 -> 95.4, 16 tokens 107 -> 97, two tiles, 32 tokens, 9496 strips of 32 blocks 75 -> 57, 48 blocks 126 -> 104).
+template <int NT, bool EXACT> constexpr bool best_kept() { return EXACT || NT == 2; }
+
+// Score rows of a workgroup's strips, kept in LDS until its weights have been streamed. (Stored strip by strip, a wavefront's next weights wait
+// behind its stores, as one counter in order of issue covers both: 151936 rows of 64 blocks, 32 tokens, us: 113 -> 99.)
+constexpr int kRowsLdsMax = 96 * 1024;
+template <typename ST, int EPI, bool EXACT, int IS> constexpr bool rows_in_lds() { return EPI == EPI_ROWS && EXACT && IS == 1 && ST::kBytes == 2; }
+// where quarter q (rows 4q .. 4q + 3) of a strip's row block for token column n lies: columns XORed so that 16 lanes which read
+// neighbouring strips' quarters of one token meet 16 different places
+__device__ __forceinline__ int rows_lds_at(int strip, int q, int n) { return q * 16 + (n ^ ((strip * 4 + q) & 15)); }
 
 // KBW: 1 KiB blocks a wavefront takes per step (EXACT: every step has exactly KBW, no masking);
 // PF: steps of weight loads kept in flight; NT: 16-token tiles held in registers; IS: strips
@@ -88,6 +102,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
   constexpr int SPU = (EPI == EPI_SWIGLU) ? 2 : 1;  // strips per unit of work
   static_assert(EPI != EPI_SWIGLU || IS == 1, "gate/up strips are exchanged one at a time");
   __shared__ f32x4 s_part[2][kGemmWaves][IS * NT][64];
+  extern __shared__ __attribute__((aligned(16))) f32x4 s_rows[];  // ROWS: a.rows_lds
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, known uniform
@@ -284,13 +299,33 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
                   const int col = tok0 + t * 16 + (lane & 15);
                   const bool valid = col < ntok;
                   const int m0 = (lane >> 4) * 4;  // first of this lane's 4 rows in the strip
-                  if (EPI == EPI_ARGMAX) {
+                  if (EPI == EPI_ARGMAX && best_kept<NT, EXACT>()) {
                     // best of this lane's rows in all strips of this wavefront, the lowest row on equal values
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                       const int row = strip * 16 + m0 + i;
                       if (sum[i] > best_v[t] || (sum[i] == best_v[t] && row < best_i[t])) { best_v[t] = sum[i]; best_i[t] = row; }
                     }
+                  } else if (EPI == EPI_ARGMAX) {
+                    // best of this lane's 4 rows (lowest row on equal values), then across the 4
+                    // lanes that hold the other rows of the same token
+                    float bv = sum[0];
+                    int bi = strip * 16 + m0;
+#pragma unroll
+                    for (int i = 1; i < 4; ++i)
+                      if (sum[i] > bv) { bv = sum[i]; bi = strip * 16 + m0 + i; }
+#pragma unroll
+                    for (int o = 16; o <= 32; o <<= 1) {
+                      const float ov = __shfl_xor(bv, o);
+                      const int oi = __shfl_xor(bi, o);
+                      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                    }
+                    if (valid && lane < 16) {
+                      ((float*)a.out0)[(long long)col * a.ldo + strip] = bv;
+                      ((int*)a.out1)[(long long)col * a.ldo + strip] = bi;
+                    }
+                  } else if (rows_in_lds<ST, EPI, EXACT, IS>() && a.rows_lds) {
+                    s_rows[((strip - strip0) * NT + t) * 64 + rows_lds_at(strip - strip0, lane >> 4, lane & 15)] = sum;
                   } else if (EPI == EPI_F32 || EPI == EPI_ROWS) {
                     if (valid) {
                       const long long orow = a.grouped ? (p0 + col) : col;
@@ -345,7 +380,16 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT
           }
         }
       }
-      if (EPI == EPI_ARGMAX) {
+      if (rows_in_lds<ST, EPI, EXACT, IS>() && a.rows_lds) {
+        lds_barrier();
+        const int live = tok_end - tok0 < 16 * NT ? tok_end - tok0 : 16 * NT, per_tok = nitems * 4;
+        for (int i = tid; i < live * per_tok; i += kGemmThreads) {
+          const int n = i / per_tok, r = i - n * per_tok, strip = r >> 2, q = r & 3;
+          const f32x4 v = s_rows[(strip * NT + (n >> 4)) * 64 + rows_lds_at(strip, q, n & 15)];
+          *reinterpret_cast<f32x4*>((float*)a.out0 + (long long)(tok0 + n) * a.ldo + strip0 * 16 + r * 4) = v;
+        }
+      }
+      if (EPI == EPI_ARGMAX && best_kept<NT, EXACT>()) {
         // one candidate per token and workgroup: the wavefronts' bests, then those of the 4 lanes that hold other rows of a token.
         // (151936 rows of 64 blocks, 32 tokens, us: with an exchange between lanes and a store at every strip 102, 6.1 TB/s, and 6.4
         // for the best of 9496 candidates; this way 91, 6.8 TB/s, and 4.8 for the best of 256)

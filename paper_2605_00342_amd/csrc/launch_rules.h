@@ -84,6 +84,16 @@ constexpr bool lm_one_round(int T, int n_strips, int nkb, bool bf16) {
   return bf16 && nkb <= 64 && (n_strips + 255) / 256 * nkb <= (T > 24 ? 2432 : 2048) && (T <= 32 || nkb <= 48);
 }
 
+// Strips of 64 blocks in bf16, whose scores or candidates a workgroup keeps until its strips are done (gemm_stream_kernel), are dealt out in
+// one round from 13 tokens on already: 9496 strips, score rows / arg max, us, 8 strips each -> one round, 16 tokens 101 / 98 -> 95 / 97, 17 tokens
+// 104 / 99 -> 96 / 97, 24 tokens 109 / 99 -> 97 / 97; 6400 strips, 16 tokens 74 / 75 -> 67 / 70. With one token tile two workgroups share a CU, but the
+// round of 256 is the better (19 strips each 100 / 96; 12 tokens, two strips each, 97 / 98, one round 95 / 97).
+constexpr int lm_deal(int T, int n_strips, int nkb, bool bf16) {
+  const int round = (n_strips + 255) / 256;
+  if (bf16 && nkb == 64 && T > 12 && T <= 32 && n_strips > 4096 && round * nkb <= 2432) return round;
+  return lm_one_round(T, n_strips, nkb, bf16) ? lm_strips(T, n_strips) : lm_units(T, n_strips);
+}
+
 // TopK beside the union (up to 32 tokens): four tokens per wavefront, in rows of 16 lanes with room for a pick each, once some of
 // the 16 wavefronts would have two tokens. (TopK and union, us, one -> four: 32 tokens 9.1 -> 7.3, one token 5.3 -> 6.6. Whole layers: 8 picks
 // of 128 experts, 9 tokens 41.5 -> 42.1, 17 43.3 -> 43.3, 24 44.2 -> 43.8, 32 45.5 -> 44.1; 16 picks, 9 tokens 43.9 -> 44.8, 17 46.6 -> 46.9, 24

@@ -1544,9 +1544,9 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
 #define EVICT_GEMM_LAUNCH_NT(KBW_, PF_, EXACT_, IS_, NS_)                                                                  \
   do {                                                                                                                    \
     if (a.nt_loads)                                                                                                       \
-      hipLaunchKernelGGL((gemm_stream_kernel<ST, NT, KBW_, PF_, EPI, EXACT_, IS_, NS_, true>), dim3(grid), dim3(kGemmThreads), 0, s, a);  \
+      hipLaunchKernelGGL((gemm_stream_kernel<ST, NT, KBW_, PF_, EPI, EXACT_, IS_, NS_, true>), dim3(grid), dim3(kGemmThreads), a.rows_lds, s, a);  \
     else                                                                                                                  \
-      hipLaunchKernelGGL((gemm_stream_kernel<ST, NT, KBW_, PF_, EPI, EXACT_, IS_, NS_, false>), dim3(grid), dim3(kGemmThreads), 0, s, a); \
+      hipLaunchKernelGGL((gemm_stream_kernel<ST, NT, KBW_, PF_, EPI, EXACT_, IS_, NS_, false>), dim3(grid), dim3(kGemmThreads), a.rows_lds, s, a); \
   } while (0)
   const int nkb = a.nkb;
   const int need = ((nkb > 64 ? 64 : nkb) + kGemmWaves - 1) / kGemmWaves;
@@ -1941,6 +1941,11 @@ int kernels_setup(const evict_model_desc& m) {
   EVICT_TILE_DENSE(EVICT_TILE_ATTR)
   EVICT_TILE_LM(EVICT_TILE_ATTR)
 #undef EVICT_TILE_ATTR
+#define EVICT_ROWS_ATTR(NT_, NTL_)                                                                                  \
+  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_stream_kernel<BF16, NT_, 8, 1, EPI_ROWS, true, 1, 0, NTL_>,  \
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLdsMax))
+  EVICT_ROWS_ATTR(1, true); EVICT_ROWS_ATTR(1, false); EVICT_ROWS_ATTR(2, true); EVICT_ROWS_ATTR(2, false);
+#undef EVICT_ROWS_ATTR
   EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_wave_gateup_kernel<BF16, 16, 16, 6, 64, 2>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
   EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)attn_partial_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_partial_lds_bytes(128)));

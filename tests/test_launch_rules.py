@@ -22,6 +22,7 @@ int lm(int T, int n_strips, int nkb) { return lm_tiled(T, n_strips, nkb); }
 int units(int T, int n_strips) { return lm_units(T, n_strips); }
 int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
 int one_round(int T, int n_strips, int nkb, int bf16) { return lm_one_round(T, n_strips, nkb, bf16); }
+int deal(int T, int n_strips, int nkb, int bf16) { return lm_deal(T, n_strips, nkb, bf16); }
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
@@ -146,3 +147,11 @@ def test_attention_rows(rules):
     edge = [L for L in range(64, 8192, 64) if f(128, 1, 64, 32, 4, L)][0]  # 4 row blocks x 4 heads x (chunks + 1)
     assert edge == 24 * 64 and not f(128, 1, 64, 32, 4, edge - 64) and f(128, 1, 64, 32, 4, edge - 63)
     assert rules.rows_wgs(16, 900, 32, 4, 2048) == 512 and rules.rows_wgs(1, 128, 32, 4, 4096) == 256
+
+
+def test_lm_head_deal(rules):
+    assert [rules.deal(T, 9496, 64, 1) for T in (1, 12, 13, 16, 17, 24, 32)] == [2, 2, 38, 38, 38, 38, 38]
+    assert rules.deal(16, 4096, 64, 1) == 8 and rules.deal(16, 4097, 64, 1) == 17 and rules.deal(16, 9729, 64, 1) == 8  # 39 strips: too long a round
+    for T, n, nkb, bf16 in ((16, 9496, 32, 1), (24, 9496, 128, 1), (24, 9496, 64, 0), (8, 9496, 64, 1), (48, 9496, 48, 1)):
+        old = rules.strips(T, n) if rules.one_round(T, n, nkb, bf16) else rules.units(T, n)
+        assert rules.deal(T, n, nkb, bf16) == old
