@@ -97,8 +97,11 @@ __device__ __forceinline__ int rows_lds_at(int strip, int q, int n) { return q *
 // the same address is folded by the compiler into one ordinary load. (Measured too: ordinary loads for all but
 // the last token tile of an expert, so that later tiles find the weights in L2, lose more in the following
 // kernels than they save in this one.)
+// Registers: two workgroups per CU where one token tile, or short strips, leave it at 128 of them. (Arg max of 24 blocks, two token tiles,
+// takes 137 if it may, and two rounds of workgroups then run one behind the other: 48 tokens, 3142 strips 29.1 us,
+// 26.6 with candidates stored strip by strip, 22.7 with 128; 6250 strips 42.5, 38.6, 31.9.)
 template <typename ST, int NT, int KBW, int PF, int EPI, bool EXACT, int IS = 1, int NS = 0, bool NTL = false>
-__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(NT == 1 && KBW <= 8 ? 4 : 2))) void gemm_stream_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((NT == 1 && KBW <= 8) || (EPI == EPI_ARGMAX && KBW <= 3) ? 4 : 2))) void gemm_stream_kernel(const GemmArgs a) {
   constexpr int SPU = (EPI == EPI_SWIGLU) ? 2 : 1;  // strips per unit of work
   static_assert(EPI != EPI_SWIGLU || IS == 1, "gate/up strips are exchanged one at a time");
   __shared__ f32x4 s_part[2][kGemmWaves][IS * NT][64];

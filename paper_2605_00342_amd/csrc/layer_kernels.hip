@@ -1576,8 +1576,8 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
     // 3 blocks per wavefront per strip: take 4 strips per exchange step when the chunking allows
     if (EPI == EPI_F32 && NT == 1 && a.grouped && a.chunk_units % 4 == 0)
       EVICT_GEMM_LAUNCH_NT(3, 1, true, ((EPI == EPI_F32 && NT == 1) ? 4 : 1), 0);
-    else
-      EVICT_GEMM_LAUNCH_NT(3, 4, true, 1, 0);
+    else  // (a stage less where the wavefront keeps its best of two token tiles: two workgroups per CU)
+      EVICT_GEMM_LAUNCH_NT(3, (EPI == EPI_ARGMAX && NT == 2 ? 3 : 4), true, 1, 0);
     return launch_status("gemm_stream_kernel");
   }
   }
