@@ -56,7 +56,7 @@ struct evict_ctx {
   int32_t* tok_of_pos;   // [T*k] token of each grouped position
   void* act;             // [T*k + n_shared*T][F] storage dtype (routed pairs, then shared experts x tokens)
   float* y;              // [T*k + n_shared*T][d]
-  float* lm_val;         // [T][vocab/16] best logit per token and strip
+  float* lm_val;         // [T][vocab/16] best logit per token and strip, or per token and workgroup where a workgroup keeps it
   int32_t* lm_idx;       // [T][vocab/16]
   float* samp_stats;     // [T][EVICT_SAMP_STATS] per node: maxima of the logits of each part of the row, sums of exp((logit - that maximum) / temperature); of node b also what the walk of tree b hands to its draw
   void* stack_buf[2];    // [T][d] ping-pong hidden states of evict_verify_stack
