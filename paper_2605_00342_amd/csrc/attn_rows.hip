@@ -19,13 +19,13 @@ namespace evict {
 //    workgroups per CU, whose matrix, vector and load phases overlap;
 //  - the draft nodes are the last chunks of a sequence's last split instead of a split of their own: fewer partial rows;
 //  - a batch is cut into equal shares by the kernel itself, which alone knows the sequences' lengths.
-// (us, attention alone, 16 rows -> 32: 16 trees of 48 to 64 nodes, 32 heads on 4, contexts of 1024 to 2048 92 -> 39, 0.25 -> 0.59
-// PFLOP/s; 4 such trees, contexts to 5555 48 -> 31; 128 nodes, context 4096 24 -> 20; 16 trees of 16 nodes, contexts to 6000 138 -> 33.)
-// What bounds it now: a chunk of 64 keys takes a wavefront 1024 cycles of MFMA and about 1100 of the vector unit, and two
-// wavefronts per SIMD 3000 for one each, as their phases overlap in part only; and some 9 us besides: the launch, 1.5 to 2.4 for the
+// (us, attention alone, 16 rows -> 32: 16 trees of 48 to 64 nodes, 32 heads on 4, contexts of 1024 to 2048 92 -> 40, 0.25 -> 0.57
+// PFLOP/s; 4 such trees, contexts to 5555 48 -> 33; 128 nodes, context 4096 24 -> 21; 16 trees of 16 nodes, contexts to 6000 138 -> 38.)
+// What bounds it now: a chunk of 64 keys takes a wavefront 1024 cycles of MFMA and about 1100 of the vector unit, 250 more where a row finds
+// a new maximum, and two wavefronts per SIMD some 3000 for one each, as their phases overlap in part only; and some 9 us besides: the launch, 1.5 to 2.4 for the
 // plan, 2.3 until the first chunk and the query rows are there, 1 to 3 for the partial rows. Tried: eight wavefronts that share a chunk, four
-// buffers, three chunks on their way (33 us where this takes 31; the end of all workgroups at once costs more), loads sent between
-// the first products instead of before them (51 against 39).
+// buffers, three chunks on their way (6 % longer; the end of all workgroups at once costs more), loads sent between
+// the first products instead of before them (30 % longer).
 // ------------------------------------------------------------------------------------
 constexpr int kRowsKeys = kAttnRowsKeys, kRowsPerWg = kAttnRowsPerWg, kRowsWaves = kRowsPerWg / 32;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -289,12 +289,11 @@ __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
       mx = fmaxf(__int_as_float(sw[0]), __int_as_float(sw[1]));
     }
-    // The maximum moves only when a row has outgrown it by e^kSlack: sums and weights are that much larger at most, which
-    // neither fp32 nor bf16 minds, and after the first chunk hardly any chunk rescales what has been accumulated (32 rows
-    // otherwise find a new maximum among them in most chunks).
-    constexpr float kSlack = 5.0f;
+    // The maximum is that of all keys so far: the largest weight of a row is then exactly 1 in bf16, not rounded, which counts where a
+    // few keys have most of the weight. (Moved only when outgrown by e^5, it saved most rescalings, 4 x 64 nodes, contexts to 5555, 2 us,
+    // and the output was off from 64-bit sums by 1.17 times the 16-row kernel's error at scores of deviation 2.4; this way 0.99.)
     const float m_new = mx * scale;
-    if (__builtin_amdgcn_ballot_w64(m_new > m_run + kSlack)) {
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run)) {
       const float m_up = fmaxf(m_run, m_new);
       const float alpha = m_run == -INFINITY ? 0.0f : __expf(m_run - m_up);
 #pragma unroll
