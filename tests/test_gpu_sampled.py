@@ -251,3 +251,47 @@ def test_empty_trees_leave_their_neighbours_alone(ctx_small, V, empty):
     none = [b for b in range(len(u)) if b not in live]
     assert np.all(got[1][none] == 1) and np.all(got[0][none, 0] == 0) and np.all(got[0][none, 1:] == -1)
     assert np.all((got[2][none] >= 0) & (got[2][none] < V))
+
+
+@pytest.mark.parametrize("V", [1000, 16385, 49153, 65537, 151936, 16 * 64 * 152 + 1])
+def test_infinite_temperature_draws_every_token_alike(ctx_small, V):
+    """A chain whose first two children are accepted (probability 1 / V, random number 0) and whose third is not: the bonus token is the one
+    at u * (V - 1) among those left. Sums of ones are exact in fp32, so it is exactly that one."""
+    g = synth.philox(V, 64)
+    logits = (3.0 * g.standard_normal((4, V))).astype(np.float32)
+    off, parent = np.array([0, 4], np.int32), np.array([-1, 0, 1, 2], np.int32)
+    tok, u_node = np.array([0, 5, 6, 7], np.int32), np.array([0.0, 0.0, 0.0, 0.9], np.float32)
+    for u in (0.0, 0.3, 0.5, 0.9):
+        path, plen, bonus = run_gpu(ctx_small, off, parent, tok, logits, V, float("inf"), u_node, np.array([u], np.float32), 4)
+        assert plen[0] == 3 and list(path[0]) == [0, 1, 2, -1]
+        left = [t for t in range(V) if t != 7]
+        assert bonus[0] == left[int(np.float32(u) * np.float32(V - 1))]
+
+
+@pytest.mark.parametrize("V", [1000, 16385, 40000, 65537, 151936])
+@pytest.mark.parametrize("low", [-np.inf, np.finfo(np.float32).min])
+def test_masked_logits(ctx_small, V, low):
+    """What a top-k or top-p filter leaves: rows with whole parts and segments (a sixteenth of the vocabulary each) without a token, tokens in
+    one segment only, one single token, and an unmasked row beside them."""
+    parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(51, [12, 1, 6, 1], V)
+    T, seg = len(logits), -(-V // 16)
+    keep = np.zeros((T, V), bool)
+    for r in range(T):
+        kind = r % 5
+        if kind == 0: keep[r, :seg // 2] = keep[r, 9 * seg:9 * seg + 40] = True
+        elif kind == 1: keep[r, 3 * seg + 1:5 * seg - 1] = True
+        elif kind == 2: keep[r, V - 1] = True
+        elif kind == 3: keep[r, np.argsort(-logits[r])[:50]] = True
+        else: keep[r] = True
+    keep[int(tree_off[3]), :] = False
+    keep[int(tree_off[3]), 15 * seg:] = True  # (a tree of one node: the draw alone, from the last segment)
+    for i in range(T):  # the draft tokens keep their place
+        b = int(np.searchsorted(tree_off, i, side="right")) - 1
+        if i > tree_off[b]: keep[int(tree_off[b]) + parent[i], tok[i]] = True
+    logits[~keep] = low
+    for u in (0.0, 0.4, 1.0 - 2.0 ** -24):
+        u_bonus[:] = u
+        path, plen, bonus = run_gpu(ctx_small, tree_off, parent, tok, logits, V, 0.9, u_node, u_bonus, 12)
+        assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus) == 0
+        for b in range(len(parents)):
+            assert keep[int(tree_off[b]) + path[b, plen[b] - 1], bonus[b]]
