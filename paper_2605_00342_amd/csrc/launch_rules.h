@@ -120,6 +120,11 @@ constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_c
   if (D != 128 || B > kAttnRowsMaxSeqs) return false;
   return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 400 || B >= 16 || (B == 1 && T * (Hq / Hkv) <= 64);
 }
+// Its loads go straight into LDS, 16 bytes a lane, and so need rows of the caches at multiples of 16 bytes; caches at other strides, which the 16-row
+// kernel reads through registers, stay there. (One sequence: the distance to the next is not used.)
+constexpr bool attn_rows_strides(int B, long long seq_stride, long long head_stride) {
+  return head_stride % 8 == 0 && (B == 1 || seq_stride % 8 == 0);
+}
 // Workgroups to cut the splits for: one per CU, or two, which overlap each other's phases but leave twice the partial rows to the
 // merge, once they have 16 chunks and more (one, two per CU: 8 x 32 nodes, 16 heads of one, ctx 2048 28.8, 22.6; 16 x 64 ctx 2048 57.6, 46.6; but
 // 4 x 64 ctx 2048 21.8, 24.8, 1 x 128 ctx 6000 29.4, 31.7).

@@ -1989,7 +1989,8 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
     // those past a sequence's own tiles leave at once; the split count goes by the average tree)
     const int avg_nodes = (T + B - 1) / B < max_nodes ? (T + B - 1) / B : max_nodes;
     const int avg_tiles = (avg_nodes * G + 15) / 16;
-    if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == kAttnTargetWgs && attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host)) {
+    if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == kAttnTargetWgs && attn_rows_strides(B, seq_stride, head_stride) &&
+        attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host)) {
       if (B > 1) planned = c->row_splits;
       const int rc = launch_attn_rows(c, kc, vc, seq_stride, head_stride, ctx_len, max_ctx_host, tree_off, B, T, k_new, v_new, &nsplits, s);
       if (rc) return rc;

@@ -132,3 +132,33 @@ def test_error_of_peaked_scores(scale):
         finally:
             layer.close()
     assert err[0] < 1.05 * err[1], err
+
+
+@pytest.mark.parametrize("B,n,L,pad", [(1, 8, 300, 2), (1, 64, 2100, 4), (16, 4, 130, 4), (16, 4, 130, 2)])
+def test_caches_at_strides_of_no_multiple_of_16_bytes(B, n, L, pad):
+    """Heads and sequences `pad` elements further apart than their rows take: as many calls of the 16-row kernel, which reads them through
+    registers, on the same keys and values give the same bits."""
+    cfg = cfg_of(8, 2)
+    case = batch(cfg, [n] * B, [L - 3 * b for b in range(B)], 990)
+    layer, dc = harness.DeviceLayer(cfg, case["W"], n * B, B, L), harness.DeviceCase(case)
+    try:
+        flat = [torch.zeros(B * (cfg.Hkv * (L * cfg.D + pad) + pad) + 8, dtype=torch.bfloat16, device="cuda:0") for _ in range(2)]
+        head, seq = L * cfg.D + pad, cfg.Hkv * (L * cfg.D + pad) + pad
+        for at, of in zip(flat, (dc.k_cache, dc.v_cache)):
+            at.as_strided((B, cfg.Hkv, L, cfg.D), (seq, head, cfg.D, 1)).copy_(of)
+        out = []
+        ev.evict_tune(layer.ctx, "attn_waves", 4)
+        dc.run(layer)
+        out.append((dc.out.clone(), dc.a["attn_out"].clone()))
+        for waves in (4, 0):
+            ev.evict_tune(layer.ctx, "attn_waves", waves)
+            dc.out.zero_()
+            ev.evict_verify_layer(layer.ctx, layer.weights, dc.tree_off, dc.parent, B, n * B, *flat, seq, head, dc.ctx_len, L, dc.x, dc.out,
+                                  dc.k_new, dc.v_new, dc.aux)
+            out.append((dc.out.clone(), dc.a["attn_out"].clone()))
+        torch.cuda.synchronize()
+        assert ev.evict_device_status(layer.ctx) == 0
+        assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0], out[1][0])
+        check_against_oracle(case, dict(dc.results(), out=harness.to_host(out[2][0])))  # (8 wavefronts where the size asks for them)
+    finally:
+        layer.close()

@@ -26,6 +26,7 @@ int deal(int T, int n_strips, int nkb, int bf16) { return lm_deal(T, n_strips, n
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
+int rows_strides(int B, long long seq, long long head) { return attn_rows_strides(B, seq, head); }
 int rows_wgs(int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_wgs(B, T, Hq, Hkv, ctx); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
 }
@@ -155,3 +156,13 @@ def test_lm_head_deal(rules):
     for T, n, nkb, bf16 in ((16, 9496, 32, 1), (24, 9496, 128, 1), (24, 9496, 64, 0), (8, 9496, 64, 1), (48, 9496, 48, 1)):
         old = rules.strips(T, n) if rules.one_round(T, n, nkb, bf16) else rules.units(T, n)
         assert rules.deal(T, n, nkb, bf16) == old
+
+
+def test_attention_rows_need_aligned_rows(rules):
+    def f(B, seq, head):
+        return bool(rules.rows_strides(B, ctypes.c_longlong(seq), ctypes.c_longlong(head)))
+
+    assert f(1, 0, 128 * 100) and f(4, 128 * 400, 128 * 100) and f(4, 128 * 400 + 8, 128 * 100 + 8) and f(1, 3, 8)
+    for off in (1, 2, 4, 7):
+        assert not f(1, 0, 128 * 100 + off) and not f(2, 128 * 400 + off, 128 * 100) and not f(2, 128 * 400, 128 * 100 + off)
+    assert not f(1, 0, (1 << 33) + 4) and f(1, 0, (1 << 33) + 8)
