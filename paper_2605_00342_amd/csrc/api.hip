@@ -561,10 +561,14 @@ static int launch_lm_gemm(evict_ctx* ctx, int epi, GemmArgs& a, int T, hipStream
   a.dense_units = ctx->lm_units ? ctx->lm_units : lm_deal(T, a.n_strips, a.nkb, ctx->m.dtype == EVICT_BF16);
   a.nt_loads = ctx->dense_nt_loads == 2 ? (a.dense_tiles == 1 ? 1 : 0) : ctx->dense_nt_loads;  // every strip is read by one workgroup
   const int wgs = (a.n_strips + a.dense_units - 1) / a.dense_units;
-  const bool exact = ctx->m.dtype == EVICT_BF16 && (a.nkb % 64 == 0 || a.nkb == 24);  // (the instances launch_gemm_nt takes for these)
-  if (epi == EPI_ARGMAX && (exact || nt == 2)) a.ldo = wgs;  // candidates per token
+  const bool bf16 = ctx->m.dtype == EVICT_BF16;
+  if (epi == EPI_ARGMAX && nt == 1 && lm_keeps_best(a.n_strips, a.nkb, bf16)) epi = EPI_ARGMAX_WG;
+  if (epi == EPI_ARGMAX_WG || (epi == EPI_ARGMAX && nt == 2)) a.ldo = wgs;  // candidates per token
   const int rows_lds = a.dense_units * nt * 1024;
-  if (epi == EPI_ROWS && ctx->m.dtype == EVICT_BF16 && a.nkb % 64 == 0 && rows_lds <= kRowsLdsMax) a.rows_lds = rows_lds;
+  if (epi == EPI_ROWS && lm_keeps_rows(T, a.n_strips, a.nkb, bf16) && rows_lds <= kRowsLdsMax) {
+    epi = EPI_ROWS_WG;
+    a.rows_lds = rows_lds;
+  }
   return launch_gemm(ctx->m.dtype, epi, a, nt, (wgs + 7) / 8 * 8 * a.dense_tiles, s);
 }
 

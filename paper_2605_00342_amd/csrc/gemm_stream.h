@@ -21,7 +21,9 @@ namespace evict {
 // SWIGLU and F32 (fp32 rows, the down projection) are grouped by expert, the others dense; ROWS: fp32 rows of a dense matrix (score
 // rows). What the operand is must be known at compile time: with one instance for both kinds of fp32 rows and a stride chosen
 // when it runs, score rows took up to 14 % longer (128256 rows of 96 blocks, 1 token, us: 150 -> 131; 32-bit storage, 32000 of 64 34.6 -> 30.8).
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_ARGMAX = 4, EPI_ROWS = 5 };
+// ARGMAX_WG, ROWS_WG: the same, kept by the workgroup until its strips are done (likewise: the way that is not taken, left in as a branch, costs
+// score rows of 24 blocks 2 to 5 %).
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_F32 = 3, EPI_ARGMAX = 4, EPI_ROWS = 5, EPI_ARGMAX_WG = 6, EPI_ROWS_WG = 7 };
 
 // One slot of the device-side work list = one activated expert and one tile of up to 16 of its
 // tokens: the expert, where the tile sits in the grouped order, how many tokens it has, how many
@@ -59,7 +61,7 @@ struct GemmArgs {
   int lds_dma;           // 1: strip-pair gate/up kernel stages its token operand with direct global-to-LDS loads
   int down_ws;           // gemm_wave_strip_kernel: strips (wavefronts) per workgroup, 8 or 16
   int pair_tiles;        // 1: gemm_wave_strip_kernel with two token tiles takes them from two consecutive 16-token records
-  int rows_lds;          // ROWS: bytes of LDS for the scores of all strips of a workgroup, 0: they are stored strip by strip
+  int rows_lds;          // ROWS_WG: bytes of LDS for the scores of all strips of a workgroup
   void* out0;            // QKV: q; RESID: h; SWIGLU: act; F32: y; ROWS: scores; ARGMAX: best value per token and strip, or workgroup (best_kept), [T][ldo]
   void* out1;            // QKV: k_new; ARGMAX: row index of the best value
   void* out2;            // QKV: v_new
@@ -72,15 +74,14 @@ struct GemmArgs {
 constexpr int kGemmWaves = 8;
 constexpr int kGemmThreads = kGemmWaves * 64;
 
-// ARGMAX: candidates kept by the wavefronts until a workgroup's strips are done. Not with short strips of one token tile, of which a
-// workgroup takes two: its end then takes longer than two exchanges (1 token, us: 9496 strips of 32 blocks 69 against 107, 2000 of 32
-// 20 against 27; but 64 blocks 96.7 -> 95.4, 16 tokens 107 -> 97, two tiles, 32 tokens, 9496 strips of 32 blocks 75 -> 57, 48 blocks 126 -> 104).
-template <int NT, bool EXACT> constexpr bool best_kept() { return EXACT || NT == 2; }
+// Arg max with the candidates kept by the wavefronts until a workgroup's strips are done: always with two token tiles (1 token, us: 9496 strips of
+// 32 blocks 69 strip by strip, 107 this way, 2000 of 32 20 against 27; but two tiles, 32 tokens, 9496 strips of 32 blocks 75 -> 57, 48 blocks 126 -> 104),
+// with one where lm_keeps_best says so.
+template <int EPI, int NT> constexpr bool best_kept() { return EPI == EPI_ARGMAX_WG || (EPI == EPI_ARGMAX && NT == 2); }
 
 // Score rows of a workgroup's strips, kept in LDS until its weights have been streamed. (Stored strip by strip, a wavefront's next weights wait
 // behind its stores, as one counter in order of issue covers both: 151936 rows of 64 blocks, 32 tokens, us: 113 -> 99.)
 constexpr int kRowsLdsMax = 96 * 1024;
-template <typename ST, int EPI, bool EXACT, int IS> constexpr bool rows_in_lds() { return EPI == EPI_ROWS && EXACT && IS == 1 && ST::kBytes == 2; }
 // where quarter q (rows 4q .. 4q + 3) of a strip's row block for token column n lies: columns XORed so that 16 lanes which read
 // neighbouring strips' quarters of one token meet 16 different places
 __device__ __forceinline__ int rows_lds_at(int strip, int q, int n) { return q * 16 + (n ^ ((strip * 4 + q) & 15)); }
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((N
   constexpr int SPU = (EPI == EPI_SWIGLU) ? 2 : 1;  // strips per unit of work
   static_assert(EPI != EPI_SWIGLU || IS == 1, "gate/up strips are exchanged one at a time");
   __shared__ f32x4 s_part[2][kGemmWaves][IS * NT][64];
-  extern __shared__ __attribute__((aligned(16))) f32x4 s_rows[];  // ROWS: a.rows_lds
+  extern __shared__ __attribute__((aligned(16))) f32x4 s_rows[];  // ROWS_WG: a.rows_lds
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, known uniform
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((N
                   const int col = tok0 + t * 16 + (lane & 15);
                   const bool valid = col < ntok;
                   const int m0 = (lane >> 4) * 4;  // first of this lane's 4 rows in the strip
-                  if (EPI == EPI_ARGMAX && best_kept<NT, EXACT>()) {
+                  if (best_kept<EPI, NT>()) {
                     // best of this lane's rows in all strips of this wavefront, the lowest row on equal values
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((N
                       ((float*)a.out0)[(long long)col * a.ldo + strip] = bv;
                       ((int*)a.out1)[(long long)col * a.ldo + strip] = bi;
                     }
-                  } else if (rows_in_lds<ST, EPI, EXACT, IS>() && a.rows_lds) {
+                  } else if (EPI == EPI_ROWS_WG) {
                     s_rows[((strip - strip0) * NT + t) * 64 + rows_lds_at(strip - strip0, lane >> 4, lane & 15)] = sum;
                   } else if (EPI == EPI_F32 || EPI == EPI_ROWS) {
                     if (valid) {
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((N
           }
         }
       }
-      if (rows_in_lds<ST, EPI, EXACT, IS>() && a.rows_lds) {
+      if (EPI == EPI_ROWS_WG) {
         lds_barrier();
         const int live = tok_end - tok0 < 16 * NT ? tok_end - tok0 : 16 * NT, per_tok = nitems * 4;
         for (int i = tid; i < live * per_tok; i += kGemmThreads) {
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu((N
           *reinterpret_cast<f32x4*>((float*)a.out0 + (long long)(tok0 + n) * a.ldo + strip0 * 16 + r * 4) = v;
         }
       }
-      if (EPI == EPI_ARGMAX && best_kept<NT, EXACT>()) {
+      if (best_kept<EPI, NT>()) {
         // one candidate per token and workgroup: the wavefronts' bests, then those of the 4 lanes that hold other rows of a token.
         // (151936 rows of 64 blocks, 32 tokens, us: with an exchange between lanes and a store at every strip 102, 6.1 TB/s, and 6.4
         // for the best of 9496 candidates; this way 91, 6.8 TB/s, and 4.8 for the best of 256)

@@ -94,6 +94,21 @@ constexpr int lm_deal(int T, int n_strips, int nkb, bool bf16) {
   return lm_one_round(T, n_strips, nkb, bf16) ? lm_strips(T, n_strips) : lm_units(T, n_strips);
 }
 
+// Candidates of the arg max, one token tile, kept by a workgroup until its strips are done (ARGMAX_WG): from so many strips on that the fewer
+// stores and candidates make up for the exchange at its end, which few strips per workgroup do not. (Head and arg max, us, strip by strip ->
+// kept. 64 blocks, 16 tokens: 64 strips 13.0 -> 13.9, 500 15.4 -> 15.7, 1000 20.7 -> 20.9, 2000 32.1 -> 32.1, 3142 43.9 -> 42.3, 9496 109 -> 104; 24
+// blocks: 500 12.9 -> 13.3, 1000 14.7 -> 15.0, 2000 20.8 -> 19.7, 9496 57 -> 49; 128 blocks, 8 tokens: 64 17.2 -> 17.7, 2000 49.5 -> 49.7, 3142 75.8 -> 75.3.)
+constexpr bool lm_keeps_best(int n_strips, int nkb, bool bf16) {
+  return bf16 && (nkb % 64 == 0 ? n_strips > 2048 : nkb == 24 && n_strips > 1536);
+}
+
+// Score rows kept in LDS until then (ROWS_WG). (us, strip by strip -> kept: 64 blocks, 32 tokens 500 strips 19.1 -> 18.9, 3142 43.3 -> 41.2, 9496
+// 117 -> 106; 48 tokens 64 strips 13.8 -> 14.4, 1000 19.5 -> 19.6; 16 tokens 64 strips 9.8 -> 10.2, 3142 40.0 -> 40.0, 6400 79 -> 72; 8 tokens
+// 9496 100.6 -> 99.9. 128 blocks, 8 tokens: 2000 46.0 -> 46.3, 9496 187.4 -> 187.9, 24 tokens 4097 106.4 -> 104.5.)
+constexpr bool lm_keeps_rows(int T, int n_strips, int nkb, bool bf16) {
+  return bf16 && nkb % 64 == 0 && n_strips > 2048 && (nkb == 64 || T > 12);
+}
+
 // TopK beside the union (up to 32 tokens): four tokens per wavefront, in rows of 16 lanes with room for a pick each, once some of
 // the 16 wavefronts would have two tokens. (TopK and union, us, one -> four: 32 tokens 9.1 -> 7.3, one token 5.3 -> 6.6. Whole layers: 8 picks
 // of 128 experts, 9 tokens 41.5 -> 42.1, 17 43.3 -> 43.3, 24 44.2 -> 43.8, 32 45.5 -> 44.1; 16 picks, 9 tokens 43.9 -> 44.8, 17 46.6 -> 46.9, 24

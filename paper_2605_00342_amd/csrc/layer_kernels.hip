@@ -1550,6 +1550,7 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
   } while (0)
   const int nkb = a.nkb;
   const int need = ((nkb > 64 ? 64 : nkb) + kGemmWaves - 1) / kGemmWaves;
+  constexpr bool by_wg = EPI == EPI_ARGMAX_WG || EPI == EPI_ROWS_WG;  // (bf16, strips of whole steps only: lm_keeps_best, lm_keeps_rows)
   constexpr bool bf16 = ST::kBytes == 2;
   if constexpr (bf16) {
   if (EPI == EPI_SWIGLU && gateup_long_steps(EVICT_BF16, a, NT)) {
@@ -1572,7 +1573,9 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
       EVICT_GEMM_LAUNCH_NT(8, 1, true, 1, (EPI == EPI_RESID ? 2 : 0));
     else EVICT_GEMM_LAUNCH_NT(8, 1, true, 1, 0);
     return launch_status("gemm_stream_kernel");
-  } else if (nkb == 24) {
+  }
+  if constexpr (EPI != EPI_ROWS_WG) {
+  if (nkb == 24) {
     // 3 blocks per wavefront per strip: take 4 strips per exchange step when the chunking allows
     if (EPI == EPI_F32 && NT == 1 && a.grouped && a.chunk_units % 4 == 0)
       EVICT_GEMM_LAUNCH_NT(3, 1, true, ((EPI == EPI_F32 && NT == 1) ? 4 : 1), 0);
@@ -1581,7 +1584,11 @@ int launch_gemm_nt(const GemmArgs& a, int grid, hipStream_t s) {
     return launch_status("gemm_stream_kernel");
   }
   }
-  if (need <= 4) {
+  }
+  if constexpr (by_wg) {
+    set_error("gemm_stream_kernel: no instance for epilogue %d and %d contraction blocks", EPI, nkb);
+    return EVICT_E_INVALID;
+  } else if (need <= 4) {
     // four stages of weight loads; three where the epilogue prefetch also needs registers (four would spill)
     constexpr int kStages = (EPI == EPI_QKV || EPI == EPI_RESID) ? 3 : 4;
     EVICT_GEMM_LAUNCH(4, kStages, false);
@@ -1866,6 +1873,8 @@ int launch_gemm(int dtype, int epi, const GemmArgs& a, int nt, int grid, hipStre
     EVICT_GEMM_CASE(EPI_F32)
     EVICT_GEMM_CASE(EPI_ARGMAX)
     EVICT_GEMM_CASE(EPI_ROWS)
+    case EPI_ARGMAX_WG: return launch_gemm_nt<BF16, 1, EPI_ARGMAX_WG>(a, grid, s);
+    case EPI_ROWS_WG: return nt == 2 ? launch_gemm_nt<BF16, 2, EPI_ROWS_WG>(a, grid, s) : launch_gemm_nt<BF16, 1, EPI_ROWS_WG>(a, grid, s);
   }
 #undef EVICT_GEMM_CASE
   set_error("unknown epilogue %d", epi);
@@ -1942,7 +1951,7 @@ int kernels_setup(const evict_model_desc& m) {
   EVICT_TILE_LM(EVICT_TILE_ATTR)
 #undef EVICT_TILE_ATTR
 #define EVICT_ROWS_ATTR(NT_, NTL_)                                                                                  \
-  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_stream_kernel<BF16, NT_, 8, 1, EPI_ROWS, true, 1, 0, NTL_>,  \
+  EVICT_HIP_CHECK(hipFuncSetAttribute((const void*)gemm_stream_kernel<BF16, NT_, 8, 1, EPI_ROWS_WG, true, 1, 0, NTL_>,  \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLdsMax))
   EVICT_ROWS_ATTR(1, true); EVICT_ROWS_ATTR(1, false); EVICT_ROWS_ATTR(2, true); EVICT_ROWS_ATTR(2, false);
 #undef EVICT_ROWS_ATTR

@@ -19,6 +19,8 @@ DEV = "cuda:0"
     ("bf16", 2048, 16 * 4096, (13, 16, 17, 32)), ("bf16", 2048, 16 * 3, (1, 16, 17, 32)), ("bf16", 4096, 16 * 101, (1, 11)),
     ("bf16", 768, 16 * 3143, (1, 9, 16, 17, 33)), ("bf16", 1024, 16 * 2000, (1, 13, 17, 48)), ("bf16", 1536, 16 * 517, (2, 20)),
     ("f32", 256, 16 * 2001, (1, 14, 17, 40)),
+    ("bf16", 2048, 16 * 2048, (1, 13, 32)), ("bf16", 2048, 16 * 2049, (1, 12, 16, 17, 32, 48)),  # kept by the workgroup from 2049 strips on,
+    ("bf16", 768, 16 * 1536, (1, 16)), ("bf16", 768, 16 * 1537, (1, 16)), ("bf16", 4096, 16 * 2049, (1, 11, 13, 32)),  # of 24 blocks from 1537
 ])
 def test_rows_and_best(dtype, d, V, Ts):
     cfg = synth.ModelCfg("lm", dtype, d=d, Hq=4, Hkv=4, D=64, E=16, k=2, F=64, theta=1e4)

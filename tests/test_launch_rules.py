@@ -23,6 +23,8 @@ int units(int T, int n_strips) { return lm_units(T, n_strips); }
 int strips(int T, int n_strips) { return lm_strips(T, n_strips); }
 int one_round(int T, int n_strips, int nkb, int bf16) { return lm_one_round(T, n_strips, nkb, bf16); }
 int deal(int T, int n_strips, int nkb, int bf16) { return lm_deal(T, n_strips, nkb, bf16); }
+int keeps_best(int n_strips, int nkb, int bf16) { return lm_keeps_best(n_strips, nkb, bf16); }
+int keeps_rows(int T, int n_strips, int nkb, int bf16) { return lm_keeps_rows(T, n_strips, nkb, bf16); }
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
@@ -166,3 +168,15 @@ def test_attention_rows_need_aligned_rows(rules):
     for off in (1, 2, 4, 7):
         assert not f(1, 0, 128 * 100 + off) and not f(2, 128 * 400 + off, 128 * 100) and not f(2, 128 * 400, 128 * 100 + off)
     assert not f(1, 0, (1 << 33) + 4) and f(1, 0, (1 << 33) + 8)
+
+
+def test_lm_head_keeps_results_only_of_many_strips(rules):
+    """Where a workgroup has few strips, what it would keep is stored strip by strip, as it is where the kept form is not built."""
+    for nkb in (64, 128, 192):
+        assert [rules.keeps_best(n, nkb, 1) for n in (1, 64, 1000, 2048, 2049, 9496)] == [0, 0, 0, 0, 1, 1]
+        assert [rules.keeps_rows(13, n, nkb, 1) for n in (1, 64, 1000, 2048, 2049, 9496)] == [0, 0, 0, 0, 1, 1]
+    assert [rules.keeps_best(n, 24, 1) for n in (64, 1536, 1537)] == [0, 0, 1]
+    assert rules.keeps_rows(1, 9496, 64, 1) and not rules.keeps_rows(12, 9496, 128, 1)
+    for nkb in (8, 16, 24, 32, 48, 96):
+        assert not rules.keeps_rows(32, 9496, nkb, 1) and (nkb == 24 or not rules.keeps_best(9496, nkb, 1))
+    assert not rules.keeps_best(9496, 64, 0) and not rules.keeps_rows(32, 9496, 64, 0)
