@@ -396,7 +396,7 @@ int launch_attn_rows(const evict_ctx* c, const void* kc, const void* vc, long lo
   int cps = (chunks + kAttnRowsMaxSplits - 1) / kAttnRowsMaxSplits, head_wgs, row_blocks = max_rb;
   dim3 grid;
   if (B == 1) {
-    const int want = target / (m.Hkv * max_rb) > 1 ? target / (m.Hkv * max_rb) : 1;
+    const int want = attn_rows_splits(target, m.Hkv, max_rb);
     cps = cps > (chunks + want - 1) / want ? cps : (chunks + want - 1) / want;
     head_wgs = *nsplits = (chunks + cps - 1) / cps;
     if (c->t_dev) row_blocks = -max_rb;

@@ -146,6 +146,13 @@ constexpr bool attn_rows_strides(int B, long long seq_stride, long long head_str
 constexpr int attn_rows_wgs(int B, int T, int Hq, int Hkv, int max_ctx) {
   return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 16 * 256 ? 512 : 256;
 }
+// One tree: most splits that this leaves for Hkv heads of `rbs` row blocks. A unit's row blocks are on one XCD, so what counts is the fullest
+// XCD: 21 splits of 4 heads are 84 units, 11 of them on four XCDs, and with three row blocks each 33 workgroups on 32 CUs. (48 nodes of 4
+// heads of 8, whole small layer, us, 21 splits by the total alone -> 18 and 19: ctx 8000 66.5 -> 62.6, ctx 12000 73.5 -> 65.5; the 16-row kernel 63.5 and 69.2.)
+constexpr int attn_rows_splits(int wgs, int Hkv, int rbs) {
+  const int units = wgs / 8 / rbs * 8;
+  return units / Hkv > 1 ? units / Hkv : 1;
+}
 
 // Weight loads of the down projections, as the knob says; auto: non-temporal, but ordinary ones for the 8 contraction blocks
 // of expert width 256 (13.8 us for 40 experts; the better from 64 tokens on).

@@ -28,6 +28,7 @@ int keeps_rows(int T, int n_strips, int nkb, int bf16) { return lm_keeps_rows(T,
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
+int rows_splits(int wgs, int Hkv, int rbs) { return attn_rows_splits(wgs, Hkv, rbs); }
 int rows_strides(int B, long long seq, long long head) { return attn_rows_strides(B, seq, head); }
 int rows_wgs(int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_wgs(B, T, Hq, Hkv, ctx); }
 int down_nt(int knob, int nkb) { return down_nt_loads(knob, nkb); }
@@ -180,3 +181,14 @@ def test_lm_head_keeps_results_only_of_many_strips(rules):
     for nkb in (8, 16, 24, 32, 48, 96):
         assert not rules.keeps_rows(32, 9496, nkb, 1) and (nkb == 24 or not rules.keeps_best(9496, nkb, 1))
     assert not rules.keeps_best(9496, 64, 0) and not rules.keeps_rows(32, 9496, 64, 0)
+
+
+def test_attention_splits_leave_no_xcd_a_second_round(rules):
+    for wgs in (256, 512):
+        for Hkv in (1, 2, 4, 8, 16, 32):
+            for rbs in range(1, 65):
+                n = rules.rows_splits(wgs, Hkv, rbs)
+                assert n >= 1
+                if n > 1:
+                    assert (n * Hkv + 7) // 8 * rbs <= wgs // 8, (wgs, Hkv, rbs, n)
+    assert [rules.rows_splits(256, 4, r) for r in (1, 2, 3, 4, 7, 8)] == [64, 32, 20, 16, 8, 8]
