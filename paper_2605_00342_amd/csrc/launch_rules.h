@@ -124,16 +124,26 @@ constexpr long long attn_rows_work(int B, int T, int Hq, int Hkv, int max_ctx) {
   const long long rbs = ((long long)T * (Hq / Hkv) + kAttnRowsPerWg - 1) / kAttnRowsPerWg;
   return (rbs > B ? rbs : B) * Hkv * ((max_ctx + kAttnRowsKeys - 1) / kAttnRowsKeys + 1);
 }
-// Attention and merge, us, 16 rows -> 32. Many chunks: 1 x 64 nodes of 4 KV heads of 8, ctx 2048 18.4 -> 17.8, ctx 6000 25.0 -> 21.2, 1 x 128 ctx 16000
-// 70.3 -> 50.0, 4 x 64 ctx 6000 56.6 -> 37.8, 16 x 64 ctx 2048 101.5 -> 46.6; one KV head of 8, 2 x 128 ctx 2048 20.4 -> 19.0; 16 heads of one, 4 x 64
-// ctx 600 19.4 -> 14.2. Many small trees, whose empty row blocks the 16-row kernel deals out between the others (half to three quarters of
-// the CUs get none): 16 x 16 ctx 600 51.4 -> 17.9, 64 x 8 ctx 100 45.2 -> 22.7. One tree that fills at most two wavefronts, which then take a
-// chunk of 64 keys each where the other kernel takes 128: 1 x 8 ctx 600 10.0 -> 9.2, 16 heads of one, 1 x 64 ctx 2048 16.2 -> 13.2.
+// Attention and merge, us, 16 rows -> 32. Many chunks: 1 x 64 nodes of 4 KV heads of 8, ctx 6000 25.0 -> 22.3, 1 x 128 ctx 16000
+// 70.3 -> 54, 4 x 64 ctx 6000 56.6 -> 40, 16 x 64 ctx 2048 101.5 -> 49; 16 heads of one, 4 x 64 ctx 600 19.4 -> 15. Many small trees, whose empty
+// row blocks the 16-row kernel deals out between the others (half to three quarters of the CUs get none): 16 x 16 ctx 600 51.4 -> 18,
+// 64 x 8 ctx 100 45.2 -> 23. One tree that fills at most two wavefronts, which then take a chunk of 64 keys each where the other kernel
+// takes 128: 1 x 8 ctx 600 10.0 -> 9.0, 16 heads of one, 1 x 64 ctx 2048 16.2 -> 14.1.
 // Not where few chunks leave most of a workgroup's time to its start and its end: 1 x 64 ctx 600 13.4 (14.9), 1 x 32 ctx 600 11.5 (13.0), one KV
-// head, 2 x 128 ctx 600 12.8 (17.1), 1 x 64 ctx 6000 15.8 (16.7).
+// head, 2 x 128 ctx 600 12.8 (17.1), 1 x 64 ctx 6000 15.8 (16.7). The line lies higher where the 16-row kernel has few empty row blocks (whole
+// small layers, us, 16 rows -> 32, chunks in brackets): one or two KV heads, 1 to 4 trees, 8/1 2 x 96 ctx 3000 58.0 -> 61.7 (576), 3 x 128 ctx 2048 65.0 -> 66.5
+// (792), 16/2 1 x 64 ctx 4096 55.0 -> 56.4 (520), but 8/1 1 x 128 ctx 8000 62.2 -> 62.1 (1008); 64 heads on 8, 1 x 48 ctx 2048 65.7 -> 66.7 (792), 3000 69.6 ->
+// 67.8 (1128); 2 to 4 trees of more than 72 nodes, 16/16 2 x 96 ctx 1000 69.3 -> 70.4 (544), 1500 71.2 -> 72.0 (800), 2048 76.1 -> 72.4 (1056). And where
+// it has none, as a batch of trees of few rows lies within one of its workgroups (8 nodes of 4 trees, 16 heads of one: ctx 1000 47.4 -> 48.2,
+// 3000 60.4 -> 61.4, 4096 67.2 -> 62.7; one node, 8 trees 1000 51.3 -> 55.1, 2048 62.1 -> 56.5): from 16 chunks a workgroup on, or with more units
+// (sequences x KV heads) than half of the CUs from 8 on (12 trees of one node 300 47.0 -> 48.2, 600 58.0 -> 56.3), or more than CUs.
 constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_ctx) {
   if (D != 128 || B > kAttnRowsMaxSeqs) return false;
-  return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 400 || B >= 16 || (B == 1 && T * (Hq / Hkv) <= 64);
+  const long long work = attn_rows_work(B, T, Hq, Hkv, max_ctx), units = (long long)B * Hkv, rows = (long long)T * (Hq / Hkv);
+  if (rows <= 64) return B == 1 || work >= 16 * 256 || units > 256 || (units > 128 && work >= 5 * 256);
+  if (B >= 16) return true;
+  const bool few_empty = B <= 4 && (Hkv <= 2 || (B == 1 ? Hq >= 64 : T > 72 * B));
+  return work >= (few_empty ? 830 : 400);
 }
 // Its loads go straight into LDS, 16 bytes a lane, and so need rows of the caches at multiples of 16 bytes; caches at other strides, which the 16-row
 // kernel reads through registers, stay there. (One sequence: the distance to the next is not used.)

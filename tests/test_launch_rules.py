@@ -192,3 +192,18 @@ def test_attention_splits_leave_no_xcd_a_second_round(rules):
                 if n > 1:
                     assert (n * Hkv + 7) // 8 * rbs <= wgs // 8, (wgs, Hkv, rbs, n)
     assert [rules.rows_splits(256, 4, r) for r in (1, 2, 3, 4, 7, 8)] == [64, 32, 20, 16, 8, 8]
+
+
+def test_attention_rows_where_they_were_measured_faster(rules):
+    """Batches of few rows, which lie within one workgroup of the 16-row kernel per KV head, and large trees of one or two KV heads."""
+    f = rules.rows_applies
+    for ctx, want in ((600, 0), (1000, 0), (3000, 0), (4096, 1), (10000, 1)):  # 4 trees of 8 nodes, 16 heads of one: 64 units
+        assert bool(f(128, 4, 32, 16, 16, ctx)) == bool(want), ctx
+    assert [bool(f(128, 8, 8, 16, 16, c)) for c in (100, 1000, 1984, 2048)] == [False, False, True, True]
+    assert [bool(f(128, 12, 12, 16, 16, c)) for c in (100, 300, 384, 600)] == [False, False, True, True]  # 192 units
+    assert f(128, 20, 20, 16, 16, 100) and not f(128, 16, 16, 16, 16, 100)  # 320 units and 256
+    assert [bool(f(128, 8, 8, 32, 4, c)) for c in (600, 2048, 6000)] == [False, False, False] and f(128, 9, 9, 32, 4, 6000)
+    for shape, lo, hi in (((2, 187, 8, 1), 3000, 5000), ((3, 369, 8, 1), 2048, 4000), ((1, 64, 16, 2), 6000, 8192), ((1, 48, 64, 8), 2048, 3000),
+                          ((2, 187, 16, 16), 1500, 2048)):
+        assert not f(128, *shape, lo) and f(128, *shape, hi), shape
+    assert f(128, 1, 100, 16, 16, 1600) and f(128, 2, 120, 32, 4, 1500) and f(128, 5, 360, 8, 1, 2000)
