@@ -280,8 +280,8 @@ int evict_accept_path_sampled(evict_ctx* ctx, const int32_t* tree_off, const int
 
 /* For callers that cannot allocate device memory (code under HIP-graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): evict_accept_path_sampled without a context's scratch.
- * The per-node softmax statistics (64 floats per node) live in a static device array inside the
- * library, sized for EVICT_NOALLOC_MAX_NODES nodes per call (1 MiB, held on every GPU the library
+ * The per-node softmax statistics (80 floats per node) live in a static device array inside the
+ * library, sized for EVICT_NOALLOC_MAX_NODES nodes per call (1.25 MiB, held on every GPU the library
  * runs on until the process ends); its device address is looked up on the first call on a device.
  * The call itself allocates and frees nothing. Arguments, outputs and results are exactly those of
  * evict_accept_path_sampled; ctx may be NULL (then invalid ids are not reported). T above

@@ -575,9 +575,11 @@ __device__ __forceinline__ float stats_sum(const float* __restrict__ st, float m
   return z;
 }
 
-// Short rows: both numbers by one workgroup per row in one launch, the same additions in the same order; maximum and sum go to
-// the first slot of the partial maxima and of the partial sums. Two launches cost more than they save there (256 rows: 1000
-// logits 2.9 us this way, 8.3 in two launches; 16000 logits 8.0 and 8.3).
+// Short rows: both numbers by one workgroup per row, the maximum of the whole row first, then the sum relative to it; they go side by side to the
+// first two slots, as the walk fetches them for every node's parent (1024 nodes of 16384 logits, all launches, us: 42.6, and 44.2 with the
+// sum 64 bytes behind the maximum). In parts, by the kernel above, the same takes (trees of 32 nodes, four of 32, eight of 64) 16.6, 17.1, 20.3 at 4000
+// logits, here 12.4, 12.8, 14.9; at 8000 15.9, 16.6, 20.8 (13.9, 14.3, 18.0), at 12000 16.3, 17.4, 21.6 (15.8, 18.1, 22.9). At 16384 the parts are the
+// faster, 16.8, 17.7, 22.5 (18.4, 20.7, 25.5): the line was drawn when they took a launch more, about 2 us.
 constexpr int kShortRow = 16384;
 __global__ __launch_bounds__(kSampThreads) void short_row_stats_kernel(const float* __restrict__ logits, int V, float inv_temp,
                                                                        float* __restrict__ stats, const int* __restrict__ t_dev) {
@@ -601,7 +603,7 @@ __global__ __launch_bounds__(kSampThreads) void short_row_stats_kernel(const flo
     float t = 0.0f;
     for (int i = 0; i < kSampWaves; ++i) t += s_red[1][i];
     stats[(size_t)blockIdx.x * kSampStats] = m;
-    stats[(size_t)blockIdx.x * kSampStats + kSampWaves] = t;
+    stats[(size_t)blockIdx.x * kSampStats + 1] = t;
   }
 }
 
@@ -645,7 +647,7 @@ __device__ __forceinline__ void sampled_walk(
         const float* st = stats + prow * kSampStats;
         const float logit = logits[prow * V + tk];
         const float m = SHORT ? st[0] : stats_max(st);
-        pr = __expf((logit - m) * inv_temp) / (SHORT ? st[kSampWaves] : stats_sum(st, m, inv_temp));
+        pr = __expf((logit - m) * inv_temp) / (SHORT ? st[1] : stats_sum(st, m, inv_temp));
       }
     }
     s.par[i] = i == 0 ? -1 : pa;
@@ -1418,7 +1420,7 @@ int evict_accept_path_sampled_noalloc(evict_ctx* ctx, const int32_t* tree_off, c
   if (rc) return rc;
   const float inv_temp = 1.0f / temperature;
   hipStream_t s = (hipStream_t)stream;
-  // (rows [0, T) of the statistics are written in full before they are read: nothing has to start at zero)
+  // (what a call reads of the statistics it has written before: nothing has to start at zero)
   return launch_accept_sampled(tree_off, parent, draft_tok, logits, vocab, inv_temp, stats, u_node, u_bonus, B, T, path, path_stride,
                                path_len, bonus_tok, ctx ? ctx->status : nullptr, ctx ? ctx->t_dev : nullptr, s);
 }
