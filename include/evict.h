@@ -460,11 +460,14 @@ int evict_device_status(evict_ctx* ctx, int32_t* status_host, void* stream);
  *                     the latter from 128 or 256 tokens on); "dense_ntw" its token tiles per workgroup, 1, 2 or 0 = auto
  *   "lm_units", "lm_nt" LM head: consecutive 16-row strips and 16-token tiles a workgroup takes, 0 = auto (bf16, d of 2048
  *                     and 4096, "dense_nt_loads" 2: the tiled kernel for many tokens and a vocabulary large enough)
- *   "attn_target_wgs" workgroups the bf16 attention kernel aims for when it cuts the context into splits
+ *   "attn_target_wgs" workgroups the bf16 attention kernel of 16 query rows per wavefront aims for when it cuts the
+ *                     context into splits (until set: 512, or the kernel of 32 rows in its place where that is the
+ *                     faster, head dimension 128; once this knob is set, or "attn_waves" or "attn_row_blocks" is not 0,
+ *                     calls stay with the kernel of 16 rows that these three shape)
  *   "moe_nt"          16-token tiles per work-list slot of the grouped expert GEMMs: 1, 2, or 0 = auto (1)
  *   "attn_waves"      wavefronts per workgroup of that kernel: 4, 8 (two LDS buffers, next chunk fetched
  *                     during the matrix work), or 0 = auto
- *   "attn_row_blocks" workgroups per (KV split, KV head) in the bf16 attention kernel, 0 = auto
+ *   "attn_row_blocks" workgroups per (KV split, KV head) in that kernel, 0 = auto
  *   "moe_pair_down"   down projection: two consecutive 16-token slots of an expert through one weight stream:
  *                     0 off, 1 on (where the kernel's LDS budget allows), 2 = auto (from 128 tokens on)
  *   "moe_down_ws"     down projection, strip-per-wavefront kernel: strips (wavefronts) per workgroup, 8, 16,

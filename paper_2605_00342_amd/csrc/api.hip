@@ -143,7 +143,7 @@ int evict_create(evict_ctx** out, const evict_model_desc* m, int max_tokens, int
   c.moe_nt_loads = 2;
   c.dense_nt_loads = 2;
   c.dense_nt = 0;
-  c.attn_target_wgs = kAttnTargetWgs;
+  c.attn_target_wgs = 0;
   c.attn_waves = 0;
   c.moe_nt = 0;
   c.dense_units = 0;

@@ -1998,18 +1998,18 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
     // those past a sequence's own tiles leave at once; the split count goes by the average tree)
     const int avg_nodes = (T + B - 1) / B < max_nodes ? (T + B - 1) / B : max_nodes;
     const int avg_tiles = (avg_nodes * G + 15) / 16;
-    if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == kAttnTargetWgs && attn_rows_strides(B, seq_stride, head_stride) &&
+    if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == 0 && attn_rows_strides(B, seq_stride, head_stride) &&
         attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host)) {
       if (B > 1) planned = c->row_splits;
       const int rc = launch_attn_rows(c, kc, vc, seq_stride, head_stride, ctx_len, max_ctx_host, tree_off, B, T, k_new, v_new, &nsplits, s);
       if (rc) return rc;
     } else {
-      const int chunks = (max_ctx_host + kMfmaKeys - 1) / kMfmaKeys;
+      const int chunks = (max_ctx_host + kMfmaKeys - 1) / kMfmaKeys, target_wgs = c->attn_target_wgs ? c->attn_target_wgs : kAttnTargetWgs;
       // 8-wavefront workgroups with two LDS buffers (the next chunk is fetched during the matrix work) once
       // there is more than one round of 4-wavefront workgroups to run. With fewer than 8 row tiles some of the
       // 8 wavefronts only stage; measured to pay down to 4 tiles (many KV heads, few rows per head).
       const long long chunk_wgs4 = (long long)chunks * m.Hkv * B * ((avg_tiles + 3) / 4);
-      int nw = (avg_tiles >= 4 && chunk_wgs4 > c->attn_target_wgs) ? 8 : 4;
+      int nw = (avg_tiles >= 4 && chunk_wgs4 > target_wgs) ? 8 : 4;
       if (c->attn_waves == 4 || c->attn_waves == 8) nw = c->attn_waves;
       const int rb = c->attn_row_blocks > 0 ? c->attn_row_blocks : (ntiles + nw - 1) / nw;
       const int rb_avg = (avg_tiles + nw - 1) / nw;
@@ -2017,7 +2017,7 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
       // draft-node split of every unit comes on top, so one split of the budget is kept for it: a grid a
       // few workgroups above what the chip holds at once would run a nearly empty second round. (Not in a
       // batch: splits past a shorter sequence's context leave at once, so the grid is not what runs.)
-      int want = (nw == 8 ? c->attn_target_wgs / 2 : c->attn_target_wgs) / (m.Hkv * B * rb_avg) - (B == 1 ? 1 : 0);
+      int want = (nw == 8 ? target_wgs / 2 : target_wgs) / (m.Hkv * B * rb_avg) - (B == 1 ? 1 : 0);
       want = want < 1 ? 1 : want;
       // (the merge walks the splits of a row in batches of 17, one round trip each: beyond about 32 splits a
       // second chunk per workgroup costs less than the extra batches; measured at 8 nodes, ctx 8192)

@@ -30,7 +30,7 @@ constexpr int kAttnMfmaMaxSplits = 34;  // bf16 attention: at most 32 context sp
 int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long long seq_stride, long long head_stride,
                      const int32_t* ctx_len, int max_ctx_host, const int32_t* tree_off, int B, int T, const void* k_new,
                      const void* v_new, void* aux_out, hipStream_t s);
-constexpr int kAttnTargetWgs = 512;  // the knob's own value
+constexpr int kAttnTargetWgs = 512;  // until the knob is set
 constexpr int kAttnRowsMaxSplits = 32;
 int launch_attn_rows(const evict_ctx* c, const void* kc, const void* vc, long long seq_stride, long long head_stride, const int32_t* ctx_len,
                      int max_ctx_host, const int32_t* tree_off, int B, int T, const void* k_new, const void* v_new, int* nsplits, hipStream_t s);

@@ -162,3 +162,12 @@ def test_caches_at_strides_of_no_multiple_of_16_bytes(B, n, L, pad):
         check_against_oracle(case, dict(dc.results(), out=harness.to_host(out[2][0])))  # (8 wavefronts where the size asks for them)
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("tune", [{"attn_target_wgs": 512}, {"attn_target_wgs": 511}, {"attn_row_blocks": 1}])
+def test_a_knob_that_is_set_keeps_the_kernel_it_shapes(tune):
+    """Also when it is set to what it stands at: the 16-row kernel's bits (4 splits either way), and not those of a context as it is."""
+    cfg = cfg_of(16, 2)
+    case = synth.make_case(cfg.name, n=8, L=500, seed=991, sigma=0.5, tree="random", cfg=cfg)
+    want, got, auto = (run_case(case, tune=t)["attn_out"] for t in ({"attn_waves": 4}, tune, {}))
+    assert np.array_equal(got, want) and not np.array_equal(got, auto)
