@@ -806,7 +806,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MB == 17
   // (PLANNED: the attention kernel cut every sequence into splits of its own number; a wavefront goes by the most of its rows')
   int mine = nsplits;
   if (PLANNED) {
-    mine = t < T ? row_splits[t] : 0;  // (tokens of a tree that was too large have none)
+    mine = t < T ? row_splits[t] : 0;  // (clamped: a tree's nodes past its 128th, whose rows are undefined, have what an earlier call left)
     mine = mine < 0 ? 0 : (mine > nsplits ? nsplits : mine);
     nsplits = (int)wave_max_u32((unsigned)mine);
   }

@@ -34,7 +34,7 @@ def batch(cfg, sizes, Ls, seed):
 
 @pytest.mark.parametrize("n,L,Hq,Hkv", [
     (1, 0, 8, 1), (1, 1, 8, 1), (8, 63, 16, 2), (8, 64, 8, 1), (7, 65, 8, 1), (64, 129, 4, 4), (33, 700, 2, 2), (63, 4200, 2, 2),
-    (128, 6400, 8, 1), (100, 3333, 16, 2),
+    (128, 6400, 8, 1), (100, 3333, 16, 2), (10, 500, 12, 2), (21, 130, 6, 2), (90, 2500, 20, 4), (7, 64, 14, 2),  # (6, 3, 5, 7 heads a group)
 ])
 def test_one_tree(n, L, Hq, Hkv):
     cfg = cfg_of(Hq, Hkv)
@@ -47,6 +47,12 @@ def test_one_tree(n, L, Hq, Hkv):
     ([3, 65, 20] * 6, [100, 33, 1500] * 6, 8, 2),
     ([128, 40], [4000, 10], 16, 2),
     ([5] * 33, [17 + 40 * (i % 7) for i in range(33)], 4, 4),
+    ([1 + i % 9 for i in range(17)], [90 * (i % 5) for i in range(17)], 14, 2),
+    # sequences of 1 to 32 splits side by side (a chunk each: 181 workgroups), so that the merge's wavefronts hold rows of different counts
+    ([1] * 16, [max(64 * (n - 1) - 5, 0) for n in (5, 6, 17, 18, 32, 1, 2, 9, 10, 16, 3, 31, 4, 7, 8, 12)], 8, 1),
+    ([2] * 16, [max(64 * (n - 1) - 64 * (n % 2), 0) for n in (32, 17, 1, 18, 2, 33, 5, 1, 6, 30, 3, 1, 16, 4, 1, 9)], 8, 1),
+    ([1, 2] * 32, [37 * (i % 6) for i in range(64)], 8, 1),   # a sequence in every lane of the plan
+    ([1, 2] * 32 + [3], [37 * (i % 6) for i in range(65)], 8, 1),  # one more: the 16-row kernel
 ])
 def test_batches(sizes, Ls, Hq, Hkv):
     case = batch(cfg_of(Hq, Hkv), sizes, Ls, 950)

@@ -1,5 +1,6 @@
 """The merge of the attention's partial softmaxes where its unrolling changes: up to 5, 9 and 17 splits in one go, a second batch of
-17, the other held pairs up to 48 and batches of 16 beyond; with splits that are empty for the shorter sequence."""
+17, the other held pairs up to 48 and batches of 16 beyond; with splits that are empty for the shorter sequence. In bf16 for the splits
+of the 16-row attention kernel (chunks of 128 keys, one split more for the draft nodes) and of the 32-row one (chunks of 64)."""
 import pytest
 
 import synth
@@ -26,4 +27,11 @@ def test_bf16_split_counts(chunks, D):
     # way, 1/100 to 6/100 of it seen, is what the protocol's bound of 5e-2 on the contribution is to tell from a wrong expert)
     cfg = synth.ModelCfg("bf16merge", "bf16", d=512, Hq=8, Hkv=2, D=D, E=32, k=4, F=192)
     case = synth.make_case(cfg.name, n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random", cfg=cfg)
+    check_against_oracle(case, run_case(case, tune={"attn_waves": 4}))  # (the 16-row kernel, as it is without the knob for 64 columns)
+
+
+@pytest.mark.parametrize("splits", [1, 2, 5, 6, 9, 10, 17, 18, 31, 32])
+def test_bf16_split_counts_of_64_keys(splits):
+    cfg = synth.ModelCfg("bf16merge", "bf16", d=512, Hq=8, Hkv=2, D=128, E=32, k=4, F=192)
+    case = synth.make_case(cfg.name, n=9, L=max(64 * (splits - 1) - 5, 0), seed=splits, sigma=0.5, tree="random", cfg=cfg)
     check_against_oracle(case, run_case(case))

@@ -295,3 +295,52 @@ def test_masked_logits(ctx_small, V, low):
         assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path, plen, bonus) == 0
         for b in range(len(parents)):
             assert keep[int(tree_off[b]) + path[b, plen[b] - 1], bonus[b]]
+
+
+@pytest.mark.parametrize("V", [1000, 65537])
+def test_many_trees_and_statistics_of_an_earlier_call(V):
+    """More than 64 trees, some of them empty, right after a call on the same context with other logits: the rows that a call leaves out (nodes
+    without children, past 65536 logits) hold the earlier call's statistics, and none of them is used."""
+    cfg = synth.CONFIGS["tiny"]
+    sizes = [1 + (5 * b) % 4 for b in range(70)]
+    parents, tree_off, parent, logits, tok, u_node, u_bonus = make_sampling_case(71, sizes, V)
+    off, u, live = [0], [], []
+    for b in range(70):
+        if b % 9 == 4:
+            off.append(off[-1])
+            u.append(0.999)
+        live.append(len(u))
+        off.append(int(tree_off[b + 1]))
+        u.append(u_bonus[b])
+    off, u = np.array(off, np.int32), np.array(u, np.float32)
+    ctx = ev.evict_create(harness.model_desc(cfg), int(tree_off[-1]), len(u), 16)
+    try:
+        run_gpu(ctx, off, np.where(parent > 0, 0, parent).astype(np.int32), tok, np.ascontiguousarray(-2.0 * logits[::-1]), V, 0.7, u_node, u, 4)
+        path, plen, bonus = run_gpu(ctx, off, parent, tok, logits, V, 0.9, u_node, u, 4)
+        assert check_against_oracle(parents, tree_off, logits, tok, u_node, u_bonus, 0.9, path[live], plen[live], bonus[live]) == 0
+        assert plen.max() > 1 and ev.evict_device_status(ctx) == 0
+    finally:
+        ev.evict_destroy(ctx)
+
+
+@pytest.mark.parametrize("V", [1000, 65537])
+@pytest.mark.parametrize("bad", [[-1, 7], [-1, -3], [-1, 1], [-1, 7, 0, 5], [-1, 0, 2, 1]])
+def test_invalid_parents_count_as_the_root(V, bad):
+    """Every decision as with the root for a parent, right after a call with other logits; the status word says so. (The root's row is needed even
+    where no node names it.)"""
+    cfg = synth.CONFIGS["tiny"]
+    n = len(bad)
+    par = np.array([p if i == 0 or 0 <= p < i else 0 for i, p in enumerate(bad)], np.int32)
+    g = synth.philox(V + n, 65)
+    logits = (3.0 * g.standard_normal((n, V))).astype(np.float32)
+    tok = np.array([0] + [int(np.argsort(-logits[par[i]])[i]) for i in range(1, n)], np.int32)
+    off = np.array([0, n], np.int32)
+    ctx = ev.evict_create(harness.model_desc(cfg), n, 1, 16)
+    try:
+        for u_node in (np.zeros(n, np.float32), np.full(n, 0.03, np.float32), np.full(n, 0.999, np.float32)):
+            run_gpu(ctx, off, np.array(bad, np.int32), tok, np.ascontiguousarray(logits[::-1] * 1.5), V, 0.7, u_node, np.array([0.2], np.float32), 4)
+            path, plen, bonus = run_gpu(ctx, off, np.array(bad, np.int32), tok, logits, V, 0.9, u_node, np.array([0.6], np.float32), 4)
+            assert check_against_oracle([par], off, logits, tok, u_node, np.array([0.6], np.float32), 0.9, path, plen, bonus) == 0
+        assert ev.evict_device_status(ctx) & ev.EVICT_ST_BAD_PARENT
+    finally:
+        ev.evict_destroy(ctx)
