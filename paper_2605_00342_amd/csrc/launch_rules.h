@@ -85,9 +85,10 @@ constexpr bool lm_one_round(int T, int n_strips, int nkb, bool bf16) {
 }
 
 // Strips of 64 blocks in bf16, whose scores or candidates a workgroup keeps until its strips are done (gemm_stream_kernel), are dealt out in
-// one round from 13 tokens on already: 9496 strips, score rows / arg max, us, 8 strips each -> one round, 16 tokens 101 / 98 -> 95 / 97, 17 tokens
-// 104 / 99 -> 96 / 97, 24 tokens 109 / 99 -> 97 / 97; 6400 strips, 16 tokens 74 / 75 -> 67 / 70. With one token tile two workgroups share a CU, but the
-// round of 256 is the better (19 strips each 100 / 96; 12 tokens, two strips each, 97 / 98, one round 95 / 97).
+// one round from 13 tokens on already (us, 8 strips each -> one round, score rows / arg max: 6400 strips, 16 tokens 74 / 75 -> 67 / 70; 9496, 16 tokens 106 / 102 ->
+// 103 / 103, 17 tokens 109 / 105 -> 103 / 104, 24 tokens 114 / 105 -> 104 / 103). With one token tile two workgroups share a CU, but the round of 256 is the
+// better (19 strips each 100 / 96; 12 tokens, two strips each, 97 / 98, one round 95 / 97). The line lies where the measurements of the form before ended. Past
+// it, 32 tokens: 42 strips each 134 / 121 -> 118 / 115, 47 147 / 128 -> 132 / 129, 48 149 / 132 -> 141 / 136; 16 tokens: 47 132 / 125 -> 128 / 128, 48 135 / 128 -> 135 / 137.
 constexpr int lm_deal(int T, int n_strips, int nkb, bool bf16) {
   const int round = (n_strips + 255) / 256;
   if (bf16 && nkb == 64 && T > 12 && T <= 32 && n_strips > 4096 && round * nkb <= 2432) return round;
@@ -151,8 +152,9 @@ constexpr bool attn_rows_strides(int B, long long seq_stride, long long head_str
   return head_stride % 8 == 0 && (B == 1 || seq_stride % 8 == 0);
 }
 // Workgroups to cut the splits for: one per CU, or two, which overlap each other's phases but leave twice the partial rows to the
-// merge, once they have 16 chunks and more (one, two per CU: 8 x 32 nodes, 16 heads of one, ctx 2048 28.8, 22.6; 16 x 64 ctx 2048 57.6, 46.6; but
-// 4 x 64 ctx 2048 21.8, 24.8, 1 x 128 ctx 6000 29.4, 31.7).
+// merge, once they have 16 chunks and more (whole small layers, us, one per CU, two, chunks in brackets: 4 heads of 8, 4 x 64 nodes ctx 2048 75.1, 77.2 (2112),
+// 1 x 128 ctx 6000 75.5, 78.2 (3040), 8 x 64 ctx 2048 110.2, 105.3 (4224), 16 x 64 156.5, 145.4 (8448); 16 heads of one, 8 x 8 ctx 2048 71.3, 61.7 (4224). It is not
+// the chunks alone: 16 heads of one, 4 x 128 ctx 6000 117, 121 (6080), 16 x 8 ctx 600 72.1, 67.3 (2816); one head of 8, 8 x 128 ctx 6000 101, 110 (6080)).
 constexpr int attn_rows_wgs(int B, int T, int Hq, int Hkv, int max_ctx) {
   return attn_rows_work(B, T, Hq, Hkv, max_ctx) >= 16 * 256 ? 512 : 256;
 }

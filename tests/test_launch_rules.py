@@ -155,7 +155,7 @@ def test_attention_rows(rules):
 
 def test_lm_head_deal(rules):
     assert [rules.deal(T, 9496, 64, 1) for T in (1, 12, 13, 16, 17, 24, 32)] == [2, 2, 38, 38, 38, 38, 38]
-    assert rules.deal(16, 4096, 64, 1) == 8 and rules.deal(16, 4097, 64, 1) == 17 and rules.deal(16, 9729, 64, 1) == 8  # 39 strips: too long a round
+    assert rules.deal(16, 4096, 64, 1) == 8 and rules.deal(16, 4097, 64, 1) == 17 and rules.deal(16, 9729, 64, 1) == 8  # 39 strips: past the line
     for T, n, nkb, bf16 in ((16, 9496, 32, 1), (24, 9496, 128, 1), (24, 9496, 64, 0), (8, 9496, 64, 1), (48, 9496, 48, 1)):
         old = rules.strips(T, n) if rules.one_round(T, n, nkb, bf16) else rules.units(T, n)
         assert rules.deal(T, n, nkb, bf16) == old
