@@ -21,8 +21,8 @@ namespace evict {
 //  - a batch is cut into equal shares by the kernel itself, which alone knows the sequences' lengths.
 // (us, attention alone, 16 rows -> 32: 16 trees of 48 to 64 nodes, 32 heads on 4, contexts of 1024 to 2048 92 -> 40, 0.25 -> 0.57
 // PFLOP/s; 4 such trees, contexts to 5555 48 -> 33; 128 nodes, context 4096 24 -> 21; 16 trees of 16 nodes, contexts to 6000 138 -> 38.)
-// What bounds it now: a chunk of 64 keys takes a wavefront 1024 cycles of MFMA and about 1100 of the vector unit, 250 more where a row finds
-// a new maximum, and two wavefronts per SIMD some 3000 for one each, as their phases overlap in part only; and some 9 us besides: the launch, 1.5 to 2.4 for the
+// What bounds it now: a chunk of 64 keys takes a wavefront 1024 cycles of MFMA and 1200 (4 x 64 nodes, contexts to 5555) to 1500 (16 x 64, to 2048) of
+// the vector unit, and two wavefronts per SIMD some 3000 for one each, as their phases overlap in part only; and some 9 us besides: the launch, 1.5 to 2.4 for the
 // plan, 2.3 until the first chunk and the query rows are there, 1 to 3 for the partial rows. Tried: eight wavefronts that share a chunk, four
 // buffers, three chunks on their way (6 % longer; the end of all workgroups at once costs more), loads sent between
 // the first products instead of before them (30 % longer).
