@@ -133,7 +133,8 @@ constexpr long long attn_rows_work(int B, int T, int Hq, int Hkv, int max_ctx) {
 // Not where few chunks leave most of a workgroup's time to its start and its end: 1 x 64 ctx 600 13.4 (14.9), 1 x 32 ctx 600 11.5 (13.0), one KV
 // head, 2 x 128 ctx 600 12.8 (17.1), 1 x 64 ctx 6000 15.8 (16.7). The line lies higher where the 16-row kernel has few empty row blocks (whole
 // small layers, us, 16 rows -> 32, chunks in brackets): one or two KV heads, 1 to 4 trees, 8/1 2 x 96 ctx 3000 58.0 -> 61.7 (576), 3 x 128 ctx 2048 65.0 -> 66.5
-// (792), 16/2 1 x 64 ctx 4096 55.0 -> 56.4 (520), but 8/1 1 x 128 ctx 8000 62.2 -> 62.1 (1008); 64 heads on 8, 1 x 48 ctx 2048 65.7 -> 66.7 (792), 3000 69.6 ->
+// (792), 16/2 1 x 64 ctx 4096 55.0 -> 56.4 (520), but 8/1 1 x 128 ctx 8000 62.2 -> 62.1 (1008), and with long contexts, where both cut as often as they
+// may, 8/1 1 x 64 ctx 8192 51.7 -> 52.3 (516), 10000 54.6 -> 53.2 (632), a layer of 4096 columns, 1 x 44 ctx 15161 103.1 -> 101.2 (714); 64 heads on 8, 1 x 48 ctx 2048 65.7 -> 66.7 (792), 3000 69.6 ->
 // 67.8 (1128); 2 to 4 trees of more than 72 nodes, 16/16 2 x 96 ctx 1000 69.3 -> 70.4 (544), 1500 71.2 -> 72.0 (800), 2048 76.1 -> 72.4 (1056). And where
 // it has none, as a batch of trees of few rows lies within one of its workgroups (8 nodes of 4 trees, 16 heads of one: ctx 1000 47.4 -> 48.2,
 // 3000 60.4 -> 61.4, 4096 67.2 -> 62.7; one node, 8 trees 1000 51.3 -> 55.1, 2048 62.1 -> 56.5): from 16 chunks a workgroup on, or with more units
@@ -143,7 +144,7 @@ constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_c
   const long long work = attn_rows_work(B, T, Hq, Hkv, max_ctx), units = (long long)B * Hkv, rows = (long long)T * (Hq / Hkv);
   if (rows <= 64) return B == 1 || work >= 16 * 256 || units > 256 || (units > 128 && work >= 5 * 256);
   if (B >= 16) return true;
-  const bool few_empty = B <= 4 && (Hkv <= 2 || (B == 1 ? Hq >= 64 : T > 72 * B));
+  const bool few_empty = max_ctx <= 8192 && B <= 4 && (Hkv <= 2 || (B == 1 ? Hq >= 64 : T > 72 * B));
   return work >= (few_empty ? 830 : 400);
 }
 // Its loads go straight into LDS, 16 bytes a lane, and so need rows of the caches at multiples of 16 bytes; caches at other strides, which the 16-row

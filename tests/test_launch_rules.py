@@ -206,4 +206,5 @@ def test_attention_rows_where_they_were_measured_faster(rules):
     for shape, lo, hi in (((2, 187, 8, 1), 3000, 5000), ((3, 369, 8, 1), 2048, 4000), ((1, 64, 16, 2), 6000, 8192), ((1, 48, 64, 8), 2048, 3000),
                           ((2, 187, 16, 16), 1500, 2048)):
         assert not f(128, *shape, lo) and f(128, *shape, hi), shape
+    assert f(128, 1, 44, 8, 1, 15161) and f(128, 1, 64, 8, 1, 8193) and not f(128, 1, 64, 8, 1, 8192)  # long contexts
     assert f(128, 1, 100, 16, 16, 1600) and f(128, 2, 120, 32, 4, 1500) and f(128, 5, 360, 8, 1, 2000)
