@@ -195,19 +195,21 @@ __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu
   auto stage = [&](int i, int it, uint16_t* buf, int32_t pages, int at_lane) __attribute__((always_inline)) {
     const bool tree = i >= n_ctx;
     const int first = tree ? (tree_begin + i - n_ctx) * kRowsKeys : key_begin + i * kRowsKeys;
-    const int most = key_end + (tree ? past_ctx : 0) - first - 1;  // rows past the end: the last key again (never weighted, and finite if that is)
+    const int most = key_end + (tree ? past_ctx : 0) - first - 1;  // rows past the end: of K the last one again, whose scores are masked; of V zeros, as a
+                                                                   // weight of zero does not take an infinity out of the product
     const size_t step = tree ? (size_t)Hkv * D : (size_t)D;
     const uint16_t* kl = (const uint16_t*)((uintptr_t)kctx + (tree ? k_to_tree : 0)) + (PAGED && !tree ? 0 : (size_t)first * step);
     const uint16_t* vl = (const uint16_t*)((uintptr_t)vctx + (tree ? v_to_tree : 0)) + (PAGED && !tree ? 0 : (size_t)first * step);
     int row = srow + 4 * it;
     const int kp = sp ^ (row & 15), vp = sp ^ ((row & 3) << 2);
-    row = row < most ? row : most;
+    const bool there = row <= most;
+    row = there ? row : most;
     uint16_t *sk = buf + (w * LI + it) * 512, *sv = sk + kRowsKeys * D;
     if (PAGED == 2 && !tree) {  // a page of its own for every row, anywhere in the pool
       const int32_t page = check_page(ptab[(first + row) >> pg.page_shift]);
       const size_t off = (size_t)page * seq_stride + (size_t)((first + row) & pmask) * D;
       __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(kl + off + kp * 8), (void __attribute__((address_space(3)))*)sk, 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(vl + off + vp * 8), (void __attribute__((address_space(3)))*)sv, 16, 0, 0);
+      if (there) __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(vl + off + vp * 8), (void __attribute__((address_space(3)))*)sv, 16, 0, 0);
       return;
     }
     if (PAGED == 1 && !tree) {  // the load's four rows are in one page (of at least 4 positions; those past the end read one and the same row)
@@ -220,10 +222,18 @@ __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu
     const unsigned at = __umul24(row, (unsigned)step * 2);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)kl, 0, 0x7FFFFFFF, 0x27000),
                                              (void __attribute__((address_space(3)))*)sk, 16, at + kp * 16, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)vl, 0, 0x7FFFFFFF, 0x27000),
-                                             (void __attribute__((address_space(3)))*)sv, 16, at + vp * 16, 0, 0, 0);
+    if (there)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)vl, 0, 0x7FFFFFFF, 0x27000),
+                                               (void __attribute__((address_space(3)))*)sv, 16, at + vp * 16, 0, 0, 0);
   };
   auto stage_all = [&](int i, uint16_t* buf, int32_t pages, int at_lane) __attribute__((always_inline)) {
+    // (before the chunk's loads: a write behind one that is on its way into the same object would wait for it)
+    const int past = i >= n_ctx ? n - (tree_begin + i - n_ctx) * kRowsKeys : key_end - key_begin - i * kRowsKeys;
+    if (past < kRowsKeys) {
+#pragma unroll
+      for (int it = 0; it < LI; ++it)
+        if (srow + 4 * it >= past) *reinterpret_cast<u32x4*>(buf + kRowsKeys * D + (w * LI + it) * 512 + lane * 8) = u32x4{0, 0, 0, 0};
+    }
 #pragma unroll
     for (int it = 0; it < LI; ++it) stage(i, it, buf, pages, at_lane);
   };

@@ -177,3 +177,25 @@ def test_a_knob_that_is_set_keeps_the_kernel_it_shapes(tune):
     case = synth.make_case(cfg.name, n=8, L=500, seed=991, sigma=0.5, tree="random", cfg=cfg)
     want, got, auto = (run_case(case, tune=t)["attn_out"] for t in ({"attn_waves": 4}, tune, {}))
     assert np.array_equal(got, want) and not np.array_equal(got, auto)
+
+
+@pytest.mark.parametrize("n,L", [(5, 70), (8, 64), (3, 1), (64, 2100), (40, 129), (17, 63), (1, 4033)])
+@pytest.mark.parametrize("waves", [0, 4])
+def test_an_infinite_value_stays_in_its_column(n, L, waves):
+    """An infinity in column 3 of the cache's last value, in a whole chunk and in ragged ones: that column is infinite in every node, which all
+    see the key, the others keep their bits. (Rows past a chunk's end weigh nothing, but zero times an infinity is no number.)"""
+    cfg = cfg_of(2, 2)
+    case = synth.make_case(cfg.name, n=n, L=L, seed=992, sigma=0.5, tree="random", cfg=cfg)
+    out = []
+    for value in (0.0, float("inf")):
+        layer, dc = harness.DeviceLayer(cfg, case["W"], n, 1, L), harness.DeviceCase(case)
+        try:
+            ev.evict_tune(layer.ctx, "attn_waves", waves)
+            dc.v_cache[0, :, L - 1, 3] = value
+            dc.run(layer)
+            torch.cuda.synchronize()
+            out.append(dc.a["attn_out"].float())
+        finally:
+            layer.close()
+    rest = [c for c in range(cfg.D) if c != 3]
+    assert bool((out[1][:, :, 3] == float("inf")).all()) and torch.equal(out[0][:, :, rest], out[1][:, :, rest])
