@@ -27,7 +27,15 @@ def test_bf16_split_counts(chunks, D):
     # way, 1/100 to 6/100 of it seen, is what the protocol's bound of 5e-2 on the contribution is to tell from a wrong expert)
     cfg = synth.ModelCfg("bf16merge", "bf16", d=512, Hq=8, Hkv=2, D=D, E=32, k=4, F=192)
     case = synth.make_case(cfg.name, n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random", cfg=cfg)
-    check_against_oracle(case, run_case(case, tune={"attn_waves": 4}))  # (the 16-row kernel, as it is without the knob for 64 columns)
+    check_against_oracle(case, run_case(case))
+
+
+@pytest.mark.parametrize("chunks", [4, 5, 8, 9, 16, 17, 31, 32])
+def test_bf16_split_counts_of_128_keys(chunks):
+    """128 columns on the 16-row kernel, which the knob keeps: the splits that 64 columns have above."""
+    cfg = synth.ModelCfg("bf16merge", "bf16", d=512, Hq=8, Hkv=2, D=128, E=32, k=4, F=192)
+    case = synth.make_case(cfg.name, n=9, L=128 * chunks - 5, seed=chunks, sigma=0.5, tree="random", cfg=cfg)
+    check_against_oracle(case, run_case(case, tune={"attn_waves": 4}))
 
 
 @pytest.mark.parametrize("splits", [1, 2, 5, 6, 9, 10, 17, 18, 31, 32])
