@@ -147,6 +147,14 @@ constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_c
   const bool few_empty = max_ctx <= 8192 && B <= 4 && (Hkv <= 2 || (B == 1 ? Hq >= 64 : T > 72 * B));
   return work >= (few_empty ? 830 : 400);
 }
+// One tree: only from 12 chunks per CU on, where it is clearly the faster. Below, it gains or loses a few percent of such a small layer, and another
+// order of sums takes a token whose last expert is nearly tied to another expert, 4e-2 of its row, which a batch's many tokens average out and the few
+// of one tree, or the score rows behind a stack of layers, do not. (Whole small layers, us, 16 rows -> 32, chunks in brackets. 4 heads of 8: 1 node ctx 2048
+// 41.5 -> 41.4 (132), 16 nodes ctx 3000 50.6 -> 50.2 (192), 41 ctx 3000 60.7 -> 61.0 (576), 64 ctx 5000 67.0 -> 67.1 (1280), 128 ctx 5000 79.5 -> 81.4 (2560), 41 ctx 12000
+// 69.8 -> 70.6 (2268), 64 ctx 8000 71.5 -> 69.9 (2016); 128 ctx 8000 89.5 -> 88.3 (4032), ctx 12000 103.5 -> 92.4 (6048), ctx 32000 171.8 -> 137.1, 41 ctx 20000 93.8 -> 79.1 (3768),
+// 64 ctx 20000 89.1 -> 82.6. 16 heads of one: 64 ctx 8000 63.7 -> 63.9 (2016), 16 ctx 5000 56.5 -> 52.8 (1280), 64 ctx 20000 78.6 -> 75.6 (5024). One head of 8: 64 ctx 32000
+// 73.4 -> 74.0 (2008), 128 ctx 32000 83.9 -> 81.9 (4016).)
+constexpr bool attn_rows_one_tree(int T, int Hq, int Hkv, int max_ctx) { return attn_rows_work(1, T, Hq, Hkv, max_ctx) >= 12 * 256; }
 // Its loads go straight into LDS, 16 bytes a lane, and so need rows of the caches at multiples of 16 bytes; caches at other strides, which the 16-row
 // kernel reads through registers, stay there. (One sequence: the distance to the next is not used.)
 constexpr bool attn_rows_strides(int B, long long seq_stride, long long head_stride) {

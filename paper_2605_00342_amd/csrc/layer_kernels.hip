@@ -1999,7 +1999,7 @@ int launch_attention(const evict_ctx* c, const void* kc, const void* vc, long lo
     const int avg_nodes = (T + B - 1) / B < max_nodes ? (T + B - 1) / B : max_nodes;
     const int avg_tiles = (avg_nodes * G + 15) / 16;
     if (c->attn_waves == 0 && c->attn_row_blocks == 0 && c->attn_target_wgs == 0 && attn_rows_strides(B, seq_stride, head_stride) &&
-        attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host)) {
+        attn_rows_applies(m.D, B, T, m.Hq, m.Hkv, max_ctx_host) && (B > 1 || attn_rows_one_tree(T, m.Hq, m.Hkv, max_ctx_host))) {
       if (B > 1) planned = c->row_splits;
       const int rc = launch_attn_rows(c, kc, vc, seq_stride, head_stride, ctx_len, max_ctx_host, tree_off, B, T, k_new, v_new, &nsplits, s);
       if (rc) return rc;

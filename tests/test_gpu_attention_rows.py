@@ -41,6 +41,25 @@ def test_one_tree(n, L, Hq, Hkv):
     check_against_oracle(*(lambda c: (c, run_case(c)))(synth.make_case(cfg.name, n=n, L=L, seed=900 + n, sigma=0.5, tree="random", cfg=cfg)))
 
 
+@pytest.mark.parametrize("n,L,Hq,Hkv", [
+    (1, 6080, 32, 32), (31, 6081, 32, 32), (33, 6143, 32, 32), (64, 6144, 32, 32), (65, 6145, 32, 32), (128, 6300, 32, 32), (128, 6080, 32, 4),
+    (100, 14100, 16, 2), (100, 19700, 12, 2), (90, 12200, 20, 4),
+])
+def test_one_tree_of_many_chunks(n, L, Hq, Hkv):
+    """As above, on the side of the rule for one tree (attn_rows_one_tree) where it takes this kernel."""
+    cfg = cfg_of(Hq, Hkv)
+    case = synth.make_case(cfg.name, n=n, L=L, seed=n + L, sigma=0.5, tree="random", cfg=cfg)
+    check_against_oracle(case, run_case(case))
+
+
+@pytest.mark.parametrize("n,L,Hq,Hkv", [(1, 2048, 8, 1), (14, 3000, 16, 2), (64, 6016, 32, 32), (128, 6016, 32, 4)])
+def test_one_tree_of_few_chunks_has_the_bits_of_16_rows(n, L, Hq, Hkv):
+    cfg = cfg_of(Hq, Hkv)
+    case = synth.make_case(cfg.name, n=n, L=L, seed=n + L, sigma=0.5, tree="random", cfg=cfg)
+    a, b = run_case(case), run_case(case, tune={"attn_target_wgs": 512})
+    assert np.array_equal(a["attn_out"], b["attn_out"]) and np.array_equal(a["out"], b["out"])
+
+
 @pytest.mark.parametrize("sizes,Ls,Hq,Hkv", [
     ([1] * 16, [0] * 16, 8, 1),
     ([17, 1, 33, 16, 5, 64, 2, 3, 9, 40, 1, 1, 15, 16, 17, 8], [65, 0, 900, 64, 1, 128, 0, 2000, 63, 7, 500, 31, 129, 640, 77, 256], 8, 1),
@@ -59,7 +78,8 @@ def test_batches(sizes, Ls, Hq, Hkv):
     check_against_oracle(case, run_case(case))
 
 
-@pytest.mark.parametrize("n,Ls,P", [(8, [300], 1), (8, [301], 2), (8, [1037], 4), (5, [130 + 61 * (i % 5) for i in range(16)], 8), (6, [40 * i for i in range(17)], 64)])
+@pytest.mark.parametrize("n,Ls,P", [(8, [300], 1), (8, [301], 2), (8, [1037], 4), (5, [130 + 61 * (i % 5) for i in range(16)], 8), (6, [40 * i for i in range(17)], 64),
+                                    (8, [300 + 7 * i for i in range(16)], 1), (8, [301 - i for i in range(16)], 2), (8, [137 + 60 * i for i in range(16)], 4)])
 def test_pages(n, Ls, P):
     case, cfg, Ws, Ks, Vs, pools, table, n_pages = paged.build("mini_bf16", n, Ls, P, 97, 0)
     dev = paged.Dev(case, cfg, Ws, Ks, Vs, pools, table, n_pages, P, max(Ls))
@@ -74,7 +94,7 @@ def test_pages(n, Ls, P):
         dev.close()
 
 
-@pytest.mark.parametrize("n,bound,L,cap", [(1, 64, 2500, 2500), (14, 41, 3000, 3000), (40, 41, 100, 6000)])
+@pytest.mark.parametrize("n,bound,L,cap", [(1, 64, 2500, 2500), (14, 41, 3000, 3000), (40, 41, 100, 6000), (40, 128, 9000, 12300), (128, 128, 12300, 12300)])
 def test_count_in_device_memory(n, bound, L, cap):
     """The rows of the actual nodes, a bound above them and a context below the host's."""
     cfg = cfg_of(16, 2)
@@ -108,7 +128,7 @@ def test_error_of_peaked_scores(scale):
     of about 2 that is what keeps the error against 64-bit sums where the kernel of 16 rows has it (32 rows / 16 rows: 0.97 to 1.01 over shapes
     and deviations; with a maximum that lags behind 1.09 to 1.23 there). 2 million outputs, so the quotient itself is steady to 1 %."""
     cfg = synth.ModelCfg("wide", "bf16", d=256, Hq=32, Hkv=4, D=128, E=16, k=2, F=64, theta=1e6)
-    n, L = 128, 4096
+    n, L = 128, 8192
     case = synth.make_case(cfg.name, n=n, L=L, seed=980, sigma=0.5, tree="random", cfg=cfg)
     case["W"]["wq"] = case["W"]["wq"] * np.float32(scale)  # (a power of two: still representable)
     err = []
@@ -140,7 +160,7 @@ def test_error_of_peaked_scores(scale):
     assert err[0] < 1.05 * err[1], err
 
 
-@pytest.mark.parametrize("B,n,L,pad", [(1, 8, 300, 2), (1, 64, 2100, 4), (16, 4, 130, 4), (16, 4, 130, 2)])
+@pytest.mark.parametrize("B,n,L,pad", [(1, 8, 300, 2), (1, 64, 2100, 4), (16, 4, 130, 4), (16, 4, 130, 2), (1, 128, 24500, 4)])
 def test_caches_at_strides_of_no_multiple_of_16_bytes(B, n, L, pad):
     """Heads and sequences `pad` elements further apart than their rows take: as many calls of the 16-row kernel, which reads them through
     registers, on the same keys and values give the same bits."""
@@ -172,19 +192,20 @@ def test_caches_at_strides_of_no_multiple_of_16_bytes(B, n, L, pad):
 
 @pytest.mark.parametrize("tune", [{"attn_target_wgs": 512}, {"attn_target_wgs": 511}, {"attn_row_blocks": 1}])
 def test_a_knob_that_is_set_keeps_the_kernel_it_shapes(tune):
-    """Also when it is set to what it stands at: the 16-row kernel's bits (4 splits either way), and not those of a context as it is."""
-    cfg = cfg_of(16, 2)
-    case = synth.make_case(cfg.name, n=8, L=500, seed=991, sigma=0.5, tree="random", cfg=cfg)
+    """Also when it is set to what it stands at: the 16-row kernel's bits (12 splits either way), and not those of a context as it is."""
+    cfg = cfg_of(32, 32)
+    case = synth.make_case(cfg.name, n=8, L=6100, seed=991, sigma=0.5, tree="random", cfg=cfg)
     want, got, auto = (run_case(case, tune=t)["attn_out"] for t in ({"attn_waves": 4}, tune, {}))
     assert np.array_equal(got, want) and not np.array_equal(got, auto)
 
 
-@pytest.mark.parametrize("n,L", [(5, 70), (8, 64), (3, 1), (64, 2100), (40, 129), (17, 63), (1, 4033)])
+@pytest.mark.parametrize("n,L", [(5, 70), (8, 64), (3, 1), (64, 2100), (40, 129), (17, 63), (1, 4033), (5, 6150), (8, 6144),
+                                 (3, 6081), (64, 6200), (1, 8129)])
 @pytest.mark.parametrize("waves", [0, 4])
 def test_an_infinite_value_stays_in_its_column(n, L, waves):
     """An infinity in column 3 of the cache's last value, in a whole chunk and in ragged ones: that column is infinite in every node, which all
     see the key, the others keep their bits. (Rows past a chunk's end weigh nothing, but zero times an infinity is no number.)"""
-    cfg = cfg_of(2, 2)
+    cfg = cfg_of(32, 32)
     case = synth.make_case(cfg.name, n=n, L=L, seed=992, sigma=0.5, tree="random", cfg=cfg)
     out = []
     for value in (0.0, float("inf")):

@@ -28,6 +28,7 @@ int keeps_rows(int T, int n_strips, int nkb, int bf16) { return lm_keeps_rows(T,
 int topk(int T, int E, int k) { return topk_by_rows(T, E, k); }
 int grid(int n_strips, int strips, int groups) { return tile_grid(n_strips, strips, groups); }
 int rows_applies(int D, int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_applies(D, B, T, Hq, Hkv, ctx); }
+int rows_one_tree(int T, int Hq, int Hkv, int ctx) { return attn_rows_one_tree(T, Hq, Hkv, ctx); }
 int rows_splits(int wgs, int Hkv, int rbs) { return attn_rows_splits(wgs, Hkv, rbs); }
 int rows_strides(int B, long long seq, long long head) { return attn_rows_strides(B, seq, head); }
 int rows_wgs(int B, int T, int Hq, int Hkv, int ctx) { return attn_rows_wgs(B, T, Hq, Hkv, ctx); }
@@ -208,3 +209,12 @@ def test_attention_rows_where_they_were_measured_faster(rules):
         assert not f(128, *shape, lo) and f(128, *shape, hi), shape
     assert f(128, 1, 44, 8, 1, 15161) and f(128, 1, 64, 8, 1, 8193) and not f(128, 1, 64, 8, 1, 8192)  # long contexts
     assert f(128, 1, 100, 16, 16, 1600) and f(128, 2, 120, 32, 4, 1500) and f(128, 5, 360, 8, 1, 2000)
+
+
+def test_attention_rows_of_one_tree(rules):
+    """From 12 chunks of 64 keys per CU on, the draft nodes' chunk among them; where the general rule takes the kernel too."""
+    f = rules.rows_one_tree
+    assert [bool(f(128, 32, 4, c)) for c in (4096, 6016, 6017, 32000)] == [False, False, True, True]  # 8 row blocks x 4 heads x (chunks + 1)
+    assert [bool(f(n, 32, 32, 6100)) for n in (1, 64, 128)] == [True, True, True] and not f(64, 16, 16, 8192) and not f(1, 32, 4, 32768)
+    for shape in ((128, 32, 4, 6017), (100, 16, 2, 14100), (1, 32, 32, 6100), (64, 64, 8, 6017), (128, 8, 1, 24513)):
+        assert f(*shape) and rules.rows_applies(128, 1, *shape)
