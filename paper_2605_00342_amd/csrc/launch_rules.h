@@ -138,7 +138,7 @@ constexpr long long attn_rows_work(int B, int T, int Hq, int Hkv, int max_ctx) {
 // 67.8 (1128); 2 to 4 trees of more than 72 nodes, 16/16 2 x 96 ctx 1000 69.3 -> 70.4 (544), 1500 71.2 -> 72.0 (800), 2048 76.1 -> 72.4 (1056). And where
 // it has none, as a batch of trees of few rows lies within one of its workgroups (8 nodes of 4 trees, 16 heads of one: ctx 1000 47.4 -> 48.2,
 // 3000 60.4 -> 61.4, 4096 67.2 -> 62.7; one node, 8 trees 1000 51.3 -> 55.1, 2048 62.1 -> 56.5): from 16 chunks a workgroup on, or with more units
-// (sequences x KV heads) than half of the CUs from 8 on (12 trees of one node 300 47.0 -> 48.2, 600 58.0 -> 56.3), or more than CUs.
+// (sequences x KV heads) than half of the CUs from 8 on (12 trees of one node 300 47.0 -> 48.2, 600 58.0 -> 56.3), or more than CUs. One tree has to pass attn_rows_one_tree as well.
 constexpr bool attn_rows_applies(int D, int B, int T, int Hq, int Hkv, int max_ctx) {
   if (D != 128 || B > kAttnRowsMaxSeqs) return false;
   const long long work = attn_rows_work(B, T, Hq, Hkv, max_ctx), units = (long long)B * Hkv, rows = (long long)T * (Hq / Hkv);
